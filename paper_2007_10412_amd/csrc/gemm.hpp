@@ -592,7 +592,6 @@ __device__ __forceinline__ void epilogue_fwd(const GemmArgs& g, floatx16 (&acc)[
   // vectors, and the (y > 0) bits of the vector, taken from the values as stored, are merged with those of the
   // neighbouring lanes (the LPW lanes of a 32-column word are neighbours) by lane-permuting moves.
   ElemT* Y = reinterpret_cast<ElemT*>(g.y);
-  const bool yvec = Y && (g.ldy % VPL) == 0 && (reinterpret_cast<uintptr_t>(Y) & 15) == 0;
   constexpr int NV = BM * LPR / kGemmThreads;
   static_assert(BM * LPR % kGemmThreads == 0, "every thread takes the same number of vectors");
 #pragma unroll
@@ -605,8 +604,8 @@ __device__ __forceinline__ void epilogue_fwd(const GemmArgs& g, floatx16 (&acc)[
     const ElemT* re = reinterpret_cast<const ElemT*>(&raw);
     if (Y && valid > 0) {
       ElemT* dst = Y + (size_t)row * g.ldy + col;
-      if (yvec && valid == VPL) {
-        *reinterpret_cast<u32x4*>(dst) = raw;
+      if (valid == VPL) {
+        __builtin_memcpy(dst, &raw, 16);                   // at element alignment: rows of any width
       } else {                                             // (constant element numbers: the vector stays in registers)
 #pragma unroll
         for (int e = 0; e < VPL; ++e) if (e < valid) dst[e] = re[e];

@@ -64,7 +64,16 @@ __device__ __forceinline__ bf16x8 mn_frag_read(const unsigned char* tile, uint32
 // ------------------------------------------------------------------ loaders
 // dense, K contiguous: element (row, k) at p[row*ld + k]
 // EMODE: 0 = interior (no guards), 1 = ragged but every access a whole in-bounds or out-of-bounds 16-byte
-// vector (guard by clamping the address and zeroing), 2 = generic element-wise guards.
+// vector (guard by clamping the address and zeroing), 2 = any width, pitch and alignment: 16-byte loads that are
+// aligned to an element only (global loads may be), rows clamped as in 1, element-wise guards in the last slices
+// alone.  (Element-wise loads throughout, which mode 2 had before, made the loads the kernel: x W of
+// 1000 x 1100 x 2050 took 154 us, dX of 1000 x 1530 x 2050 300 us.)
+// 16 bytes from an address that is aligned to an element only
+__device__ __forceinline__ u32x4 load16_any(const uint16_t* p) {
+  u32x4 t;
+  __builtin_memcpy(&t, p, 16);
+  return t;
+}
 template <int R, int EMODE, bool MASKED, int NS> struct RingLoadK {
   typedef LdsBF16<R, kBK3> L;
   static constexpr bool kTr = false;
@@ -84,7 +93,7 @@ template <int R, int EMODE, bool MASKED, int NS> struct RingLoadK {
   __device__ __forceinline__ void configure(int) {}
   // KTAIL = false promises that the whole slice lies below K (every slice but the last)
   template <int SLOT, bool KTAIL = true> __device__ __forceinline__ void fetch(int k0) {
-    const bool vec = (ld & 7) == 0;
+    const bool guard = EMODE == 2 && KTAIL && k0 + kBK3 > K;     // uniform: the slice reaches past K
 #pragma unroll
     for (int i = 0; i < NCH; ++i) {
       const int c = threadIdx.x + i * kGemmThreads;
@@ -106,14 +115,17 @@ template <int R, int EMODE, bool MASKED, int NS> struct RingLoadK {
           const bool ok = !KTAIL || gk < K;
           t = *reinterpret_cast<const u32x4*>(ok ? srcc : reinterpret_cast<const uint16_t*>(kZeroChunk));
           if (MASKED) mb[SLOT][i] = mask_bits(mask, mp, grc, ok ? gk : 0);
-        } else if (gr < rmax && gk < K) {
-          if (vec && gk + 7 < K) t = *reinterpret_cast<const u32x4*>(src);
+        } else {
+          const int grc = min(gr, rmax - 1);
+          const uint16_t* srcc = p + ((uint32_t)grc * ld + (uint32_t)gk);
+          if (!guard) t = load16_any(srcc);
+          else if (gk + 8 <= K) t = load16_any(srcc);
           else {
             uint16_t* te = reinterpret_cast<uint16_t*>(&t);
 #pragma unroll
-            for (int e = 0; e < 8; ++e) if (gk + e < K) te[e] = src[e];
+            for (int e = 0; e < 8; ++e) if (gk + e < K) te[e] = srcc[e];
           }
-          if (MASKED) mb[SLOT][i] = mask_bits(mask, mp, gr, gk);
+          if (MASKED) mb[SLOT][i] = mask_bits(mask, mp, grc, !guard || gk < K ? gk : 0);
         }
       }
       v[SLOT][i] = t;
@@ -132,6 +144,18 @@ template <int R, int EMODE, bool MASKED, int NS> struct RingLoadK {
     }
   }
 };
+
+// up to eight elements from p (zeros past the first n; all zeros unless ok)
+__device__ __forceinline__ u32x4 load_row_end(const uint16_t* p, bool ok, int n) {
+  u32x4 t = {0u, 0u, 0u, 0u};
+  if (ok && n >= 8) t = load16_any(p);
+  else if (ok) {
+    uint16_t* te = reinterpret_cast<uint16_t*>(&t);
+#pragma unroll
+    for (int e = 0; e < 8; ++e) if (e < n) te[e] = p[e];
+  }
+  return t;
+}
 
 // dense, M/N contiguous: element (row, k) at p[k*ld + row].  Every thread owns a KPT(k) x 8(row) block
 // (KPT = 4 for 256-row tiles, 2 for 128-row tiles, so that all 256 threads have one and the code is free
@@ -161,7 +185,10 @@ template <int R, int EMODE, bool MASKED, int NS> struct RingLoadMN {
   __device__ __forceinline__ void bounds(int) {}
   __device__ __forceinline__ void configure(int) {}
   template <int SLOT, bool KTAIL = true> __device__ __forceinline__ void fetch(int k0) {
-    const bool vec = (ld & 7) == 0;
+    // A chunk that starts inside the operand may run past the end of its k-row into the next ones: what it brings
+    // from there feeds outputs that are never stored, and it stays inside the operand while at least eight
+    // elements follow, that is, in every slice that ends eight k-rows or more before K.
+    const bool guard = EMODE == 2 && KTAIL && k0 + kBK3 + 8 > K;
     const int rb = block_rb(), kq = block_kq();
     const int gr = r0 + rb * 8;
 #pragma unroll
@@ -180,14 +207,12 @@ template <int R, int EMODE, bool MASKED, int NS> struct RingLoadMN {
         const bool ok = !KTAIL || gk < K;
         t = *reinterpret_cast<const u32x4*>(ok ? srcc : reinterpret_cast<const uint16_t*>(kZeroChunk));
         if (MASKED) mb[SLOT][kk] = mask_bits(mask, mp, ok ? gk : 0, grc);
-      } else if (gk < K && gr < rmax) {
-        if (vec && gr + 7 < rmax) t = *reinterpret_cast<const u32x4*>(src);
-        else {
-          uint16_t* te = reinterpret_cast<uint16_t*>(&t);
-#pragma unroll
-          for (int e = 0; e < 8; ++e) if (gr + e < rmax) te[e] = src[e];
-        }
-        if (MASKED) mb[SLOT][kk] = mask_bits(mask, mp, gk, gr);
+      } else {
+        const int grc = min(gr, (rmax - 1) & ~7);
+        const uint16_t* srcc = p + ((uint32_t)gk * ld + (uint32_t)grc);
+        if (!guard) t = load16_any(srcc);
+        else t = load_row_end(srcc, gk < K, rmax - grc);
+        if (MASKED) mb[SLOT][kk] = mask_bits(mask, mp, !guard || gk < K ? gk : 0, grc);
       }
       v[SLOT][kk] = t;
     }
@@ -225,38 +250,49 @@ template <int R, int EMODE, bool MASKED, int NS> struct RingLoadMN {
 };
 
 // dense, M/N contiguous, kept in LDS as it lies in memory (LdsMN) and transposed by the fragment reads: no
-// transposition in registers, four 16-byte LDS writes per thread and slice.  256-row tiles, whole vectors only.
-template <int R, int EMODE, int NS> struct RingLoadMNT {
-  static_assert(R == 256 && EMODE < 2, "interior and vector-predicated variants of 256-row tiles");
+// transposition in registers, four 16-byte LDS writes per thread and slice.  256-row tiles.
+template <int R, int EMODE, bool MASKED, int NS> struct RingLoadMNT {
+  static_assert(R == 256, "a k-row is 32 chunks");
   static constexpr bool kTr = true;
   static constexpr int NCH = 4;                  // 32 k-rows x 32 chunks over 256 threads
-  static constexpr int kDsWrites = NCH, kVmemReads = NCH, kValuCommit = 0, kValuFetch = 0;
+  static constexpr int kDsWrites = NCH, kVmemReads = NCH * (MASKED ? 2 : 1), kValuCommit = 0, kValuFetch = 0;
   u32x4 v[NS][NCH];
-  const uint16_t* p; uint32_t ld; int r0, rmax, K;
-  __device__ __forceinline__ void init(const void* ptr, int64_t ld_, const uint32_t*, int, int r0_, int rmax_, int K_,
-                                       const StoreView&) {
-    p = static_cast<const uint16_t*>(ptr); ld = (uint32_t)ld_; r0 = r0_; rmax = rmax_; K = K_;
+  uint32_t mb[MASKED ? NS : 1][MASKED ? NCH : 1];
+  const uint16_t* p; const uint32_t* mask; uint32_t ld; int mp, r0, rmax, K;
+  __device__ __forceinline__ void init(const void* ptr, int64_t ld_, const uint32_t* mask_, int mp_, int r0_,
+                                       int rmax_, int K_, const StoreView&) {
+    p = static_cast<const uint16_t*>(ptr); ld = (uint32_t)ld_; mask = mask_; mp = mp_; r0 = r0_; rmax = rmax_; K = K_;
   }
   __device__ __forceinline__ void bounds(int) {}
   __device__ __forceinline__ void configure(int) {}
   template <int SLOT, bool KTAIL = true> __device__ __forceinline__ void fetch(int k0) {
+    const bool guard = EMODE == 2 && KTAIL && k0 + kBK3 + 8 > K;       // as in RingLoadMN
 #pragma unroll
     for (int i = 0; i < NCH; ++i) {
       const int q = i * kGemmThreads + (int)threadIdx.x;
       const int gk = k0 + (q >> 5), gr = r0 + (q & 31) * 8;
       if (EMODE == 0) {
         v[SLOT][i] = *reinterpret_cast<const u32x4*>(p + ((uint32_t)gk * ld + (uint32_t)gr));
+        if (MASKED) mb[SLOT][i] = mask_bits(mask, mp, gk, gr);
+      } else if (EMODE == 2) {
+        const int grc = min(gr, (rmax - 1) & ~7);
+        const uint16_t* src = p + ((uint32_t)gk * ld + (uint32_t)grc);
+        if (!guard) v[SLOT][i] = load16_any(src);
+        else v[SLOT][i] = load_row_end(src, gk < K, rmax - grc);
+        if (MASKED) mb[SLOT][i] = mask_bits(mask, mp, !guard || gk < K ? gk : 0, grc);
       } else {
         // as in the K-contiguous loader: chunks past the edge read the last valid chunk, k-rows past K read zeros
         const int grc = min(gr, rmax - 8);
         const bool ok = !KTAIL || gk < K;
         const uint16_t* src = p + ((uint32_t)gk * ld + (uint32_t)grc);
         v[SLOT][i] = *reinterpret_cast<const u32x4*>(ok ? src : reinterpret_cast<const uint16_t*>(kZeroChunk));
+        if (MASKED) mb[SLOT][i] = mask_bits(mask, mp, ok ? gk : 0, grc);
       }
     }
   }
   template <int SLOT, int STEP> __device__ __forceinline__ void commit_step(uint16_t* lds) {
     const int q = STEP * kGemmThreads + (int)threadIdx.x;
+    if (MASKED) mask_bf16x8(v[SLOT][STEP], mb[SLOT][STEP]);
     *reinterpret_cast<u32x4*>(reinterpret_cast<unsigned char*>(lds) + LdsMN<R>::byte_of((q & 31) * 8, q >> 5)) = v[SLOT][STEP];
   }
 };
@@ -342,11 +378,9 @@ template <int R, int SE, int NS> struct RingLoadSparse {
 template <int KIND, int R, int SE, int EMODE, bool MASKED, int NS> struct RingLoaderOf;
 template <int R, int SE, int EMODE, bool MASKED, int NS> struct RingLoaderOf<kOpK, R, SE, EMODE, MASKED, NS> { typedef RingLoadK<R, EMODE, MASKED, NS> type; };
 template <int R, int SE, int EMODE, bool MASKED, int NS> struct RingLoaderOf<kOpMN, R, SE, EMODE, MASKED, NS> {
-  static constexpr bool kT = R == 256 && EMODE < 2 && !MASKED;
-  // (the transposing-read loader is only named when it is the one chosen: its static_asserts)
-  template <bool T, int DUMMY = 0> struct Pick { typedef RingLoadMN<R, EMODE, MASKED, NS> type; };
-  template <int DUMMY> struct Pick<true, DUMMY> { typedef RingLoadMNT<R, EMODE < 2 ? EMODE : 0, NS> type; };
-  typedef typename Pick<kT>::type type;
+  template <int R_, int DUMMY = 0> struct Pick { typedef RingLoadMN<R_, EMODE, MASKED, NS> type; };
+  template <int DUMMY> struct Pick<256, DUMMY> { typedef RingLoadMNT<256, EMODE, MASKED, NS> type; };
+  typedef typename Pick<R>::type type;
 };
 template <int R, int SE, int EMODE, bool MASKED, int NS> struct RingLoaderOf<kOpSparse, R, SE, EMODE, MASKED, NS> { typedef RingLoadSparse<R, SE, NS> type; };
 
@@ -506,7 +540,6 @@ __device__ __forceinline__ void epilogue_dx_staged(const GemmArgs& g, floatx16 (
       }
   __syncthreads();
   uint16_t* C = reinterpret_cast<uint16_t*>(g.C);
-  const bool vec = (g.ldc & 7) == 0 && (reinterpret_cast<uintptr_t>(g.C) & 15) == 0;
 #pragma unroll
   for (int it = 0; it < NV; ++it) {
     const int c = (int)threadIdx.x + it * kGemmThreads;
@@ -516,8 +549,8 @@ __device__ __forceinline__ void epilogue_dx_staged(const GemmArgs& g, floatx16 (
     u32x4 v = *reinterpret_cast<const u32x4*>(&ct[r * CP + ch * 8]);
     if (g.c_mask) mask_bf16x8(v, mw[it / 4] >> (8 * (it % 4)));
     uint16_t* dst = C + (size_t)row * g.ldc + col;
-    if (vec && col + 8 <= g.N) {
-      *reinterpret_cast<u32x4*>(dst) = v;
+    if (col + 8 <= g.N) {
+      __builtin_memcpy(dst, &v, 16);                       // 16 bytes at element alignment: rows of any width
     } else {
       const uint16_t* ve = reinterpret_cast<const uint16_t*>(&v);
 #pragma unroll
@@ -679,7 +712,9 @@ __global__ __launch_bounds__(kGemmThreads) void gemm3_bf16_kernel(GemmArgs g) {
   // in slot (s - 2) % NS).  The long-K path is written without conditions so that the steady loop is
   // entered with a known set of loads in flight.
   // the steady loop never fetches the last slice of a ragged K: its loads carry no K predicate
-  const int KTs = (EMODE == 1 && (kend - kbeg) % BK != 0) ? KT - 1 : KT;
+  // (any alignment: nor the slices whose chunks could run past the end of the operand)
+  constexpr int kGuarded = EMODE == 2 ? (AK == kOpMN || BKIND == kOpMN ? 2 : 1) : 0;
+  const int KTs = (EMODE == 1 && (kend - kbeg) % BK != 0) ? KT - 1 : KT - kGuarded;
   const bool long_k = KTs > 4 + NS;
   int kt = 0;
   if (long_k) {
