@@ -940,7 +940,7 @@ static int sparse_prefetch_for(const rad_store* s, int lanes_per_row) {
 // whether dW_gemm with rows of dy dy_ld apart runs the store-fed kernel with a split K (the one path that takes a
 // pitched dy): a bf16 store with its own columns per row, sparse enough for that kernel, too few tiles to fill the chip
 static bool dw_pitched_ok(const rad_store* s, int N, int dy_ld) {
-  if (dy_ld <= N || dy_ld % 256 || s->dtype != kBF16 || s->project() || s->steps != 1) return false;
+  if (N <= dw_narrow_max(s->dtype) || dy_ld <= N || dy_ld % 256 || s->dtype != kBF16 || s->project() || s->steps != 1) return false;
   if (s->scheme == RAD_EXACT || s->scheme == RAD_FIXEDK_SHARED) return false;
   if (sparse_prefetch_for(s, 8) > gemm_bf16_sparse_max_prefetch()) return false;
   const int64_t tiles = ((s->cols + 255) / 256) * (int64_t)(dy_ld / 256);
@@ -1013,6 +1013,25 @@ static rad_status dW_gemm(rad_ctx* c, const rad_store* s, int slot, const void* 
     HIP_TRY(c, timed(c, "unpack", [&](const char**) { return launch_unpack(g.sa, kF32, dense, c->stream); }));
     g.A = dense; g.lda = s->cols;
     return run_gemm_call(c, kF32, kOpMN, kOpMN, kEpiStore, g, alg);
+  }
+  if (n_slots == 1 && n_out == N && N <= dw_narrow_max(s->dtype)) {
+    const int splits = dw_narrow_splits(s->rows, s->cols, N);
+    float* out = dW;
+    if (splits > 1) {
+      void* part = nullptr;
+      RAD_TRY(ws_get(c, WS_SPLITK, (size_t)splits * s->cols * N * 4, &part));
+      out = static_cast<float*>(part);
+    }
+    const StoreView v = g.sa;
+    HIP_TRY(c, timed(c, "dw_narrow", [&](const char**) {
+      return launch_dw_narrow(v, s->dtype, s->rows, dy, N, N, bits, bits_pitch, out, splits > 1 ? 0 : beta, splits,
+                              splits > 1 ? (int64_t)s->cols * N : 0, c->stream);
+    }));
+    if (splits > 1)
+      HIP_TRY(c, timed(c, "splitk_reduce", [&](const char**) {
+        return launch_splitk_reduce(out, splits, (int64_t)s->cols * N, dW, beta, c->stream);
+      }));
+    return RAD_OK;
   }
   // Wide bf16 layers whose shape the direct-to-LDS dense kernel takes (whole 256-row tiles of x~, an output width
   // of whole 16-byte vectors, no loader mask): the

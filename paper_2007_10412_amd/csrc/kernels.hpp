@@ -167,6 +167,13 @@ hipError_t launch_flip_weights(const float* W, int Ci, int KH, int KW, int Co, f
 // (ldy > 0: the rows of dy are ldy apart)
 hipError_t launch_dw_overflow(const StoreView& s, int rows, const void* dy, int dtype, int N, const uint32_t* bits,
                               int bits_pitch, float* dW, int cap, const int* max_seg, hipStream_t st, int64_t ldy = 0);
+// dW of a narrow layer from a store with its own columns per row (bf16: paired entries), rows split over workgroups
+// (dw_narrow.hip): partial sums [splits][cols][N] split_stride apart, or (splits 1, stride 0) dW itself
+int dw_narrow_max(int dtype);      // largest N it is the faster one for
+int dw_narrow_splits(int rows, int cols, int N);
+hipError_t launch_dw_narrow(const StoreView& s, int dtype, int rows, const void* dy, int64_t ldy, int N,
+                            const uint32_t* bits, int bits_pitch, float* out, int beta, int splits, int64_t split_stride,
+                            hipStream_t st);
 // entries per (row, bucket) the bf16 sparse dW kernel chosen for `sparse_prefetch` handles itself
 int gemm_bf16_sparse_cap(int sparse_prefetch);
 int gemm_bf16_sparse_max_prefetch();
