@@ -1635,37 +1635,12 @@ extern "C" rad_status rad_model_create_rnn(rad_ctx* c, int64_t batch, int64_t T,
   return RAD_OK;
 }
 
-// BPTT over the unrolled ReLU RNN of Appendix A.  params/grads order:
-// W_ih, W_hh, b, W_ho, b_o.
-static rad_status rnn_step(rad_ctx* c, rad_model* m, const rad_sampling* sm, const void* x, const int32_t* labels,
-                           void* const* params, void* const* grads, float* loss_host) {
-  for (int i = 0; i < 5; ++i)
-    if (!params[i] || !grads[i]) return fail(c, RAD_ERR_NULL, "null parameter or gradient pointer");
-  const int B = (int)m->batch, H = (int)m->hidden, T = (int)m->T, I = (int)m->d_input, C = (int)m->classes;
-  const float* W_ih = static_cast<const float*>(params[0]);
-  const float* W_hh = static_cast<const float*>(params[1]);
-  const float* b = static_cast<const float*>(params[2]);
-  const float* W_ho = static_cast<const float*>(params[3]);
-  const float* b_o = static_cast<const float*>(params[4]);
-  float* dW_ih = static_cast<float*>(grads[0]);
-  float* dW_hh = static_cast<float*>(grads[1]);
-  float* db = static_cast<float*>(grads[2]);
-  float* dW_ho = static_cast<float*>(grads[3]);
-  float* db_o = static_cast<float*>(grads[4]);
-  const float* xs = static_cast<const float*>(x);
+// forward of the recurrent model, a launch per time step (s2: the sampling parameters of h_T's store)
+static rad_status rnn_forward_steps(rad_ctx* c, rad_model* m, const rad_sampling* sm, const rad_sampling& s2,
+                                    const float* xs, const float* W_ih, const float* W_hh, const float* b) {
+  const int B = (int)m->batch, H = (int)m->hidden, T = (int)m->T, I = (int)m->d_input, bp = (H + 31) / 32;
   rad_store* s_hh = m->stores[0];
   rad_store* s_ho = m->stores[1];
-  const int bp = (H + 31) / 32;
-
-  // all keep sets of the step up front: they depend on (seed, step) only
-  RAD_TRY(model_clear_max_seg(c, m));
-  if (T > 1) {
-    rad_sampling s1 = *sm; s1.step = sm->step + 2;      // slot s holds h_{s+1}, drawn with step = s+2
-    RAD_TRY(store_plan(c, s_hh, &s1, m->bitmap_ws, false));
-  }
-  rad_sampling s2 = *sm; s2.stream_id = sm->stream_id + 1; s2.step = 0;
-  RAD_TRY(store_plan(c, s_ho, &s2, m->bitmap_ws ? m->bitmap_ws + s_hh->bitmap_words() : nullptr, false));
-
   // forward: h_t = ReLU(x_t W_ih + h_{t-1} W_hh + b); h_0 = 0 so step 1 has no contraction.
   // Stores whose rows are planned one by one take the samples of h_1 .. h_{T-1} eight steps at a time: the steps'
   // outputs go to a ring of eight row blocks (the chunk buffer of the backward pass, idle now) and one pack launch
@@ -1701,6 +1676,55 @@ static rad_status rnn_step(rad_ctx* c, rad_model* m, const rad_sampling* sm, con
       HIP_TRY(c, timed(c, "pack_f32", [&](const char**) { return launch_pack(ring(t0), kF32, v, c->stream); }));
     }
   }
+  return RAD_OK;
+}
+
+// BPTT over the unrolled ReLU RNN of Appendix A.  params/grads order:
+// W_ih, W_hh, b, W_ho, b_o.
+static rad_status rnn_step(rad_ctx* c, rad_model* m, const rad_sampling* sm, const void* x, const int32_t* labels,
+                           void* const* params, void* const* grads, float* loss_host) {
+  for (int i = 0; i < 5; ++i)
+    if (!params[i] || !grads[i]) return fail(c, RAD_ERR_NULL, "null parameter or gradient pointer");
+  const int B = (int)m->batch, H = (int)m->hidden, T = (int)m->T, I = (int)m->d_input, C = (int)m->classes;
+  const float* W_ih = static_cast<const float*>(params[0]);
+  const float* W_hh = static_cast<const float*>(params[1]);
+  const float* b = static_cast<const float*>(params[2]);
+  const float* W_ho = static_cast<const float*>(params[3]);
+  const float* b_o = static_cast<const float*>(params[4]);
+  float* dW_ih = static_cast<float*>(grads[0]);
+  float* dW_hh = static_cast<float*>(grads[1]);
+  float* db = static_cast<float*>(grads[2]);
+  float* dW_ho = static_cast<float*>(grads[3]);
+  float* db_o = static_cast<float*>(grads[4]);
+  const float* xs = static_cast<const float*>(x);
+  rad_store* s_hh = m->stores[0];
+  rad_store* s_ho = m->stores[1];
+  const int bp = (H + 31) / 32;
+
+  // all keep sets of the step up front: they depend on (seed, step) only
+  RAD_TRY(model_clear_max_seg(c, m));
+  if (T > 1) {
+    rad_sampling s1 = *sm; s1.step = sm->step + 2;      // slot s holds h_{s+1}, drawn with step = s+2
+    RAD_TRY(store_plan(c, s_hh, &s1, m->bitmap_ws, false));
+  }
+  rad_sampling s2 = *sm; s2.stream_id = sm->stream_id + 1; s2.step = 0;
+  RAD_TRY(store_plan(c, s_ho, &s2, m->bitmap_ws ? m->bitmap_ws + s_hh->bitmap_words() : nullptr, false));
+
+  // A small hidden state keeps W_hh in the registers of a workgroup per example: one launch per direction.
+  const bool fused = H <= rnn_fused_max_hidden() && !s_hh->project() && !s_ho->project();
+  RnnArgs ra;
+  if (fused) {
+    std::memset(&ra, 0, sizeof(ra));
+    ra.B = B; ra.T = T; ra.H = H; ra.I = I;
+    ra.xs = xs; ra.W_ih = W_ih; ra.W_hh = W_hh; ra.b = b;
+    ra.hh = {store_view(s_hh, 0), s_hh->plan_rows_per_step, s_hh->scheme == RAD_EXACT};
+    ra.ho = {store_view(s_ho, 0), s_ho->plan_rows_per_step, s_ho->scheme == RAD_EXACT};
+    ra.bits = m->rnn_bits; ra.bp = bp;
+    ra.hT = static_cast<float*>(s_ho->scheme == RAD_EXACT ? s_ho->values : m->act[T & 1]);
+    HIP_TRY(c, timed(c, "rnn_forward", [&](const char**) { return launch_rnn_forward(ra, c->stream); }));
+  } else {
+    RAD_TRY(rnn_forward_steps(c, m, sm, s2, xs, W_ih, W_hh, b));
+  }
   const void* hT = s_ho->scheme == RAD_EXACT ? s_ho->values : m->act[T & 1];
   RAD_TRY(forward_gemm(c, kF32, B, C, H, hT, H, W_ho, b_o, 0, m->logits, nullptr, 0, nullptr, nullptr, 0, 0, nullptr));
   RAD_TRY(softmax_call(c, m->logits, labels, B, C, kF32, m->dyb[0], loss_host ? c->loss_dev : nullptr));
@@ -1709,6 +1733,15 @@ static rad_status rnn_step(rad_ctx* c, rad_model* m, const rad_sampling* sm, con
   float* dz = static_cast<float*>(m->dyb[0]);
   RAD_TRY(dW_gemm(c, s_ho, 0, dz, C, nullptr, 0, dW_ho, 0));
   RAD_TRY(colsum_call(c, dz, kF32, B, C, nullptr, 0, nullptr, 0, 0, db_o, nullptr, 0));
+  if (fused) {
+    float* gT = static_cast<float*>(m->dyb[1]);
+    RAD_TRY(dX_gemm(c, kF32, B, H, C, dz, nullptr, 0, W_ho, gT, m->rnn_bits + (size_t)(T - 1) * B * bp, bp));
+    void* part = nullptr;
+    RAD_TRY(ws_get(c, WS_SPLITK, (size_t)rnn_fused_part_floats(B, H, I) * 4, &part));
+    ra.gT = gT; ra.part = static_cast<float*>(part);
+    HIP_TRY(c, timed(c, "rnn_backward", [&](const char**) { return launch_rnn_backward(ra, dW_hh, db, dW_ih, c->stream); }));
+    return step_finish(c, m, loss_host);
+  }
   // dyb holds g_t = dL/dh_t masked by the ReLU bits of step t (applied in the epilogue of the GEMM that
   // produces it)
   // g_t, t >= 2, goes to row block (t - 2) % G of rnn_g; steps 2 + jG .. 1 + (j + 1)G share a chunk, whose store

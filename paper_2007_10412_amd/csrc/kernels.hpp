@@ -191,6 +191,23 @@ hipError_t launch_reindex(const StoreView& s, int dtype, uint32_t* out_pairs, ui
 bool gemm_f32_ks_ok(const GemmArgs& g, bool b_k_contig);
 hipError_t launch_gemm_f32_ks(const GemmArgs& g, int finish, hipStream_t st);
 
+// Recurrent model with a small hidden state, all time steps in one launch per direction (rnn_fused.hip).  A store is
+// seen from its slot 0; plan_rows: keep rows per slot.  The backward launch adds its workgroups' partial sums
+// (part, rnn_fused_part_floats) into dW_hh, db and dW_ih.
+struct RnnStore { StoreView v; int plan_rows, exact; };
+struct RnnArgs {
+  int B, T, H, I;
+  const float* xs; const float* W_ih; const float* W_hh; const float* b;
+  RnnStore hh, ho;                       // samples of h_1 .. h_{T-1} (slots 0 .. T-2) and of h_T
+  uint32_t* bits; int bp;                // (h_t > 0) bits, [T][B][bp]
+  float* hT;                             // forward: dense h_T
+  const float* gT; float* part;          // backward: dL/dh_T under its ReLU bits; partial sums
+};
+int rnn_fused_max_hidden();
+int64_t rnn_fused_part_floats(int B, int H, int I);
+hipError_t launch_rnn_forward(const RnnArgs& a, hipStream_t st);
+hipError_t launch_rnn_backward(const RnnArgs& a, float* dW_hh, float* db, float* dW_ih, hipStream_t st);
+
 // Convolutions through an LDS-staged input patch (conv.hip).  launch_conv_fwd_direct takes the arguments of the
 // im2col GEMM (A = NCHW input, B = W [(c,u,v)][co], cv_* geometry, the kEpiConv fields) and serves forward and dX;
 // launch_conv_dw_direct writes conv_dw_direct_splits(...) partial sums [ci*ks*ks][co] of dW from the dense x~ and
