@@ -937,6 +937,12 @@ static int sparse_prefetch_for(const rad_store* s, int lanes_per_row) {
   return (int)std::ceil((mean + 6.0 * std::sqrt(mean)) / lanes_per_row);   // overflow beyond this is rare and handled apart
 }
 
+// whether dW of a bf16 store with its own columns per row goes through a dense x~ (see dW_gemm)
+static bool dw_dense_pays(const rad_store* s, int N) {
+  return s->dtype == kBF16 && s->cols % 256 == 0 && N % 8 == 0 && (s->cols / 256) * (int64_t)((N + 255) / 256) >= 128 &&
+         s->rows % 8 == 0 && s->rows >= 1024 && (size_t)s->cols * 2 <= 60 * 1024;
+}
+
 // whether dW_gemm with rows of dy dy_ld apart runs the store-fed kernel with a split K (the one path that takes a
 // pitched dy): a bf16 store with its own columns per row, sparse enough for that kernel, too few tiles to fill the chip
 static bool dw_pitched_ok(const rad_store* s, int N, int dy_ld) {
@@ -1038,9 +1044,7 @@ static rad_status dW_gemm(rad_ctx* c, const rad_store* s, int slot, const void* 
   // store is unpacked into a transient dense x~ (one pass over 2 B D bytes) and contracted by that kernel, which
   // beats scattering every tile's entries into LDS in each of the N / 256 workgroups that need them (4096 x 4096,
   // fraction 0.1: 14 + 92 us against 121 us).
-  const bool dense_pays = s->dtype == kBF16 && n_slots == 1 && !bits && s->cols % 256 == 0 && N % 8 == 0 &&
-                          (s->cols / 256) * (int64_t)((N + 255) / 256) >= 128 && s->rows % 8 == 0 && s->rows >= 1024 &&
-                          (size_t)s->cols * 2 <= 60 * 1024 && (reinterpret_cast<uintptr_t>(dy) & 15) == 0;
+  const bool dense_pays = n_slots == 1 && !bits && dw_dense_pays(s, N) && (reinterpret_cast<uintptr_t>(dy) & 15) == 0;
   if (s->dtype == kBF16 && (dense_pays || g.sparse_prefetch > gemm_bf16_sparse_max_prefetch())) {
     // (also: stores dense enough that scattering into LDS loses to a plain contraction whatever the shape.)
     // x~ is a transient dense operand, one layer's worth, reused by the next layer
@@ -1133,18 +1137,28 @@ static rad_status dX_gemm(rad_ctx* c, int dtype, int M, int d_in, int d_out, con
 
 static rad_status colsum_call(rad_ctx* c, const void* dy, int dtype, int rows, int N, const uint32_t* bits,
                               int bits_pitch, const float* u, int64_t u_ld, int u_n, float* out_bias, float* out_u,
-                              int beta, int u_block_rows = 0, int64_t u_block_stride = 0, int64_t dy_ld = 0) {
+                              int beta, int u_block_rows = 0, int64_t u_block_stride = 0, int64_t dy_ld = 0,
+                              void* g_out = nullptr) {
   int splits = rows / 64;
-  if (rows <= 512) splits = 1;          // few rows: one launch that writes the sums itself
+  if (rows <= 512 && !g_out) splits = 1;          // few rows: one launch that writes the sums itself
   if (splits < 1) splits = 1;
   if (splits > 32) splits = 32;
   void* part = nullptr;
   RAD_TRY(ws_get(c, WS_COLSUM, (size_t)splits * (u_n + 1) * N * 4, &part));
   HIP_TRY(c, timed(c, "colsum", [&](const char**) {
     return launch_colsum(dy, dtype, rows, N, bits, bits_pitch, u, u_ld, u_n, out_bias, out_u, beta,
-                         static_cast<float*>(part), splits, c->stream, u_block_rows, u_block_stride, dy_ld);
+                         static_cast<float*>(part), splits, c->stream, u_block_rows, u_block_stride, dy_ld, g_out, N);
   }));
   return RAD_OK;
+}
+
+// The direct-to-LDS GEMMs cannot mask an operand, and where they apply (whole 256-row tiles, half a wave of workgroups)
+// one pass that writes g = dy masked by the ReLU bits to a context workspace costs less than the masking loaders of the
+// ring kernels: 4096^3, dW 175 -> 95 + 14 (unpack) and dX 176 -> 111 us, the pass 12 us, which the bias gradient needs anyway.
+// m_dim x n_dim: the output of the GEMM; k_dim its contraction.
+static bool premask_pays(int dtype, const uint32_t* bits, int64_t m_dim, int64_t n_dim, int64_t k_dim) {
+  return dtype == kBF16 && bits && m_dim % 256 == 0 && n_dim % 8 == 0 && k_dim % 8 == 0 &&
+         (m_dim / 256) * ((n_dim + 255) / 256) >= 128;
 }
 
 // convolution pieces (defined with the CNN model below)
@@ -1195,6 +1209,14 @@ extern "C" rad_status rad_backward_dW(rad_ctx* c, const rad_layer* L, const rad_
     RAD_TRY(conv_masked_dy(c, L, s, dy, &g));
     return conv_dW_call(c, s, (int)L->batch, L->c_in, L->c_out, L->h, L->w, L->kh, g, dW, dbias);
   }
+  const bool dense = s->scheme == RAD_EXACT || (s->per_entry() && dw_dense_pays(s, (int)L->d_out));
+  if (dense && premask_pays(L->dtype, s->bits, L->d_in, L->d_out, L->batch)) {
+    void* g = nullptr;
+    RAD_TRY(ws_get(c, WS_CONVG, (size_t)L->batch * L->d_out * s->elem(), &g));
+    RAD_TRY(colsum_call(c, dy, L->dtype, (int)L->batch, (int)L->d_out, s->bits, s->bits_pitch, nullptr, 0, 0, dbias, nullptr,
+                        beta != 0.f, 0, 0, 0, g));
+    return dW_gemm(c, s, 0, g, (int)L->d_out, nullptr, 0, dW, beta != 0.f);
+  }
   RAD_TRY(dW_gemm(c, s, 0, dy, (int)L->d_out, s->bits, s->bits_pitch, dW, beta != 0.f));
   if (dbias)
     RAD_TRY(colsum_call(c, dy, L->dtype, (int)L->batch, (int)L->d_out, s->bits, s->bits_pitch, nullptr, 0, 0, dbias,
@@ -1214,6 +1236,13 @@ extern "C" rad_status rad_backward_dX(rad_ctx* c, const rad_layer* L, const rad_
     RAD_TRY(conv_masked_dy(c, L, s, dy, &g));
     return conv_dX_call(c, (int)L->batch, L->c_in, L->c_out, L->h, L->w, L->kh, g, static_cast<const float*>(W),
                         static_cast<float*>(dX));
+  }
+  if (L->d_in % 256 == 0 && premask_pays(L->dtype, s->bits, L->batch, L->d_in, L->d_out)) {
+    void* g = nullptr;
+    RAD_TRY(ws_get(c, WS_CONVG, (size_t)L->batch * L->d_out * s->elem(), &g));
+    RAD_TRY(colsum_call(c, dy, L->dtype, (int)L->batch, (int)L->d_out, s->bits, s->bits_pitch, nullptr, 0, 0, nullptr, nullptr,
+                        0, 0, 0, 0, g));
+    return dX_gemm(c, L->dtype, (int)L->batch, (int)L->d_in, (int)L->d_out, g, nullptr, 0, W, dX);
   }
   return dX_gemm(c, L->dtype, (int)L->batch, (int)L->d_in, (int)L->d_out, dy, s->bits, s->bits_pitch, W, dX);
 }
