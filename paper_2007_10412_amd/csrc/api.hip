@@ -720,21 +720,24 @@ static rad_status forward_gemm(rad_ctx* c, int dtype, int M, int N, int K, const
       return RAD_OK;
     }
   }
-  // fp32, few 64 x 64 tiles and a long contraction (a time step of the recurrent model: 128 x 1024 x 1024 is 32
-  // tiles, each a chain of 64 K-slices): split K eight ways; one kernel then adds the partial sums and does the
-  // epilogue's work (bias, input term, ReLU, bits), and the next store's sample is packed by the pack kernel
-  const int tiles64 = ((M + 63) / 64) * ((N + 63) / 64);
-  if (dtype == kF32 && tiles64 <= 64 && K >= 512) {
-    // whole 32 x 32 tiles: one launch, K split over the waves of a workgroup and added in LDS
+  // fp32, few 64 x 64 tiles (a time step of the recurrent model: 128 x 1024 x 1024 is 32 tiles, each a chain of 64
+  // K-slices): one launch of small tiles with K split over the waves of a workgroup; the next store's sample is packed
+  // by the pack kernel
+  if (dtype == kF32) {
     GemmArgs gk = g;
     gk.bias = bias; gk.relu = relu; gk.y = y; gk.ldy = N; gk.bits = relu ? bits : nullptr; gk.bits_pitch = bits_pitch;
     gk.u = u; gk.u_ld = u_ld; gk.u_n = u_n; gk.V = V;
-    if (gemm_f32_ks_ok(gk, false)) {
+    if (gemm_f32_ks_ok(gk, 1)) {
       HIP_TRY(c, timed(c, "gemm_f32_fwd_ks", [&](const char**) { return launch_gemm_f32_ks(gk, 1, c->stream); }));
       if (next)
         HIP_TRY(c, timed(c, "pack_f32", [&](const char**) { return launch_pack(y, kF32, *next, c->stream); }));
       return RAD_OK;
     }
+  }
+  // what is left of few tiles and a long contraction: split K over workgroups; one kernel then adds the partial sums
+  // and does the epilogue's work (bias, input term, ReLU, bits)
+  const int tiles64 = ((M + 63) / 64) * ((N + 63) / 64);
+  if (dtype == kF32 && tiles64 <= 64 && K >= 512) {
     int splits = K / 128, want = 256 / tiles64;            // about one workgroup per CU
     if (want < 8) want = 8;
     if (want > 32) want = 32;
@@ -946,7 +949,7 @@ static bool dw_dense_pays(const rad_store* s, int N) {
 // whether dW_gemm with rows of dy dy_ld apart runs the store-fed kernel with a split K (the one path that takes a
 // pitched dy): a bf16 store with its own columns per row, sparse enough for that kernel, too few tiles to fill the chip
 static bool dw_pitched_ok(const rad_store* s, int N, int dy_ld) {
-  if (N <= dw_narrow_max(s->dtype) || dy_ld <= N || dy_ld % 256 || s->dtype != kBF16 || s->project() || s->steps != 1) return false;
+  if (dw_narrow_pays(s->dtype, s->rows, N) || dy_ld <= N || dy_ld % 256 || s->dtype != kBF16 || s->project() || s->steps != 1) return false;
   if (s->scheme == RAD_EXACT || s->scheme == RAD_FIXEDK_SHARED) return false;
   if (sparse_prefetch_for(s, 8) > gemm_bf16_sparse_max_prefetch()) return false;
   const int64_t tiles = ((s->cols + 255) / 256) * (int64_t)(dy_ld / 256);
@@ -1020,7 +1023,7 @@ static rad_status dW_gemm(rad_ctx* c, const rad_store* s, int slot, const void* 
     g.A = dense; g.lda = s->cols;
     return run_gemm_call(c, kF32, kOpMN, kOpMN, kEpiStore, g, alg);
   }
-  if (n_slots == 1 && n_out == N && N <= dw_narrow_max(s->dtype)) {
+  if (n_slots == 1 && n_out == N && dw_narrow_pays(s->dtype, s->rows, N)) {
     const int splits = dw_narrow_splits(s->rows, s->cols, N);
     float* out = dW;
     if (splits > 1) {
@@ -1104,15 +1107,18 @@ static rad_status dX_gemm(rad_ctx* c, int dtype, int M, int d_in, int d_out, con
   g.M = M; g.N = d_in; g.K = d_out;
   g.A = dy; g.lda = dy_ld > 0 ? dy_ld : d_out; g.a_mask = bits; g.a_mask_pitch = bits_pitch;
   g.B = W; g.ldb = d_out;
-  // fp32 with few tiles and a long contraction: split K, then add the partial sums under the output mask
-  const int tiles64 = ((M + 63) / 64) * ((d_in + 63) / 64);
-  if (dtype == kF32 && tiles64 <= 64 && d_out >= 512) {
+  // fp32 with few tiles: K split over the waves of a workgroup
+  if (dtype == kF32) {
     GemmArgs gk = g;
     gk.y = dX; gk.ldy = d_in; gk.c_mask = out_bits; gk.c_mask_pitch = out_pitch;
-    if (gemm_f32_ks_ok(gk, true)) {
+    if (gemm_f32_ks_ok(gk, 2)) {
       HIP_TRY(c, timed(c, "gemm_f32_dx_ks", [&](const char**) { return launch_gemm_f32_ks(gk, 2, c->stream); }));
       return RAD_OK;
     }
+  }
+  // what is left of few tiles and a long contraction: split K, then add the partial sums under the output mask
+  const int tiles64 = ((M + 63) / 64) * ((d_in + 63) / 64);
+  if (dtype == kF32 && tiles64 <= 64 && d_out >= 512) {
     int splits = d_out / 128;
     if (splits > 8) splits = 8;
     const int ks = ((d_out + splits - 1) / splits + 31) / 32 * 32;   // whole K slices of the split kernels (32 deep)

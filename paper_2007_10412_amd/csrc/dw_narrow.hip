@@ -195,8 +195,10 @@ static int narrow_nt(int N) {
 // 65536 x 4096 and 4096 x 1000; tile kernel / this one).  fp32: N = 10 9127 / 625 and 461 / 44, 64 7755 / 1003 and
 // 424 / 62, 128 7608 / 1498 and 394 / 74: every width up to 128 (the 64 x 64 tile kernel scatters whole buckets for a
 // quarter of their columns and splits nothing).  bf16, whose tile kernel runs at 16 times the matrix rate with a
-// split K: N = 10 1180 / 505 and 54 / 43, 16 582 / 535 and 45 / 47, 32 582 / 647 and 45 / 59.
-int dw_narrow_max(int dtype) { return dtype == kBF16 ? 12 : 128; }
+// split K: N = 10 1180 / 505 and 54 / 43, 16 582 / 535 and 45 / 47, 32 582 / 647 and 45 / 59.  Few rows are a short
+// contraction for the tile kernel and one pass of mostly latency for this one: 16 rows 3.8 / 5.6, 64 rows x 128 x 64
+// 8.5 / 10.8, 150 rows x 300 x 10 19.3 / 8.6.
+bool dw_narrow_pays(int dtype, int rows, int N) { return rows > 64 && N <= (dtype == kBF16 ? 12 : 128); }
 
 // four workgroups per CU fit; a split takes whole groups of the workgroup's 32 rows
 int dw_narrow_splits(int rows, int cols, int N) {

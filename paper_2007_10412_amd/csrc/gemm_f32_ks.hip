@@ -1,8 +1,8 @@
-// fp32 GEMM for few output tiles and a long contraction (a time step of the recurrent model, Appendix A:
-// 128 x 1024 x 1024): one launch, no partial sums through memory.  A workgroup of eight waves owns a 16 x 32
-// output tile (256 workgroups for the recurrent step: one per CU); every wave takes an eighth of K, brings its own
+// fp32 GEMM for few output tiles (a time step of the recurrent model, Appendix A: 128 x 1024 x 1024; the layers of small
+// networks): one launch, no partial sums through memory.  A workgroup of eight waves owns a 16 x 32
+// output tile (256 workgroups for the recurrent step: one per CU); every wave takes a share of K, brings its own
 // operand slices in through a private LDS area and runs two chains of v_mfma_f32_16x16x4_f32 (the tile's two
-// 16-column halves); the eight waves' accumulators meet in LDS, are added in wave order, and the tile's epilogue
+// 16-column halves); the waves' accumulators meet in LDS, are added in wave order, and the tile's epilogue
 // runs in the same kernel: forward (bias, low-rank input term, ReLU, bits) or dX (output mask of the layer
 // below).  Splitting K over workgroups instead needs a second launch to add the splits (the time steps are a
 // chain of dependent launches, so a launch is what a step costs), and adding them in the same kernel needs
@@ -13,7 +13,8 @@ namespace rad {
 
 namespace {
 
-constexpr int kKsWaves = 8;
+// Workgroups of eight waves, or of four (half the LDS, so that three share a CU) where there are more tiles than CUs.
+constexpr int kKsWavesMax = 8;
 
 // A wave's operand slices reach the MFMA through its own LDS area, 64 k at a time.  K-contiguous operands (A; for
 // dX also B) are loaded with whole 256-byte rows per 16 lanes and stored [rows][64 k] at a pitch of 65 floats, so
@@ -24,16 +25,30 @@ constexpr int kKsWaves = 8;
 constexpr int kKsPitch = 65, kKsHalf = 64;
 constexpr int kKsAreaA = 16 * kKsPitch, kKsAreaB = 32 * kKsPitch;       // floats (B: the larger of the two layouts)
 
-template <bool BK_CONTIG, int FINISH>
+// EDGE: any M, N, K and alignment: rows past the edge read the last row, columns and k past the end are zeros, 16-byte
+// loads at element alignment, guarded stores.
+__device__ __forceinline__ floatx4 load4_any(const float* p, int n) {        // the first n elements, zeros after them
+  floatx4 t = {0.f, 0.f, 0.f, 0.f};
+  if (n >= 4) __builtin_memcpy(&t, p, 16);
+  else {
+#pragma unroll
+    for (int e = 0; e < 3; ++e) if (e < n) t[e] = p[e];
+  }
+  return t;
+}
+
+template <bool BK_CONTIG, int FINISH, bool EDGE, int kKsWaves>
 __global__ __launch_bounds__(64 * kKsWaves) void gemm_f32_ks_kernel(GemmArgs g) {
   extern __shared__ __align__(16) float smem_ks[];
   float (*s_acc)[2][4][64] = reinterpret_cast<float (*)[2][4][64]>(smem_ks);     // [waves][half][elem][lane], at the end
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   const int r = lane & 15, kq = lane >> 4;
-  const int tiles_n = g.N / 32;
+  const int tiles_n = (g.N + 31) / 32;
   const int m0 = ((int)blockIdx.x / tiles_n) * 16, n0 = ((int)blockIdx.x % tiles_n) * 32;
-  const int kw = g.K / kKsWaves;               // K per wave, a multiple of 8
-  const int kbeg = w * kw;
+  // K per wave: a multiple of 8 that covers K with EDGE, an exact share without
+  const int kshare = EDGE ? (g.K + kKsWaves * 8 - 1) / (kKsWaves * 8) * 8 : g.K / kKsWaves;
+  const int kbeg = w * kshare;
+  const int kw = EDGE ? min(kshare, g.K - kbeg) : kshare;          // (may be negative for the last waves: no pass)
   float* As = smem_ks + w * (kKsAreaA + kKsAreaB);          // (the accumulators take this space over at the end)
   float* Bs = As + kKsAreaA;
   const float* Ag = static_cast<const float*>(g.A);
@@ -47,10 +62,10 @@ __global__ __launch_bounds__(64 * kKsWaves) void gemm_f32_ks_kernel(GemmArgs g) 
   float addend[2] = {0.f, 0.f};
   uint32_t keepw = ~0u;
   if (w < 4) {
-    const int row = m0 + 4 * kq + w;
+    const int row = EDGE ? min(m0 + 4 * kq + w, g.M - 1) : m0 + 4 * kq + w;
 #pragma unroll
     for (int jn = 0; jn < 2; ++jn) {
-      const int col = n0 + 16 * jn + r;
+      const int col = EDGE ? min(n0 + 16 * jn + r, g.N - 1) : n0 + 16 * jn + r;
       if (FINISH == 1) {
         if (g.bias) addend[jn] = g.bias[col];
         for (int q = 0; q < g.u_n; ++q) addend[jn] += g.u[(size_t)row * g.u_ld + q] * g.V[(size_t)q * g.N + col];
@@ -62,13 +77,33 @@ __global__ __launch_bounds__(64 * kKsWaves) void gemm_f32_ks_kernel(GemmArgs g) 
   // One pass = 64 k.  The loads of pass p + 1 are issued before the LDS stores and MFMAs of pass p.
   // A: [16 rows][64 k], piece f = lane + 64 i (i < 4) is row f / 16, k 4 (f % 16).  K-contiguous B: [32 rows][64 k],
   // pieces f = lane + 64 i (i < 8).  N-contiguous B: [64 k][32 n], piece f is k f / 8, n 4 (f % 8).
+  // (EDGE, dX: A may come with ReLU bits, element (row, k) is zeroed where its bit is 0)
+  constexpr bool kMaskA = EDGE && FINISH == 2;
   floatx4 av[4], bv4[8];
+  uint32_t am[kMaskA ? 4 : 1];
   auto load_pass = [&](int k0) {
     const int kn = min(kKsHalf, kw - k0);
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
       const int f = lane + 64 * i;
       const int row = f >> 4, c4 = (f & 15) * 4;
+      if constexpr (EDGE) {
+        if (i < 4) {
+          const int arow = min(m0 + row, g.M - 1);
+          av[i] = load4_any(Ag + (size_t)arow * g.lda + kbeg + k0 + c4, kn - c4);
+          if constexpr (kMaskA) {
+            am[i] = ~0u;
+            if (g.a_mask && c4 < kn) am[i] = mask_bits(g.a_mask, g.a_mask_pitch, arow, kbeg + k0 + c4);
+          }
+        }
+        if constexpr (BK_CONTIG) {
+          bv4[i] = load4_any(Bg + (size_t)min(n0 + row, g.N - 1) * g.ldb + kbeg + k0 + c4, kn - c4);
+        } else {
+          const int kk = f >> 3, n4 = (f & 7) * 4;
+          bv4[i] = load4_any(Bg + (size_t)(kbeg + k0 + kk) * g.ldb + n0 + n4, kk < kn ? g.N - n0 - n4 : 0);
+        }
+        continue;
+      }
       if (i < 4) {
         av[i] = floatx4{0.f, 0.f, 0.f, 0.f};
         if (c4 < kn) av[i] = *reinterpret_cast<const floatx4*>(Ag + (size_t)(m0 + row) * g.lda + kbeg + k0 + c4);
@@ -82,16 +117,16 @@ __global__ __launch_bounds__(64 * kKsWaves) void gemm_f32_ks_kernel(GemmArgs g) 
       }
     }
   };
-  load_pass(0);
+  if (!EDGE || kw > 0) load_pass(0);
   for (int k0 = 0; k0 < kw; k0 += kKsHalf) {
-    const int kn = min(kKsHalf, kw - k0);      // k in this pass, a multiple of 8
+    const int kn = min(kKsHalf, kw - k0);      // k in this pass
     __builtin_amdgcn_wave_barrier();           // the reads of the previous pass are done (same wave, in order)
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
       const int f = lane + 64 * i, row = f >> 4, c4 = (f & 15) * 4;
       if (i < 4) {
 #pragma unroll
-        for (int e = 0; e < 4; ++e) As[row * kKsPitch + c4 + e] = av[i][e];
+        for (int e = 0; e < 4; ++e) As[row * kKsPitch + c4 + e] = (!kMaskA || ((am[i] >> e) & 1u)) ? av[i][e] : 0.f;
       }
       if constexpr (BK_CONTIG) {
 #pragma unroll
@@ -142,43 +177,65 @@ __global__ __launch_bounds__(64 * kKsWaves) void gemm_f32_ks_kernel(GemmArgs g) 
     } else if (!((keepw >> (col & 31)) & 1u)) {
       v[jn] = 0.f;
     }
-    static_cast<float*>(g.y)[(size_t)row * g.ldy + col] = v[jn];
+    if (EDGE && (row >= g.M || col >= g.N)) v[jn] = 0.f;
+    else static_cast<float*>(g.y)[(size_t)row * g.ldy + col] = v[jn];
   }
   if (FINISH == 1 && g.bits) {
     // a ballot holds 16 columns of each of four rows: row lane / 16 in bits 16 (lane / 16) ..
     const uint64_t b0 = __ballot(v[0] > 0.f), b1 = __ballot(v[1] > 0.f);
     const uint32_t word = (uint32_t)((b0 >> (16 * kq)) & 0xFFFFu) | ((uint32_t)((b1 >> (16 * kq)) & 0xFFFFu) << 16);
-    if (r == 0) g.bits[(size_t)row * g.bits_pitch + (n0 >> 5)] = word;
+    if (r == 0 && (!EDGE || row < g.M)) g.bits[(size_t)row * g.bits_pitch + (n0 >> 5)] = word;
   }
 }
 
 }  // namespace
 
-// Shapes this kernel takes: whole 16 x 32 tiles, K a multiple of 64 (eight waves, groups of 8), operand rows that
-// are whole 16-byte vectors; no loader masks.
-bool gemm_f32_ks_ok(const GemmArgs& g, bool b_k_contig) {
-  if (g.M < 16 || g.N < 32 || g.K < 512 || g.M % 16 || g.N % 32 || g.K % 64) return false;
-  if (g.a_mask || g.b_mask || g.lda % 4 || (reinterpret_cast<uintptr_t>(g.A) & 15)) return false;
-  if (g.ldb % 4 || (reinterpret_cast<uintptr_t>(g.B) & 15)) return false;
-  return true;
+// A whole 16 x 32 tile grid with K a multiple of 64 and operand rows that are whole 16-byte vectors needs no guards.
+static bool ks_whole(const GemmArgs& g) {
+  if (g.M % 16 || g.N % 32 || g.K % 64 || g.K < 512 || g.a_mask) return false;
+  return !(g.lda % 4 || (reinterpret_cast<uintptr_t>(g.A) & 15) || g.ldb % 4 || (reinterpret_cast<uintptr_t>(g.B) & 15));
+}
+
+// Which products run here instead of on 64 x 64 tiles (32 x 32 x 2 matrix instructions, a serial K, element loads of
+// ragged rows), measured in us, 64 x 64 tiles / here:
+//  - few tiles: forward 150 x 784 x 300 19.7 (two launches) / 8, dX 16.8 / 8; up to 128 of the 64 x 64 tiles, where those
+//    still leave half the chip idle: step of 900-600-300-50, batch 400, 229 / 203 against a limit of 64 tiles; at 256
+//    tiles (1024 x 1024 x 1024) the larger tiles are ahead, 213 / 233 for a layer;
+//  - not a contraction of a few slices, which 64 x 64 tiles finish before the waves here have added up: dX with K = 10
+//    2.6 / 5.0, 64 4.0 / 7.0; forward with K = 64 5.3 / 5.2, 128 7.0 / 6.1, many tiles 512 x 1000 x 64 80 / 83 a layer;
+//  - ragged, more tiles than CUs and a long K: split over workgroups there (300 x 700 x 2000 22.8 / 31.2); so is a very
+//    long K over a handful of tiles (class scores of a wide input: 150 x 10 x 4096 19 / 29, step of a network with
+//    64 x 10 x 8192 104 / 128).
+bool gemm_f32_ks_ok(const GemmArgs& g, int finish) {
+  if (g.b_mask || (g.a_mask && finish != 2) || g.M < 1 || g.N < 1) return false;
+  const int64_t tiles64 = (int64_t)((g.M + 63) / 64) * ((g.N + 63) / 64);
+  const int64_t tiles = (int64_t)((g.M + 15) / 16) * ((g.N + 31) / 32);
+  if (tiles64 > 128 || g.K < (tiles64 > 64 ? 128 : finish == 2 ? 112 : 64)) return false;
+  if (g.K > 2048 && tiles64 <= 64) return false;
+  return ks_whole(g) || tiles64 > 64 || tiles <= 256 || g.K < 512;
+}
+
+template <bool EDGE, int WAVES> static hipError_t launch_ks(const GemmArgs& g, int finish, hipStream_t st) {
+  const dim3 grid(((g.M + 15) / 16) * ((g.N + 31) / 32)), block(64 * WAVES);
+  // every wave's private operand areas; the accumulators (2 KB a wave) take the same space over at the end
+  constexpr size_t smem = (size_t)(WAVES * (kKsAreaA + kKsAreaB)) * 4;
+  auto kern = finish == 1 ? gemm_f32_ks_kernel<false, 1, EDGE, WAVES> : gemm_f32_ks_kernel<true, 2, EDGE, WAVES>;
+  static bool prepared[2] = {false, false};   // one host thread drives a context
+  if (!prepared[finish - 1]) {
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
+    if (e != hipSuccess) return e;
+    prepared[finish - 1] = true;
+  }
+  hipLaunchKernelGGL(kern, grid, block, smem, st, g);
+  return hipGetLastError();
 }
 
 // finish 1: y = act(A B + bias + u V) with ReLU bits (forward); finish 2: y = (A B^T) under c_mask (dX)
 hipError_t launch_gemm_f32_ks(const GemmArgs& g, int finish, hipStream_t st) {
-  const bool b_k = finish == 2;
-  if (!gemm_f32_ks_ok(g, b_k)) return hipErrorInvalidValue;
-  const dim3 grid((g.M / 16) * (g.N / 32)), block(64 * kKsWaves);
-  // every wave's private operand areas; the accumulators (16 KB) take the same space over at the end
-  const size_t smem = (size_t)(kKsWaves * (kKsAreaA + kKsAreaB)) * 4;
-  auto kern = finish == 1 ? gemm_f32_ks_kernel<false, 1> : gemm_f32_ks_kernel<true, 2>;
-  static bool prepared[2] = {false, false};   // one host thread drives a context
-  if (!prepared[b_k]) {
-    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
-    if (e != hipSuccess) return e;
-    prepared[b_k] = true;
-  }
-  hipLaunchKernelGGL(kern, grid, block, smem, st, g);
-  return hipGetLastError();
+  if (!gemm_f32_ks_ok(g, finish)) return hipErrorInvalidValue;
+  if (ks_whole(g)) return launch_ks<false, kKsWavesMax>(g, finish, st);
+  const int64_t tiles = (int64_t)((g.M + 15) / 16) * ((g.N + 31) / 32);
+  return tiles > 256 ? launch_ks<true, 4>(g, finish, st) : launch_ks<true, 8>(g, finish, st);
 }
 
 }  // namespace rad

@@ -170,7 +170,7 @@ hipError_t launch_dw_overflow(const StoreView& s, int rows, const void* dy, int 
                               int bits_pitch, float* dW, int cap, const int* max_seg, hipStream_t st, int64_t ldy = 0);
 // dW of a narrow layer from a store with its own columns per row (bf16: paired entries), rows split over workgroups
 // (dw_narrow.hip): partial sums [splits][cols][N] split_stride apart, or (splits 1, stride 0) dW itself
-int dw_narrow_max(int dtype);      // largest N it is the faster one for
+bool dw_narrow_pays(int dtype, int rows, int N);      // whether it is the faster one
 int dw_narrow_splits(int rows, int cols, int N);
 hipError_t launch_dw_narrow(const StoreView& s, int dtype, int rows, const void* dy, int64_t ldy, int N,
                             const uint32_t* bits, int bits_pitch, float* out, int beta, int splits, int64_t split_stride,
@@ -186,10 +186,10 @@ hipError_t launch_unpack_bitmap(const StoreView& s, int dtype, void* dense, hipS
 // the values in `s` and the keep bitmap / offsets of a fresh plan
 hipError_t launch_reindex(const StoreView& s, int dtype, uint32_t* out_pairs, uint16_t* out_idx, hipStream_t st);
 
-// fp32 GEMM with K split over the eight waves of a workgroup (gemm_f32_ks.hip), whole epilogue in the same launch.
-// finish 1: forward (A K-contiguous, B N-contiguous; bias, u V, ReLU, bits -> y); finish 2: dX (A and B K-contiguous;
-// c_mask -> y).  gemm_f32_ks_ok: whole 16 x 32 tiles, K % 64 == 0, 16-byte aligned rows, no loader masks.
-bool gemm_f32_ks_ok(const GemmArgs& g, bool b_k_contig);
+// fp32 GEMM with K split over the waves of a workgroup (gemm_f32_ks.hip), whole epilogue in the same launch.
+// finish 1: forward (A K-contiguous, B N-contiguous; bias, u V, ReLU, bits -> y); finish 2: dX (A and B K-contiguous,
+// A under a_mask; c_mask -> y).  gemm_f32_ks_ok: whether the product is served there.
+bool gemm_f32_ks_ok(const GemmArgs& g, int finish);
 hipError_t launch_gemm_f32_ks(const GemmArgs& g, int finish, hipStream_t st);
 
 // Recurrent model with a small hidden state, all time steps in one launch per direction (rnn_fused.hip).  A store is
