@@ -198,7 +198,16 @@ static int narrow_nt(int N) {
 // split K: N = 10 1180 / 505 and 54 / 43, 16 582 / 535 and 45 / 47, 32 582 / 647 and 45 / 59.  Few rows are a short
 // contraction for the tile kernel and one pass of mostly latency for this one: 16 rows 3.8 / 5.6, 64 rows x 128 x 64
 // 8.5 / 10.8, 150 rows x 300 x 10 19.3 / 8.6.
-bool dw_narrow_pays(int dtype, int rows, int N) { return rows > 64 && N <= (dtype == kBF16 ? 12 : 128); }
+// Wider fp32 layers: the tile kernel walks all rows as one chain (0.105 us a row, up to 512 tiles at a time), this one
+// does 18.5 T multiply-adds a second plus a pass over its partial sums.  Three calls of a layer, us, tile / here: 150
+// rows 300 x 300 42 / 38, 784 x 300 47 / 48, 1024 x 1024 63 / 74; 300 rows 784 x 300 66 / 62, 1024 x 1024 87 / 97;
+// 512 rows 300 x 300 86 / 62, 1024 x 1024 129 / 121; 1024 rows 784 x 300 164 / 94, 1024 x 1024 211 / 159.
+bool dw_narrow_pays(int dtype, int rows, int cols, int N) {
+  if (rows <= 64) return false;
+  if (dtype == kBF16) return N <= 12;
+  const double out = (double)cols * N;
+  return N <= 128 || rows * (0.105 - out / 18.5e6) > 12.0 + 12.0 * out / 1e6;
+}
 
 // four workgroups per CU fit; a split takes whole groups of the workgroup's 32 rows
 int dw_narrow_splits(int rows, int cols, int N) {

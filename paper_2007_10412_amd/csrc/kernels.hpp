@@ -170,7 +170,7 @@ hipError_t launch_dw_overflow(const StoreView& s, int rows, const void* dy, int 
                               int bits_pitch, float* dW, int cap, const int* max_seg, hipStream_t st, int64_t ldy = 0);
 // dW of a narrow layer from a store with its own columns per row (bf16: paired entries), rows split over workgroups
 // (dw_narrow.hip): partial sums [splits][cols][N] split_stride apart, or (splits 1, stride 0) dW itself
-bool dw_narrow_pays(int dtype, int rows, int N);      // whether it is the faster one
+bool dw_narrow_pays(int dtype, int rows, int cols, int N);      // whether it is the faster one
 int dw_narrow_splits(int rows, int cols, int N);
 hipError_t launch_dw_narrow(const StoreView& s, int dtype, int rows, const void* dy, int64_t ldy, int N,
                             const uint32_t* bits, int bits_pitch, float* out, int beta, int splits, int64_t split_stride,

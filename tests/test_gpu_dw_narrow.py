@@ -23,6 +23,15 @@ def ctx():
                                             ("bf16", "per_example", 0.1), ("bf16", "bernoulli", 0.15),
                                             ("f32", "replace_shared", 0.3)])
 def test_narrow_dW(ctx, n, d, o, dtype, scheme, p):
+    check_dW(ctx, n, d, o, dtype, scheme, p)
+
+
+@pytest.mark.parametrize("n,d,o", [(512, 300, 300), (700, 1030, 515), (160, 257, 290)])
+def test_wider_fp32_layers(ctx, n, d, o):
+    check_dW(ctx, n, d, o, "f32", "per_example", 0.1)
+
+
+def check_dW(ctx, n, d, o, dtype, scheme, p):
     from paper_2007_10412_amd import binding as B
     from tests.gpu_util import dev, host, empty, unpack_bits, assert_grad_close, pack_bits, TOL
     dt = B.RAD_BF16 if dtype == "bf16" else B.RAD_F32
