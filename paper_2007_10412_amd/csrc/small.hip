@@ -555,6 +555,14 @@ __global__ __launch_bounds__(256) void fill_u32_kernel(uint32_t* __restrict__ p,
   const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
   if (i < n) p[i] = v;
 }
+// large arrays (a shared store's dW is zero but for its sampled rows): 16-byte stores, four of a thread's in flight
+constexpr int kFillVecs = 4;
+__global__ __launch_bounds__(256) void fill_vec_kernel(u32x4* __restrict__ p, uint32_t v, int64_t n4) {
+  const int64_t i0 = (int64_t)blockIdx.x * 256 * kFillVecs + threadIdx.x;
+  const u32x4 x = {v, v, v, v};
+#pragma unroll
+  for (int q = 0; q < kFillVecs; ++q) if (i0 + q * 256 < n4) p[i0 + q * 256] = x;
+}
 
 }  // namespace
 
@@ -880,6 +888,11 @@ hipError_t launch_scale_cast(const float* in, void* out, int dtype, int64_t n, f
 
 hipError_t launch_fill_u32(uint32_t* p, uint32_t v, int64_t n, hipStream_t st) {
   if (n <= 0) return hipSuccess;
+  if (n >= 65536 && n % 4 == 0 && (reinterpret_cast<uintptr_t>(p) & 15) == 0) {
+    const int64_t per = 256 * kFillVecs, n4 = n / 4;
+    hipLaunchKernelGGL(fill_vec_kernel, dim3((unsigned)((n4 + per - 1) / per)), dim3(256), 0, st, reinterpret_cast<u32x4*>(p), v, n4);
+    return hipGetLastError();
+  }
   hipLaunchKernelGGL(fill_u32_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, p, v, n);
   return hipGetLastError();
 }
