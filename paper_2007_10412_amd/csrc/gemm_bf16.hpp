@@ -158,14 +158,14 @@ __device__ __forceinline__ u32x4 load_row_end(const uint16_t* p, bool ok, int n)
 }
 
 // dense, M/N contiguous: element (row, k) at p[k*ld + row].  Every thread owns a KPT(k) x 8(row) block
-// (KPT = 4 for 256-row tiles, 2 for 128-row tiles, so that all 256 threads have one and the code is free
-// of predicates) and transposes it in registers: LDS receives, for each of the 8 rows, KPT consecutive k.
+// (KPT = 2 for 128-row tiles, 1 for 64-row tiles, so that all 256 threads have one and the code is free
+// of predicates; 256-row tiles take the loader below) and transposes it in registers: LDS receives, for each of the 8 rows, KPT consecutive k.
 template <int R, int EMODE, bool MASKED, int NS> struct RingLoadMN {
   typedef LdsBF16<R, kBK3> L;
   static constexpr bool kTr = false;
   static constexpr int RB = R / 8;               // row blocks
   static constexpr int KPT = R / 64;             // k rows per thread
-  static_assert(RB * (kBK3 / KPT) == kGemmThreads, "one block per thread");
+  static_assert(KPT <= 2 && RB * (kBK3 / KPT) == kGemmThreads, "one block per thread");
   static constexpr int kDsWrites = 8, kVmemReads = KPT * (MASKED ? 2 : 1);
   static constexpr int kValuCommit = 40, kValuFetch = 8;
   // Which block a thread owns: the SUB threads that share one 16-byte unit (k sub-positions) are neighbours,
@@ -227,17 +227,7 @@ template <int R, int EMODE, bool MASKED, int NS> struct RingLoadMN {
     const int kfirst = kq * KPT;                   // first k of this thread inside the slice
     uint16_t* dlo = &lds[L::unit(rb * 8 + 2 * D, kfirst >> 3) * 8 + (kfirst & 7)];
     uint16_t* dhi = &lds[L::unit(rb * 8 + 2 * D + 1, kfirst >> 3) * 8 + (kfirst & 7)];
-    if constexpr (KPT == 4) {
-      u32x2 lo, hi;
-#pragma unroll
-      for (int q = 0; q < 2; ++q) {
-        const uint32_t a = v[SLOT][2 * q][D], b = v[SLOT][2 * q + 1][D];
-        lo[q] = __builtin_amdgcn_perm(b, a, 0x05040100u);   // (a.lo, b.lo)
-        hi[q] = __builtin_amdgcn_perm(b, a, 0x07060302u);   // (a.hi, b.hi)
-      }
-      *reinterpret_cast<u32x2*>(dlo) = lo;
-      *reinterpret_cast<u32x2*>(dhi) = hi;
-    } else if constexpr (KPT == 2) {
+    if constexpr (KPT == 2) {
       const uint32_t a = v[SLOT][0][D], b = v[SLOT][1][D];
       *reinterpret_cast<uint32_t*>(dlo) = __builtin_amdgcn_perm(b, a, 0x05040100u);
       *reinterpret_cast<uint32_t*>(dhi) = __builtin_amdgcn_perm(b, a, 0x07060302u);

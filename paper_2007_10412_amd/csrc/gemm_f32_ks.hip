@@ -211,7 +211,7 @@ bool gemm_f32_ks_ok(const GemmArgs& g, int finish) {
   const int64_t tiles64 = (int64_t)((g.M + 63) / 64) * ((g.N + 63) / 64);
   const int64_t tiles = (int64_t)((g.M + 15) / 16) * ((g.N + 31) / 32);
   if (tiles64 > 128 || g.K < (tiles64 > 64 ? 128 : finish == 2 ? 112 : 64)) return false;
-  if (g.K > 2048 && tiles64 <= 64) return false;
+  if (g.K > (tiles < 32 ? 1024 : 2048) && tiles64 <= 64) return false;
   return ks_whole(g) || tiles64 > 64 || tiles <= 256 || g.K < 512;
 }
 
