@@ -14,6 +14,7 @@ struct PlanArgs {
   int k_pitch;         // shared scheme: entries between consecutive rows of the compact values (>= k)
   uint64_t thresh;     // Bernoulli: keep iff key < thresh
   int key_shift;       // 0; tests raise it to force equal keys
+  uint32_t guess, gap; // fixed-k schemes: where the k-th smallest of uniform keys is expected, and their mean distance
   uint32_t* bitmap;    // [plan_rows][bm_pitch]
   int bm_pitch;
   uint16_t* bucket_off;  // [plan_rows][nb+1]

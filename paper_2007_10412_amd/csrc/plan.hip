@@ -259,6 +259,112 @@ __global__ __launch_bounds__(kPlanThreads) void plan_fixedk_kernel(PlanArgs a) {
   finish_row(a, prow, s_bm, s_scan);
 }
 
+// Fixed-k per example for rows of up to 1024 columns: a wave per row, four rows a workgroup, no barriers.  A lane holds
+// QPL Philox calls.  Any threshold below which exactly k keys lie selects the row, and the keys are uniform: from
+// k/cols 2^32 on, the count below the threshold says how many mean gaps to move it, and a few counts (a ballot per key slot)
+// find one; the bisection of what is left ends the search when that does not, or when equal keys straddle the cut.
+// With a workgroup per row most of its 256 threads had no key and every pass its barriers: 117450 rows of 100 columns
+// (the recurrent store) 235 us.
+template <int QPL>
+__global__ __launch_bounds__(256) void plan_fixedk_wave_kernel(PlanArgs a) {
+  constexpr int NE = QPL * 4;
+  __shared__ uint32_t s_bm[4][QPL * 8];
+  const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const int prow = blockIdx.x * 4 + w;
+  if (prow >= a.plan_rows) return;
+  const int t_step = prow / a.rows_per_step, b = prow % a.rows_per_step;
+  const uint64_t f0 = (uint64_t)b * (uint64_t)a.cols, q0 = f0 >> 2;
+  const int lead = (int)(f0 & 3);
+  const int nq = (int)(((f0 + (uint64_t)a.cols - 1) >> 2) - q0) + 1;       // <= 64 QPL (the launcher's rule)
+  uint32_t key[NE];
+  uint64_t valid[NE];                        // lanes whose slot e holds an element of the row
+#pragma unroll
+  for (int i = 0; i < QPL; ++i) {
+    const int qi = lane + i * 64;
+    const u32x4 k4 = element_quad_keys(q0 + (uint64_t)qi, a.stream_id, a.step0 + (uint32_t)t_step, a.seed_lo, a.seed_hi);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      key[4 * i + e] = k4[e];
+      const int j = qi * 4 + e - lead;
+      valid[4 * i + e] = __ballot(qi < nq && j >= 0 && j < a.cols);
+    }
+  }
+  auto count = [&](uint32_t t) {             // keys <= t
+    int n = 0;
+#pragma unroll
+    for (int e = 0; e < NE; ++e) n += __popcll(__ballot(key[e] <= t) & valid[e]);
+    return n;
+  };
+  int64_t lo = -1, hi = 0xFFFFFFFFll;        // fewer than k keys are <= lo, k or more are <= hi
+  int64_t t = a.k >= a.cols ? hi : (int64_t)a.guess;
+  bool exact = false;
+  for (int pass = 0; pass < 64; ++pass) {    // (bisection alone needs 33)
+    const int c = count((uint32_t)t);
+    if (c == a.k) { exact = true; break; }
+    if (c < a.k) lo = t; else hi = t;
+    if (hi - lo <= 1) break;                 // several keys equal hi: the cut goes through them
+    t += (int64_t)(a.k - c) * (int64_t)a.gap;
+    if (pass >= 12 || t <= lo || t >= hi) t = lo + (hi - lo) / 2;
+  }
+  uint64_t keep[NE];
+  if (exact) {
+#pragma unroll
+    for (int e = 0; e < NE; ++e) keep[e] = __ballot(key[e] <= (uint32_t)t) & valid[e];
+  } else {
+    // all keys below hi, and of its copies those in the lowest columns (slot-major, then lane, then word)
+    const uint32_t v = (uint32_t)hi;
+    int left = a.k - (lo >= 0 ? count((uint32_t)lo) : 0);
+#pragma unroll
+    for (int i = 0; i < QPL; ++i) {
+      int before = 0, all = 0;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const uint64_t eq = __ballot(key[4 * i + e] == v) & valid[4 * i + e];
+        before += lanes_below(eq); all += __popcll(eq);
+      }
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const bool ok = (valid[4 * i + e] >> lane) & 1ull, same = ok && key[4 * i + e] == v;
+        keep[4 * i + e] = __ballot(ok && (key[4 * i + e] < v || (same && before < left)));
+        before += same ? 1 : 0;
+      }
+      left -= all < left ? all : left;
+    }
+  }
+  // bitmap of the row: nibbles into the wave's words
+  uint32_t* const bm = s_bm[w];
+  if (lane < QPL * 8) bm[lane] = 0u;
+  __builtin_amdgcn_wave_barrier();
+#pragma unroll
+  for (int i = 0; i < QPL; ++i) {
+    uint32_t nib = 0u;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) nib |= (uint32_t)((keep[4 * i + e] >> lane) & 1ull) << e;
+    or_nibble(bm, nib, (lane + i * 64) * 4 - lead, lead);
+  }
+  __builtin_amdgcn_wave_barrier();
+  const uint32_t word = lane < a.bm_pitch ? bm[lane] : 0u;
+  if (lane < a.bm_pitch) a.bitmap[(size_t)prow * a.bm_pitch + lane] = word;
+  const int cnt = __popc(word);
+  int inc = cnt;
+#pragma unroll
+  for (int o = 1; o < QPL * 8; o <<= 1) {
+    const int up = __shfl_up(inc, o);
+    if (lane >= o) inc += up;
+  }
+  const int excl = inc - cnt, after = __shfl(inc, (lane | 7) & 63);         // up to the end of the lane's bucket
+  uint16_t* const bo = a.bucket_off + (size_t)prow * (a.nb + 1);
+  const bool first = (lane & 7) == 0 && (lane >> 3) < a.nb;                // first word of a bucket
+  if (first) bo[lane >> 3] = (uint16_t)excl;
+  if (lane == 0) {
+    bo[a.nb] = (uint16_t)a.k;
+    a.row_ptr[prow] = (uint32_t)((uint64_t)prow * a.k);
+    if (prow == a.plan_rows - 1) a.row_ptr[a.plan_rows] = (uint32_t)((uint64_t)a.plan_rows * a.k);
+  }
+  // running maximum of entries per bucket: an atomic only where a row raises it
+  if (a.max_seg && first && after - excl > *reinterpret_cast<volatile int*>(a.max_seg)) atomicMax(a.max_seg, after - excl);
+}
+
 // With replacement (Section 3.2, the matrix P as printed): draw s of the row maps its key to the column
 // floor(key * cols / 2^32).  The draws are counted per column in LDS (16-bit counters: a count cannot
 // exceed k <= cols <= 16384); a column with a non-zero count is kept once, and its count goes to
@@ -724,6 +830,14 @@ hipError_t launch_plan(const PlanArgs& a, hipStream_t st) {
   // rows start on a Philox call boundary when cols is a multiple of 4
   const int nq_max = (a.cols % 4 == 0) ? a.cols / 4 : a.cols / 4 + 2;
   const int qpt = (nq_max + kPlanThreads - 1) / kPlanThreads;
+  // a wave per row while its lanes hold the row's keys (the test hook's shifted keys are mostly equal: general kernel)
+  if (a.scheme == kFixedKPerExample && a.key_shift == 0 && nq_max <= 256) {
+    const dim3 rows4((unsigned)((a.plan_rows + 3) / 4));
+    if (nq_max <= 64) hipLaunchKernelGGL(plan_fixedk_wave_kernel<1>, rows4, block, 0, st, a);
+    else if (nq_max <= 128) hipLaunchKernelGGL(plan_fixedk_wave_kernel<2>, rows4, block, 0, st, a);
+    else hipLaunchKernelGGL(plan_fixedk_wave_kernel<4>, rows4, block, 0, st, a);
+    return hipGetLastError();
+  }
   const bool full = a.cols == qpt * 4 * kPlanThreads;     // then also a multiple of 4: rows start on a call boundary
   if (qpt <= 1) {
     if (full) hipLaunchKernelGGL((plan_fixedk_kernel<1, true>), grid, block, 0, st, a);
