@@ -9,7 +9,7 @@
 // is fetched a step ahead by keep bitmap): dW_hh, db and dW_ih leave the launch as one partial array per workgroup.
 // What bounds a step is the latency of LDS, barriers and the dependent adds, not arithmetic; one launch per step and
 // product cost 10 us instead.  A training step, fraction 0.1, us, launch per step / this: hidden 100, batch 150, T = 784
-// 17137 / 1789; T = 200: hidden 64 3857 / 401, 128 4668 / 520, 192 5680 / 639 (batch 150), 192 8114 / 1840 (batch 600).
+// 17137 / 1600; T = 200: hidden 64 3857 / 401, 128 4668 / 520, 192 5680 / 639 (batch 150), 192 8114 / 1840 (batch 600).
 // Hidden 192 is where the two arrays fill the registers of a workgroup of 16 waves; wider states keep a launch per step.
 #include "gemm.hpp"
 
@@ -108,13 +108,12 @@ __global__ __launch_bounds__(S::THREADS, 4) void rnn_forward_kernel(RnnArgs a) {
     for (int c = 0; c < CPL; ++c) part[w][c * 64 + lane] = acc[c];
     __syncthreads();
     if (sums) {
-      float s = bias;
-#pragma unroll
-      for (int i = 0; i < IN; ++i) if (IN == 1 || i < a.I) s = fmaf(u[i], V[i], s);
       float p0 = part[0][n], p1 = part[1][n];
 #pragma unroll
       for (int q = 2; q < NW; q += 2) { p0 += part[q][n]; p1 += part[q + 1][n]; }
-      s += p0 + p1;
+      float s = (p0 + p1) + bias;
+#pragma unroll
+      for (int i = 0; i < IN; ++i) if (IN == 1 || i < a.I) s = fmaf(u[i], V[i], s);
       const float h = (n < H && s > 0.f) ? s : 0.f;
       if (n < NW * KPW) hs[t & 1][n] = h;
       // off the chain: bits, the sample of h_t, the dense h_T
@@ -164,9 +163,10 @@ __global__ __launch_bounds__(S::THREADS, 4) void rnn_backward_kernel(RnnArgs a) 
     }
   const bool sums = w < CPL;
   const int n = w * 64 + lane;
-  float db = 0.f, dV[IN], u[IN];
+  // (db and dW_ih are sums of every step: 8 steps at a time, so that hundreds of steps do not cost them digits)
+  float db = 0.f, dV[IN], u[IN], db8 = 0.f, dV8[IN];
 #pragma unroll
-  for (int i = 0; i < IN; ++i) dV[i] = u[i] = 0.f;
+  for (int i = 0; i < IN; ++i) dV[i] = dV8[i] = u[i] = 0.f;
 
   for (int row = blockIdx.x; row < a.B; row += gridDim.x) {
     // sampled h of slot s (what step s + 2 multiplies g with), this lane's columns
@@ -230,9 +230,14 @@ __global__ __launch_bounds__(S::THREADS, 4) void rnn_backward_kernel(RnnArgs a) 
         for (int q = 2; q < NW; q += 2) { p0 += part[q][n]; p1 += part[q + 1][n]; }
         const float gn = ((mask >> (n & 31)) & 1u) ? p0 + p1 : 0.f;
         if (n < NW * KPW) gl[(t & 1) ^ 1][n] = gn;
-        db += g;
+        db8 += g;
 #pragma unroll
-        for (int i = 0; i < IN; ++i) if (IN == 1 || i < a.I) dV[i] = fmaf(u[i], g, dV[i]);
+        for (int i = 0; i < IN; ++i) if (IN == 1 || i < a.I) dV8[i] = fmaf(u[i], g, dV8[i]);
+        if ((t & 7) == 1) {               // (t = 1, the last one, too)
+          db += db8; db8 = 0.f;
+#pragma unroll
+          for (int i = 0; i < IN; ++i) { dV[i] += dV8[i]; dV8[i] = 0.f; }
+        }
         g = gn;
         if (t >= 2) prefetch(t - 1);
       }
