@@ -206,7 +206,7 @@ bool dw_narrow_pays(int dtype, int rows, int cols, int N) {
   if (rows <= 64) return false;
   if (dtype == kBF16) return N <= 12;
   const double out = (double)cols * N;
-  return N <= 128 || rows * (0.105 - out / 18.5e6) > 12.0 + 12.0 * out / 1e6;
+  return N <= 128 || (N <= 16384 && rows * (0.105 - out / 18.5e6) > 12.0 + 12.0 * out / 1e6);
 }
 
 // four workgroups per CU fit; a split takes whole groups of the workgroup's 32 rows
