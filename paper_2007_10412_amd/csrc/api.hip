@@ -23,8 +23,10 @@ struct rad_ctx {
   std::string err;
   int key_shift = 0;
   // side stream of the recurrent model's backward pass (created on first use): the gradients formed per chunk of
-  // time steps run there, beside the chain of dX GEMMs
+  // time steps run there, beside the chain of dX GEMMs.  While calls are enqueued there, `stream` and `side` are
+  // swapped and on_side is 1 (swap_streams).
   hipStream_t side = nullptr;
+  int on_side = 0;
   hipEvent_t ev_ready[2] = {nullptr, nullptr}, ev_done[2] = {nullptr, nullptr}, ev_join = nullptr;
   // timing
   bool timing = false;
@@ -32,9 +34,10 @@ struct rad_ctx {
   struct Rec { std::string name; hipEvent_t a, b; double alg_flops, exe_flops; };
   std::vector<Rec> recs;
   std::vector<hipEvent_t> pool;
-  // grow-only workspaces
-  void* ws[11] = {};
-  size_t ws_bytes[11] = {};
+  // grow-only workspaces, a set for each of the two streams: what is enqueued on one never shares a buffer with what
+  // runs beside it on the other
+  void* ws[2][11] = {};
+  size_t ws_bytes[2][11] = {};
   float* loss_dev = nullptr;
 };
 
@@ -82,20 +85,26 @@ static rad_status hip_fail(rad_ctx* c, hipError_t e, const char* what) {
     if (s__ != RAD_OK) return s__;                                \
   } while (0)
 
+// a workspace of the stream that calls are enqueued on now
 static rad_status ws_get(rad_ctx* c, int which, size_t bytes, void** out) {
-  if (bytes > c->ws_bytes[which]) {
-    if (c->ws[which]) {
-      // either stream may still read the old buffer (the recurrent model's backward pass swaps the two)
-      HIP_TRY(c, hipStreamSynchronize(c->stream));
-      if (c->side) HIP_TRY(c, hipStreamSynchronize(c->side));
-      HIP_TRY(c, hipFree(c->ws[which]));
-      c->ws[which] = nullptr; c->ws_bytes[which] = 0;
+  void*& ws = c->ws[c->on_side][which];
+  size_t& have = c->ws_bytes[c->on_side][which];
+  if (bytes > have) {
+    if (ws) {
+      HIP_TRY(c, hipStreamSynchronize(c->stream));         // it may still read the old buffer
+      HIP_TRY(c, hipFree(ws));
+      ws = nullptr; have = 0;
     }
-    HIP_TRY(c, hipMalloc(&c->ws[which], bytes));
-    c->ws_bytes[which] = bytes;
+    HIP_TRY(c, hipMalloc(&ws, bytes));
+    have = bytes;
   }
-  *out = c->ws[which];
+  *out = ws;
   return RAD_OK;
+}
+
+static void swap_streams(rad_ctx* c) {
+  std::swap(c->stream, c->side);
+  c->on_side ^= 1;
 }
 
 // runs `launch` (which enqueues exactly one logical kernel and reports its
@@ -151,7 +160,8 @@ extern "C" rad_status rad_ctx_destroy(rad_ctx* c) {
   if (c->side) { (void)hipStreamSynchronize(c->side); (void)hipStreamDestroy(c->side); }
   for (hipEvent_t e : {c->ev_ready[0], c->ev_ready[1], c->ev_done[0], c->ev_done[1], c->ev_join}) if (e) (void)hipEventDestroy(e);
   for (auto& e : c->pool) (void)hipEventDestroy(e);
-  for (void* w : c->ws) if (w) (void)hipFree(w);
+  for (auto& set : c->ws)
+    for (void* w : set) if (w) (void)hipFree(w);
   if (c->loss_dev) (void)hipFree(c->loss_dev);
   delete c;
   return RAD_OK;
@@ -1818,7 +1828,7 @@ static rad_status rnn_step(rad_ctx* c, rad_model* m, const rad_sampling* sm, con
       if (side) {
         if (!ok(hipEventRecord(c->ev_ready[half], c->stream), "event record")) break;
         if (!ok(hipStreamWaitEvent(c->side, c->ev_ready[half], 0), "stream wait")) break;
-        std::swap(c->stream, c->side);
+        swap_streams(c);
       }
       rs = dW_gemm(c, s_hh, t - 2, g_of(t), H, nullptr, 0, dW_hh, first_dw ? 0 : 1, n);
       first_dw = false;
@@ -1828,7 +1838,7 @@ static rad_status rnn_step(rad_ctx* c, rad_model* m, const rad_sampling* sm, con
                          dW_ih, first_cs ? 0 : 1, B, I);
       first_cs = false;
       if (side) {
-        std::swap(c->stream, c->side);
+        swap_streams(c);
         if (rs == RAD_OK && ok(hipEventRecord(c->ev_done[half], c->side), "event record")) done_pending[half] = true;
         // the dX below starts the other chunk's rows: their last reader must be through
         if (rs == RAD_OK && done_pending[half ^ 1]) {
