@@ -1670,7 +1670,8 @@ extern "C" rad_status rad_model_create_rnn(rad_ctx* c, int64_t batch, int64_t T,
   m->stores.push_back(s);
   const size_t hb = (size_t)batch * hidden * 4;
   bool ok = true;
-  for (void** p2 : {&m->act[0], &m->act[1], &m->dyb[0], &m->dyb[1]}) ok = ok && hipMalloc(p2, hb) == hipSuccess;
+  for (void** p2 : {&m->act[0], &m->act[1], &m->dyb[1]}) ok = ok && hipMalloc(p2, hb) == hipSuccess;
+  ok = ok && hipMalloc(&m->dyb[0], std::max(hb, (size_t)batch * classes * 4)) == hipSuccess;      // the loss gradient
   ok = ok && hipMalloc(&m->logits, (size_t)batch * classes * 4) == hipSuccess;
   ok = ok && hipMalloc((void**)&m->rnn_bits, (size_t)T * batch * ((hidden + 31) / 32) * 4) == hipSuccess;
   ok = ok && hipMalloc((void**)&m->rnn_g, (size_t)2 * kRnnChunk * hb) == hipSuccess;

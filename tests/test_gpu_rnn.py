@@ -124,3 +124,11 @@ def test_paper_rnn_widths_projected(ctx):
     from paper_2007_10412_amd import synth
     d = synth.rnn(seed=78, batch=150, T=12, d_input=1, hidden=100, classes=10, identity=True)
     run_rnn(ctx, d, 6, 0.1, seed=9)
+
+
+@pytest.mark.parametrize("batch,hidden,classes", [(2048, 2, 10), (5, 1, 700), (64, 200, 500)])
+def test_more_classes_than_hidden_units(ctx, batch, hidden, classes):
+    """The loss gradient (batch x classes) is then the larger of the model's transient gradients."""
+    from paper_2007_10412_amd import synth
+    d = synth.rnn(seed=batch + hidden, batch=batch, T=4, d_input=1, hidden=hidden, classes=classes, identity=False)
+    run_rnn(ctx, d, 1, 0.5, seed=6)
