@@ -205,14 +205,22 @@ static bool ks_whole(const GemmArgs& g) {
 //    2.6 / 5.0, 64 4.0 / 7.0; forward with K = 64 5.3 / 5.2, 128 7.0 / 6.1, many tiles 512 x 1000 x 64 80 / 83 a layer;
 //  - ragged, more tiles than CUs and a long K: split over workgroups there (300 x 700 x 2000 22.8 / 31.2); so is a very
 //    long K over a handful of tiles (class scores of a wide input: 150 x 10 x 4096 19 / 29, step of a network with
-//    64 x 10 x 8192 104 / 128).
+//    64 x 10 x 8192 104 / 128);
+//  - whole tiles (M x K x N, K split over workgroups / here) keep a K of any length here while there is at most one of
+//    them a CU: dX 16 x 1536 x 512 12.6 / 8.7, 16 x 4096 x 4096 32.9 / 19.6, 64 x 4096 x 512 20.6 / 18.9, 64 x 8192 x 512
+//    33.3 / 34.2; with two a CU and K above 2048 not, 64 x 4096 x 4096 31.3 / 37.5.  Forward the same, 16 x 2048 x 512
+//    14.7 / 12.0, 16 x 4096 x 4096 33.3 / 20.8, 64 x 4096 x 2048 22.2 / 21.0, but for a K above 3072 over fewer than 32 of
+//    the 64 x 64 tiles, or above 2048 over fewer than eight here, which is split up to 32 ways there: 16 x 3072 x 512
+//    17.0 / 16.0 and x 64 14.9 / 15.7, 64 x 4096 x 512 18.6 / 20.1, 64 x 8192 x 512 21.8 / 35.4.
 bool gemm_f32_ks_ok(const GemmArgs& g, int finish) {
   if (g.b_mask || (g.a_mask && finish != 2) || g.M < 1 || g.N < 1) return false;
   const int64_t tiles64 = (int64_t)((g.M + 63) / 64) * ((g.N + 63) / 64);
   const int64_t tiles = (int64_t)((g.M + 15) / 16) * ((g.N + 31) / 32);
   if (tiles64 > 128 || g.K < (tiles64 > 64 ? 128 : finish == 2 ? 112 : 64)) return false;
-  if (g.K > (tiles < 32 ? 1024 : 2048) && tiles64 <= 64) return false;
-  return ks_whole(g) || tiles64 > 64 || tiles <= 256 || g.K < 512;
+  if (tiles64 > 64) return true;
+  if (ks_whole(g)) return tiles > 256 ? g.K <= 2048 : finish == 2 || g.K <= (tiles < 8 ? 2048 : 3072) || tiles64 >= 32;
+  if (g.K > (tiles < 32 ? 1024 : 2048)) return false;
+  return tiles <= 256 || g.K < 512;
 }
 
 template <bool EDGE, int WAVES> static hipError_t launch_ks(const GemmArgs& g, int finish, hipStream_t st) {
