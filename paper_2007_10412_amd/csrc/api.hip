@@ -961,7 +961,8 @@ static bool dw_dense_pays(const rad_store* s, int N) {
 // whether dW_gemm with rows of dy dy_ld apart runs the store-fed kernel with a split K (the one path that takes a
 // pitched dy): a bf16 store with its own columns per row, sparse enough for that kernel, too few tiles to fill the chip
 static bool dw_pitched_ok(const rad_store* s, int N, int dy_ld) {
-  if (dw_narrow_pays(s->dtype, s->rows, s->cols, N) || dy_ld <= N || dy_ld % 256 || s->dtype != kBF16 || s->project() || s->steps != 1) return false;
+  if (dy_ld <= N || dy_ld % 256 || s->dtype != kBF16 || s->project() || s->steps != 1) return false;
+  if (dw_narrow_pays(s->dtype, s->rows, s->cols, N, sparse_prefetch_for(s, 8), false)) return false;
   if (s->scheme == RAD_EXACT || s->scheme == RAD_FIXEDK_SHARED) return false;
   if (sparse_prefetch_for(s, 8) > gemm_bf16_sparse_max_prefetch()) return false;
   const int64_t tiles = ((s->cols + 255) / 256) * (int64_t)(dy_ld / 256);
@@ -1035,7 +1036,7 @@ static rad_status dW_gemm(rad_ctx* c, const rad_store* s, int slot, const void* 
     g.A = dense; g.lda = s->cols;
     return run_gemm_call(c, kF32, kOpMN, kOpMN, kEpiStore, g, alg);
   }
-  if (n_slots == 1 && n_out == N && dw_narrow_pays(s->dtype, s->rows, s->cols, N)) {
+  if (n_slots == 1 && n_out == N && dw_narrow_pays(s->dtype, s->rows, s->cols, N, g.sparse_prefetch, bits != nullptr)) {
     const int splits = dw_narrow_splits(s->rows, s->cols, N);
     float* out = dW;
     if (splits > 1) {

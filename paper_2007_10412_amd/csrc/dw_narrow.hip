@@ -8,6 +8,8 @@
 // usual fractions the dense form is as fast as read-modify-write of the sums in LDS and does not depend on the
 // fraction), so the rows are split until the chip is full; the partial sums of a workgroup's four waves are added in
 // LDS and those of the splits by the reduction kernel, both in a fixed order.
+#include <algorithm>
+
 #include "gemm.hpp"
 
 namespace rad {
@@ -191,34 +193,50 @@ static int narrow_nt(int N) {
   return ((N + parts - 1) / parts + 3) / 4 * 4;
 }
 
-// The widest output this kernel serves, both sides measured (us of rad_sample_pack + rad_backward_dW, fraction 0.1,
-// 65536 x 4096 and 4096 x 1000; tile kernel / this one).  fp32: N = 10 9127 / 625 and 461 / 44, 64 7755 / 1003 and
-// 424 / 62, 128 7608 / 1498 and 394 / 74: every width up to 128 (the 64 x 64 tile kernel scatters whole buckets for a
-// quarter of their columns and splits nothing).  bf16, whose tile kernel runs at 16 times the matrix rate with a
-// split K: N = 10 1180 / 505 and 54 / 43, 16 582 / 535 and 45 / 47, 32 582 / 647 and 45 / 59.  Few rows are a short
-// contraction for the tile kernel and one pass of mostly latency for this one: 16 rows 3.8 / 5.6, 64 rows x 128 x 64
-// 8.5 / 10.8, 150 rows x 300 x 10 19.3 / 8.6.
-// Wider fp32 layers: the tile kernel walks all rows as one chain (0.105 us a row, up to 512 tiles at a time), this one
-// does 18.5 T multiply-adds a second plus a pass over its partial sums.  Three calls of a layer, us, tile / here: 150
-// rows 300 x 300 42 / 38, 784 x 300 47 / 48, 1024 x 1024 63 / 74; 300 rows 784 x 300 66 / 62, 1024 x 1024 87 / 97;
-// 512 rows 300 x 300 86 / 62, 1024 x 1024 129 / 121; 1024 rows 784 x 300 164 / 94, 1024 x 1024 211 / 159.
-bool dw_narrow_pays(int dtype, int rows, int cols, int N) {
-  if (rows <= 64) return false;
-  if (dtype == kBF16) return N <= 12;
-  const double out = (double)cols * N;
-  return N <= 128 || (N <= 16384 && rows * (0.105 - out / 18.5e6) > 12.0 + 12.0 * out / 1e6);
+static int64_t narrow_blocks(int cols, int N) {             // workgroups of one split
+  const int nt = narrow_nt(N);
+  return (int64_t)((cols + kBucket - 1) / kBucket) * ((N + nt - 1) / nt);
 }
+static int narrow_groups(int rows) { return (rows + kRows * kWaves - 1) / (kRows * kWaves); }
 
 // four workgroups per CU fit; a split takes whole groups of the workgroup's 32 rows
 int dw_narrow_splits(int rows, int cols, int N) {
-  const int nt = narrow_nt(N);
-  const int64_t blocks = (int64_t)((cols + kBucket - 1) / kBucket) * ((N + nt - 1) / nt);
+  const int64_t blocks = narrow_blocks(cols, N);
   int64_t splits = blocks < 1024 ? 1024 / blocks : 1;       // rounded down: one wave of workgroups and no remainder
-  const int groups = (rows + kRows * kWaves - 1) / (kRows * kWaves);
+  const int groups = narrow_groups(rows);
   if (splits > groups) splits = groups;
   if (splits > 128) splits = 128;
   const int per = (int)((groups + splits - 1) / splits);
   return (groups + per - 1) / per;
+}
+
+// Whether this kernel is faster than the tile kernels, both sides measured (us of rad_backward_dW, tile kernel / here).
+// bf16, whose tile kernel runs at 16 times the matrix rate with a split K, up to 12 columns: 65536 x 4096 x 10 792 / 130,
+// 4096 x 1000 x 10 28 / 17, 150 x 784 x 10 12.8 / 9.2; with the sampling 16 columns 582 / 535 and 45 / 47, 32 582 / 647.
+// Not 64 rows or fewer, a short contraction there and a pass of mostly latency here: 16 rows 3.8 / 5.6.
+// fp32 up to 12 columns (100 x 4096 x 10 12.5 / 8.8, 65536 x 4096 x 10 7318 / 132), and wider where an estimate of each
+// side says so.  The tile kernel walks all rows as one chain, 0.07 us a row and more with the tiles a CU has, nearly
+// twice that where a bucket's entries take its wide loader, so the fraction counts; here a round of up to 1024 workgroups
+// takes 3 to 5 us per group of 32 rows and every split writes and adds an array of partial sums.  The estimates are
+// within 15 % of nine tenths of 1650 calls (65 to 8192 rows, 64 to 65535 columns, 4 to 8000 outputs, fractions 0.02 to
+// 0.5), the choice within 11 % of the better side in all but five: at fraction 0.1 100 x 1024 x 100 12 / 13,
+// 65 x 4096 x 128 8.8 / 19, 200 x 4096 x 128 19 / 32, 1000 x 65535 x 128 217 / 258, 4096 x 1000 x 128 306 / 47,
+// 150 x 784 x 300 15 / 19, 300 x 784 x 300 25 / 28, 512 x 784 x 300 40 / 27, 512 x 1024 x 1024 41 / 48, 1024 x 1024 x 1024
+// 79 / 64; at 0.5 300 x 784 x 300 47 / 30, 512 x 1024 x 1024 78 / 57.  Above a million outputs with more than 128 columns
+// the two are close or unmeasured, and a grid's third axis holds 65535 parts.
+bool dw_narrow_pays(int dtype, int rows, int cols, int N, int sparse_prefetch, bool masked) {
+  if (rows <= 64) return false;
+  if (dtype == kBF16 || N <= 12) return N <= 12;
+  if (N > 128 && (N > 16384 || (int64_t)cols * N > (1 << 20))) return false;
+  const bool wide = f32_sparse_wide(sparse_prefetch);
+  const double out = (double)cols * N / 1e6, blocks = (double)narrow_blocks(cols, N);
+  const int splits = dw_narrow_splits(rows, cols, N), per = (narrow_groups(rows) + splits - 1) / splits;
+  const double group = 2.8 + (wide ? 2.0 : 0.4) * std::min(1.0, blocks * splits / 1024);
+  const double here = 3.0 + 4.5 * narrow_nt(N) / 16 + per * std::max(1.0, blocks / 1024) * group + (splits > 1 ? 6.4 * splits * out : 0.0);
+  const double tiles128 = ((cols + 127) / 128) * (double)((N + 127) / 128), tiles64 = ((cols + 63) / 64) * (double)((N + 63) / 64);
+  const double load = tiles128 >= 192 ? tiles128 / 256 : tiles64 / 512;
+  const double row = (wide ? 0.126 : 0.069) * std::max(1.0, load) + (wide ? 0.030 : 0.019) * std::min(1.0, load) + (masked ? 0.010 : 0.0);
+  return here < 3.5 + rows * row;
 }
 
 hipError_t launch_dw_narrow(const StoreView& s, int dtype, int rows, const void* dy, int64_t ldy, int N,
@@ -228,8 +246,7 @@ hipError_t launch_dw_narrow(const StoreView& s, int dtype, int rows, const void*
   NarrowArgs a;
   a.s = s; a.rows = rows; a.N = N; a.M = s.cols; a.dy = dy; a.ldy = ldy; a.bits = bits; a.bits_pitch = bits_pitch;
   a.out = out; a.split_stride = split_stride; a.beta = beta;
-  const int groups = (rows + kRows * kWaves - 1) / (kRows * kWaves);
-  a.rows_per_split = (groups + splits - 1) / splits * (kRows * kWaves);
+  a.rows_per_split = (narrow_groups(rows) + splits - 1) / splits * (kRows * kWaves);
   return dtype == kBF16 ? launch_t<uint16_t>(a, narrow_nt(N), splits, st) : launch_t<float>(a, narrow_nt(N), splits, st);
 }
 

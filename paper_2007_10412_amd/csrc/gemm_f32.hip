@@ -18,7 +18,7 @@ hipError_t launch_gemm_f32(int a_kind, int b_kind, int epi, const GemmArgs& g, h
     if (big) { nm = "gemm_f32_dw_dense_128"; e = run_gemm<F32Tag, kOpMN, kOpMN, kEpiStore, 128, 128, 16, 0, false, true>(g, st); }
     else { nm = "gemm_f32_dw_dense_64"; e = run_gemm<F32Tag, kOpMN, kOpMN, kEpiStore, 64, 64, 16, 0, false, true>(g, st); }
   } else if (a_kind == kOpSparse && b_kind == kOpMN && epi == kEpiStore) {
-    const bool wide = g.sparse_prefetch > 4;
+    const bool wide = f32_sparse_wide(g.sparse_prefetch);
     if (big) {
       if (wide) { nm = "gemm_f32_dw_sparse_128"; e = run_gemm<F32Tag, kOpSparse, kOpMN, kEpiStore, 128, 128, 16, 16, false, true, false>(g, st); }
       else { nm = "gemm_f32_dw_sparse_128"; e = run_gemm<F32Tag, kOpSparse, kOpMN, kEpiStore, 128, 128, 16, 4, false, true, false>(g, st); }

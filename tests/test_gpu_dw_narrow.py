@@ -63,3 +63,19 @@ def check_dW(ctx, n, d, o, dtype, scheme, p):
         assert_grad_close(host(dW), 2 * want, TOL[B.RAD_F32], n, "dW + dW")
     finally:
         B.rad_store_destroy(st)
+
+
+@pytest.mark.parametrize("n,d,o,p,here", [(150, 784, 10, 0.1, True), (65, 4096, 128, 0.1, False), (200, 4096, 128, 0.1, False),
+                                          (600, 4096, 128, 0.1, True), (200, 784, 300, 0.1, False), (200, 784, 300, 0.5, True),
+                                          (512, 1024, 1024, 0.1, False), (512, 1024, 1024, 0.5, True), (64, 784, 10, 0.1, False)])
+def test_faster_route(ctx, n, d, o, p, here):
+    """The side that was measured as the faster one is taken, and the product is right on both."""
+    from paper_2007_10412_amd import binding as B
+    B.rad_ctx_timing(ctx, "dw_narrow")
+    B.rad_ctx_timing_reset(ctx)
+    try:
+        check_dW(ctx, n, d, o, "f32", "per_example", p)
+        assert B.rad_ctx_timing_read(ctx, None)[0] == (2 if here else 0)
+    finally:
+        B.rad_ctx_timing(ctx, "")
+        B.rad_ctx_timing_reset(ctx)

@@ -56,11 +56,11 @@ def test_split_sums_of_both_streams(ctx, batch, hidden, T, seed, scheme):  # noq
         B.rad_ctx_timing(ctx, kernel)                                    # chunk's; their reductions and T - 2 or more of dX
         B.rad_ctx_timing_reset(ctx)
         try:
-            runs = step_twice(ctx, d, scheme, 0.1, seed=9)
+            runs = step_twice(ctx, d, scheme, 0.3, seed=9)
             assert B.rad_ctx_timing_read(ctx, kernel)[0] >= 3 * least
         finally:
             B.rad_ctx_timing(ctx, "")
             B.rad_ctx_timing_reset(ctx)
         assert_identical(*runs)
-    assert_identical(*step_twice(ctx, d, scheme, 0.1, seed=9))
-    run_rnn(ctx, d, scheme, 0.1, seed=9)
+    assert_identical(*step_twice(ctx, d, scheme, 0.3, seed=9))
+    run_rnn(ctx, d, scheme, 0.3, seed=9)
