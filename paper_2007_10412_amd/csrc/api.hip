@@ -569,8 +569,8 @@ static rad_status store_plan(rad_ctx* c, rad_store* s, const rad_sampling* sm, u
   a.rows_per_step = s->rows;
   a.cols = s->cols; a.k = s->k; a.k_pitch = s->k_pitch;
   a.thresh = (uint64_t)std::llround(s->p * 4294967296.0) >> c->key_shift;
-  a.guess = (uint32_t)std::min(4294967295.0, std::floor((double)s->k / (double)s->cols * 4294967296.0));
-  a.gap = (uint32_t)std::min(4294967295.0, std::floor(4294967296.0 / (double)s->cols));
+  a.guess = (uint32_t)std::min(4294967295.0, std::floor((double)s->k / (double)s->cols * 4294967296.0)) >> c->key_shift;
+  a.gap = (uint32_t)std::min(4294967295.0, std::floor(4294967296.0 / (double)s->cols)) >> c->key_shift;
   a.key_shift = c->key_shift;
   c->key_shift = 0;                 // the test hook serves one draw: it cannot be left on
   a.bitmap = bitmap; a.bm_pitch = s->bm_pitch;

@@ -284,7 +284,7 @@ __global__ __launch_bounds__(256) void plan_fixedk_wave_kernel(PlanArgs a) {
     const u32x4 k4 = element_quad_keys(q0 + (uint64_t)qi, a.stream_id, a.step0 + (uint32_t)t_step, a.seed_lo, a.seed_hi);
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
-      key[4 * i + e] = k4[e];
+      key[4 * i + e] = k4[e] >> a.key_shift;
       const int j = qi * 4 + e - lead;
       valid[4 * i + e] = __ballot(qi < nq && j >= 0 && j < a.cols);
     }
@@ -830,8 +830,8 @@ hipError_t launch_plan(const PlanArgs& a, hipStream_t st) {
   // rows start on a Philox call boundary when cols is a multiple of 4
   const int nq_max = (a.cols % 4 == 0) ? a.cols / 4 : a.cols / 4 + 2;
   const int qpt = (nq_max + kPlanThreads - 1) / kPlanThreads;
-  // a wave per row while its lanes hold the row's keys (the test hook's shifted keys are mostly equal: general kernel)
-  if (a.scheme == kFixedKPerExample && a.key_shift == 0 && nq_max <= 256) {
+  // a wave per row while its lanes hold the row's keys
+  if (a.scheme == kFixedKPerExample && nq_max <= 256) {
     const dim3 rows4((unsigned)((a.plan_rows + 3) / 4));
     if (nq_max <= 64) hipLaunchKernelGGL(plan_fixedk_wave_kernel<1>, rows4, block, 0, st, a);
     else if (nq_max <= 128) hipLaunchKernelGGL(plan_fixedk_wave_kernel<2>, rows4, block, 0, st, a);
