@@ -1,6 +1,7 @@
-"""GPU parity of the dW of narrow layers from a compressed store against the oracle's product with the exported sample:
-widths around the kernel's vectors and parts, rows around its groups of 8 and 32, columns around a 256-column bucket,
-ReLU bits, accumulation, and rows with more entries than the kernel holds in registers."""
+"""GPU parity of the dW of narrow layers from a compressed store against the oracle's product with the exported sample, on
+both sides of the rule that chooses the row-split kernel: widths around its vectors and parts, rows around its groups of 8
+and 32, columns around a 256-column bucket, ReLU bits, accumulation, one split, and rows with more entries than it holds
+in registers."""
 import numpy as np
 import pytest
 
@@ -24,6 +25,41 @@ def ctx():
                                             ("f32", "replace_shared", 0.3)])
 def test_narrow_dW(ctx, n, d, o, dtype, scheme, p):
     check_dW(ctx, n, d, o, dtype, scheme, p)
+
+
+def check_here(ctx, *case):
+    """check_dW, with both of its calls on the row-split kernel."""
+    from paper_2007_10412_amd import binding as B
+    B.rad_ctx_timing(ctx, "dw_narrow")
+    B.rad_ctx_timing_reset(ctx)
+    try:
+        check_dW(ctx, *case)
+        assert B.rad_ctx_timing_read(ctx, None)[0] == 2
+    finally:
+        B.rad_ctx_timing(ctx, "")
+        B.rad_ctx_timing_reset(ctx)
+
+
+@pytest.mark.parametrize("n", [65, 71, 72, 73, 95, 96, 97])
+@pytest.mark.parametrize("d", [3, 255, 256, 257])
+@pytest.mark.parametrize("o", [1, 4, 5, 12])
+@pytest.mark.parametrize("dtype,scheme,p", [("f32", "bernoulli", 0.1), ("f32", "per_example", 0.7), ("bf16", "per_example", 0.1),
+                                            ("bf16", "bernoulli", 0.5), ("bf16", "replace_shared", 0.3)])
+def test_edges_of_groups_and_buckets(ctx, n, d, o, dtype, scheme, p):
+    check_here(ctx, n, d, o, dtype, scheme, p)
+
+
+@pytest.mark.parametrize("n,d", [(257, 255), (300, 513), (320, 256)])
+@pytest.mark.parametrize("o", [13, 16, 17, 33, 100, 128, 129])
+@pytest.mark.parametrize("scheme,p", [("bernoulli", 0.1), ("per_example", 0.7)])
+def test_widths_of_several_parts(ctx, n, d, o, scheme, p):
+    check_here(ctx, n, d, o, "f32", scheme, p)
+
+
+def test_one_split(ctx):
+    """256 buckets by three parts: the rows are not split and the kernel writes (and accumulates into) dW itself."""
+    check_here(ctx, 300, 65535, 40, "f32", "bernoulli", 0.02)
+    check_here(ctx, 300, 65535, 41, "f32", "bernoulli", 0.3)
 
 
 @pytest.mark.parametrize("n,d,o", [(512, 300, 300), (700, 1030, 515), (160, 257, 290)])
@@ -71,11 +107,13 @@ def check_dW(ctx, n, d, o, dtype, scheme, p):
 def test_faster_route(ctx, n, d, o, p, here):
     """The side that was measured as the faster one is taken, and the product is right on both."""
     from paper_2007_10412_amd import binding as B
+    if here:
+        return check_here(ctx, n, d, o, "f32", "per_example", p)
     B.rad_ctx_timing(ctx, "dw_narrow")
     B.rad_ctx_timing_reset(ctx)
     try:
         check_dW(ctx, n, d, o, "f32", "per_example", p)
-        assert B.rad_ctx_timing_read(ctx, None)[0] == (2 if here else 0)
+        assert B.rad_ctx_timing_read(ctx, None)[0] == 0
     finally:
         B.rad_ctx_timing(ctx, "")
         B.rad_ctx_timing_reset(ctx)

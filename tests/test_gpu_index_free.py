@@ -156,6 +156,28 @@ def test_paper_convnet_keeps_the_bytes_the_paper_counts(ctx):
     assert 4 * (sum(ks) + 10) + (16384 + 8192 + 8192 + 2048) / 8 == 19560
 
 
+@pytest.mark.parametrize("scheme", [1, 3, 5])
+@pytest.mark.parametrize("T", [2, 3, 21])
+def test_wide_rnn_equals_indexed_model(ctx, scheme, T):
+    """Hidden above 192: x~ of a chunk of time steps is rebuilt on the side stream, from the keep bitmap of the step's own
+    plan, or (T = 2, a store of one step) by drawing again.  Stores and loss are the same bits; the gradients sum the same
+    products in the order of another kernel."""
+    from paper_2007_10412_amd import synth
+    from tests.test_gpu_rnn_streams import step_twice, assert_identical
+    from tests.gpu_util import assert_grad_close
+    d = synth.rnn(seed=40 + T, batch=24, T=T, d_input=1, hidden=200, classes=10, identity=False)
+    res = {}
+    for mode in (False, True):
+        a, b = step_twice(ctx, d, scheme, 0.2, seed=9, index_free=mode)
+        assert_identical(a, b)
+        res[mode] = a
+    assert res[False][0] == res[True][0]
+    for u, v in zip(res[False][2], res[True][2]):
+        assert np.array_equal(u, v)
+    for u, v in zip(res[True][1], res[False][1]):
+        assert_grad_close(u, v, 1e-5, T * 24)
+
+
 @pytest.mark.parametrize("scheme", [3, 1])
 def test_paper_rnn_keeps_the_bytes_the_paper_counts(ctx, scheme):
     """The recurrent architecture of Appendix A (hidden state 100, one-dimensional input, 784 steps) at fraction
