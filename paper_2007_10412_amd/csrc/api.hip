@@ -1436,7 +1436,8 @@ struct rad_model {
   int64_t T = 0, d_input = 0, hidden = 0, classes = 0;
   uint32_t* rnn_bits = nullptr;         // [T][batch][hidden/32]
   float* rnn_g = nullptr;               // [2][kRnnChunk][batch][hidden]: g of the time steps whose dW is formed together,
-                                        // two chunks: one being read by the side stream, one being filled
+                                        // two chunks: one being read by the side stream, one being filled (none
+                                        // where all time steps are one launch per direction)
   uint32_t* bitmap_ws = nullptr;        // keep bitmaps of every step (transient within a step)
   // CNN
   struct Conv { int ci, co, h, w, pool; uint32_t* arg; };
@@ -1647,6 +1648,11 @@ static rad_status mlp_step(rad_ctx* c, rad_model* m, const rad_sampling* sm, con
   return step_finish(c, m, loss_host);
 }
 
+// A small hidden state keeps W_hh in the registers of a workgroup per example: one launch per direction.
+static bool rnn_one_launch(const rad_model* m) {
+  return m->hidden <= rnn_fused_max_hidden() && !m->stores[0]->project() && !m->stores[1]->project();
+}
+
 extern "C" rad_status rad_model_create_rnn(rad_ctx* c, int64_t batch, int64_t T, int64_t d_input, int64_t hidden,
                                            int64_t classes, int32_t scheme, double p, rad_model** out) {
   if (!c) return RAD_ERR_NULL;
@@ -1675,7 +1681,7 @@ extern "C" rad_status rad_model_create_rnn(rad_ctx* c, int64_t batch, int64_t T,
   ok = ok && hipMalloc(&m->dyb[0], std::max(hb, (size_t)batch * classes * 4)) == hipSuccess;      // the loss gradient
   ok = ok && hipMalloc(&m->logits, (size_t)batch * classes * 4) == hipSuccess;
   ok = ok && hipMalloc((void**)&m->rnn_bits, (size_t)T * batch * ((hidden + 31) / 32) * 4) == hipSuccess;
-  ok = ok && hipMalloc((void**)&m->rnn_g, (size_t)2 * kRnnChunk * hb) == hipSuccess;
+  if (!rnn_one_launch(m)) ok = ok && hipMalloc((void**)&m->rnn_g, (size_t)2 * kRnnChunk * hb) == hipSuccess;
   const size_t bmw = m->stores[0]->bitmap_words() + m->stores[1]->bitmap_words();
   if (bmw) ok = ok && hipMalloc((void**)&m->bitmap_ws, bmw * 4) == hipSuccess;
   if (!ok) { rad_model_destroy(m); return fail(c, RAD_ERR_DEVICE, "model allocation failed"); }
@@ -1759,8 +1765,7 @@ static rad_status rnn_step(rad_ctx* c, rad_model* m, const rad_sampling* sm, con
   rad_sampling s2 = *sm; s2.stream_id = sm->stream_id + 1; s2.step = 0;
   RAD_TRY(store_plan(c, s_ho, &s2, m->bitmap_ws ? m->bitmap_ws + s_hh->bitmap_words() : nullptr, false));
 
-  // A small hidden state keeps W_hh in the registers of a workgroup per example: one launch per direction.
-  const bool fused = H <= rnn_fused_max_hidden() && !s_hh->project() && !s_ho->project();
+  const bool fused = rnn_one_launch(m);
   RnnArgs ra;
   if (fused) {
     std::memset(&ra, 0, sizeof(ra));
