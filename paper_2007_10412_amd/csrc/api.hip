@@ -1173,7 +1173,8 @@ static rad_status colsum_call(rad_ctx* c, const void* dy, int dtype, int rows, i
 
 // The direct-to-LDS GEMMs cannot mask an operand, and where they apply (whole 256-row tiles, half a wave of workgroups)
 // one pass that writes g = dy masked by the ReLU bits to a context workspace costs less than the masking loaders of the
-// ring kernels: 4096^3, dW 175 -> 95 + 14 (unpack) and dX 176 -> 111 us, the pass 12 us, which the bias gradient needs anyway.
+// ring kernels: 4096^3, dW 175 -> 95 + 14 (unpack) and dX 176 -> 105 us, the pass 20 us a call, which on the dW side has the
+// bias gradient in it.
 // m_dim x n_dim: the output of the GEMM; k_dim its contraction.
 static bool premask_pays(int dtype, const uint32_t* bits, int64_t m_dim, int64_t n_dim, int64_t k_dim) {
   return dtype == kBF16 && bits && m_dim % 256 == 0 && n_dim % 8 == 0 && k_dim % 8 == 0 &&

@@ -242,7 +242,7 @@ bool dw_narrow_pays(int dtype, int rows, int cols, int N, int sparse_prefetch, b
 hipError_t launch_dw_narrow(const StoreView& s, int dtype, int rows, const void* dy, int64_t ldy, int N,
                             const uint32_t* bits, int bits_pitch, float* out, int beta, int splits, int64_t split_stride,
                             hipStream_t st) {
-  if (s.nb > 65535 || splits < 1 || splits > 128) return hipErrorInvalidValue;
+  if (splits < 1 || splits > 128) return hipErrorInvalidValue;
   NarrowArgs a;
   a.s = s; a.rows = rows; a.N = N; a.M = s.cols; a.dy = dy; a.ldy = ldy; a.bits = bits; a.bits_pitch = bits_pitch;
   a.out = out; a.split_stride = split_stride; a.beta = beta;
