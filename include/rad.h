@@ -178,6 +178,13 @@ rad_status rad_probe_ceiling(rad_ctx* ctx, int32_t kind, const void* operands, v
  * 0 cancels it.  Not for index-free stores (their backward pass draws again). */
 rad_status rad_debug_key_shift(rad_ctx* ctx, int32_t shift);
 
+/* Test hook: in the next recurrent step of a hidden width of 193 to 1024, the
+ * kernels' waits for the other workgroups give up after `polls` looks (at
+ * least 1), so that the chunks of time steps are computed by the kernel that
+ * stands in for such launches.  The library returns to its own limit after
+ * that step; 0 cancels the hook. */
+rad_status rad_debug_poll_limit(rad_ctx* ctx, int32_t polls);
+
 /* Allocates the store for `layer` under `scheme`/`p`: value and index arrays
  * sized for batch*k entries (fixed-k), batch*d_in (EXACT), or the Bernoulli
  * mean plus eight standard deviations; row pointers, per-256-column offsets,

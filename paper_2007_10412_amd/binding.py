@@ -65,6 +65,7 @@ SIGNATURES = {
     "rad_ctx_timing_read_flops": (C.c_int, [P, C.c_char_p, C.POINTER(C.c_double), C.POINTER(C.c_double)]),
     "rad_ctx_timing_reset": (C.c_int, [P]),
     "rad_debug_key_shift": (C.c_int, [P, C.c_int32]),
+    "rad_debug_poll_limit": (C.c_int, [P, C.c_int32]),
     "rad_probe_ceiling": (C.c_int, [P, C.c_int32, P, P, C.c_uint64, C.c_int32, C.POINTER(C.c_double)]),
     "rad_store_create": (C.c_int, [P, C.POINTER(rad_layer), C.c_int32, C.c_double, C.c_int32, C.POINTER(P)]),
     "rad_store_destroy": (C.c_int, [P]),
@@ -205,6 +206,10 @@ def rad_probe_ceiling(ctx, kind, operands, sink, nbytes, reps=10):
 
 def rad_debug_key_shift(ctx, shift):
     _check(ctx, lib().rad_debug_key_shift(ctx, shift))
+
+
+def rad_debug_poll_limit(ctx, polls):
+    _check(ctx, lib().rad_debug_poll_limit(ctx, polls))
 
 
 def rad_store_create(ctx, layer, scheme, p, steps=1):

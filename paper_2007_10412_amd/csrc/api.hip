@@ -22,6 +22,8 @@ struct rad_ctx {
   int device = 0;
   std::string err;
   int key_shift = 0;
+  int compute_units = 0;
+  uint32_t poll_limit = 0;        // test hook: bound of the waits of the next recurrent step's kernels, 0 = the library's own
   // side stream of the recurrent model's backward pass (created on first use): the gradients formed per chunk of
   // time steps run there, beside the chain of dX GEMMs.  While calls are enqueued there, `stream` and `side` are
   // swapped and on_side is 1 (swap_streams).
@@ -36,13 +38,13 @@ struct rad_ctx {
   std::vector<hipEvent_t> pool;
   // grow-only workspaces, a set for each of the two streams: what is enqueued on one never shares a buffer with what
   // runs beside it on the other
-  void* ws[2][11] = {};
-  size_t ws_bytes[2][11] = {};
+  void* ws[2][12] = {};
+  size_t ws_bytes[2][12] = {};
   float* loss_dev = nullptr;
 };
 
 enum { WS_BITMAP = 0, WS_DENSE = 1, WS_ROWLOSS = 2, WS_COLSUM = 3, WS_SPLITK = 4, WS_WT = 5, WS_PROJ_R = 6, WS_PROJ_T = 7,
-       WS_PROJ_TB = 8, WS_REINDEX = 9, WS_CONVG = 10 };
+       WS_PROJ_TB = 8, WS_REINDEX = 9, WS_CONVG = 10, WS_RNNSYNC = 11 };
 
 static const char* kNoCtx = "no context";
 
@@ -147,6 +149,7 @@ extern "C" rad_status rad_ctx_create(rad_ctx** out, void* hip_stream) {
   hipDeviceProp_t prop;
   if (hipGetDeviceProperties(&prop, c->device) != hipSuccess) { delete c; return RAD_ERR_DEVICE; }
   if (std::strncmp(prop.gcnArchName, "gfx950", 6) != 0) { delete c; return RAD_ERR_UNSUPPORTED; }
+  c->compute_units = prop.multiProcessorCount;
   if (hipMalloc(reinterpret_cast<void**>(&c->loss_dev), sizeof(float)) != hipSuccess) { delete c; return RAD_ERR_DEVICE; }
   if (scratch_resolve(c->device) != hipSuccess) { (void)hipFree(c->loss_dev); delete c; return RAD_ERR_DEVICE; }
   *out = c;
@@ -222,6 +225,14 @@ extern "C" rad_status rad_debug_key_shift(rad_ctx* c, int32_t shift) {
   if (!c) return RAD_ERR_NULL;
   if (shift < 0 || shift > 31) return fail(c, RAD_ERR_PARAM, "key shift must be in [0, 31]");
   c->key_shift = shift;
+  return RAD_OK;
+}
+
+// test hook: bound of the waits of the next recurrent step's kernels (see rnn_wide.hip); that step resets it
+extern "C" rad_status rad_debug_poll_limit(rad_ctx* c, int32_t polls) {
+  if (!c) return RAD_ERR_NULL;
+  if (polls < 0) return fail(c, RAD_ERR_PARAM, "polls must not be negative");
+  c->poll_limit = (uint32_t)polls;
   return RAD_OK;
 }
 
@@ -1420,6 +1431,8 @@ extern "C" rad_status rad_path_sample_gradient(rad_ctx* c, const rad_graph* g, i
 // ------------------------------------------------------------------ models
 enum ModelKind { kMlp = 0, kRnn = 1, kCnn = 2 };
 constexpr int kRnnChunk = 8;            // time steps whose recurrent dW is one contraction over steps x batch
+constexpr int kRnnWideChunk = 32;       // the same where a launch takes a chunk of time steps (rnn_wide.hip): a launch costs about
+                                        // five steps' time, and the dense h or g of a chunk is kept (batch x hidden numbers a step)
 
 struct rad_model {
   int kind = kMlp;
@@ -1436,7 +1449,9 @@ struct rad_model {
   // RNN
   int64_t T = 0, d_input = 0, hidden = 0, classes = 0;
   uint32_t* rnn_bits = nullptr;         // [T][batch][hidden/32]
-  float* rnn_g = nullptr;               // [2][kRnnChunk][batch][hidden]: g of the time steps whose dW is formed together,
+  bool rnn_wide = false;                // a chunk of time steps per launch
+  float* rnn_g = nullptr;               // wide: [kRnnWideChunk][batch][hidden], dense h or g of the chunk at hand; else
+                                        // [2][kRnnChunk][batch][hidden]: g of the time steps whose dW is formed together,
                                         // two chunks: one being read by the side stream, one being filled (none
                                         // where all time steps are one launch per direction)
   uint32_t* bitmap_ws = nullptr;        // keep bitmaps of every step (transient within a step)
@@ -1682,13 +1697,21 @@ extern "C" rad_status rad_model_create_rnn(rad_ctx* c, int64_t batch, int64_t T,
   ok = ok && hipMalloc(&m->dyb[0], std::max(hb, (size_t)batch * classes * 4)) == hipSuccess;      // the loss gradient
   ok = ok && hipMalloc(&m->logits, (size_t)batch * classes * 4) == hipSuccess;
   ok = ok && hipMalloc((void**)&m->rnn_bits, (size_t)T * batch * ((hidden + 31) / 32) * 4) == hipSuccess;
-  if (!rnn_one_launch(m)) ok = ok && hipMalloc((void**)&m->rnn_g, (size_t)2 * kRnnChunk * hb) == hipSuccess;
+  m->rnn_wide = rnn_wide_ok(batch, hidden, d_input, c->compute_units) && !m->stores[0]->project() && !m->stores[1]->project();
+  if (!rnn_one_launch(m))
+    ok = ok && hipMalloc((void**)&m->rnn_g, (m->rnn_wide ? (size_t)std::min<int64_t>(T, kRnnWideChunk) : (size_t)2 * kRnnChunk) * hb) == hipSuccess;
   const size_t bmw = m->stores[0]->bitmap_words() + m->stores[1]->bitmap_words();
   if (bmw) ok = ok && hipMalloc((void**)&m->bitmap_ws, bmw * 4) == hipSuccess;
   if (!ok) { rad_model_destroy(m); return fail(c, RAD_ERR_DEVICE, "model allocation failed"); }
   { rad_status fs = model_share_flags(c, m); if (fs != RAD_OK) { rad_model_destroy(m); return fs; } }
   *out = m;
   return RAD_OK;
+}
+
+// whether the rows of the recurrent store are planned one by one and kept with their columns, so that consecutive step
+// slots can be packed and contracted together
+static bool rnn_rows_planned(const rad_store* s) {
+  return s->scheme == RAD_BERNOULLI || s->scheme == RAD_FIXEDK_PER_EXAMPLE || s->scheme == RAD_REPLACE_PER_EXAMPLE;
 }
 
 // forward of the recurrent model, a launch per time step (s2: the sampling parameters of h_T's store)
@@ -1701,8 +1724,7 @@ static rad_status rnn_forward_steps(rad_ctx* c, rad_model* m, const rad_sampling
   // Stores whose rows are planned one by one take the samples of h_1 .. h_{T-1} eight steps at a time: the steps'
   // outputs go to a ring of eight row blocks (the chunk buffer of the backward pass, idle now) and one pack launch
   // covers their consecutive store slots.
-  const bool chunk_pack = T > 1 && (s_hh->scheme == RAD_BERNOULLI || s_hh->scheme == RAD_FIXEDK_PER_EXAMPLE ||
-                                    s_hh->scheme == RAD_REPLACE_PER_EXAMPLE);
+  const bool chunk_pack = T > 1 && rnn_rows_planned(s_hh);
   auto ring = [&](int t) -> float* { return m->rnn_g + (size_t)((t - 1) % kRnnChunk) * B * H; };     // h_t, t < T
   for (int t = 1; t <= T; ++t) {
     StoreView nv; const StoreView* next = nullptr;
@@ -1732,6 +1754,93 @@ static rad_status rnn_forward_steps(rad_ctx* c, rad_model* m, const rad_sampling
       HIP_TRY(c, timed(c, "pack_f32", [&](const char**) { return launch_pack(ring(t0), kF32, v, c->stream); }));
     }
   }
+  return RAD_OK;
+}
+
+// the launches of a step that takes a chunk of time steps per launch: synchronisation words zeroed, common arguments set
+static rad_status rnn_wide_begin(rad_ctx* c, const rad_model* m, const float* xs, const float* W_ih, const float* W_hh,
+                                 const float* b, RnnWideArgs* a) {
+  std::memset(a, 0, sizeof(*a));
+  a->B = (int)m->batch; a->T = (int)m->T; a->H = (int)m->hidden; a->I = (int)m->d_input; a->bp = (a->H + 31) / 32;
+  a->xs = xs; a->W_ih = W_ih; a->W_hh = W_hh; a->b = b; a->bits = m->rnn_bits;
+  a->poll_limit = c->poll_limit ? c->poll_limit : 1u << 19;          // (a look takes 0.3 us or more)
+  c->poll_limit = 0;
+  const int launches = 2 * ((a->T + kRnnWideChunk - 1) / kRnnWideChunk);
+  const size_t bytes = rnn_wide_sync_bytes(a->B, a->H, launches);
+  void* ws = nullptr;
+  RAD_TRY(ws_get(c, WS_RNNSYNC, bytes, &ws));
+  rnn_wide_sync_layout(a, ws, launches);
+  HIP_TRY(c, timed(c, "fill", [&](const char**) {
+    return launch_fill_u32(static_cast<uint32_t*>(ws), 0u, (int64_t)(bytes / 4), c->stream);
+  }));
+  return RAD_OK;
+}
+
+static rad_status rnn_wide_launch(rad_ctx* c, bool forward, RnnWideArgs* a) {
+  a->seq0 = 1u + (uint32_t)a->launch * kRnnWideChunk;
+  HIP_TRY(c, timed(c, forward ? "rnn_wide_fwd" : "rnn_wide_bwd", [&](const char**) { return launch_rnn_wide(forward, *a, c->stream); }));
+  ++a->launch;
+  return RAD_OK;
+}
+
+// forward, kRnnWideChunk time steps per launch; their dense outputs are in the chunk buffer (exact store: in the store)
+// until the chunk is packed.  The last h of a chunk is carried to the next launch in act[], ending in h_T's place.
+static rad_status rnn_wide_forward(rad_ctx* c, rad_model* m, RnnWideArgs* a) {
+  const int B = a->B, H = a->H, T = a->T, chunks = (T + kRnnWideChunk - 1) / kRnnWideChunk;
+  rad_store *s_hh = m->stores[0], *s_ho = m->stores[1];
+  const float* src = nullptr;
+  a->t_out = T - 1;                                       // (h_T has no slot in the recurrent store)
+  for (int q = 0; q < chunks; ++q) {
+    a->t0 = a->t_lo = 1 + q * kRnnWideChunk;
+    a->n = std::min(T, a->t0 + kRnnWideChunk - 1) - a->t0 + 1;
+    a->src = src;
+    a->out = s_hh->scheme == RAD_EXACT ? static_cast<float*>(s_hh->values) + (size_t)(a->t0 - 1) * B * H : m->rnn_g;
+    a->carry = static_cast<float*>(q == chunks - 1 && s_ho->scheme == RAD_EXACT ? s_ho->values : m->act[(T + chunks - 1 - q) & 1]);
+    RAD_TRY(rnn_wide_launch(c, true, a));
+    src = a->carry;
+    if (s_hh->scheme == RAD_EXACT) continue;
+    const int per = rnn_rows_planned(s_hh) ? kRnnWideChunk : 1;      // step slots per pack launch
+    for (int t = a->t0; t < std::min(T, a->t0 + a->n); t += per) {
+      StoreView v = store_view(s_hh, t - 1);
+      v.rows = B * std::min(per, std::min(T, a->t0 + a->n) - t);
+      const float* h = a->out + (size_t)(t - a->t0) * B * H;
+      HIP_TRY(c, timed(c, "pack_f32", [&](const char**) { return launch_pack(h, kF32, v, c->stream); }));
+    }
+  }
+  return s_ho->scheme == RAD_EXACT ? RAD_OK : store_pack(c, s_ho, src, 0);
+}
+
+// backward from g_T (dz W_ho^T under the bits of step T, formed here), a chunk of time steps per launch, each followed by
+// the chunk's dW_hh, db and dW_ih
+static rad_status rnn_wide_backward(rad_ctx* c, rad_model* m, RnnWideArgs* a, const float* dz, const float* W_ho, float* dW_hh,
+                                    float* db, float* dW_ih) {
+  const int B = a->B, H = a->H, T = a->T, I = a->I, C = (int)m->classes;
+  rad_store* s_hh = m->stores[0];
+  const size_t block = (size_t)B * H;
+  const bool together = s_hh->scheme == RAD_EXACT || rnn_rows_planned(s_hh);
+  a->out = m->rnn_g; a->t_out = T;
+  bool first = true;
+  for (int t_hi = T, q = 0; t_hi >= 1; t_hi -= kRnnWideChunk, ++q) {
+    const int t_lo = std::max(1, t_hi - kRnnWideChunk + 1);
+    float* const g_hi = m->rnn_g + (size_t)(t_hi - t_lo) * block;
+    if (q == 0)
+      RAD_TRY(dX_gemm(c, kF32, B, H, C, dz, nullptr, 0, W_ho, g_hi, a->bits + (size_t)(T - 1) * B * a->bp, a->bp));
+    a->t0 = q == 0 ? T - 1 : t_hi;
+    a->t_lo = t_lo; a->n = a->t0 - t_lo + 1;
+    a->src = q == 0 ? g_hi : static_cast<const float*>(m->act[(q - 1) & 1]);
+    a->carry = static_cast<float*>(m->act[q & 1]);
+    if (a->n > 0) RAD_TRY(rnn_wide_launch(c, false, a));
+    // step t's sampled h_{t-1} is in slot t - 2; step 1 has none
+    const int t2 = std::max(2, t_lo), per = together ? kRnnWideChunk : 1;
+    for (int t = t2; t <= t_hi; t += per) {
+      RAD_TRY(dW_gemm(c, s_hh, t - 2, m->rnn_g + (size_t)(t - t_lo) * block, H, nullptr, 0, dW_hh, first ? 0 : 1,
+                      std::min(per, t_hi - t + 1)));
+      first = false;
+    }
+    RAD_TRY(colsum_call(c, m->rnn_g, kF32, (t_hi - t_lo + 1) * B, H, nullptr, 0, a->xs + (size_t)(t_lo - 1) * I, (int64_t)T * I, I,
+                        db, dW_ih, q == 0 ? 0 : 1, B, I));
+  }
+  if (T == 1) HIP_TRY(c, launch_fill_u32(reinterpret_cast<uint32_t*>(dW_hh), 0u, (int64_t)H * H, c->stream));
   return RAD_OK;
 }
 
@@ -1768,6 +1877,7 @@ static rad_status rnn_step(rad_ctx* c, rad_model* m, const rad_sampling* sm, con
 
   const bool fused = rnn_one_launch(m);
   RnnArgs ra;
+  RnnWideArgs wa;
   if (fused) {
     std::memset(&ra, 0, sizeof(ra));
     ra.B = B; ra.T = T; ra.H = H; ra.I = I;
@@ -1777,6 +1887,9 @@ static rad_status rnn_step(rad_ctx* c, rad_model* m, const rad_sampling* sm, con
     ra.bits = m->rnn_bits; ra.bp = bp;
     ra.hT = static_cast<float*>(s_ho->scheme == RAD_EXACT ? s_ho->values : m->act[T & 1]);
     HIP_TRY(c, timed(c, "rnn_forward", [&](const char**) { return launch_rnn_forward(ra, c->stream); }));
+  } else if (m->rnn_wide) {
+    RAD_TRY(rnn_wide_begin(c, m, xs, W_ih, W_hh, b, &wa));
+    RAD_TRY(rnn_wide_forward(c, m, &wa));
   } else {
     RAD_TRY(rnn_forward_steps(c, m, sm, s2, xs, W_ih, W_hh, b));
   }
@@ -1797,14 +1910,17 @@ static rad_status rnn_step(rad_ctx* c, rad_model* m, const rad_sampling* sm, con
     HIP_TRY(c, timed(c, "rnn_backward", [&](const char**) { return launch_rnn_backward(ra, dW_hh, db, dW_ih, c->stream); }));
     return step_finish(c, m, loss_host);
   }
+  if (m->rnn_wide) {
+    RAD_TRY(rnn_wide_backward(c, m, &wa, dz, W_ho, dW_hh, db, dW_ih));
+    return step_finish(c, m, loss_host);
+  }
   // dyb holds g_t = dL/dh_t masked by the ReLU bits of step t (applied in the epilogue of the GEMM that
   // produces it)
   // g_t, t >= 2, goes to row block (t - 2) % G of rnn_g; steps 2 + jG .. 1 + (j + 1)G share a chunk, whose store
   // slots t - 2 are consecutive, so that dW_hh of the chunk is one contraction over (steps x batch) rows instead
   // of one short contraction per step.  Stores planned per step (shared index sets) or rebuilt before use
   // (index-free) keep the step-by-step form (two row blocks, used in turn).  g_1 has no dW_hh and lives in dyb[1].
-  const bool per_row = s_hh->scheme == RAD_EXACT || s_hh->scheme == RAD_BERNOULLI || s_hh->scheme == RAD_FIXEDK_PER_EXAMPLE ||
-                       s_hh->scheme == RAD_REPLACE_PER_EXAMPLE;
+  const bool per_row = s_hh->scheme == RAD_EXACT || rnn_rows_planned(s_hh);
   const int G = per_row ? kRnnChunk : 1;
   const int Gp = G > 1 ? 2 * G : 2;                      // row blocks in use: two chunks, or two single steps
   const size_t gstride = (size_t)B * H;

@@ -213,6 +213,26 @@ int64_t rnn_fused_part_floats(int B, int H, int I);
 hipError_t launch_rnn_forward(const RnnArgs& a, hipStream_t st);
 hipError_t launch_rnn_backward(const RnnArgs& a, float* dW_hh, float* db, float* dW_ih, hipStream_t st);
 
+// The recurrent model with a hidden state of 193 to 1024 units, a chunk of n time steps in one launch per direction
+// (rnn_wide.hip).  Forward: h_t of steps t0 .. t0 + n - 1; backward: g_t of steps t0, t0 - 1, .. t0 - n + 1 (step t under the
+// ReLU bits of step t).  src: dense h or g of the step before the first (null: zeros); out: [steps t_lo .. t_out][B][H];
+// carry: the last step's output too, or null (not src: a launch that gave up is computed again from src).
+// xch, flags, tickets and abort_words lie in a workspace of rnn_wide_sync_bytes that is zero before the first of
+// `launches` launches (numbered by `launch`); seq0 grows by at least n from launch to launch and starts at 1 or more.
+constexpr int kRnnWideGroups = 8, kRnnWideMaxIn = 8;
+struct RnnWideArgs {
+  int B, T, H, I, t0, n, t_lo, t_out, bp, launch;
+  uint32_t seq0, poll_limit;
+  const float* xs; const float* W_ih; const float* W_hh; const float* b;
+  uint32_t* bits;                        // (h_t > 0) bits, [T][B][bp]: written forward, read backward
+  const float* src; float* out; float* carry;
+  float* xch; uint32_t* flags; uint32_t* tickets; uint32_t* abort_words;
+};
+bool rnn_wide_ok(int64_t B, int64_t H, int64_t I, int compute_units);
+size_t rnn_wide_sync_bytes(int B, int H, int launches);
+void rnn_wide_sync_layout(RnnWideArgs* a, void* ws, int launches);      // a->B and a->H are set
+hipError_t launch_rnn_wide(bool forward, const RnnWideArgs& a, hipStream_t st);
+
 // Convolutions through an LDS-staged input patch (conv.hip).  launch_conv_fwd_direct takes the arguments of the
 // im2col GEMM (A = NCHW input, B = W [(c,u,v)][co], cv_* geometry, the kEpiConv fields) and serves forward and dX;
 // launch_conv_dw_direct writes conv_dw_direct_splits(...) partial sums [ci*ks*ks][co] of dW from the dense x~ and

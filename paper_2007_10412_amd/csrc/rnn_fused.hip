@@ -11,7 +11,7 @@
 // product cost 10 us instead.  A training step, fraction 0.1, us, launch per step / this: hidden 100, batch 150, T = 784
 // 17137 / 1600; T = 200: hidden 64 3857 / 401, 128 4668 / 520, 192 5680 / 639 (batch 150), 192 8114 / 1840 (batch 600);
 // T = 49, batch 8192: 64 14558 / 1397, 100 17731 / 2104, 128 14777 / 2133, 192 15346 / 4149, so the batch sets no limit.
-// Hidden 192 is where the two arrays fill the registers of a workgroup of 16 waves; wider states keep a launch per step.
+// Hidden 192 is where the two arrays fill the registers of a workgroup of 16 waves; wider states are in rnn_wide.hip.
 #include "gemm.hpp"
 
 namespace rad {

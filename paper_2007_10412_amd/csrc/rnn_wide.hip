@@ -1,0 +1,302 @@
+// The recurrent model with a hidden state of 193 to 1024 units: a chunk of time steps in one launch per direction.
+//
+// h_t = ReLU(x_t W_ih + h_{t-1} W_hh + b) and g_{t-1} = (g_t W_hh^T) under the ReLU bits are chains of small products
+// (128 x 1024 x 1024: 1.9 us at the fp32 matrix rate) whose operand W_hh is the same at every step.  A launch per step
+// pays the launch and reads W_hh again (7.6 us).  Here W_hh stays in the registers of the chip: the 32 CUs of one XCD hold
+// it once, 32 columns each, and the eight XCDs take an eighth of the batch each.  Examples do not depend on each other,
+// so the only exchange is that of a step's h (or g) among the workgroups of one XCD, through that XCD's L2.
+//
+// A workgroup of eight waves owns 16 NC columns; wave w multiplies k in [16 J w, 16 J (w + 1)) (16x16x4 matrix
+// instructions), the waves' partial sums meet in LDS, the finished 16-column blocks go to the exchange buffer in the order
+// in which the waves' A fragments are loaded (1 KB runs), and a flag per (block, accumulator element) says that a step's
+// piece is there.  A wave waits only for the flags of its own k range (one 128-byte line), so a step has one workgroup
+// barrier.  Two exchange buffers suffice: who publishes step s has read step s - 1 of everybody.
+//
+// A step takes 3.2 us at batch 128, hidden 1024 (1.7 us of matrix instructions, then the latencies of the flags, of the
+// fragments from L2 and of the sum through LDS) and 1.2 us at hidden 256.  A training step with fraction 0.1, a launch per
+// step / this, us: batch 128, hidden 1024, T = 784 14776 / 9789; T = 200: batch 192, hidden 1000 14817 / 4397, 192 x 640
+// 3939 / 3154, 16 x 700 4158 / 1502; batch 40, hidden 300, T = 300 4792 / 1572.  A batch above 192, or a hidden state that
+// does not fit 32 columns a CU, keeps a launch per step.
+//
+// The workgroups find their XCD in the hardware register and take a place in it from a counter; the loads of flags and
+// exchanged values pass by the L1 (agent scope, sc1), which is all the coherence that sharers of one L2 need.  Every wait is bounded: if
+// the workgroups of a group do not all get to run (another process's kernel on some CUs, another partition mode), one of
+// them gives up, sets the launch's abort word, and rnn_wide_redo_kernel, which follows every launch and otherwise returns
+// at once, computes the chunk again without any exchange.
+#include "gemm.hpp"
+
+namespace rad {
+
+namespace {
+
+constexpr int kWaves = 8, kGroups = kRnnWideGroups, kFlagsPerGroup = 256;     // flags: 64 blocks x 4 accumulator elements
+constexpr int kXccIdReg = 20;                                                 // HW_REG_XCC_ID
+
+__device__ __forceinline__ float load_or_zero(const float* p, bool ok) { return ok ? *p : 0.f; }
+
+template <int J, int NC, int R, bool FWD>
+__global__ __launch_bounds__(64 * kWaves, R == 1 ? 4 : 2) void rnn_wide_kernel(RnnWideArgs a) {
+  __shared__ float part[2][kWaves][R][NC][4][64];
+  __shared__ float s_V[kRnnWideMaxIn + 1][16 * NC];       // W_ih and the bias of this workgroup's columns
+  __shared__ int s_member, s_dead;
+  const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const int r = lane & 15, kq = lane >> 4, H = a.H, B = a.B;
+  const int xcc = (int)(__builtin_amdgcn_s_getreg((3 << 11) | kXccIdReg) & 15u);
+  uint32_t* const abort_word = a.abort_words + a.launch;
+  if (threadIdx.x == 0) {
+    s_dead = 0;
+    s_member = xcc < kGroups ? (int)atomicAdd(a.tickets + a.launch * kGroups + xcc, 1u) : 0x7fffffff;
+    if (xcc >= kGroups) __hip_atomic_store(abort_word, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+  __syncthreads();
+  const int member = __builtin_amdgcn_readfirstlane(s_member), nblk = (H + 15) / 16;
+  const int rg = (B + kGroups - 1) / kGroups, row0 = xcc * rg, row_end = min(B, row0 + rg);
+  if (member >= (nblk + NC - 1) / NC || row0 >= row_end) return;
+  const int n0 = member * 16 * NC;
+
+  float wr[J][4][NC];                        // W_hh[k][n] (forward) or W_hh[n][k], k = 16 (J w + j) + 4 kq + e
+#pragma unroll
+  for (int j = 0; j < J; ++j)
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+#pragma unroll
+      for (int c = 0; c < NC; ++c) {
+        const int k = 16 * (J * w + j) + 4 * kq + e, n = n0 + 16 * c + r;
+        const size_t at = FWD ? (size_t)k * H + n : (size_t)n * H + k;
+        wr[j][e][c] = load_or_zero(a.W_hh + at, k < H && n < H);
+      }
+
+  // this wave finishes accumulator element fe of column block fc
+  const int fc = NC == 2 ? w >> 2 : 0, fe = w & 3, blk = n0 / 16 + fc, col = 16 * blk + r;
+  const bool finishes = (NC == 2 || w < 4) && blk < nblk, col_ok = col < H;
+  if (FWD) {
+    for (int q = threadIdx.x; q < (a.I + 1) * 16 * NC; q += 64 * kWaves) {
+      const int i = q / (16 * NC), n = n0 + q % (16 * NC);
+      s_V[i][q % (16 * NC)] = load_or_zero((i < a.I ? a.W_ih + (size_t)i * H : a.b) + n, n < H);
+    }
+    __syncthreads();
+  }
+
+  const size_t area = (size_t)kWaves * R * J * 256;            // floats of one exchange buffer of a group
+  float* const xch[2] = {a.xch + (size_t)xcc * area, a.xch + (size_t)(kGroups + xcc) * area};
+  uint32_t* const flags = a.flags + (size_t)xcc * kFlagsPerGroup;
+  const int wait_flags = 4 * min(J, nblk - J * w);             // flags of this wave's k range; <= 0: all of it is padding
+  uint16_t* const bits16 = reinterpret_cast<uint16_t*>(a.bits);
+
+  for (int i = 0; i < a.n; ++i) {
+    const int t = FWD ? a.t0 + i : a.t0 - i;                   // the step whose h_t or g_t is formed
+    // what the epilogue adds or masks with, fetched now so that it has arrived by then
+    float addend[R];
+    uint32_t keep[R];
+#pragma unroll
+    for (int rt = 0; rt < R; ++rt) {
+      const int row = min(row0 + 16 * rt + 4 * kq + fe, row_end - 1);
+      addend[rt] = 0.f; keep[rt] = 0u;
+      if (!finishes) continue;
+      if (FWD) {
+        addend[rt] = s_V[a.I][16 * fc + r];
+        for (int q = 0; q < a.I; ++q)
+          addend[rt] = fmaf(a.xs[((size_t)row * a.T + (t - 1)) * a.I + q], s_V[q][16 * fc + r], addend[rt]);
+      } else {
+        keep[rt] = bits16[((size_t)(t - 1) * B + row) * (2 * a.bp) + blk];
+      }
+    }
+    floatx4 av[R][J], acc[R][NC];
+#pragma unroll
+    for (int rt = 0; rt < R; ++rt) {
+#pragma unroll
+      for (int c = 0; c < NC; ++c) acc[rt][c] = floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int j = 0; j < J; ++j) av[rt][j] = floatx4{0.f, 0.f, 0.f, 0.f};
+    }
+    if (i == 0) {
+      if (a.src) {
+#pragma unroll
+        for (int rt = 0; rt < R; ++rt) {
+          const int row = row0 + 16 * rt + r;
+#pragma unroll
+          for (int j = 0; j < J; ++j)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+              const int k = 16 * (J * w + j) + 4 * kq + e;
+              av[rt][j][e] = load_or_zero(a.src + (size_t)row * H + k, row < row_end && k < H);
+            }
+        }
+      }
+    } else if (wait_flags > 0) {
+      const uint32_t need = a.seq0 + (uint32_t)i - 1u;
+      const uint32_t* const fl = flags + 4 * J * w + lane;
+      uint32_t polls = 0;
+      for (;;) {
+        const uint32_t v = lane < wait_flags ? __hip_atomic_load(fl, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : need;
+        if (__all((int)(v - need) >= 0)) break;
+        ++polls;
+        if (polls >= a.poll_limit ||
+            (polls % 256u == 0 && __hip_atomic_load(abort_word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))) {
+          s_dead = 1;                        // seen by the whole workgroup at the barrier below
+          if (lane == 0) __hip_atomic_store(abort_word, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          break;
+        }
+      }
+      asm volatile("" ::: "memory");
+      auto rsrc = __builtin_amdgcn_make_buffer_rsrc(xch[(i - 1) & 1] + (size_t)w * R * J * 256, 0, R * J * 1024, 0x00020000);
+#pragma unroll
+      for (int rt = 0; rt < R; ++rt)
+#pragma unroll
+        for (int j = 0; j < J; ++j) {
+          const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(rsrc, lane * 16, (rt * J + j) * 1024, 16);     // sc1
+          av[rt][j] = __builtin_bit_cast(floatx4, v);
+        }
+    }
+#pragma unroll
+    for (int j = 0; j < J; ++j)
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+#pragma unroll
+        for (int rt = 0; rt < R; ++rt)
+#pragma unroll
+          for (int c = 0; c < NC; ++c)
+            acc[rt][c] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[rt][j][e], wr[j][e][c], acc[rt][c], 0, 0, 0);
+#pragma unroll
+    for (int rt = 0; rt < R; ++rt)
+#pragma unroll
+      for (int c = 0; c < NC; ++c)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) part[i & 1][w][rt][c][e][lane] = acc[rt][c][e];
+    __syncthreads();
+    if (s_dead) return;
+    if (finishes) {
+      float v[R];
+#pragma unroll
+      for (int rt = 0; rt < R; ++rt) {
+        const float* const p = &part[i & 1][0][rt][fc][fe][lane];
+        constexpr int kStep = R * NC * 4 * 64;
+        float s0 = p[0], s1 = p[kStep];
+#pragma unroll
+        for (int q = 2; q < kWaves; q += 2) { s0 += p[q * kStep]; s1 += p[(q + 1) * kStep]; }
+        v[rt] = s0 + s1;
+        if (FWD) { v[rt] += addend[rt]; v[rt] = v[rt] > 0.f ? v[rt] : 0.f; }
+        else if (!((keep[rt] >> r) & 1u)) v[rt] = 0.f;
+        if (!col_ok) v[rt] = 0.f;
+        // element (row, column) of the block: fragment lane 16 (column / 4) + row, component column % 4
+        float* const x = xch[i & 1] + ((size_t)(blk / J * R + rt) * J + blk % J) * 256;
+        x[((r >> 2) * 16 + 4 * kq + fe) * 4 + (r & 3)] = v[rt];
+      }
+      if (i + 1 < a.n) {
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");         // the values are in L2
+        if (lane == 0)
+          __hip_atomic_store(flags + 4 * blk + fe, a.seq0 + (uint32_t)i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+      }
+      // off the chain: dense output, ReLU bits
+#pragma unroll
+      for (int rt = 0; rt < R; ++rt) {
+        const int row = row0 + 16 * rt + 4 * kq + fe;
+        const bool row_ok = row < row_end;
+        if (row_ok && col_ok) {
+          if (t <= a.t_out) a.out[((size_t)(t - a.t_lo) * B + row) * H + col] = v[rt];
+          if (i + 1 == a.n && a.carry) a.carry[(size_t)row * H + col] = v[rt];
+        }
+        if (FWD) {
+          const uint64_t on = __ballot(v[rt] > 0.f);
+          if (r == 0 && row_ok) {
+            uint16_t* const word = bits16 + ((size_t)(t - 1) * B + row) * (2 * a.bp) + blk;
+            word[0] = (uint16_t)(on >> (16 * kq));
+            if (blk == nblk - 1 && (nblk & 1)) word[1] = 0;      // the padding half of the last word
+          }
+        }
+      }
+    }
+  }
+}
+
+// The chunk again, an example per workgroup, if the launch before gave up.
+template <bool FWD>
+__global__ __launch_bounds__(1024) void rnn_wide_redo_kernel(RnnWideArgs a) {
+  if (a.abort_words[a.launch] == 0u) return;
+  __shared__ float s[1024];
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, row = blockIdx.x, H = a.H, B = a.B, n = threadIdx.x;
+  s[n] = a.src && n < H ? a.src[(size_t)row * H + n] : 0.f;
+  for (int i = 0; i < a.n; ++i) {
+    const int t = FWD ? a.t0 + i : a.t0 - i;
+    const size_t out = ((size_t)(t - a.t_lo) * B + row) * H;
+    uint32_t* const words = a.bits + ((size_t)(t - 1) * B + row) * a.bp;
+    __syncthreads();
+    if (FWD) {
+      float v = 0.f;
+      if (n < H) {
+        for (int k = 0; k < H; ++k) v = fmaf(s[k], a.W_hh[(size_t)k * H + n], v);
+        v += a.b[n];
+        for (int q = 0; q < a.I; ++q) v = fmaf(a.xs[((size_t)row * a.T + (t - 1)) * a.I + q], a.W_ih[(size_t)q * H + n], v);
+        v = v > 0.f ? v : 0.f;
+        if (t <= a.t_out) a.out[out + n] = v;
+        if (i + 1 == a.n && a.carry) a.carry[(size_t)row * H + n] = v;
+      }
+      const uint64_t on = __ballot(v > 0.f);
+      if ((lane & 31) == 0 && n / 32 < a.bp) words[n / 32] = (uint32_t)(on >> lane);
+      __syncthreads();
+      s[n] = v;
+    } else {
+      __shared__ float nxt[1024];
+      for (int k = w; k < H; k += 16) {
+        float v = 0.f;
+        for (int m = lane; m < H; m += 64) v = fmaf(s[m], a.W_hh[(size_t)k * H + m], v);
+        for (int d = 32; d > 0; d >>= 1) v += __shfl_xor(v, d);
+        if (lane == 0) nxt[k] = ((words[k / 32] >> (k % 32)) & 1u) ? v : 0.f;
+      }
+      __syncthreads();
+      s[n] = n < H ? nxt[n] : 0.f;
+      if (n < H) {
+        if (t <= a.t_out) a.out[out + n] = s[n];
+        if (i + 1 == a.n && a.carry) a.carry[(size_t)row * H + n] = s[n];
+      }
+    }
+  }
+}
+
+template <int J, int NC> hipError_t start(bool forward, const RnnWideArgs& a, hipStream_t st) {
+  const int members = ((a.H + 15) / 16 + NC - 1) / NC;
+  const bool two = a.B > 16 * kGroups;
+  auto kern = two ? (forward ? rnn_wide_kernel<J, NC, 2, true> : rnn_wide_kernel<J, NC, 2, false>)
+                  : (forward ? rnn_wide_kernel<J, NC, 1, true> : rnn_wide_kernel<J, NC, 1, false>);
+  hipLaunchKernelGGL(kern, dim3(members * kGroups), dim3(64 * kWaves), 0, st, a);
+  return hipGetLastError();
+}
+
+}  // namespace
+
+bool rnn_wide_ok(int64_t B, int64_t H, int64_t I, int compute_units) {
+  return H > rnn_fused_max_hidden() && H <= 1024 && B <= 24 * kGroups && I <= kRnnWideMaxIn && compute_units == 32 * kGroups;
+}
+
+size_t rnn_wide_sync_bytes(int B, int H, int launches) {
+  const size_t J = (size_t)(H + 127) / 128, R = B > 16 * kGroups ? 2 : 1;
+  return ((size_t)2 * kGroups * kWaves * R * J * 256 + (size_t)kGroups * kFlagsPerGroup + (size_t)launches * (kGroups + 1)) * 4;
+}
+
+void rnn_wide_sync_layout(RnnWideArgs* a, void* ws, int launches) {
+  const size_t J = (size_t)(a->H + 127) / 128, R = a->B > 16 * kGroups ? 2 : 1;
+  a->xch = static_cast<float*>(ws);
+  a->flags = reinterpret_cast<uint32_t*>(a->xch + (size_t)2 * kGroups * kWaves * R * J * 256);
+  a->tickets = a->flags + (size_t)kGroups * kFlagsPerGroup;
+  a->abort_words = a->tickets + (size_t)launches * kGroups;
+}
+
+hipError_t launch_rnn_wide(bool forward, const RnnWideArgs& a, hipStream_t st) {
+  if (!rnn_wide_ok(a.B, a.H, a.I, 32 * kGroups) || a.n < 1) return hipErrorInvalidValue;
+  hipError_t e = hipErrorInvalidValue;
+  switch ((a.H + 127) / 128) {
+    case 2: e = start<2, 1>(forward, a, st); break;
+    case 3: e = start<3, 1>(forward, a, st); break;
+    case 4: e = start<4, 1>(forward, a, st); break;
+    case 5: e = start<5, 2>(forward, a, st); break;
+    case 6: e = start<6, 2>(forward, a, st); break;
+    case 7: e = start<7, 2>(forward, a, st); break;
+    case 8: e = start<8, 2>(forward, a, st); break;
+  }
+  if (e != hipSuccess) return e;
+  auto redo = forward ? rnn_wide_redo_kernel<true> : rnn_wide_redo_kernel<false>;
+  hipLaunchKernelGGL(redo, dim3(a.B), dim3(1024), 0, st, a);
+  return hipGetLastError();
+}
+
+}  // namespace rad

@@ -1,0 +1,77 @@
+"""The recurrent model with a hidden state of 193 to 1024 units (a chunk of time steps per launch, W_hh in the registers of
+the chip): widths around its 16- and 128-column ranges, batches around its groups and row tiles, lengths around its chunks."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+from tests.test_gpu_rnn import ctx, run_rnn  # noqa: F401
+
+
+def margin(d):
+    """Smallest |pre-activation| over all examples, steps and units, in units of their root mean square."""
+    x, h, low, sq, n = d["x"].astype(np.float64), 0.0, np.inf, 0.0, 0
+    W_ih, W_hh, b = (d[k].astype(np.float64) for k in ("W_ih", "W_hh", "b"))
+    for t in range(x.shape[1]):
+        a = x[:, t] @ W_ih + b + (h @ W_hh if t else 0.0)
+        low, sq, n, h = min(low, np.abs(a).min()), sq + np.square(a).sum(), n + a.size, np.maximum(a, 0.0)
+    return low / np.sqrt(sq / n)
+
+
+def data(seed, batch, T, hidden, d_input=1, classes=10):
+    """The first of the seeds from `seed` on whose pre-activations stay clear of zero: an fp32 sum of up to 1024 products
+    is within about 3e-7 of their size (sqrt(1024) / 2 roundings of 6e-8 each at a third of it), and a ReLU bit that
+    falls the other way for one example is no rounding error (128 x 600 units, 4 steps: one in three of the seeds)."""
+    from paper_2007_10412_amd import synth
+    for s in range(seed, seed + 1000):
+        d = synth.rnn(seed=s, batch=batch, T=T, d_input=d_input, hidden=hidden, classes=classes, identity=False)
+        if margin(d) > 1e-6:
+            return d
+    raise AssertionError("no such data")
+
+
+@pytest.mark.parametrize("hidden", [193, 256, 257, 383, 400, 512, 513, 528, 640, 700, 800, 896, 1000, 1023, 1024])
+def test_widths(ctx, hidden):  # noqa: F811
+    run_rnn(ctx, data(hidden, 20, 5, hidden), 1, 0.2, seed=3)
+
+
+@pytest.mark.parametrize("batch", [1, 7, 8, 9, 127, 128, 129, 137, 185, 192, 193])
+@pytest.mark.parametrize("hidden", [250, 600])
+def test_batches(ctx, batch, hidden):  # noqa: F811
+    run_rnn(ctx, data(batch, batch, 4, hidden), 3, 0.1, seed=4)
+
+
+@pytest.mark.parametrize("T", [1, 2, 31, 32, 33, 34, 64, 65])
+@pytest.mark.parametrize("scheme,p", [(0, 1.0), (1, 0.3), (2, 0.25), (4, 0.25), (5, 0.25)])
+def test_lengths(ctx, T, scheme, p):  # noqa: F811
+    run_rnn(ctx, data(T, 6, T, 210, d_input=3, classes=5), scheme, p, seed=T, check_store=T > 1)
+
+
+def test_wider_than_the_chip_holds(ctx):  # noqa: F811
+    run_rnn(ctx, data(9, 6, 4, 1100), 1, 0.2, seed=5)
+
+
+@pytest.mark.parametrize("hidden,batch", [(200, 20), (1024, 130)])
+@pytest.mark.parametrize("scheme", [0, 1])
+def test_chunks_whose_launch_gave_up(ctx, hidden, batch, scheme):  # noqa: F811
+    """A wait bound of one look: some workgroup gives up at once, and the stand-in kernel computes the chunk."""
+    from paper_2007_10412_amd import binding as B
+    B.rad_debug_poll_limit(ctx, 1)
+    run_rnn(ctx, data(hidden, batch, 40, hidden, d_input=2), scheme, 0.2 if scheme else 1.0, seed=6)
+
+
+def test_repeated_steps_are_identical(ctx):  # noqa: F811
+    from paper_2007_10412_amd import binding as B
+    from tests.gpu_util import dev, host, empty
+    d = data(11, 70, 70, 360)
+    names = ["W_ih", "W_hh", "b", "W_ho", "b_o"]
+    m = B.rad_model_create_rnn(ctx, 70, 70, 1, 360, 10, 1, 0.1)
+    try:
+        params, grads = [dev(d[n]) for n in names], [empty(d[n].shape) for n in names]
+        x, labels, runs = dev(d["x"]), dev(d["labels"]), []
+        for _ in range(3):
+            B.rad_train_step(ctx, m, B.make_sampling(1, 0.1, 5, 20, 0), x, labels, params, grads)
+            runs.append([host(g).copy() for g in grads])
+        assert all(np.array_equal(a, b) for r in runs[1:] for a, b in zip(r, runs[0]))
+    finally:
+        B.rad_model_destroy(m)
