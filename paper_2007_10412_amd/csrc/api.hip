@@ -980,6 +980,29 @@ static bool dw_pitched_ok(const rad_store* s, int N, int dy_ld) {
   return tiles < 128 && 256 / tiles >= 2 && s->rows >= 2048;
 }
 
+// C = beta C + A^T B over the rows of many time steps (fp32): 128 x 128 tiles with the rows split over about one workgroup
+// per CU, each split's partial sums in an array of its own.  4096 rows, 1024 x 1024: 86 + 9 us (the reduction) against 113
+// for 64 x 64 tiles, whose waves read two LDS operands per matrix instruction; a split of fewer than 512 rows pays for the
+// partial sums more than it gains.
+static rad_status dw_dense_f32(rad_ctx* c, GemmArgs g, double alg) {
+  const int tiles = ((g.M + 127) / 128) * ((g.N + 127) / 128);
+  int splits = 256 / tiles;
+  if (splits > 16) splits = 16;
+  const int ks = splits > 1 ? ((g.K + splits - 1) / splits + 15) / 16 * 16 : g.K;
+  splits = (g.K + ks - 1) / ks;
+  if (splits < 2 || ks < 512) return run_gemm_call(c, kF32, kOpMN, kOpMN, kEpiStore, g, alg);
+  void* part = nullptr;
+  RAD_TRY(ws_get(c, WS_SPLITK, (size_t)splits * g.M * g.N * 4, &part));
+  float* const out = static_cast<float*>(g.C);
+  const int beta = g.beta;
+  g.C = part; g.ldc = g.N; g.beta = 0; g.k_split = ks; g.k_splits = splits;
+  RAD_TRY(run_gemm_call(c, kF32, kOpMN, kOpMN, kEpiSplitK, g, alg));
+  HIP_TRY(c, timed(c, "splitk_reduce", [&](const char**) {
+    return launch_splitk_reduce(static_cast<const float*>(part), splits, (int64_t)g.M * g.N, out, beta, c->stream);
+  }));
+  return RAD_OK;
+}
+
 // dW = beta dW + store(slot)^T (dy masked by bits)
 // n_slots > 1: the contraction runs over that many consecutive step slots of a multi-step store at once (their
 // rows lie one after another in the store; dy then holds the rows of all those steps in the same order); only for
@@ -1001,7 +1024,7 @@ static rad_status dW_gemm(rad_ctx* c, const rad_store* s, int slot, const void* 
   if (s->scheme == RAD_EXACT) {
     g.M = s->cols;
     g.A = static_cast<const char*>(s->values) + (size_t)slot * s->rows * s->cols * s->elem(); g.lda = s->cols;
-    return run_gemm_call(c, s->dtype, kOpMN, kOpMN, kEpiStore, g);
+    return n_slots > 1 && s->dtype == kF32 ? dw_dense_f32(c, g, 0.0) : run_gemm_call(c, s->dtype, kOpMN, kOpMN, kEpiStore, g);
   }
   if (s->scheme == RAD_FIXEDK_SHARED) {
     // compact problem: only the k sampled rows of dW are touched, the rest is zero
@@ -1030,7 +1053,7 @@ static rad_status dW_gemm(rad_ctx* c, const rad_store* s, int slot, const void* 
     HIP_TRY(c, timed(c, "unpack", [&](const char**) { return launch_unpack_bitmap(v, kF32, dense, c->stream); }));
     g.K = v.rows; g.A = dense; g.lda = s->cols;
     const double kept = s->scheme == RAD_BERNOULLI ? s->p * (double)v.rows * s->cols : (double)v.rows * s->k;
-    return run_gemm_call(c, kF32, kOpMN, kOpMN, kEpiStore, g, 2.0 * kept * N);
+    return dw_dense_f32(c, g, 2.0 * kept * N);
   }
   RAD_TRY(backward_view(c, s, slot, &g.sa));
   g.sa.rows = s->rows * n_slots;
@@ -1045,7 +1068,7 @@ static rad_status dW_gemm(rad_ctx* c, const rad_store* s, int slot, const void* 
     RAD_TRY(ws_get(c, WS_DENSE, (size_t)g.sa.rows * s->cols * 4, &dense));
     HIP_TRY(c, timed(c, "unpack", [&](const char**) { return launch_unpack(g.sa, kF32, dense, c->stream); }));
     g.A = dense; g.lda = s->cols;
-    return run_gemm_call(c, kF32, kOpMN, kOpMN, kEpiStore, g, alg);
+    return dw_dense_f32(c, g, alg);
   }
   if (n_slots == 1 && n_out == N && dw_narrow_pays(s->dtype, s->rows, s->cols, N, g.sparse_prefetch, bits != nullptr)) {
     const int splits = dw_narrow_splits(s->rows, s->cols, N);
@@ -1811,7 +1834,8 @@ static rad_status rnn_wide_forward(rad_ctx* c, rad_model* m, RnnWideArgs* a) {
 }
 
 // backward from g_T (dz W_ho^T under the bits of step T, formed here), a chunk of time steps per launch, each followed by
-// the chunk's dW_hh, db and dW_ih
+// the chunk's dW_hh, db and dW_ih.  (On the side stream, beside the next chunk's chain, these gained 5 % where the two
+// streams had hardware queues of their own and lost 1 % where they had not: both want the matrix units.)
 static rad_status rnn_wide_backward(rad_ctx* c, rad_model* m, RnnWideArgs* a, const float* dz, const float* W_ho, float* dW_hh,
                                     float* db, float* dW_ih) {
   const int B = a->B, H = a->H, T = a->T, I = a->I, C = (int)m->classes;

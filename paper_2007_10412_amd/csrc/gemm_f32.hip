@@ -33,6 +33,10 @@ hipError_t launch_gemm_f32(int a_kind, int b_kind, int epi, const GemmArgs& g, h
   } else if (a_kind == kOpK && b_kind == kOpK && epi == kEpiSplitK) {
     nm = "gemm_f32_dx_splitk_64"; e = run_gemm<F32Tag, kOpK, kOpK, kEpiSplitK, 64, 64, 32, 0, true, false>(g, st);
   }
+  else if (a_kind == kOpMN && b_kind == kOpMN && epi == kEpiSplitK) {
+    // a contraction over the rows of many time steps: 128 x 128 tiles, partial sums per range of rows
+    nm = "gemm_f32_dw_splitk_128"; e = run_gemm<F32Tag, kOpMN, kOpMN, kEpiSplitK, 128, 128, 16, 0, false, false>(g, st);
+  }
   else if (a_kind == kOpIm2colRows && b_kind == kOpMN && epi == kEpiConv) {
     // convolution forward / dX: positions x channels, channels fit one 64-wide tile column
     nm = "gemm_f32_conv_64"; e = run_gemm<F32Tag, kOpIm2colRows, kOpMN, kEpiConv, 64, 64, 16, 0, false, false, false>(g, st);

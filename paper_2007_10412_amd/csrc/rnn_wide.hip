@@ -14,8 +14,8 @@
 //
 // A step takes 3.2 us at batch 128, hidden 1024 (1.7 us of matrix instructions, then the latencies of the flags, of the
 // fragments from L2 and of the sum through LDS) and 1.2 us at hidden 256.  A training step with fraction 0.1, a launch per
-// step / this, us: batch 128, hidden 1024, T = 784 14776 / 9789; T = 200: batch 192, hidden 1000 14817 / 4397, 192 x 640
-// 3939 / 3154, 16 x 700 4158 / 1502; batch 40, hidden 300, T = 300 4792 / 1572.  A batch above 192, or a hidden state that
+// step / this, us: batch 128, hidden 1024, T = 784 14757 / 9329; T = 200: batch 192, hidden 1000 14777 / 4024, 192 x 640
+// 3932 / 2545, 16 x 700 4153 / 1507; batch 40, hidden 300, T = 300 4806 / 1574.  A batch above 192, or a hidden state that
 // does not fit 32 columns a CU, keeps a launch per step.
 //
 // The workgroups find their XCD in the hardware register and take a place in it from a counter; the loads of flags and
@@ -23,6 +23,8 @@
 // the workgroups of a group do not all get to run (another process's kernel on some CUs, another partition mode), one of
 // them gives up, sets the launch's abort word, and rnn_wide_redo_kernel, which follows every launch and otherwise returns
 // at once, computes the chunk again without any exchange.
+#include <algorithm>
+
 #include "gemm.hpp"
 
 namespace rad {
@@ -209,12 +211,14 @@ __global__ __launch_bounds__(64 * kWaves, R == 1 ? 4 : 2) void rnn_wide_kernel(R
   }
 }
 
-// The chunk again, an example per workgroup, if the launch before gave up.
+// The chunk again, an example at a time per workgroup (few: normally it returns at once), if the launch before gave up.
 template <bool FWD>
 __global__ __launch_bounds__(1024) void rnn_wide_redo_kernel(RnnWideArgs a) {
   if (a.abort_words[a.launch] == 0u) return;
   __shared__ float s[1024];
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, row = blockIdx.x, H = a.H, B = a.B, n = threadIdx.x;
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, H = a.H, B = a.B, n = threadIdx.x;
+  for (int row = blockIdx.x; row < B; row += gridDim.x) {
+  __syncthreads();
   s[n] = a.src && n < H ? a.src[(size_t)row * H + n] : 0.f;
   for (int i = 0; i < a.n; ++i) {
     const int t = FWD ? a.t0 + i : a.t0 - i;
@@ -250,6 +254,7 @@ __global__ __launch_bounds__(1024) void rnn_wide_redo_kernel(RnnWideArgs a) {
         if (i + 1 == a.n && a.carry) a.carry[(size_t)row * H + n] = s[n];
       }
     }
+  }
   }
 }
 
@@ -295,7 +300,7 @@ hipError_t launch_rnn_wide(bool forward, const RnnWideArgs& a, hipStream_t st) {
   }
   if (e != hipSuccess) return e;
   auto redo = forward ? rnn_wide_redo_kernel<true> : rnn_wide_redo_kernel<false>;
-  hipLaunchKernelGGL(redo, dim3(a.B), dim3(1024), 0, st, a);
+  hipLaunchKernelGGL(redo, dim3(std::min(a.B, 32)), dim3(1024), 0, st, a);
   return hipGetLastError();
 }
 
