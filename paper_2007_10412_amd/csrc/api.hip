@@ -865,7 +865,8 @@ static rad_status project_forward(rad_ctx* c, rad_store* s, const rad_sampling* 
 
 // dW = beta dW + R (z^T g) / sqrt(k): the k x N product first, then R times it
 static rad_status project_dW(rad_ctx* c, const rad_store* s, const void* dy, int N, const uint32_t* bits,
-                             int bits_pitch, float* dW, int beta, int slot = 0) {
+                             int bits_pitch, float* dW, int beta, int slot = 0, int64_t g_ld = 0) {
+  const int64_t ldy = g_ld > 0 ? g_ld : N;
   if (!s->proj_valid) return fail(c, RAD_ERR_PARAM, "the store holds no projection yet");
   const void* zsrc = static_cast<const char*>(s->values) + (size_t)slot * s->rows * s->k_pitch * s->elem();
   const uint32_t step = s->proj_step + (uint32_t)slot;
@@ -882,7 +883,7 @@ static rad_status project_dW(rad_ctx* c, const rad_store* s, const void* dy, int
     GemmArgs g = gemm_zero();
     g.M = s->cols; g.N = N; g.K = s->rows;
     g.A = dense; g.lda = s->cols;
-    g.B = dy; g.ldb = N; g.b_mask = bits; g.b_mask_pitch = bits_pitch;
+    g.B = dy; g.ldb = ldy; g.b_mask = bits; g.b_mask_pitch = bits_pitch;
     g.C = dW; g.ldc = N; g.beta = beta; g.c_dtype = kF32;
     return run_gemm_call(c, s->dtype, kOpMN, kOpMN, kEpiStore, g);
   }
@@ -894,7 +895,7 @@ static rad_status project_dW(rad_ctx* c, const rad_store* s, const void* dy, int
   GemmArgs g = gemm_zero();
   g.M = s->k_pitch; g.N = N; g.K = s->rows;
   g.A = zsrc; g.lda = s->k_pitch;
-  g.B = dy; g.ldb = N; g.b_mask = bits; g.b_mask_pitch = bits_pitch;
+  g.B = dy; g.ldb = ldy; g.b_mask = bits; g.b_mask_pitch = bits_pitch;
   g.C = T; g.ldc = N; g.beta = 0; g.c_dtype = kF32;
   SplitPlan sp;
   if (s->dtype == kBF16) RAD_TRY(split_k_for_few_tiles(c, &g, &sp));
@@ -1009,17 +1010,19 @@ static rad_status dw_dense_f32(rad_ctx* c, GemmArgs g, double alg) {
 // stores whose rows are planned one by one and kept with their indices
 // dy_ld > N (see dw_pitched_ok): the rows of dy are dy_ld apart, a multiple of 256, and zero past column N; the
 // contraction then runs on whole tiles of dy_ld columns and only the reduction of its split-K partial sums knows N
+// g_ld > N: the rows of dy are g_ld apart, whatever the path
 static bool dw_pitched_ok(const rad_store* s, int N, int dy_ld);
 static rad_status dW_gemm(rad_ctx* c, const rad_store* s, int slot, const void* dy, int N, const uint32_t* bits,
-                          int bits_pitch, float* dW, int beta, int n_slots = 1, int dy_ld = 0) {
+                          int bits_pitch, float* dW, int beta, int n_slots = 1, int dy_ld = 0, int64_t g_ld = 0) {
   if (dy_ld > 0 && dy_ld != N && (n_slots != 1 || bits || !dw_pitched_ok(s, N, dy_ld)))
     return fail(c, RAD_ERR_PARAM, "pitched dy outside the split-K path of dW");
   const int n_out = N;
   if (dy_ld > N) N = dy_ld;
-  if (s->project()) return project_dW(c, s, dy, N, bits, bits_pitch, dW, beta, slot);
+  const int64_t ldy = g_ld > 0 ? g_ld : N;
+  if (s->project()) return project_dW(c, s, dy, N, bits, bits_pitch, dW, beta, slot, g_ld);
   GemmArgs g = gemm_zero();
   g.N = N; g.K = s->rows * n_slots;
-  g.B = dy; g.ldb = N; g.b_mask = bits; g.b_mask_pitch = bits_pitch;
+  g.B = dy; g.ldb = ldy; g.b_mask = bits; g.b_mask_pitch = bits_pitch;
   g.C = dW; g.ldc = N; g.beta = beta; g.c_dtype = kF32;
   if (s->scheme == RAD_EXACT) {
     g.M = s->cols;
@@ -1080,7 +1083,7 @@ static rad_status dW_gemm(rad_ctx* c, const rad_store* s, int slot, const void* 
     }
     const StoreView v = g.sa;
     HIP_TRY(c, timed(c, "dw_narrow", [&](const char**) {
-      return launch_dw_narrow(v, s->dtype, s->rows, dy, N, N, bits, bits_pitch, out, splits > 1 ? 0 : beta, splits,
+      return launch_dw_narrow(v, s->dtype, s->rows, dy, ldy, N, bits, bits_pitch, out, splits > 1 ? 0 : beta, splits,
                               splits > 1 ? (int64_t)s->cols * N : 0, c->stream);
     }));
     if (splits > 1)
@@ -1138,7 +1141,7 @@ static rad_status dW_gemm(rad_ctx* c, const rad_store* s, int slot, const void* 
     // the bf16 kernel keeps a fixed number of entries per (row, bucket) in registers; the rest, if any, here
     const int cap = gemm_bf16_sparse_cap(g.sparse_prefetch);
     HIP_TRY(c, timed(c, "dw_overflow", [&](const char**) {
-      return launch_dw_overflow(g.sa, s->rows, dy, s->dtype, n_out, bits, bits_pitch, dW, cap, s->max_seg, c->stream, N);
+      return launch_dw_overflow(g.sa, s->rows, dy, s->dtype, n_out, bits, bits_pitch, dW, cap, s->max_seg, c->stream, ldy);
     }));
   }
   return RAD_OK;
@@ -1205,14 +1208,35 @@ static rad_status colsum_call(rad_ctx* c, const void* dy, int dtype, int rows, i
   return RAD_OK;
 }
 
-// The direct-to-LDS GEMMs cannot mask an operand, and where they apply (whole 256-row tiles, half a wave of workgroups)
-// one pass that writes g = dy masked by the ReLU bits to a context workspace costs less than the masking loaders of the
-// ring kernels: 4096^3, dW 175 -> 95 + 14 (unpack) and dX 176 -> 105 us, the pass 20 us a call, which on the dW side has the
-// bias gradient in it.
-// m_dim x n_dim: the output of the GEMM; k_dim its contraction.
-static bool premask_pays(int dtype, const uint32_t* bits, int64_t m_dim, int64_t n_dim, int64_t k_dim) {
-  return dtype == kBF16 && bits && m_dim % 256 == 0 && n_dim % 8 == 0 && k_dim % 8 == 0 &&
-         (m_dim / 256) * ((n_dim + 255) / 256) >= 128;
+// bf16 layers with ReLU: one pass writes g = dy under the bits to a context workspace, rows padded to whole cache lines, and
+// the products read that.  A loader that masks asks for a word of bits per 16 bytes, scattered like its chunks, again in
+// every tile that reads them (dX of 1000 x 768 x 3072 65 us against 27, dW of 256 x 4096 x 4096 112 against 44), and the
+// direct-to-LDS kernels cannot mask at all.  The three calls of a layer (batch x d_in x d_out), us, before / now:
+// 1000 x 768 x 3072 138 / 106, 512 x 1024 x 1024 72 / 62, 2000 x 1000 x 1000 119 / 104, 4096 x 512 x 1024 175 / 123,
+// 256 x 4096 x 4096 181 / 126.  The pass costs 3 us a call, so narrow outputs, whose few slices mask fast, keep the
+// masking loaders (1000 x 1000 x 128 67.7 / 67.7, 200 x 500 x 64 43 / 46), and so do many rows of a narrow input, whose
+// gradient few tiles read (8192 x 300 x 300 88 / 90).
+static bool premask_pays(const rad_layer* L, const uint32_t* bits) {
+  return L->dtype == kBF16 && bits && L->d_out >= 256 && (L->d_in >= 512 || L->batch <= 1024);
+}
+// dX of few columns over whole 256-row tiles: the direct-to-LDS kernel on masked rows is ahead at any width of dy
+static bool premask_pays_dx(const rad_layer* L, const uint32_t* bits) {
+  return premask_pays(L, bits) || (L->dtype == kBF16 && bits && L->batch % 256 == 0 && L->d_in % 256 == 0 && L->d_out % 8 == 0 &&
+                                   (L->batch / 256) * (L->d_in / 256) >= 128);
+}
+// g for them.  On the dW side the column sums of a wide layer's bias gradient read dy anyway and write g on the way.
+static rad_status masked_dy(rad_ctx* c, const rad_layer* L, const rad_store* s, const void* dy, float* dbias, int beta,
+                            void** g, int64_t* g_ld) {
+  *g_ld = (L->d_out + 63) / 64 * 64;
+  RAD_TRY(ws_get(c, WS_CONVG, (size_t)L->batch * *g_ld * 2, g));
+  const int rows = (int)L->batch, N = (int)L->d_out;
+  if (dbias && N >= 512 && *g_ld == N)
+    return colsum_call(c, dy, L->dtype, rows, N, s->bits, s->bits_pitch, nullptr, 0, 0, dbias, nullptr, beta, 0, 0, 0, *g);
+  HIP_TRY(c, timed(c, "mask_rows", [&](const char**) {
+    return launch_mask_rows(dy, rows, N, s->bits, s->bits_pitch, *g, *g_ld, c->stream);
+  }));
+  if (!dbias) return RAD_OK;
+  return colsum_call(c, *g, L->dtype, rows, N, nullptr, 0, nullptr, 0, 0, dbias, nullptr, beta, 0, 0, *g_ld);
 }
 
 // convolution pieces (defined with the CNN model below)
@@ -1263,13 +1287,13 @@ extern "C" rad_status rad_backward_dW(rad_ctx* c, const rad_layer* L, const rad_
     RAD_TRY(conv_masked_dy(c, L, s, dy, &g));
     return conv_dW_call(c, s, (int)L->batch, L->c_in, L->c_out, L->h, L->w, L->kh, g, dW, dbias);
   }
-  const bool dense = s->scheme == RAD_EXACT || (s->per_entry() && dw_dense_pays(s, (int)L->d_out));
-  if (dense && premask_pays(L->dtype, s->bits, L->d_in, L->d_out, L->batch)) {
+  const int N = (int)L->d_out;
+  const bool narrow = s->per_entry() && dw_narrow_pays(s->dtype, s->rows, s->cols, N, sparse_prefetch_for(s, 8), s->bits != nullptr);
+  if (!narrow && premask_pays(L, s->bits)) {          // (the kernel for narrow layers masks a row once)
     void* g = nullptr;
-    RAD_TRY(ws_get(c, WS_CONVG, (size_t)L->batch * L->d_out * s->elem(), &g));
-    RAD_TRY(colsum_call(c, dy, L->dtype, (int)L->batch, (int)L->d_out, s->bits, s->bits_pitch, nullptr, 0, 0, dbias, nullptr,
-                        beta != 0.f, 0, 0, 0, g));
-    return dW_gemm(c, s, 0, g, (int)L->d_out, nullptr, 0, dW, beta != 0.f);
+    int64_t g_ld = 0;
+    RAD_TRY(masked_dy(c, L, s, dy, dbias, beta != 0.f, &g, &g_ld));
+    return dW_gemm(c, s, 0, g, N, nullptr, 0, dW, beta != 0.f, 1, 0, g_ld);
   }
   RAD_TRY(dW_gemm(c, s, 0, dy, (int)L->d_out, s->bits, s->bits_pitch, dW, beta != 0.f));
   if (dbias)
@@ -1291,12 +1315,11 @@ extern "C" rad_status rad_backward_dX(rad_ctx* c, const rad_layer* L, const rad_
     return conv_dX_call(c, (int)L->batch, L->c_in, L->c_out, L->h, L->w, L->kh, g, static_cast<const float*>(W),
                         static_cast<float*>(dX));
   }
-  if (L->d_in % 256 == 0 && premask_pays(L->dtype, s->bits, L->batch, L->d_in, L->d_out)) {
+  if (premask_pays_dx(L, s->bits)) {
     void* g = nullptr;
-    RAD_TRY(ws_get(c, WS_CONVG, (size_t)L->batch * L->d_out * s->elem(), &g));
-    RAD_TRY(colsum_call(c, dy, L->dtype, (int)L->batch, (int)L->d_out, s->bits, s->bits_pitch, nullptr, 0, 0, nullptr, nullptr,
-                        0, 0, 0, 0, g));
-    return dX_gemm(c, L->dtype, (int)L->batch, (int)L->d_in, (int)L->d_out, g, nullptr, 0, W, dX);
+    int64_t g_ld = 0;
+    RAD_TRY(masked_dy(c, L, s, dy, nullptr, 0, &g, &g_ld));
+    return dX_gemm(c, L->dtype, (int)L->batch, (int)L->d_in, (int)L->d_out, g, nullptr, 0, W, dX, nullptr, 0, (int)g_ld);
   }
   return dX_gemm(c, L->dtype, (int)L->batch, (int)L->d_in, (int)L->d_out, dy, s->bits, s->bits_pitch, W, dX);
 }

@@ -35,6 +35,15 @@ __device__ __forceinline__ int lanes_below(uint64_t ballot) {
                                    __builtin_amdgcn_mbcnt_lo((uint32_t)ballot, 0));
 }
 
+// =========================================================== bf16 helper
+__device__ __forceinline__ void mask_bf16x8(u32x4& t, uint32_t mb) {
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    const uint32_t keep = ((mb >> (2 * e)) & 1u ? 0x0000FFFFu : 0u) | ((mb >> (2 * e + 1)) & 1u ? 0xFFFF0000u : 0u);
+    t[e] &= keep;
+  }
+}
+
 // View of a compressed store as kernels see it.  All pointers are device memory.
 struct StoreView {
   void* values;              // capacity entries, storage dtype

@@ -223,15 +223,6 @@ template <int R, int BK, int SE> struct F32LoadSparse {
   }
 };
 
-// =========================================================== bf16 helper
-__device__ __forceinline__ void mask_bf16x8(u32x4& t, uint32_t mb) {
-#pragma unroll
-  for (int e = 0; e < 4; ++e) {
-    const uint32_t keep = ((mb >> (2 * e)) & 1u ? 0x0000FFFFu : 0u) | ((mb >> (2 * e + 1)) & 1u ? 0xFFFF0000u : 0u);
-    t[e] &= keep;
-  }
-}
-
 // ========================================================= im2col loaders
 // position index gm = b*H*W + y*W + x; reduction index gk = (c*KH + u)*KW + v;
 // element = src[b][c][y+u-pad][x+v-pad], zero outside the image.

@@ -99,6 +99,9 @@ hipError_t launch_colsum(const void* dy, int dtype, int rows, int N, const uint3
                          int beta, float* partial, int splits, hipStream_t st, int u_block_rows = 0,
                          int64_t u_block_stride = 0, int64_t ldy = 0,        // ldy > 0: the rows of dy are ldy apart
                          void* g_out = nullptr, int64_t g_ld = 0);           // g_out: g itself too, its rows g_ld apart
+// g [rows][g_ld] = dy [rows][N] (bf16) under its ReLU bits, zeros in columns N .. g_ld - 1; g_ld a multiple of 8
+hipError_t launch_mask_rows(const void* dy, int rows, int N, const uint32_t* bits, int bits_pitch, void* g, int64_t g_ld,
+                            hipStream_t st);
 hipError_t launch_fill_u32(uint32_t* p, uint32_t v, int64_t n, hipStream_t st);
 // Rademacher matrix of the projection scheme: R [d][kp] and its transpose Rt [kp][d] in the given dtype, +1 / -1
 // from the key stream (entry (j, s) = bit j*k + s), zero in the padding columns s >= k (both must be zeroed first)

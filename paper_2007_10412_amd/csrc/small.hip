@@ -590,6 +590,40 @@ hipError_t launch_softmax_ce(const void* logits, const int32_t* labels, int rows
   return hipGetLastError();
 }
 
+// g = dy under its ReLU bits, rows g_ld apart (a whole number of 16-byte vectors, zeros past column N): one pass at the copy
+// rate ahead of the bf16 products, which then read aligned rows and no bits
+__global__ __launch_bounds__(256) void mask_rows_kernel(const uint16_t* __restrict__ dy, int64_t chunks, int N, int cpr,
+                                                        const uint32_t* __restrict__ bits, int bits_pitch,
+                                                        uint16_t* __restrict__ g) {
+  for (int64_t c = (int64_t)blockIdx.x * 256 + threadIdx.x; c < chunks; c += (int64_t)gridDim.x * 256) {
+    const int64_t row = c / cpr;
+    const int col = (int)(c - row * cpr) * 8;
+    u32x4 v = {0u, 0u, 0u, 0u};
+    if (col < N) {
+      const uint16_t* src = dy + row * N + col;
+      const uint32_t keep = bits[row * bits_pitch + (col >> 5)] >> (col & 31);
+      if (col + 8 <= N) __builtin_memcpy(&v, src, 16);
+      else {
+        uint16_t* ve = reinterpret_cast<uint16_t*>(&v);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) if (col + e < N) ve[e] = src[e];
+      }
+      mask_bf16x8(v, keep);
+    }
+    reinterpret_cast<u32x4*>(g)[c] = v;
+  }
+}
+
+hipError_t launch_mask_rows(const void* dy, int rows, int N, const uint32_t* bits, int bits_pitch, void* g, int64_t g_ld,
+                            hipStream_t st) {
+  if (g_ld % 8 || g_ld < N) return hipErrorInvalidValue;
+  const int cpr = (int)(g_ld / 8);
+  const int64_t chunks = (int64_t)rows * cpr, blocks = (chunks + 255) / 256;
+  hipLaunchKernelGGL(mask_rows_kernel, dim3((unsigned)(blocks < 65536 ? blocks : 65536)), dim3(256), 0, st,
+                     static_cast<const uint16_t*>(dy), chunks, N, cpr, bits, bits_pitch, static_cast<uint16_t*>(g));
+  return hipGetLastError();
+}
+
 hipError_t launch_colsum(const void* dy, int dtype, int rows, int N, const uint32_t* bits, int bits_pitch,
                          const float* u, int64_t u_ld, int u_n, float* out_bias, float* out_u, int beta,
                          float* partial, int splits, hipStream_t st, int u_block_rows, int64_t u_block_stride,
