@@ -60,6 +60,8 @@ __device__ __forceinline__ bf16x8 mn_frag_read(const unsigned char* tile, uint32
   return u.v;
 }
 
+// thread number among the 256 threads that work on one K range of a tile (a workgroup has one such group, or two)
+__device__ __forceinline__ int gemm_tid() { return (int)(threadIdx.x & (kGemmThreads - 1)); }
 
 // ------------------------------------------------------------------ loaders
 // dense, K contiguous: element (row, k) at p[row*ld + k]
@@ -96,7 +98,7 @@ template <int R, int EMODE, bool MASKED, int NS> struct RingLoadK {
     const bool guard = EMODE == 2 && KTAIL && k0 + kBK3 > K;     // uniform: the slice reaches past K
 #pragma unroll
     for (int i = 0; i < NCH; ++i) {
-      const int c = threadIdx.x + i * kGemmThreads;
+      const int c = gemm_tid() + i * kGemmThreads;
       u32x4 t = {0u, 0u, 0u, 0u};
       if (MASKED) mb[SLOT][i] = 0u;
       if (TOTAL % kGemmThreads == 0 || c < TOTAL) {
@@ -135,7 +137,7 @@ template <int R, int EMODE, bool MASKED, int NS> struct RingLoadK {
   template <int SLOT, int STEP> __device__ __forceinline__ void commit_step(uint16_t* lds) {
 #pragma unroll
     for (int i = STEP; i < NCH; i += 4) {
-      const int c = threadIdx.x + i * kGemmThreads;
+      const int c = gemm_tid() + i * kGemmThreads;
       if (TOTAL % kGemmThreads == 0 || c < TOTAL) {
         const int row = c / L::CH, kc = c % L::CH;
         if (MASKED) mask_bf16x8(v[SLOT][i], mb[SLOT][i]);
@@ -174,7 +176,7 @@ template <int R, int EMODE, bool MASKED, int NS> struct RingLoadMN {
   static constexpr int SUB = 8 / KPT;
   static_assert(RB * SUB == 64, "a wave covers every row block at one unit column");
   static __device__ __forceinline__ int block_rb() { return (threadIdx.x & 63) / SUB; }
-  static __device__ __forceinline__ int block_kq() { return (threadIdx.x >> 6) * SUB + (threadIdx.x & 63) % SUB; }
+  static __device__ __forceinline__ int block_kq() { return (gemm_tid() >> 6) * SUB + (threadIdx.x & 63) % SUB; }
   u32x4 v[NS][KPT];                          // v[..][kk] = 8 consecutive rows at k = kq*KPT + kk
   uint32_t mb[MASKED ? NS : 1][MASKED ? KPT : 1];
   const uint16_t* p; const uint32_t* mask; uint32_t ld; int mp, r0, rmax, K;
@@ -259,7 +261,7 @@ template <int R, int EMODE, bool MASKED, int NS> struct RingLoadMNT {
     const bool guard = EMODE == 2 && KTAIL && k0 + kBK3 + 8 > K;       // as in RingLoadMN
 #pragma unroll
     for (int i = 0; i < NCH; ++i) {
-      const int q = i * kGemmThreads + (int)threadIdx.x;
+      const int q = i * kGemmThreads + gemm_tid();
       const int gk = k0 + (q >> 5), gr = r0 + (q & 31) * 8;
       if (EMODE == 0) {
         v[SLOT][i] = *reinterpret_cast<const u32x4*>(p + ((uint32_t)gk * ld + (uint32_t)gr));
@@ -281,7 +283,7 @@ template <int R, int EMODE, bool MASKED, int NS> struct RingLoadMNT {
     }
   }
   template <int SLOT, int STEP> __device__ __forceinline__ void commit_step(uint16_t* lds) {
-    const int q = STEP * kGemmThreads + (int)threadIdx.x;
+    const int q = STEP * kGemmThreads + gemm_tid();
     if (MASKED) mask_bf16x8(v[SLOT][STEP], mb[SLOT][STEP]);
     *reinterpret_cast<u32x4*>(reinterpret_cast<unsigned char*>(lds) + LdsMN<R>::byte_of((q & 31) * 8, q >> 5)) = v[SLOT][STEP];
   }
@@ -314,7 +316,7 @@ template <int R, int SE, int NS> struct RingLoadSparse {
   // Segment of the next slice's store row inside this tile's 256-column bucket.  Only the loads are issued
   // here; the arithmetic on them waits until the next fetch, one whole iteration later.
   __device__ __forceinline__ void bounds(int k0) {
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const int lane = threadIdx.x & 63, w = gemm_tid() >> 6;
     const int b = k0 + w * RPW + lane / LPR;
     // no branch: rows past K read row K-1 and get an empty segment
     const int row = b < K ? b : K - 1;
@@ -343,7 +345,7 @@ template <int R, int SE, int NS> struct RingLoadSparse {
   }
   // steps 0 and 1 clear the wave's unit column of the tile, steps 2 and 3 scatter the entries into it
   template <int SLOT, int STEP> __device__ __forceinline__ void commit_step(uint16_t* lds) {
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const int lane = threadIdx.x & 63, w = gemm_tid() >> 6;
     if (STEP < 2) {
       const u32x4 z = {0u, 0u, 0u, 0u};
 #pragma unroll
@@ -480,10 +482,12 @@ template <int Q, int TM, int TN, class RA, class RB> __device__ __forceinline__ 
 }
 
 // STAGED: the store epilogue passes the bf16 output tile through LDS (dX family)
-template <int EPI, int BM, int BN, bool STAGED>
+// HALVES: two K ranges, each with stages of its own; the second group's sums go through the same space at the end
+template <int EPI, int BM, int BN, bool STAGED, bool HALVES = false>
 struct Gemm3Smem {
   static constexpr int STAGE = (BM + BN) * kBK3 * 2 + 128;   // + spare bytes for the sparse loader
-  static constexpr int MAIN = 3 * STAGE;
+  static constexpr int STAGES = (HALVES ? 2 : 1) * 3 * STAGE, SUMS = HALVES ? BM * BN * 4 : 0;
+  static constexpr int MAIN = STAGES > SUMS ? STAGES : SUMS;
   static constexpr int CT = EPI == kEpiFwd ? FwdEpiLds<uint16_t, BM, BN>::BYTES : STAGED ? BM * (BN + 8) * 2 : 0;
   static constexpr int BYTES = CT > MAIN ? CT : MAIN;
 };
@@ -551,21 +555,28 @@ __device__ __forceinline__ void epilogue_dx_staged(const GemmArgs& g, floatx16 (
 
 template <int V> using IntC = std::integral_constant<int, V>;
 
+// kFlagKHalves: a workgroup of 512 threads, whose two groups of 256 take half of the K range each, with stages of their own;
+// the second group's sums are added to the first's through LDS, and the first goes on to the epilogue (a wave that has ended
+// takes no part in barriers).  For dW from the store on grids of at most a workgroup a CU, where clearing and scattering
+// leaves the one wave per SIMD waiting: dW of 2000 rows, 1000 x 1000 (8 x 16 tiles) 30 -> 26 us, 1000 rows, 1000 x 128 24 -> 20;
+// forward and dX of such grids are bound by the loads of the CU and gain nothing.
 template <int AK, int BKIND, int EPI, int BM, int BN, int SE, int FLAGS>
-__global__ __launch_bounds__(kGemmThreads) void gemm3_bf16_kernel(GemmArgs g) {
+__global__ __launch_bounds__(kGemmThreads * ((FLAGS & kFlagKHalves) ? 2 : 1)) void gemm3_bf16_kernel(GemmArgs g) {
+  constexpr bool kHalves = (FLAGS & kFlagKHalves) != 0;
   constexpr bool EDGE = (FLAGS & (kFlagEdge | kFlagEdgeVec)) != 0;
   constexpr int EMODE = (FLAGS & kFlagEdge) ? 2 : (FLAGS & kFlagEdgeVec) ? 1 : 0;
   constexpr int BK = kBK3;
   constexpr bool kStaged = EPI == kEpiStore && AK == kOpK;
-  typedef Gemm3Smem<EPI, BM, BN, kStaged> S;
+  typedef Gemm3Smem<EPI, BM, BN, kStaged, kHalves> S;
   constexpr int NS = (BM * BN >= 256 * 256) ? 1 : 3;
   typedef typename RingLoaderOf<AK, BM, SE, EMODE, (FLAGS & kFlagMaskA) != 0, NS>::type LoadA;
   typedef typename RingLoaderOf<BKIND, BN, SE, EMODE, (FLAGS & kFlagMaskB) != 0, NS>::type LoadB;
   constexpr int TM = BM / 64, TN = BN / 64;
   constexpr bool kAT = LoadA::kTr, kBT = LoadB::kTr;   // fragments of that operand come from transposing reads
   extern __shared__ __align__(16) unsigned char smem_raw[];
-  uint16_t* const smem = reinterpret_cast<uint16_t*>(smem_raw);
   constexpr int kStageElems = S::STAGE / 2;
+  const int kgrp = kHalves ? __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kGemmThreads)) : 0;
+  uint16_t* const smem = reinterpret_cast<uint16_t*>(smem_raw) + (kHalves ? kgrp * 3 * kStageElems : 0);
   constexpr int kAElems = BM * BK;
 
   // Tile order.  Workgroup ids go round-robin over the 8 XCDs, each with its own L2, so ids are first
@@ -583,7 +594,7 @@ __global__ __launch_bounds__(kGemmThreads) void gemm3_bf16_kernel(GemmArgs g) {
   const int gh = min(GM, tiles_m - grp * GM);      // rows in this (possibly last, shorter) group
   const int tm = grp * GM + within % gh, tn = within / gh;
   const int m0 = tm * BM, n0 = tn * BN;
-  const int w = threadIdx.x >> 6;
+  const int w = gemm_tid() >> 6;
   const int wm0 = (w >> 1) * (BM / 2), wn0 = (w & 1) * (BN / 2);
   uint32_t atr[TM], btr[TN];
 #pragma unroll
@@ -600,8 +611,14 @@ __global__ __launch_bounds__(kGemmThreads) void gemm3_bf16_kernel(GemmArgs g) {
       for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
 
   // split K: blockIdx.y takes the K range [kbeg, kend) and the epilogue adds its partial result atomically
-  const int kbeg = g.k_splits > 1 ? (int)blockIdx.y * g.k_split : 0;
-  const int kend = g.k_splits > 1 ? min(g.K, kbeg + g.k_split) : g.K;
+  int kbeg = g.k_splits > 1 ? (int)blockIdx.y * g.k_split : 0;
+  int kend = g.k_splits > 1 ? min(g.K, kbeg + g.k_split) : g.K;
+  int KT_all = 0;                                  // slices of the longer half: both groups pass that many barriers
+  if constexpr (kHalves) {
+    KT_all = (kend - kbeg + 2 * BK - 1) / (2 * BK);
+    const int mid = min(kend, kbeg + KT_all * BK);
+    if (kgrp == 0) kend = mid; else kbeg = mid;
+  }
   LoadA la; LoadB lb;
   la.init(g.A, g.lda, g.a_mask, g.a_mask_pitch, m0, g.m_load > g.M ? g.m_load : g.M, kend, g.sa);
   lb.init(g.B, g.ldb, g.b_mask, g.b_mask_pitch, n0, g.N, kend, g.sa);
@@ -761,6 +778,28 @@ __global__ __launch_bounds__(kGemmThreads) void gemm3_bf16_kernel(GemmArgs g) {
     body(IntC<0>(), std::false_type(), kt);
     if (kt + 1 < KT) body(IntC<1>(), std::false_type(), kt + 1);
     if (kt + 2 < KT) body(IntC<2>(), std::false_type(), kt + 2);
+  }
+
+  if constexpr (kHalves) {
+    for (int i = KT; i < KT_all; ++i) __syncthreads();       // (the same number of barriers in both groups)
+    float* const sums = reinterpret_cast<float*>(smem_raw) + gemm_tid();
+    if (kgrp == 1) {
+#pragma unroll
+      for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+#pragma unroll
+          for (int e = 0; e < 16; ++e) sums[((i * TN + j) * 16 + e) * kGemmThreads] = acc[i][j][e];
+    }
+    __syncthreads();
+    if (kgrp == 1) return;
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int j = 0; j < TN; ++j)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) acc[i][j][e] += sums[((i * TN + j) * 16 + e) * kGemmThreads];
+    __syncthreads();                                         // the epilogue's tile takes that space
   }
 
   if constexpr (EPI == kEpiStore) {

@@ -7,15 +7,19 @@
 
 namespace rad {
 
+inline int tiles_of(const GemmArgs& g, int bm, int bn) {
+  return ((g.M + bm - 1) / bm) * ((g.N + bn - 1) / bn);
+}
+
 // Launches a GEMM kernel; with timing events in the arguments the dispatch itself records them (start and end
 // of the kernel), so timing one kernel of a step puts no extra packets, and no bubbles, on the stream.
 template <class K>
-hipError_t launch_gemm_kernel(K kern, dim3 grid, int smem, hipStream_t st, const GemmArgs& g) {
+hipError_t launch_gemm_kernel(K kern, dim3 grid, int smem, hipStream_t st, const GemmArgs& g, int threads = kGemmThreads) {
   if (g.ev_start && g.ev_stop)
-    hipExtLaunchKernelGGL(kern, grid, dim3(kGemmThreads), smem, st, static_cast<hipEvent_t>(g.ev_start),
+    hipExtLaunchKernelGGL(kern, grid, dim3(threads), smem, st, static_cast<hipEvent_t>(g.ev_start),
                           static_cast<hipEvent_t>(g.ev_stop), 0, g);
   else
-    hipLaunchKernelGGL(kern, grid, dim3(kGemmThreads), smem, st, g);
+    hipLaunchKernelGGL(kern, grid, dim3(threads), smem, st, g);
   return hipGetLastError();
 }
 
@@ -69,7 +73,8 @@ hipError_t run_gemm(const GemmArgs& g, hipStream_t st) {
 template <int AK, int BKIND, int EPI, int BM, int BN, int SE, int FLAGS>
 hipError_t run_gemm3_variant(const GemmArgs& g, hipStream_t st) {
   auto kern = gemm3_bf16_kernel<AK, BKIND, EPI, BM, BN, SE, FLAGS>;
-  constexpr int smem = Gemm3Smem<EPI, BM, BN, EPI == kEpiStore && AK == kOpK>::BYTES;
+  constexpr bool halves = (FLAGS & kFlagKHalves) != 0;
+  constexpr int smem = Gemm3Smem<EPI, BM, BN, EPI == kEpiStore && AK == kOpK, halves>::BYTES;
   static_assert(smem <= 160 * 1024, "tile does not fit the 160 KB LDS of a gfx950 CU");
   static bool prepared = false;   // one host thread drives a context
   if (!prepared) {
@@ -80,7 +85,8 @@ hipError_t run_gemm3_variant(const GemmArgs& g, hipStream_t st) {
   }
   const int tiles_m = (g.M + BM - 1) / BM, tiles_n = (g.N + BN - 1) / BN;
   if (tiles_m <= 0 || tiles_n <= 0) return hipSuccess;
-  return launch_gemm_kernel(kern, dim3(tiles_m * tiles_n, g.k_splits > 1 ? g.k_splits : 1), smem, st, g);
+  return launch_gemm_kernel(kern, dim3(tiles_m * tiles_n, g.k_splits > 1 ? g.k_splits : 1), smem, st, g,
+                            halves ? 2 * kGemmThreads : kGemmThreads);
 }
 
 // ---- bf16 kernels whose operands go from global memory straight into LDS: whole 256-row tiles (a ragged last
@@ -136,6 +142,16 @@ hipError_t run_gemm3(const GemmArgs& g, hipStream_t st) {
   const bool ma = MASK_A && g.a_mask != nullptr, mb = MASK_B && g.b_mask != nullptr;
   if ((g.a_mask && !MASK_A) || (g.b_mask && !MASK_B)) return hipErrorInvalidValue;
   constexpr int FA = MASK_A ? kFlagMaskA : 0, FB = MASK_B ? kFlagMaskB : 0;
+  // dW from the store with at most a workgroup a CU and a chain of several slices: two groups of threads share it
+  if constexpr (AK == kOpSparse && BM * BN <= 128 * 128) {
+    const int splits = g.k_splits > 1 ? g.k_splits : 1;
+    if (tiles_of(g, BM, BN) * splits <= 256 && (splits > 1 ? g.k_split : g.K) >= 128) {
+      constexpr int H = kFlagKHalves;
+      if (ma || mb) return run_gemm3_variant<AK, BKIND, EPI, BM, BN, SE, kFlagEdge | FA | FB | H>(g, st);
+      if (gemm_is_vec_edge<AK, BKIND>(g)) return run_gemm3_variant<AK, BKIND, EPI, BM, BN, SE, kFlagEdgeVec | H>(g, st);
+      return run_gemm3_variant<AK, BKIND, EPI, BM, BN, SE, kFlagEdge | H>(g, st);
+    }
+  }
   if (ma || mb) return run_gemm3_variant<AK, BKIND, EPI, BM, BN, SE, kFlagEdge | FA | FB>(g, st);
   if (BOTH_EDGE && gemm_is_full<BF16Tag, AK, BM, BN, 32>(g)) return run_gemm3_variant<AK, BKIND, EPI, BM, BN, SE, 0>(g, st);
   if (gemm_is_vec_edge<AK, BKIND>(g)) return run_gemm3_variant<AK, BKIND, EPI, BM, BN, SE, kFlagEdgeVec>(g, st);
@@ -144,9 +160,5 @@ hipError_t run_gemm3(const GemmArgs& g, hipStream_t st) {
 
 hipError_t launch_gemm_f32(int a_kind, int b_kind, int epi, const GemmArgs& g, hipStream_t st, const char** name);
 hipError_t launch_gemm_bf16(int a_kind, int b_kind, int epi, const GemmArgs& g, hipStream_t st, const char** name);
-
-inline int tiles_of(const GemmArgs& g, int bm, int bn) {
-  return ((g.M + bm - 1) / bm) * ((g.N + bn - 1) / bn);
-}
 
 }  // namespace rad
