@@ -567,44 +567,57 @@ extern "C" rad_status rad_store_import_bits(rad_ctx* c, rad_store* s, const uint
   return RAD_OK;
 }
 
-// draws the keep sets of every row and step of `s` into `bitmap`
+// draws the keep sets of every row and step of n stores into their bitmaps, in as few launches as their schemes and widths
+// allow; sm: sampling parameters of each
 // clear_max_seg = false when the caller has already zeroed the segment maxima of all its stores at once
-static rad_status store_plan(rad_ctx* c, rad_store* s, const rad_sampling* sm, uint32_t* bitmap,
-                             bool clear_max_seg = true, bool untimed = false) {
-  if (s->scheme == RAD_EXACT || s->project()) return RAD_OK;
-  PlanArgs a;
-  a.seed_lo = (uint32_t)sm->seed; a.seed_hi = (uint32_t)(sm->seed >> 32);
-  a.stream_id = sm->stream_id; a.step0 = sm->step;
-  a.scheme = s->scheme;
-  a.plan_rows = s->steps * s->plan_rows_per_step;
-  a.rows_per_step = s->rows;
-  a.cols = s->cols; a.k = s->k; a.k_pitch = s->k_pitch;
-  a.thresh = (uint64_t)std::llround(s->p * 4294967296.0) >> c->key_shift;
-  a.guess = (uint32_t)std::min(4294967295.0, std::floor((double)s->k / (double)s->cols * 4294967296.0)) >> c->key_shift;
-  a.gap = (uint32_t)std::min(4294967295.0, std::floor(4294967296.0 / (double)s->cols)) >> c->key_shift;
-  a.key_shift = c->key_shift;
-  c->key_shift = 0;                 // the test hook serves one draw: it cannot be left on
-  a.bitmap = bitmap; a.bm_pitch = s->bm_pitch;
-  a.bucket_off = s->bucket_off; a.nb = s->nb;
-  a.row_cnt = s->row_cnt; a.row_ptr = s->row_ptr;
-  a.max_seg = s->max_seg;
-  a.mult = s->mult;
-  s->last_plan = *sm; s->planned = true;
-  s->bitmap = bitmap;
-  if (clear_max_seg) HIP_TRY(c, launch_fill_u32(reinterpret_cast<uint32_t*>(s->max_seg), 0u, 1, c->stream));
-  if (untimed) {              // launches only: the timing wrapper may create events
-    HIP_TRY(c, launch_plan(a, c->stream));
-    if (s->counted_rows())
-      HIP_TRY(c, launch_row_scan(s->row_cnt, s->row_ptr, s->steps * s->rows, s->capacity, s->overflow, c->stream));
+static rad_status stores_plan(rad_ctx* c, rad_store* const* stores, const rad_sampling* sm, uint32_t* const* bitmaps, int n,
+                              bool clear_max_seg, bool untimed = false) {
+  PlanArgs args[kPlanBatch];
+  ScanArgs scans[kPlanBatch];
+  int na = 0, ns = 0;
+  auto flush = [&]() -> rad_status {
+    if (na > 0) {
+      if (untimed) HIP_TRY(c, launch_plan(args, na, c->stream));       // launches only: the timing wrapper may create events
+      else HIP_TRY(c, timed(c, "plan", [&](const char**) { return launch_plan(args, na, c->stream); }));
+    }
+    if (ns > 0) {
+      if (untimed) HIP_TRY(c, launch_row_scan(scans, ns, c->stream));
+      else HIP_TRY(c, timed(c, "row_scan", [&](const char**) { return launch_row_scan(scans, ns, c->stream); }));
+    }
+    na = ns = 0;
     return RAD_OK;
+  };
+  for (int i = 0; i < n; ++i) {
+    rad_store* s = stores[i];
+    if (s->scheme == RAD_EXACT || s->project()) continue;
+    PlanArgs& a = args[na++];
+    a.seed_lo = (uint32_t)sm[i].seed; a.seed_hi = (uint32_t)(sm[i].seed >> 32);
+    a.stream_id = sm[i].stream_id; a.step0 = sm[i].step;
+    a.scheme = s->scheme;
+    a.plan_rows = s->steps * s->plan_rows_per_step;
+    a.rows_per_step = s->rows;
+    a.cols = s->cols; a.k = s->k; a.k_pitch = s->k_pitch;
+    a.thresh = (uint64_t)std::llround(s->p * 4294967296.0) >> c->key_shift;
+    a.guess = (uint32_t)std::min(4294967295.0, std::floor((double)s->k / (double)s->cols * 4294967296.0)) >> c->key_shift;
+    a.gap = (uint32_t)std::min(4294967295.0, std::floor(4294967296.0 / (double)s->cols)) >> c->key_shift;
+    a.key_shift = c->key_shift;
+    c->key_shift = 0;               // the test hook serves one draw: it cannot be left on
+    a.bitmap = bitmaps[i]; a.bm_pitch = s->bm_pitch;
+    a.bucket_off = s->bucket_off; a.nb = s->nb;
+    a.row_cnt = s->row_cnt; a.row_ptr = s->row_ptr;
+    a.max_seg = s->dtype == kBF16 ? s->max_seg : nullptr;      // only the bf16 dW kernels hold a limited number of entries
+    a.mult = s->mult;
+    s->last_plan = sm[i]; s->planned = true;
+    s->bitmap = bitmaps[i];
+    if (clear_max_seg && a.max_seg) HIP_TRY(c, launch_fill_u32(reinterpret_cast<uint32_t*>(s->max_seg), 0u, 1, c->stream));
+    if (s->counted_rows()) scans[ns++] = {s->row_cnt, s->row_ptr, s->steps * s->rows, s->capacity, s->overflow};
+    if (na == kPlanBatch) RAD_TRY(flush());
   }
-  HIP_TRY(c, timed(c, "plan", [&](const char**) { return launch_plan(a, c->stream); }));
-  if (s->counted_rows()) {
-    HIP_TRY(c, timed(c, "row_scan", [&](const char**) {
-      return launch_row_scan(s->row_cnt, s->row_ptr, s->steps * s->rows, s->capacity, s->overflow, c->stream);
-    }));
-  }
-  return RAD_OK;
+  return flush();
+}
+static rad_status store_plan(rad_ctx* c, rad_store* s, const rad_sampling* sm, uint32_t* bitmap, bool clear_max_seg = true,
+                             bool untimed = false) {
+  return stores_plan(c, &s, sm, &bitmap, 1, clear_max_seg, untimed);
 }
 
 static rad_status check_sampling(rad_ctx* c, const rad_sampling* sm, const rad_store* s) {
@@ -1609,10 +1622,28 @@ static rad_status model_share_flags(rad_ctx* c, rad_model* m) {
 
 static rad_status model_clear_max_seg(rad_ctx* c, rad_model* m) {
   const size_t n = m->stores.size();
+  if (m->dtype != kBF16) return RAD_OK;
   HIP_TRY(c, timed(c, "fill", [&](const char**) {
     return launch_fill_u32(reinterpret_cast<uint32_t*>(m->flags + n), 0u, (int64_t)n, c->stream);
   }));
   return RAD_OK;
+}
+
+// keep sets of all layers of a step up front (they depend on seed, step and layer only); bitmaps in one workspace
+static rad_status model_plan(rad_ctx* c, rad_model* m, const rad_sampling* sm) {
+  RAD_TRY(model_clear_max_seg(c, m));
+  size_t words = 0;
+  for (rad_store* s : m->stores) words += s->bitmap_words();
+  if (!words) return RAD_OK;
+  void* bm = nullptr;
+  RAD_TRY(ws_get(c, WS_BITMAP, words * 4, &bm));
+  std::vector<rad_sampling> sl(m->stores.size(), *sm);
+  std::vector<uint32_t*> at(m->stores.size(), static_cast<uint32_t*>(bm));
+  for (size_t l = 0, w = 0; l < m->stores.size(); w += m->stores[l++]->bitmap_words()) {
+    sl[l].stream_id = sm->stream_id + (uint32_t)l;
+    at[l] += w;
+  }
+  return stores_plan(c, m->stores.data(), sl.data(), at.data(), (int)m->stores.size(), false);
 }
 
 // end of a step: with loss_host the step is waited for, the loss read back and a capacity overflow (also
@@ -1641,20 +1672,11 @@ static rad_status mlp_step(rad_ctx* c, rad_model* m, const rad_sampling* sm, con
     if (!params[i] || !grads[i]) return fail(c, RAD_ERR_NULL, "null parameter or gradient pointer");
   auto Wp = [&](int l) { return params[l * per]; };
   auto bp = [&](int l) { return m->has_bias ? static_cast<const float*>(params[l * per + 1]) : nullptr; };
-  size_t bm_words = 0;
-  for (rad_store* s : m->stores) if (s->bitmap_words() > bm_words) bm_words = s->bitmap_words();
-  void* bm = nullptr;
-  if (bm_words) RAD_TRY(ws_get(c, WS_BITMAP, bm_words * 4, &bm));
-
   // forward: layer l consumes the dense activation of layer l-1 (kept only
   // until then) and leaves the packed sample of its own output for layer l+1
-  RAD_TRY(model_clear_max_seg(c, m));
+  RAD_TRY(model_plan(c, m, sm));
   const bool proj = m->scheme == RAD_PROJECT_SHARED || m->scheme == RAD_PROJECT_PER_EXAMPLE;
-  rad_sampling s0 = *sm;
-  if (!proj) {
-    RAD_TRY(store_plan(c, m->stores[0], &s0, static_cast<uint32_t*>(bm), false));
-    RAD_TRY(store_pack(c, m->stores[0], x, 0));
-  }
+  if (!proj) RAD_TRY(store_pack(c, m->stores[0], x, 0));
   const void* a_in = x;
   for (int l = 0; l < Lc; ++l) {
     const bool last = l == Lc - 1;
@@ -1665,8 +1687,6 @@ static rad_status mlp_step(rad_ctx* c, rad_model* m, const rad_sampling* sm, con
     } else if (!last) {
       rad_store* sn = m->stores[(size_t)l + 1];
       if (sn->scheme != RAD_EXACT) {
-        rad_sampling sl = *sm; sl.stream_id = sm->stream_id + (uint32_t)(l + 1);
-        RAD_TRY(store_plan(c, sn, &sl, static_cast<uint32_t*>(bm), false));
         nv = store_view(sn, 0); next = &nv;
       }
     }
@@ -1915,12 +1935,13 @@ static rad_status rnn_step(rad_ctx* c, rad_model* m, const rad_sampling* sm, con
 
   // all keep sets of the step up front: they depend on (seed, step) only
   RAD_TRY(model_clear_max_seg(c, m));
-  if (T > 1) {
-    rad_sampling s1 = *sm; s1.step = sm->step + 2;      // slot s holds h_{s+1}, drawn with step = s+2
-    RAD_TRY(store_plan(c, s_hh, &s1, m->bitmap_ws, false));
-  }
-  rad_sampling s2 = *sm; s2.stream_id = sm->stream_id + 1; s2.step = 0;
-  RAD_TRY(store_plan(c, s_ho, &s2, m->bitmap_ws ? m->bitmap_ws + s_hh->bitmap_words() : nullptr, false));
+  rad_sampling sms[2] = {*sm, *sm};
+  sms[0].step = sm->step + 2;                           // slot s holds h_{s+1}, drawn with step = s+2
+  rad_sampling& s2 = sms[1];
+  s2.stream_id = sm->stream_id + 1; s2.step = 0;
+  uint32_t* const bms[2] = {m->bitmap_ws, m->bitmap_ws ? m->bitmap_ws + s_hh->bitmap_words() : nullptr};
+  const int one = T > 1 ? 0 : 1;                        // (a single step draws for h_T only)
+  RAD_TRY(stores_plan(c, m->stores.data() + one, sms + one, bms + one, 2 - one, false));
 
   const bool fused = rnn_one_launch(m);
   RnnArgs ra;
@@ -2205,11 +2226,7 @@ static rad_status cnn_step(rad_ctx* c, rad_model* m, const rad_sampling* sm, con
   const int B = (int)m->batch, ks = m->ksize, C = (int)m->classes;
   for (int i = 0; i < 2 * (nc + 1); ++i)
     if (!params[i] || !grads[i]) return fail(c, RAD_ERR_NULL, "null parameter or gradient pointer");
-  size_t bm_words = 0;
-  for (rad_store* s : m->stores) if (s->bitmap_words() > bm_words) bm_words = s->bitmap_words();
-  void* bm = nullptr;
-  if (bm_words) RAD_TRY(ws_get(c, WS_BITMAP, bm_words * 4, &bm));
-  RAD_TRY(model_clear_max_seg(c, m));
+  RAD_TRY(model_plan(c, m, sm));
 
   // forward: every conv input is sampled (flattened per example), then convolved exactly
   const float* act = static_cast<const float*>(x);
@@ -2217,8 +2234,6 @@ static rad_status cnn_step(rad_ctx* c, rad_model* m, const rad_sampling* sm, con
   for (int l = 0; l < nc; ++l) {
     const rad_model::Conv& cv = m->convs[(size_t)l];
     rad_store* s = m->stores[(size_t)l];
-    rad_sampling sl = *sm; sl.stream_id = sm->stream_id + (uint32_t)l;
-    RAD_TRY(store_plan(c, s, &sl, static_cast<uint32_t*>(bm), false));
     RAD_TRY(store_pack(c, s, act, 0));
     const int yb = (in_buf + 1 + 3) % 3, pb = (in_buf + 2 + 3) % 3;
     RAD_TRY(conv_gemm(c, B, cv.ci, cv.co, cv.h, cv.w, ks, act, static_cast<const float*>(params[2 * l]),
@@ -2240,11 +2255,7 @@ static rad_status cnn_step(rad_ctx* c, rad_model* m, const rad_sampling* sm, con
     } else { act = static_cast<const float*>(m->buf[yb]); in_buf = yb; }
   }
   rad_store* sfc = m->stores[(size_t)nc];
-  {
-    rad_sampling sl = *sm; sl.stream_id = sm->stream_id + (uint32_t)nc;
-    RAD_TRY(store_plan(c, sfc, &sl, static_cast<uint32_t*>(bm), false));
-    RAD_TRY(store_pack(c, sfc, act, 0));
-  }
+  RAD_TRY(store_pack(c, sfc, act, 0));
   RAD_TRY(forward_gemm(c, kF32, B, C, m->fc_in, act, m->fc_in, params[2 * nc], static_cast<const float*>(params[2 * nc + 1]),
                        0, m->logits, nullptr, 0, nullptr, nullptr, 0, 0, nullptr));
   RAD_TRY(softmax_call(c, m->logits, labels, B, C, kF32, m->dyb[0], loss_host ? c->loss_dev : nullptr));

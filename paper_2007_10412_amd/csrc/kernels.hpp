@@ -21,14 +21,15 @@ struct PlanArgs {
   int nb;
   uint32_t* row_cnt;   // [plan_rows], Bernoulli only
   uint32_t* row_ptr;   // [steps*rows + 1], written here for the fixed-k schemes
-  int* max_seg;        // running maximum of entries per (row, 256-column bucket)
+  int* max_seg;        // running maximum of entries per (row, 256-column bucket), or null
   uint16_t* mult;      // with-replacement draws: draw counts of the kept columns, [plan_rows][k] in entry order
 };
 
-hipError_t launch_plan(const PlanArgs& a, hipStream_t st);
+constexpr int kPlanBatch = 8;          // stores that one call draws for
+hipError_t launch_plan(const PlanArgs* a, int n, hipStream_t st);
 int plan_max_cols(int scheme);
-hipError_t launch_row_scan(const uint32_t* row_cnt, uint32_t* row_ptr, int rows, int64_t capacity,
-                           int* overflow, hipStream_t st);
+struct ScanArgs { const uint32_t* row_cnt; uint32_t* row_ptr; int rows; int64_t capacity; int* overflow; };
+hipError_t launch_row_scan(const ScanArgs* a, int n, hipStream_t st);
 hipError_t launch_pack(const void* x, int dtype, const StoreView& s, hipStream_t st);
 
 // ---------------------------------------------------------------- GEMM family

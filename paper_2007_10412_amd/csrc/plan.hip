@@ -18,6 +18,18 @@ namespace {
 
 constexpr int kPlanThreads = 256;
 
+// The draws of one launch: the rows of several stores (the layers of a model) one after another.
+struct PlanBatch {
+  int n, first[kPlanBatch + 1];        // workgroups first[i] .. first[i + 1] - 1 draw for a[i]
+  PlanArgs a[kPlanBatch];
+};
+__device__ __forceinline__ const PlanArgs& plan_of(const PlanBatch& p, int* block) {
+  int i = 0;
+  while (i + 1 < p.n && (int)blockIdx.x >= p.first[i + 1]) ++i;
+  *block = (int)blockIdx.x - p.first[i];
+  return p.a[i];
+}
+
 // exclusive prefix sum over the 256 threads of a block; *total = block sum
 __device__ __forceinline__ int block_excl_scan(int v, int* total, int* smem) {
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
@@ -105,11 +117,11 @@ __device__ __forceinline__ void or_nibble(uint32_t* s_bm, uint32_t nib, int j0, 
 }
 
 // Bernoulli: keep iff key < T.  Keys are consumed as they are generated.
-__global__ __launch_bounds__(kPlanThreads) void plan_bernoulli_kernel(PlanArgs a) {
+__device__ __forceinline__ void plan_bernoulli_rows(const PlanArgs& a, int block) {
   __shared__ uint32_t s_bm[2048];      // keep bitmap of the row (cols <= 65535)
   __shared__ int s_scan[8];
   const int tid = threadIdx.x;
-  const int prow = blockIdx.x;
+  const int prow = block;
   const int t_step = prow / a.rows_per_step, b = prow % a.rows_per_step;
   const uint32_t step = a.step0 + (uint32_t)t_step;
   const uint64_t f0 = (uint64_t)b * (uint64_t)a.cols;
@@ -131,6 +143,11 @@ __global__ __launch_bounds__(kPlanThreads) void plan_bernoulli_kernel(PlanArgs a
   __syncthreads();
   finish_row(a, prow, s_bm, s_scan);
 }
+__global__ __launch_bounds__(kPlanThreads) void plan_bernoulli_kernel(PlanBatch p) {
+  int block;
+  const PlanArgs& a = plan_of(p, &block);
+  plan_bernoulli_rows(a, block);
+}
 
 // Fixed-k: the k smallest (key, column) pairs of the row.  QPT = Philox calls
 // (groups of four consecutive elements) per thread; the row's keys stay in
@@ -138,7 +155,7 @@ __global__ __launch_bounds__(kPlanThreads) void plan_bernoulli_kernel(PlanArgs a
 // QPT * 4 * 256 columns and starts on a Philox call boundary, so every register
 // slot holds an element and the per-element validity tests fold away.
 template <int QPT, bool FULL>
-__global__ __launch_bounds__(kPlanThreads) void plan_fixedk_kernel(PlanArgs a) {
+__device__ __forceinline__ void plan_fixedk_rows(const PlanArgs& a, int block) {
   static_assert(QPT <= 16, "keep/valid masks are 64 bits");
   __shared__ uint32_t s_bm[2048];
   __shared__ int s_hist[256];
@@ -146,7 +163,7 @@ __global__ __launch_bounds__(kPlanThreads) void plan_fixedk_kernel(PlanArgs a) {
   __shared__ int s_sel[3];
 
   const int tid = threadIdx.x;
-  const int prow = blockIdx.x;         // plan row
+  const int prow = block;         // plan row
   int t_step, b;
   if (a.scheme == kFixedKShared) { t_step = prow; b = 0; }
   else { t_step = prow / a.rows_per_step; b = prow % a.rows_per_step; }
@@ -258,6 +275,12 @@ __global__ __launch_bounds__(kPlanThreads) void plan_fixedk_kernel(PlanArgs a) {
   __syncthreads();
   finish_row(a, prow, s_bm, s_scan);
 }
+template <int QPT, bool FULL>
+__global__ __launch_bounds__(kPlanThreads) void plan_fixedk_kernel(PlanBatch p) {
+  int block;
+  const PlanArgs& a = plan_of(p, &block);
+  plan_fixedk_rows<QPT, FULL>(a, block);
+}
 
 // Fixed-k per example for rows of up to 1024 columns: a wave per row, four rows a workgroup, no barriers.  A lane holds
 // QPL Philox calls.  Any threshold below which exactly k keys lie selects the row, and the keys are uniform: from
@@ -266,11 +289,11 @@ __global__ __launch_bounds__(kPlanThreads) void plan_fixedk_kernel(PlanArgs a) {
 // With a workgroup per row most of its 256 threads had no key and every pass its barriers: 117450 rows of 100 columns
 // (the recurrent store) 235 us.
 template <int QPL>
-__global__ __launch_bounds__(256) void plan_fixedk_wave_kernel(PlanArgs a) {
+__device__ __forceinline__ void plan_fixedk_wave_rows(const PlanArgs& a, int block) {
   constexpr int NE = QPL * 4;
   __shared__ uint32_t s_bm[4][QPL * 8];
   const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-  const int prow = blockIdx.x * 4 + w;
+  const int prow = block * 4 + w;
   if (prow >= a.plan_rows) return;
   const int t_step = prow / a.rows_per_step, b = prow % a.rows_per_step;
   const uint64_t f0 = (uint64_t)b * (uint64_t)a.cols, q0 = f0 >> 2;
@@ -364,18 +387,24 @@ __global__ __launch_bounds__(256) void plan_fixedk_wave_kernel(PlanArgs a) {
   // running maximum of entries per bucket: an atomic only where a row raises it
   if (a.max_seg && first && after - excl > *reinterpret_cast<volatile int*>(a.max_seg)) atomicMax(a.max_seg, after - excl);
 }
+template <int QPL>
+__global__ __launch_bounds__(256) void plan_fixedk_wave_kernel(PlanBatch p) {
+  int block;
+  const PlanArgs& a = plan_of(p, &block);
+  plan_fixedk_wave_rows<QPL>(a, block);
+}
 
 // With replacement (Section 3.2, the matrix P as printed): draw s of the row maps its key to the column
 // floor(key * cols / 2^32).  The draws are counted per column in LDS (16-bit counters: a count cannot
 // exceed k <= cols <= 16384); a column with a non-zero count is kept once, and its count goes to
 // mult[row][entry] in the entry order of the row, so that whoever packs the row scales entry e by
 // mult[e] * cols/k.
-__global__ __launch_bounds__(kPlanThreads) void plan_replace_kernel(PlanArgs a) {
+__device__ __forceinline__ void plan_replace_rows(const PlanArgs& a, int block) {
   __shared__ uint32_t s_bm[512];       // cols <= 16384
   extern __shared__ uint32_t s_cnt[];  // two 16-bit counters per word: (cols + 1) / 2 words, sized at launch
   __shared__ int s_scan[8];
   const int tid = threadIdx.x;
-  const int prow = blockIdx.x;
+  const int prow = block;
   int t_step, b;
   if (a.scheme == kReplaceShared) { t_step = prow; b = 0; }
   else { t_step = prow / a.rows_per_step; b = prow % a.rows_per_step; }
@@ -412,14 +441,22 @@ __global__ __launch_bounds__(kPlanThreads) void plan_replace_kernel(PlanArgs a) 
   for (uint32_t bits = b1; bits; bits &= bits - 1) mrow[rel++] = (uint16_t)count_of(w1 * 32 + (__ffs(bits) - 1));
   finish_row(a, prow, s_bm, s_scan);
 }
+__global__ __launch_bounds__(kPlanThreads) void plan_replace_kernel(PlanBatch p) {
+  int block;
+  const PlanArgs& a = plan_of(p, &block);
+  plan_replace_rows(a, block);
+}
 
-// row_ptr = exclusive scan of row_cnt (Bernoulli).  One block; flags overflow.  A thread takes eight rows at a time in
+// row_ptr = exclusive scan of row_cnt (Bernoulli).  One block a store; flags overflow.  A thread takes eight rows at a time in
 // 16-byte vectors, the next eight in flight during the scan: what bounds it is the latency of one pass of the block, so
 // few passes (65536 rows: 58 us with a row per thread).
 constexpr int kScanRows = 8;
-__global__ __launch_bounds__(1024) void row_scan_kernel(const uint32_t* __restrict__ row_cnt,
-                                                        uint32_t* __restrict__ row_ptr, int rows,
-                                                        int64_t capacity, int* __restrict__ overflow) {
+struct ScanBatch { ScanArgs a[kPlanBatch]; };
+__global__ __launch_bounds__(1024) void row_scan_kernel(ScanBatch p) {
+  const ScanArgs& s = p.a[blockIdx.x];
+  const uint32_t* const row_cnt = s.row_cnt;
+  uint32_t* const row_ptr = s.row_ptr;
+  const int rows = s.rows;
   __shared__ uint32_t s_w[2][16];
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   struct Rows { uint32_t c[kScanRows]; };
@@ -466,7 +503,7 @@ __global__ __launch_bounds__(1024) void row_scan_kernel(const uint32_t* __restri
   }
   if (tid == 0) {
     row_ptr[rows] = carry;
-    if ((int64_t)carry > capacity) *overflow = 1;
+    if ((int64_t)carry > s.capacity) *s.overflow = 1;
   }
 }
 
@@ -815,49 +852,86 @@ hipError_t launch_unpack(const StoreView& s, int dtype, void* dense, hipStream_t
   return hipGetLastError();
 }
 
-hipError_t launch_plan(const PlanArgs& a, hipStream_t st) {
-  dim3 grid(a.plan_rows), block(kPlanThreads);
-  if (a.cols < 1 || a.cols > 65535) return hipErrorInvalidValue;
-  if (a.scheme == kBernoulli) {
-    hipLaunchKernelGGL(plan_bernoulli_kernel, grid, block, 0, st, a);
-    return hipGetLastError();
-  }
-  if (a.scheme == kReplaceShared || a.scheme == kReplacePerExample) {
-    if (a.cols > 16384 || !a.mult) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(plan_replace_kernel, grid, block, (size_t)((a.cols + 1) / 2) * 4, st, a);
-    return hipGetLastError();
-  }
+// Which kernel draws the rows of `a`, as a number that is the same for stores one launch can serve together.
+enum PlanKind { kPlanBernoulli, kPlanReplace, kPlanWave1, kPlanWave2, kPlanWave4, kPlanFixed1, kPlanFixed1Full, kPlanFixed4,
+                kPlanFixed4Full, kPlanFixed16, kPlanFixed16Full, kPlanNone };
+static PlanKind plan_kind(const PlanArgs& a) {
+  if (a.cols < 1 || a.cols > 65535) return kPlanNone;
+  if (a.scheme == kBernoulli) return kPlanBernoulli;
+  if (a.scheme == kReplaceShared || a.scheme == kReplacePerExample) return a.cols > 16384 || !a.mult ? kPlanNone : kPlanReplace;
   // rows start on a Philox call boundary when cols is a multiple of 4
   const int nq_max = (a.cols % 4 == 0) ? a.cols / 4 : a.cols / 4 + 2;
   const int qpt = (nq_max + kPlanThreads - 1) / kPlanThreads;
   // a wave per row while its lanes hold the row's keys
-  if (a.scheme == kFixedKPerExample && nq_max <= 256) {
-    const dim3 rows4((unsigned)((a.plan_rows + 3) / 4));
-    if (nq_max <= 64) hipLaunchKernelGGL(plan_fixedk_wave_kernel<1>, rows4, block, 0, st, a);
-    else if (nq_max <= 128) hipLaunchKernelGGL(plan_fixedk_wave_kernel<2>, rows4, block, 0, st, a);
-    else hipLaunchKernelGGL(plan_fixedk_wave_kernel<4>, rows4, block, 0, st, a);
-    return hipGetLastError();
-  }
+  if (a.scheme == kFixedKPerExample && nq_max <= 256) return nq_max <= 64 ? kPlanWave1 : nq_max <= 128 ? kPlanWave2 : kPlanWave4;
   const bool full = a.cols == qpt * 4 * kPlanThreads;     // then also a multiple of 4: rows start on a call boundary
-  if (qpt <= 1) {
-    if (full) hipLaunchKernelGGL((plan_fixedk_kernel<1, true>), grid, block, 0, st, a);
-    else hipLaunchKernelGGL((plan_fixedk_kernel<1, false>), grid, block, 0, st, a);
-  } else if (qpt <= 4) {
-    if (full && qpt == 4) hipLaunchKernelGGL((plan_fixedk_kernel<4, true>), grid, block, 0, st, a);
-    else hipLaunchKernelGGL((plan_fixedk_kernel<4, false>), grid, block, 0, st, a);
-  } else if (qpt <= 16) {
-    if (full && qpt == 16) hipLaunchKernelGGL((plan_fixedk_kernel<16, true>), grid, block, 0, st, a);
-    else hipLaunchKernelGGL((plan_fixedk_kernel<16, false>), grid, block, 0, st, a);
-  } else return hipErrorInvalidValue;
-  return hipGetLastError();
+  if (qpt <= 1) return full ? kPlanFixed1Full : kPlanFixed1;
+  if (qpt <= 4) return full && qpt == 4 ? kPlanFixed4Full : kPlanFixed4;
+  if (qpt <= 16) return full && qpt == 16 ? kPlanFixed16Full : kPlanFixed16;
+  return kPlanNone;
+}
+
+// The draws of n <= kPlanBatch stores: as many launches as they need different kernels (a launch costs as much as drawing a
+// few hundred rows, and the layers of a model need one kernel mostly; a few short rows take the kernel for longer ones with
+// them: steps of 784-300-300-10, batch 150 and 1100-2050-1530-100, batch 1000, 117 and 274 us with a launch a store, 104 and
+// 262 here).
+hipError_t launch_plan(const PlanArgs* args, int n, hipStream_t st) {
+  if (n < 1 || n > kPlanBatch) return hipErrorInvalidValue;
+  PlanKind kind[kPlanBatch];
+  int64_t wave_rows = 0;
+  PlanKind widest = kPlanWave1;
+  for (int i = 0; i < n; ++i) {
+    kind[i] = plan_kind(args[i]);
+    if (kind[i] == kPlanNone) return hipErrorInvalidValue;
+    if (kind[i] >= kPlanWave1 && kind[i] <= kPlanWave4) { wave_rows += args[i].plan_rows; widest = kind[i] > widest ? kind[i] : widest; }
+  }
+  if (wave_rows <= 4096)
+    for (int i = 0; i < n; ++i) if (kind[i] >= kPlanWave1 && kind[i] <= kPlanWave4) kind[i] = widest;
+  bool done[kPlanBatch] = {};
+  for (int i = 0; i < n; ++i) {
+    if (done[i]) continue;
+    const PlanKind k = kind[i];
+    const bool wave = k >= kPlanWave1 && k <= kPlanWave4;
+    PlanBatch p;
+    p.n = 0; p.first[0] = 0;
+    int widest_cols = 0;
+    for (int j = i; j < n; ++j) {
+      if (done[j] || kind[j] != k) continue;
+      done[j] = true;
+      p.a[p.n] = args[j];
+      p.first[p.n + 1] = p.first[p.n] + (wave ? (args[j].plan_rows + 3) / 4 : args[j].plan_rows);
+      ++p.n;
+      widest_cols = args[j].cols > widest_cols ? args[j].cols : widest_cols;
+    }
+    const dim3 grid((unsigned)p.first[p.n]), block(kPlanThreads);
+    if (p.first[p.n] == 0) continue;
+    switch (k) {
+      case kPlanBernoulli: hipLaunchKernelGGL(plan_bernoulli_kernel, grid, block, 0, st, p); break;
+      case kPlanReplace: hipLaunchKernelGGL(plan_replace_kernel, grid, block, (size_t)((widest_cols + 1) / 2) * 4, st, p); break;
+      case kPlanWave1: hipLaunchKernelGGL(plan_fixedk_wave_kernel<1>, grid, block, 0, st, p); break;
+      case kPlanWave2: hipLaunchKernelGGL(plan_fixedk_wave_kernel<2>, grid, block, 0, st, p); break;
+      case kPlanWave4: hipLaunchKernelGGL(plan_fixedk_wave_kernel<4>, grid, block, 0, st, p); break;
+      case kPlanFixed1: hipLaunchKernelGGL((plan_fixedk_kernel<1, false>), grid, block, 0, st, p); break;
+      case kPlanFixed1Full: hipLaunchKernelGGL((plan_fixedk_kernel<1, true>), grid, block, 0, st, p); break;
+      case kPlanFixed4: hipLaunchKernelGGL((plan_fixedk_kernel<4, false>), grid, block, 0, st, p); break;
+      case kPlanFixed4Full: hipLaunchKernelGGL((plan_fixedk_kernel<4, true>), grid, block, 0, st, p); break;
+      case kPlanFixed16: hipLaunchKernelGGL((plan_fixedk_kernel<16, false>), grid, block, 0, st, p); break;
+      default: hipLaunchKernelGGL((plan_fixedk_kernel<16, true>), grid, block, 0, st, p); break;
+    }
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
 }
 
 // widest row the plan kernels handle for a scheme
 int plan_max_cols(int scheme) { return scheme == kBernoulli ? 65535 : 16384; }
 
-hipError_t launch_row_scan(const uint32_t* row_cnt, uint32_t* row_ptr, int rows, int64_t capacity,
-                           int* overflow, hipStream_t st) {
-  hipLaunchKernelGGL(row_scan_kernel, dim3(1), dim3(1024), 0, st, row_cnt, row_ptr, rows, capacity, overflow);
+hipError_t launch_row_scan(const ScanArgs* args, int n, hipStream_t st) {
+  if (n < 1 || n > kPlanBatch) return hipErrorInvalidValue;
+  ScanBatch p;
+  for (int i = 0; i < n; ++i) p.a[i] = args[i];
+  hipLaunchKernelGGL(row_scan_kernel, dim3(n), dim3(1024), 0, st, p);
   return hipGetLastError();
 }
 
