@@ -977,6 +977,9 @@ static int sparse_prefetch_for(const rad_store* s, int lanes_per_row) {
   return (int)std::ceil((mean + 6.0 * std::sqrt(mean)) / lanes_per_row);   // overflow beyond this is rare and handled apart
 }
 
+// fraction of a row's columns that a sampled store holds (expected, for Bernoulli draws)
+static double kept_fraction(const rad_store* s) { return s->scheme == RAD_BERNOULLI ? s->p : (double)s->k / (double)s->cols; }
+
 // whether dW of a bf16 store with its own columns per row goes through a dense x~ (see dW_gemm)
 static bool dw_dense_pays(const rad_store* s, int N) {
   return s->dtype == kBF16 && s->cols % 256 == 0 && N % 8 == 0 && (s->cols / 256) * (int64_t)((N + 255) / 256) >= 128 &&
@@ -987,7 +990,7 @@ static bool dw_dense_pays(const rad_store* s, int N) {
 // pitched dy): a bf16 store with its own columns per row, sparse enough for that kernel, too few tiles to fill the chip
 static bool dw_pitched_ok(const rad_store* s, int N, int dy_ld) {
   if (dy_ld <= N || dy_ld % 256 || s->dtype != kBF16 || s->project() || s->steps != 1) return false;
-  if (dw_narrow_pays(s->dtype, s->rows, s->cols, N, sparse_prefetch_for(s, 8), false)) return false;
+  if (dw_narrow_pays(s->dtype, s->rows, s->cols, N, sparse_prefetch_for(s, 8), false, kept_fraction(s))) return false;
   if (s->scheme == RAD_EXACT || s->scheme == RAD_FIXEDK_SHARED) return false;
   if (sparse_prefetch_for(s, 8) > gemm_bf16_sparse_max_prefetch()) return false;
   const int64_t tiles = ((s->cols + 255) / 256) * (int64_t)(dy_ld / 256);
@@ -1086,7 +1089,7 @@ static rad_status dW_gemm(rad_ctx* c, const rad_store* s, int slot, const void* 
     g.A = dense; g.lda = s->cols;
     return dw_dense_f32(c, g, alg);
   }
-  if (n_slots == 1 && n_out == N && dw_narrow_pays(s->dtype, s->rows, s->cols, N, g.sparse_prefetch, bits != nullptr)) {
+  if (n_slots == 1 && n_out == N && dw_narrow_pays(s->dtype, s->rows, s->cols, N, g.sparse_prefetch, bits != nullptr, kept_fraction(s))) {
     const int splits = dw_narrow_splits(s->rows, s->cols, N);
     float* out = dW;
     if (splits > 1) {
@@ -1097,7 +1100,7 @@ static rad_status dW_gemm(rad_ctx* c, const rad_store* s, int slot, const void* 
     const StoreView v = g.sa;
     HIP_TRY(c, timed(c, "dw_narrow", [&](const char**) {
       return launch_dw_narrow(v, s->dtype, s->rows, dy, ldy, N, bits, bits_pitch, out, splits > 1 ? 0 : beta, splits,
-                              splits > 1 ? (int64_t)s->cols * N : 0, c->stream);
+                              splits > 1 ? (int64_t)s->cols * N : 0, kept_fraction(s), c->stream);
     }));
     if (splits > 1)
       HIP_TRY(c, timed(c, "splitk_reduce", [&](const char**) {
@@ -1301,7 +1304,7 @@ extern "C" rad_status rad_backward_dW(rad_ctx* c, const rad_layer* L, const rad_
     return conv_dW_call(c, s, (int)L->batch, L->c_in, L->c_out, L->h, L->w, L->kh, g, dW, dbias);
   }
   const int N = (int)L->d_out;
-  const bool narrow = s->per_entry() && dw_narrow_pays(s->dtype, s->rows, s->cols, N, sparse_prefetch_for(s, 8), s->bits != nullptr);
+  const bool narrow = s->per_entry() && dw_narrow_pays(s->dtype, s->rows, s->cols, N, sparse_prefetch_for(s, 8), s->bits != nullptr, kept_fraction(s));
   if (!narrow && premask_pays(L, s->bits)) {          // (the kernel for narrow layers masks a row once)
     void* g = nullptr;
     int64_t g_ld = 0;

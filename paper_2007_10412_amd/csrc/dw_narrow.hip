@@ -1,14 +1,20 @@
 // dW of a narrow layer (class scores: few output columns) from a compressed store, fp32 sums.
 //
-// dW[j][n] = sum over rows b of x~[b][j] g[b][n] with N around ten: a matrix-core tile would be filled to a sixth and
-// its output gives a handful of tiles, so the work is split over rows instead.  A wave takes one 256-column bucket and
-// eight store rows at a time: it scatters their entries into a zeroed 8 x 256 LDS stage of its own (eight lanes per
-// row), reads them back as four consecutive columns per lane and adds 4 x NT products per row to registers with g
-// broadcast from LDS.  What bounds it is the vector ALU, 4 NT multiply-adds per row and wave (zeros included: at the
-// usual fractions the dense form is as fast as read-modify-write of the sums in LDS and does not depend on the
-// fraction), so the rows are split until the chip is full; the partial sums of a workgroup's four waves are added in
-// LDS and those of the splits by the reduction kernel, both in a fixed order.
+// dW[j][n] = sum over rows b of x~[b][j] g[b][n] with N around ten: a 16- or 32-wide matrix-core tile would be filled to a
+// part and its output gives a handful of tiles, so the work is split over rows instead.  A wave takes one 256-column bucket
+// and eight store rows at a time: it scatters their entries into a zeroed 8 x 256 LDS stage of its own (eight lanes per
+// row), reads them back as four consecutive columns per lane and adds 4 x NT products per row to registers with 4x4x1
+// matrix instructions, g broadcast by them (zeros included: at the usual fractions the dense form is as fast as
+// read-modify-write of the sums in LDS and does not depend on the fraction).  The rows are split until the chip is full;
+// the partial sums of a workgroup's four waves are added in LDS and those of the splits by the reduction kernel, both in a
+// fixed order.
+// 65536 x 4096 fp32, 10 outputs, fraction 0.1: 110 us, about 41 each of matrix instructions, LDS and address arithmetic; 158
+// with loads under conditions, which the wave waited for one by one, vector-ALU products and buckets of the same rows on
+// different XCDs (matrix instructions alone 153, the regrouping 145).
 #include <algorithm>
+#include <cmath>
+#include <type_traits>
+#include <utility>
 
 #include "gemm.hpp"
 
@@ -18,7 +24,6 @@ namespace {
 
 constexpr int kRows = 8, kWaves = 4;         // store rows of a wave at a time, waves of a workgroup
 constexpr int kLanes = 64 / kRows;           // lanes that share a store row
-constexpr int kHeld = 4;                     // entries per lane in flight in registers (32 of a row's bucket)
 
 struct NarrowArgs {
   StoreView s;
@@ -29,106 +34,136 @@ struct NarrowArgs {
   int beta, rows_per_split;
 };
 
+// An entry as it is loaded (nothing is computed from it until it is scattered: arithmetic at the load would wait for it).
 template <typename T> struct Entry;
 template <> struct Entry<float> {
-  static __device__ __forceinline__ void get(const StoreView& s, uint32_t e, int bucket, int* col, float* v) {
-    *col = (int)s.indices[e] - bucket * kBucket;
-    *v = reinterpret_cast<const float*>(s.values)[e];
+  float v; uint32_t c;
+  __device__ __forceinline__ void load(const StoreView& s, uint32_t e) {
+    c = s.indices[e];
+    v = reinterpret_cast<const float*>(s.values)[e];
   }
+  __device__ __forceinline__ int col() const { return c & (kBucket - 1); }          // inside its bucket
+  __device__ __forceinline__ float value() const { return v; }
 };
 template <> struct Entry<uint16_t> {         // paired entries
-  static __device__ __forceinline__ void get(const StoreView& s, uint32_t e, int, int* col, float* v) {
-    const uint32_t u = reinterpret_cast<const uint32_t*>(s.values)[e];
-    *col = pair_col(u, 0);
-    *v = __uint_as_float(u & 0xFFFF0000u);
-  }
+  uint32_t u;
+  __device__ __forceinline__ void load(const StoreView& s, uint32_t e) { u = reinterpret_cast<const uint32_t*>(s.values)[e]; }
+  __device__ __forceinline__ int col() const { return pair_col(u, 0); }
+  __device__ __forceinline__ float value() const { return __uint_as_float(u & 0xFFFF0000u); }
 };
 
-template <typename T, int NT>
-__global__ __launch_bounds__(64 * kWaves, 4) void dw_narrow_kernel(NarrowArgs a) {
+__device__ __forceinline__ float raw_value(float v) { return v; }
+__device__ __forceinline__ float raw_value(uint32_t bf16) { return __uint_as_float(bf16 << 16); }
+
+// row Q of the group: acc[j][n4] += g[row][4 n4 ..] x~[row][4 lane + j].  A 4x4x1 matrix instruction is sixteen outer
+// products of four values each; the broadcast controls hand block ABID of the register that holds g (four of a row's
+// values) to all sixteen, so g is never staged, and the second operand is the lane's column.
+template <int NT, int Q, int... N4>
+__device__ __forceinline__ void row_products(const float* gc, floatx4* mine, floatx4 (&acc)[4][NT / 4],
+                                             std::integer_sequence<int, N4...>) {
+  const floatx4 x = mine[Q * (kBucket / 4)];
+  mine[Q * (kBucket / 4)] = floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int j = 0; j < 4; ++j)
+    ((acc[j][N4] = __builtin_amdgcn_mfma_f32_4x4x1f32(gc[(Q * NT / 4 + N4) / 16], x[j], acc[j][N4], 4, (Q * NT / 4 + N4) % 16, 0)), ...);
+}
+template <int NT, int... Q>
+__device__ __forceinline__ void products(const float* gc, floatx4* mine, floatx4 (&acc)[4][NT / 4], std::integer_sequence<int, Q...>) {
+  (row_products<NT, Q>(gc, mine, acc, std::make_integer_sequence<int, NT / 4>()), ...);
+}
+
+// HELD: entries per lane and row group that are in flight in registers; what a row has beyond them is loaded when it is
+// needed, a whole memory latency each time, so they cover a row's bucket nearly always.
+// Loads are unconditional, at addresses clamped into the arrays, and what they bring is judged when it is used: a condition
+// around a load, or arithmetic on its result beside it, made the wave wait for each load in turn.
+template <typename T, int NT, int HELD, bool MASKED>
+__global__ __launch_bounds__(64 * kWaves, NT == 16 || HELD > 5 ? 3 : 4) void dw_narrow_kernel(NarrowArgs a) {
   constexpr int NG = (kRows * NT + 63) / 64;             // values of g per lane and row group
   __shared__ __align__(16) float stage[kWaves][kRows * kBucket];
-  __shared__ __align__(16) float gs[kWaves][kRows * NT];
+  __shared__ float spare[kWaves][64];                    // where slots without an entry go
   const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-  const int bucket = blockIdx.x, n0 = blockIdx.z * NT;
-  const int rbeg = blockIdx.y * a.rows_per_split, rend = min(a.rows, rbeg + a.rows_per_split);
+  // Workgroups go round-robin over the eight XCDs: all buckets of a range of rows on one of them, whose L2 then holds the
+  // cache lines that the segments of neighbouring buckets share.
+  const int id = blockIdx.x + a.s.nb * blockIdx.y, whole = (int)gridDim.y / 8 * 8;
+  const bool regroup = id < whole * a.s.nb;
+  const int bucket = regroup ? id / 8 % a.s.nb : (int)blockIdx.x;
+  const int split = regroup ? id / 8 / a.s.nb * 8 + id % 8 : (int)blockIdx.y;
+  const int n0 = blockIdx.z * NT;
+  const int rbeg = split * a.rows_per_split, rend = min(a.rows, rbeg + a.rows_per_split);
   const int rr = lane / kLanes, sub = lane % kLanes;
   float* const st = stage[w];
-  float* const gw = gs[w];
+  float* const none = spare[w] + lane;
   floatx4* const mine = reinterpret_cast<floatx4*>(st + lane * 4);       // this lane's columns of stage row 0
   const floatx4 z4 = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
   for (int q = 0; q < kRows; ++q) mine[q * (kBucket / 4)] = z4;
 
-  float acc[4][NT];
+  floatx4 acc[4][NT / 4];                    // dW of column 4 lane + j, outputs 4 n4 .. 4 n4 + 3
 #pragma unroll
   for (int j = 0; j < 4; ++j)
 #pragma unroll
-    for (int n = 0; n < NT; ++n) acc[j][n] = 0.f;
+    for (int n4 = 0; n4 < NT / 4; ++n4) acc[j][n4] = z4;
 
-  uint32_t beg = 0, end = 0;
-  int col[kHeld]; float val[kHeld]; float gv[NG];
-  auto load_segment = [&](int r0) {
-    const int row = r0 + rr;
-    beg = end = 0u;
-    if (row < rend) store_segment(a.s, row, bucket, &beg, &end);
-  };
-  auto load_rows = [&](int r0) {             // entries and g of the rows whose segment was loaded last
+  // g value c = lane + 64 q of a row group: row c / NT of the group, output n0 + c % NT
+  int g_row[NG], g_n[NG]; bool g_ok[NG];
 #pragma unroll
-    for (int i = 0; i < kHeld; ++i) {
-      const uint32_t e = beg + sub + i * kLanes;
-      col[i] = -1; val[i] = 0.f;
-      if (e < end) Entry<T>::get(a.s, e, bucket, &col[i], &val[i]);
-    }
+  for (int q = 0; q < NG; ++q) {
+    const int c = min(lane + 64 * q, kRows * NT - 1);
+    g_row[q] = c / NT;
+    g_ok[q] = lane + 64 * q < kRows * NT && n0 + c % NT < a.N;
+    g_n[q] = min(n0 + c % NT, a.N - 1);
+  }
+  struct Bounds { uint32_t base, b0, b1; };     // of a row's segment, as loaded
+  const uint32_t last = (uint32_t)(a.s.capacity - 1);
+  Entry<T> ent[HELD];
+  typedef typename std::conditional<sizeof(T) == 2, uint32_t, float>::type Raw;
+  Raw gv[NG];
+  uint32_t gm[MASKED ? NG : 1];
+  uint32_t beg, end;                                     // segment of the row in flight
+  auto load_bounds = [&](int r0) {
+    const int row = min(r0 + rr, rend - 1);
+    const uint16_t* const bo = a.s.bucket_off + (size_t)(row * a.s.plan_row_stride) * (a.s.nb + 1) + bucket;
+    return Bounds{a.s.row_ptr[row], bo[0], bo[1]};
+  };
+  auto load_rows = [&](int r0, Bounds b) {               // entries and g of a row group
+    const uint32_t cap = (uint32_t)a.s.capacity;         // (an overflowed draw never reads past the arrays)
+    end = min(b.base + b.b1, cap);
+    beg = r0 + rr < rend ? min(b.base + b.b0, end) : end;
+#pragma unroll
+    for (int i = 0; i < HELD; ++i) ent[i].load(a.s, min(beg + sub + i * kLanes, last));
 #pragma unroll
     for (int q = 0; q < NG; ++q) {
-      const int c = lane + 64 * q, row = r0 + c / NT, n = n0 + c % NT;
-      gv[q] = 0.f;
-      if ((kRows * NT % 64 == 0 || c < kRows * NT) && row < rend && n < a.N) {
-        const float v = get_elem(static_cast<const T*>(a.dy) + (size_t)row * a.ldy + n);
-        gv[q] = !a.bits || (mask_bits(a.bits, a.bits_pitch, row, n) & 1u) ? v : 0.f;
-      }
+      const int row = min(r0 + g_row[q], rend - 1);
+      gv[q] = static_cast<const T*>(a.dy)[(size_t)row * a.ldy + g_n[q]];
+      if (MASKED) gm[MASKED ? q : 0] = a.bits[(size_t)row * a.bits_pitch + (g_n[q] >> 5)];
     }
   };
 
   constexpr int kStep = kRows * kWaves;
-  int r0 = rbeg + w * kRows;
-  load_segment(r0);
-  load_rows(r0);
-  uint32_t cbeg = beg, cend = end;
-  load_segment(r0 + kStep);
-  for (; r0 < rend; r0 += kStep) {
-    // scatter the held entries and whatever a row has beyond them; then the loads of the next rows are in flight
-    // while these are multiplied
+  const int r_first = rbeg + w * kRows;
+  load_rows(r_first, load_bounds(r_first));
+  Bounds next = load_bounds(r_first + kStep);
+  for (int r0 = r_first; r0 < rend; r0 += kStep) {
+    // scatter the held entries and whatever a row has beyond them; then the loads of the group after those in flight
+    // start, and these rows are multiplied
 #pragma unroll
-    for (int i = 0; i < kHeld; ++i) if (col[i] >= 0) st[rr * kBucket + col[i]] = val[i];
-    for (uint32_t e = cbeg + sub + kHeld * kLanes; e < cend; e += kLanes) {
-      int c; float v;
-      Entry<T>::get(a.s, e, bucket, &c, &v);
-      st[rr * kBucket + c] = v;
+    for (int i = 0; i < HELD; ++i) {
+      float* const at = st + rr * kBucket + ent[i].col();
+      *(beg + sub + i * kLanes < end ? at : none) = ent[i].value();
     }
-#pragma unroll
-    for (int q = 0; q < NG; ++q) {
-      const int c = lane + 64 * q;
-      if (kRows * NT % 64 == 0 || c < kRows * NT) gw[c] = gv[q];
+    for (uint32_t e = beg + sub + HELD * kLanes; e < end; e += kLanes) {
+      Entry<T> x;
+      x.load(a.s, e);
+      st[rr * kBucket + x.col()] = x.value();
     }
-    load_rows(r0 + kStep);
-    cbeg = beg; cend = end;
-    load_segment(r0 + 2 * kStep);
-    __builtin_amdgcn_wave_barrier();         // the stage belongs to this wave: its LDS accesses complete in order
+    float gc[NG];                          // g of these rows: value q NT + n of the group in lane (q NT + n) % 64
 #pragma unroll
-    for (int q = 0; q < kRows; ++q) {
-      const floatx4 x = mine[q * (kBucket / 4)];
-      mine[q * (kBucket / 4)] = z4;
-#pragma unroll
-      for (int n4 = 0; n4 < NT / 4; ++n4) {
-        const floatx4 g = *reinterpret_cast<const floatx4*>(&gw[q * NT + n4 * 4]);
-#pragma unroll
-        for (int e = 0; e < 4; ++e)
-#pragma unroll
-          for (int j = 0; j < 4; ++j) acc[j][n4 * 4 + e] = fmaf(x[j], g[e], acc[j][n4 * 4 + e]);
-      }
-    }
+    for (int q = 0; q < NG; ++q)
+      gc[q] = g_ok[q] && r0 + g_row[q] < rend && (!MASKED || ((gm[MASKED ? q : 0] >> (g_n[q] & 31)) & 1u)) ? raw_value(gv[q]) : 0.f;
+    load_rows(r0 + kStep, next);
+    next = load_bounds(r0 + 2 * kStep);
+    __builtin_amdgcn_wave_barrier();       // the stage belongs to this wave: its LDS accesses complete in order
+    products<NT>(gc, mine, acc, std::make_integer_sequence<int, kRows>());
     __builtin_amdgcn_wave_barrier();
   }
 
@@ -139,13 +174,13 @@ __global__ __launch_bounds__(64 * kWaves, 4) void dw_narrow_kernel(NarrowArgs a)
 #pragma unroll
     for (int n = 0; n < NT; ++n)
 #pragma unroll
-      for (int j = 0; j < 4; ++j) p[(n * 4 + j) * 64 + lane] = acc[j][n];
+      for (int j = 0; j < 4; ++j) p[(n * 4 + j) * 64 + lane] = acc[j][n / 4][n % 4];
   };
   auto add = [&](const float* p) {
 #pragma unroll
     for (int n = 0; n < NT; ++n)
 #pragma unroll
-      for (int j = 0; j < 4; ++j) acc[j][n] += p[(n * 4 + j) * 64 + lane];
+      for (int j = 0; j < 4; ++j) acc[j][n / 4][n % 4] += p[(n * 4 + j) * 64 + lane];
   };
   __syncthreads();
   if (w >= 2) put(all + (w - 2) * kBucket * NT);
@@ -156,7 +191,7 @@ __global__ __launch_bounds__(64 * kWaves, 4) void dw_narrow_kernel(NarrowArgs a)
   __syncthreads();
   if (w != 0) return;
   add(all);
-  float* const out = a.out + (int64_t)blockIdx.y * a.split_stride;
+  float* const out = a.out + (int64_t)split * a.split_stride;
 #pragma unroll
   for (int j = 0; j < 4; ++j) {
     const int m = bucket * kBucket + lane * 4 + j;
@@ -165,23 +200,27 @@ __global__ __launch_bounds__(64 * kWaves, 4) void dw_narrow_kernel(NarrowArgs a)
     for (int n = 0; n < NT; ++n)
       if (n0 + n < a.N) {
         float* dst = out + (size_t)m * a.N + n0 + n;
-        *dst = a.beta ? *dst + acc[j][n] : acc[j][n];
+        *dst = a.beta ? *dst + acc[j][n / 4][n % 4] : acc[j][n / 4][n % 4];
       }
   }
 }
 
-template <typename T, int NT> hipError_t launch_nt(const NarrowArgs& a, int splits, hipStream_t st) {
-  hipLaunchKernelGGL((dw_narrow_kernel<T, NT>), dim3((unsigned)a.s.nb, (unsigned)splits, (unsigned)((a.N + NT - 1) / NT)),
-                     dim3(64 * kWaves), 0, st, a);
+template <typename T, int NT, int HELD> hipError_t launch_held(const NarrowArgs& a, int splits, hipStream_t st) {
+  auto kern = a.bits ? dw_narrow_kernel<T, NT, HELD, true> : dw_narrow_kernel<T, NT, HELD, false>;
+  hipLaunchKernelGGL(kern, dim3((unsigned)a.s.nb, (unsigned)splits, (unsigned)((a.N + NT - 1) / NT)), dim3(64 * kWaves), 0, st, a);
   return hipGetLastError();
 }
-
-template <typename T> hipError_t launch_t(const NarrowArgs& a, int nt, int splits, hipStream_t st) {
+template <typename T, int NT> hipError_t launch_nt(const NarrowArgs& a, int entries, int splits, hipStream_t st) {
+  if (entries <= 3 * kLanes) return launch_held<T, NT, 3>(a, splits, st);
+  if (entries <= 5 * kLanes) return launch_held<T, NT, 5>(a, splits, st);
+  return launch_held<T, NT, 10>(a, splits, st);
+}
+template <typename T> hipError_t launch_t(const NarrowArgs& a, int nt, int entries, int splits, hipStream_t st) {
   switch (nt) {
-    case 4: return launch_nt<T, 4>(a, splits, st);
-    case 8: return launch_nt<T, 8>(a, splits, st);
-    case 12: return launch_nt<T, 12>(a, splits, st);
-    default: return launch_nt<T, 16>(a, splits, st);
+    case 4: return launch_nt<T, 4>(a, entries, splits, st);
+    case 8: return launch_nt<T, 8>(a, entries, splits, st);
+    case 12: return launch_nt<T, 12>(a, entries, splits, st);
+    default: return launch_nt<T, 16>(a, entries, splits, st);
   }
 }
 
@@ -214,25 +253,26 @@ int dw_narrow_splits(int rows, int cols, int N) {
 // bf16, whose tile kernel runs at 16 times the matrix rate with a split K, up to 12 columns: 65536 x 4096 x 10 792 / 130,
 // 4096 x 1000 x 10 28 / 17, 150 x 784 x 10 12.8 / 9.2; with the sampling 16 columns 582 / 535 and 45 / 47, 32 582 / 647.
 // Not 64 rows or fewer, a short contraction there and a pass of mostly latency here: 16 rows 3.8 / 5.6.
-// fp32 up to 12 columns (100 x 4096 x 10 12.5 / 8.8, 65536 x 4096 x 10 7318 / 132), and wider where an estimate of each
+// fp32 up to 12 columns (100 x 4096 x 10 12.5 / 8.8, 65536 x 4096 x 10 7318 / 110), and wider where an estimate of each
 // side says so.  The tile kernel walks all rows as one chain, 0.07 us a row and more with the tiles a CU has, nearly
 // twice that where a bucket's entries take its wide loader, so the fraction counts; here a round of up to 1024 workgroups
-// takes 3 to 5 us per group of 32 rows and every split writes and adds an array of partial sums.  The estimates are
-// within 15 % of nine tenths of 1650 calls (65 to 8192 rows, 64 to 65535 columns, 4 to 8000 outputs, fractions 0.02 to
-// 0.5), the choice within 11 % of the better side in all but five: at fraction 0.1 100 x 1024 x 100 12 / 13,
-// 65 x 4096 x 128 8.8 / 19, 200 x 4096 x 128 19 / 32, 1000 x 65535 x 128 217 / 258, 4096 x 1000 x 128 306 / 47,
-// 150 x 784 x 300 15 / 19, 300 x 784 x 300 25 / 28, 512 x 784 x 300 40 / 27, 512 x 1024 x 1024 41 / 48, 1024 x 1024 x 1024
-// 79 / 64; at 0.5 300 x 784 x 300 47 / 30, 512 x 1024 x 1024 78 / 57.  Above a million outputs with more than 128 columns
-// the two are close or unmeasured, and a grid's third axis holds 65535 parts.
-bool dw_narrow_pays(int dtype, int rows, int cols, int N, int sparse_prefetch, bool masked) {
+// takes 2 us and 0.03 an entry of a row's bucket per group of 32 rows, and every split writes and adds an array of partial
+// sums.  Fitted to 908 pairs of calls (65 to 8192 rows, 64 to 65535 columns, 10 to 8000 outputs, fractions 0.02 to 0.5): the
+// estimates are within 15 and 17 % of nine tenths of them, the choice within 10 % of the better side in all but eight (the
+// worst 300 x 16384 x 128 at 0.3, 62 / 48, left on the tiles).  At fraction 0.1 100 x 1024 x 100 12 / 11,
+// 65 x 4096 x 128 8.8 / 19, 200 x 4096 x 128 19 / 31, 150 x 784 x 300 15 / 15, 300 x 784 x 300 25 / 20, 512 x 784 x 300
+// 40 / 21, 512 x 1024 x 1024 41 / 43, 1024 x 1024 x 1024 79 / 57; at 0.5 300 x 784 x 300 47 / 24, 512 x 1024 x 1024 78 / 49,
+// 1024 x 2048 x 1024 237 / 129.  Above 2.2 million outputs with more than 128 columns nothing is measured.
+// kept: the fraction of a row's columns that the store holds
+bool dw_narrow_pays(int dtype, int rows, int cols, int N, int sparse_prefetch, bool masked, double kept) {
   if (rows <= 64) return false;
   if (dtype == kBF16 || N <= 12) return N <= 12;
-  if (N > 128 && (N > 16384 || (int64_t)cols * N > (1 << 20))) return false;
+  if (N > 128 && (N > 16384 || (int64_t)cols * N > 2200000)) return false;
   const bool wide = f32_sparse_wide(sparse_prefetch);
   const double out = (double)cols * N / 1e6, blocks = (double)narrow_blocks(cols, N);
   const int splits = dw_narrow_splits(rows, cols, N), per = (narrow_groups(rows) + splits - 1) / splits;
-  const double group = 2.8 + (wide ? 2.0 : 0.4) * std::min(1.0, blocks * splits / 1024);
-  const double here = 3.0 + 4.5 * narrow_nt(N) / 16 + per * std::max(1.0, blocks / 1024) * group + (splits > 1 ? 6.4 * splits * out : 0.0);
+  const double group = 0.5 + (1.6 + 0.030 * kept * std::min(cols, kBucket)) * std::min(1.0, blocks * splits / 1024);
+  const double here = 3.4 * narrow_nt(N) / 16 + per * std::max(1.0, blocks / 1024) * group + (splits > 1 ? 4.7 + 6.3 * splits * out : 24.7);
   const double tiles128 = ((cols + 127) / 128) * (double)((N + 127) / 128), tiles64 = ((cols + 63) / 64) * (double)((N + 63) / 64);
   const double load = tiles128 >= 192 ? tiles128 / 256 : tiles64 / 512;
   const double row = (wide ? 0.126 : 0.069) * std::max(1.0, load) + (wide ? 0.030 : 0.019) * std::min(1.0, load) + (masked ? 0.010 : 0.0);
@@ -241,13 +281,16 @@ bool dw_narrow_pays(int dtype, int rows, int cols, int N, int sparse_prefetch, b
 
 hipError_t launch_dw_narrow(const StoreView& s, int dtype, int rows, const void* dy, int64_t ldy, int N,
                             const uint32_t* bits, int bits_pitch, float* out, int beta, int splits, int64_t split_stride,
-                            hipStream_t st) {
+                            double kept, hipStream_t st) {
   if (splits < 1 || splits > 128) return hipErrorInvalidValue;
   NarrowArgs a;
   a.s = s; a.rows = rows; a.N = N; a.M = s.cols; a.dy = dy; a.ldy = ldy; a.bits = bits; a.bits_pitch = bits_pitch;
   a.out = out; a.split_stride = split_stride; a.beta = beta;
   a.rows_per_split = (narrow_groups(rows) + splits - 1) / splits * (kRows * kWaves);
-  return dtype == kBF16 ? launch_t<uint16_t>(a, narrow_nt(N), splits, st) : launch_t<float>(a, narrow_nt(N), splits, st);
+  const double mean = kept * std::min(s.cols, kBucket);
+  const int entries = (int)(mean + 2.5 * std::sqrt(mean));             // (a row beyond that: one in a hundred)
+  return dtype == kBF16 ? launch_t<uint16_t>(a, narrow_nt(N), entries, splits, st)
+                        : launch_t<float>(a, narrow_nt(N), entries, splits, st);
 }
 
 }  // namespace rad

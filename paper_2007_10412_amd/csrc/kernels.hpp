@@ -175,12 +175,13 @@ hipError_t launch_dw_overflow(const StoreView& s, int rows, const void* dy, int 
                               int bits_pitch, float* dW, int cap, const int* max_seg, hipStream_t st, int64_t ldy = 0);
 // dW of a narrow layer from a store with its own columns per row (bf16: paired entries), rows split over workgroups
 // (dw_narrow.hip): partial sums [splits][cols][N] split_stride apart, or (splits 1, stride 0) dW itself
-// whether it is the faster one (sparse_prefetch as in GemmArgs; masked: dy comes with ReLU bits)
-bool dw_narrow_pays(int dtype, int rows, int cols, int N, int sparse_prefetch, bool masked);
+// whether it is the faster one (sparse_prefetch as in GemmArgs; masked: dy comes with ReLU bits; kept: the fraction of a
+// row's columns that the store holds)
+bool dw_narrow_pays(int dtype, int rows, int cols, int N, int sparse_prefetch, bool masked, double kept);
 int dw_narrow_splits(int rows, int cols, int N);
 hipError_t launch_dw_narrow(const StoreView& s, int dtype, int rows, const void* dy, int64_t ldy, int N,
                             const uint32_t* bits, int bits_pitch, float* out, int beta, int splits, int64_t split_stride,
-                            hipStream_t st);
+                            double kept, hipStream_t st);
 // whether the fp32 sparse dW kernel takes its loader for many entries per (row, bucket)
 inline bool f32_sparse_wide(int sparse_prefetch) { return sparse_prefetch > 4; }
 // entries per (row, bucket) the bf16 sparse dW kernel chosen for `sparse_prefetch` handles itself
