@@ -254,15 +254,16 @@ int dw_narrow_splits(int rows, int cols, int N) {
 // 4096 x 1000 x 10 28 / 17, 150 x 784 x 10 12.8 / 9.2; with the sampling 16 columns 582 / 535 and 45 / 47, 32 582 / 647.
 // Not 64 rows or fewer, a short contraction there and a pass of mostly latency here: 16 rows 3.8 / 5.6.
 // fp32 up to 12 columns (100 x 4096 x 10 12.5 / 8.8, 65536 x 4096 x 10 7318 / 110), and wider where an estimate of each
-// side says so.  The tile kernel walks all rows as one chain, 0.07 us a row and more with the tiles a CU has, nearly
+// side says so.  The tile kernel walks all rows as one chain, 0.056 us a row and more with the tiles a CU has, nearly
 // twice that where a bucket's entries take its wide loader, so the fraction counts; here a round of up to 1024 workgroups
 // takes 2 us and 0.03 an entry of a row's bucket per group of 32 rows, and every split writes and adds an array of partial
 // sums.  Fitted to 908 pairs of calls (65 to 8192 rows, 64 to 65535 columns, 10 to 8000 outputs, fractions 0.02 to 0.5): the
-// estimates are within 15 and 17 % of nine tenths of them, the choice within 10 % of the better side in all but eight (the
-// worst 300 x 16384 x 128 at 0.3, 62 / 48, left on the tiles).  At fraction 0.1 100 x 1024 x 100 12 / 11,
-// 65 x 4096 x 128 8.8 / 19, 200 x 4096 x 128 19 / 31, 150 x 784 x 300 15 / 15, 300 x 784 x 300 25 / 20, 512 x 784 x 300
-// 40 / 21, 512 x 1024 x 1024 41 / 43, 1024 x 1024 x 1024 79 / 57; at 0.5 300 x 784 x 300 47 / 24, 512 x 1024 x 1024 78 / 49,
-// 1024 x 2048 x 1024 237 / 129.  Above 2.2 million outputs with more than 128 columns nothing is measured.
+// estimates are within 15 and 10 % of nine tenths of them, the choice within 10 % of the better side in all but five
+// (the worst 300 x 65535 x 16 at 0.1, 58 / 35, left on the tiles).  At fraction 0.1 100 x 1024 x 128 9.1 / 10.8,
+// 65 x 4096 x 128 7.5 / 17, 200 x 4096 x 128 15 / 31, 150 x 784 x 300 12 / 18, 300 x 784 x 300 20 / 25, 512 x 784 x 300
+// 32 / 26, 512 x 1024 x 1024 32 / 44, 1024 x 1024 x 1024 61 / 54, 8192 x 1100 x 1000 599 / 270; at 0.5 300 x 784 x 300
+// 31 / 27, 512 x 1024 x 1024 51 / 56, 1024 x 2048 x 1024 125 / 130.  Above 2.2 million outputs with more than 128 columns
+// nothing is measured.
 // kept: the fraction of a row's columns that the store holds
 bool dw_narrow_pays(int dtype, int rows, int cols, int N, int sparse_prefetch, bool masked, double kept) {
   if (rows <= 64) return false;
@@ -275,8 +276,8 @@ bool dw_narrow_pays(int dtype, int rows, int cols, int N, int sparse_prefetch, b
   const double here = 3.4 * narrow_nt(N) / 16 + per * std::max(1.0, blocks / 1024) * group + (splits > 1 ? 4.7 + 6.3 * splits * out : 24.7);
   const double tiles128 = ((cols + 127) / 128) * (double)((N + 127) / 128), tiles64 = ((cols + 63) / 64) * (double)((N + 63) / 64);
   const double load = tiles128 >= 192 ? tiles128 / 256 : tiles64 / 512;
-  const double row = (wide ? 0.126 : 0.069) * std::max(1.0, load) + (wide ? 0.030 : 0.019) * std::min(1.0, load) + (masked ? 0.010 : 0.0);
-  return here < 3.5 + rows * row;
+  const double row = (wide ? 0.095 : 0.056) * std::max(1.0, load) + (wide ? 0.023 : 0.018) * std::min(1.0, load) + (masked ? 0.009 : 0.0);
+  return here < 3.7 + rows * row;
 }
 
 hipError_t launch_dw_narrow(const StoreView& s, int dtype, int rows, const void* dy, int64_t ldy, int N,

@@ -165,17 +165,6 @@ template <int R, int BK, bool EDGE, bool MASKED> struct F32LoadMN {
   }
 };
 
-// Segment of a store row that falls into one 256-column bucket.
-__device__ __forceinline__ void store_segment(const StoreView& s, int row, int bucket, uint32_t* beg, uint32_t* end) {
-  const uint16_t* bo = s.bucket_off + (size_t)(row * s.plan_row_stride) * (s.nb + 1) + bucket;
-  const uint32_t base = s.row_ptr[row];
-  uint32_t b = base + bo[0], e = base + bo[1];
-  const uint32_t cap = (uint32_t)s.capacity;     // an overflowed Bernoulli draw never reads past the arrays
-  if (e > cap) e = cap;
-  if (b > e) b = e;
-  *beg = b; *end = e;
-}
-
 // compressed store as the A operand of dW: K index = store row (example b),
 // M index = column j.  Wave w owns the k rows [w*BK/4, (w+1)*BK/4) of the LDS
 // tile: it clears them and scatters the entries of those store rows whose
@@ -184,26 +173,30 @@ template <int R, int BK, int SE> struct F32LoadSparse {
   typedef LdsF32<R, BK> L;
   static constexpr int RPW = BK / 4;            // k rows per wave
   static constexpr int LPR = 64 / RPW;          // lanes per k row
-  float val[SE]; int col[SE];
-  uint32_t beg, end, nbeg, nend;
+  // What a load brings is judged when it is committed: a condition around it, or arithmetic on it beside it, makes the wave
+  // wait for each load in turn.  Rows past K and entries past a segment's end read some valid place instead.
+  float val[SE]; uint32_t col[SE];
+  uint32_t beg, end;                            // segment of the entries held
+  uint32_t nbase, nb0, nb1; bool nrow;          // of the next slice, as loaded
   StoreView s; int m0, K;
   __device__ __forceinline__ void init(const void*, int64_t, const uint32_t*, int, int r0_, int, int K_,
                                        const StoreView& sv, const GemmArgs&) { s = sv; m0 = r0_; K = K_; }
   __device__ __forceinline__ void bounds(int k0) {
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    const int b = k0 + w * RPW + lane / LPR;
-    nbeg = nend = 0;
-    if (b < K) store_segment(s, b, m0 / kBucket, &nbeg, &nend);
+    const int b = k0 + w * RPW + lane / LPR, row = min(b, K - 1);
+    const uint16_t* bo = s.bucket_off + (size_t)(row * s.plan_row_stride) * (s.nb + 1) + m0 / kBucket;
+    nrow = b < K;
+    nbase = s.row_ptr[row]; nb0 = bo[0]; nb1 = bo[1];
   }
   __device__ __forceinline__ void fetch(int) {
-    const int sub = (threadIdx.x & 63) % LPR;
-    beg = nbeg; end = nend;
+    const uint32_t cap = (uint32_t)s.capacity;  // an overflowed Bernoulli draw never reads past the arrays
+    end = min(nbase + nb1, cap);
+    beg = (nrow ? min(nbase + nb0, end) : end) + (threadIdx.x & 63) % LPR;
     const float* vals = reinterpret_cast<const float*>(s.values);
 #pragma unroll
     for (int i = 0; i < SE; ++i) {
-      const uint32_t e = beg + sub + i * LPR;
-      col[i] = -1; val[i] = 0.f;
-      if (e < end) { col[i] = (int)s.indices[e] - m0; val[i] = vals[e]; }
+      const uint32_t e = min(beg + i * LPR, cap - 1u);
+      col[i] = s.indices[e]; val[i] = vals[e];
     }
   }
   __device__ __forceinline__ void commit(float* lds) {
@@ -211,14 +204,16 @@ template <int R, int BK, int SE> struct F32LoadSparse {
     const floatx4 z = {0.f, 0.f, 0.f, 0.f};
     for (int c = lane; c < RPW * (L::P / 4); c += 64)
       *reinterpret_cast<floatx4*>(&lds[(w * RPW) * L::P + c * 4]) = z;
-    const int kr = w * RPW + lane / LPR, sub = lane % LPR;
+    const int kr = w * RPW + lane / LPR;
 #pragma unroll
-    for (int i = 0; i < SE; ++i)
-      if (col[i] >= 0 && col[i] < R) lds[L::at(col[i], kr)] = val[i];
+    for (int i = 0; i < SE; ++i) {
+      const uint32_t c = col[i] - (uint32_t)m0;
+      if (beg + i * LPR < end && c < (uint32_t)R) lds[L::at((int)c, kr)] = val[i];
+    }
     const float* vals = reinterpret_cast<const float*>(s.values);
-    for (uint32_t e = beg + sub + SE * LPR; e < end; e += LPR) {
-      const int c = (int)s.indices[e] - m0;
-      if (c >= 0 && c < R) lds[L::at(c, kr)] = vals[e];
+    for (uint32_t e = beg + SE * LPR; e < end; e += LPR) {
+      const uint32_t c = s.indices[e] - (uint32_t)m0;
+      if (c < (uint32_t)R) lds[L::at((int)c, kr)] = vals[e];
     }
   }
 };
