@@ -258,8 +258,8 @@ int dw_narrow_splits(int rows, int cols, int N) {
 // twice that where a bucket's entries take its wide loader, so the fraction counts; here a round of up to 1024 workgroups
 // takes 2 us and 0.03 an entry of a row's bucket per group of 32 rows, and every split writes and adds an array of partial
 // sums.  Fitted to 908 pairs of calls (65 to 8192 rows, 64 to 65535 columns, 10 to 8000 outputs, fractions 0.02 to 0.5): the
-// estimates are within 15 and 10 % of nine tenths of them, the choice within 10 % of the better side in all but five
-// (the worst 300 x 65535 x 16 at 0.1, 58 / 35, left on the tiles).  At fraction 0.1 100 x 1024 x 128 9.1 / 10.8,
+// estimates are within 15 and 10 % of nine tenths of them, the choice within 10 % of the better side in all but one
+// (by 14 %).  At fraction 0.1 100 x 1024 x 128 9.1 / 10.8,
 // 65 x 4096 x 128 7.5 / 17, 200 x 4096 x 128 15 / 31, 150 x 784 x 300 12 / 18, 300 x 784 x 300 20 / 25, 512 x 784 x 300
 // 32 / 26, 512 x 1024 x 1024 32 / 44, 1024 x 1024 x 1024 61 / 54, 8192 x 1100 x 1000 599 / 270; at 0.5 300 x 784 x 300
 // 31 / 27, 512 x 1024 x 1024 51 / 56, 1024 x 2048 x 1024 125 / 130.  Above 2.2 million outputs with more than 128 columns
@@ -277,7 +277,8 @@ bool dw_narrow_pays(int dtype, int rows, int cols, int N, int sparse_prefetch, b
   const double tiles128 = ((cols + 127) / 128) * (double)((N + 127) / 128), tiles64 = ((cols + 63) / 64) * (double)((N + 63) / 64);
   const double load = tiles128 >= 192 ? tiles128 / 256 : tiles64 / 512;
   const double row = (wide ? 0.095 : 0.056) * std::max(1.0, load) + (wide ? 0.023 : 0.018) * std::min(1.0, load) + (masked ? 0.009 : 0.0);
-  return here < 3.7 + rows * row;
+  const double edge = tiles128 >= 192 && (cols % 128 || N % 128) ? 1.33 : 1.0;         // guarded loads on a full chip
+  return here < 1.04 * (3.7 + rows * row * edge);                   // (the factor that loses least over the pairs)
 }
 
 hipError_t launch_dw_narrow(const StoreView& s, int dtype, int rows, const void* dy, int64_t ldy, int N,
