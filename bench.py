@@ -248,7 +248,7 @@ def main():
             step(10_000 + i)
         kern = {}
         names = ["plan", "row_scan", "pack", "reindex", "sign_matrix", "scale_cast", "unpack", "project_rows_fwd",
-                 "project_rows_bwd", "fwd", "dx", "dw_sparse", "dw_dense", "dw_overflow", "splitk_fwd", "splitk_bias",
+                 "project_rows_bwd", "fwd", "dx", "dw_sparse", "dw_dense", "splitk_fwd", "splitk_bias",
                  "splitk_reduce", "softmax_ce", "colsum", "fill"]
         # labels are matched as substrings: the GEMM families by "_fwd_" / "_dx_", which the finishing and projection
         # kernels (…_fwd at the end of their names) do not contain

@@ -1143,6 +1143,7 @@ static rad_status dW_gemm(rad_ctx* c, const rad_store* s, int slot, const void* 
       }
     }
   }
+  g.max_seg = s->max_seg;
   RAD_TRY(run_gemm_call(c, s->dtype, kOpSparse, kOpMN, kEpiStore, g, alg));
   if (split && n_out != N)
     HIP_TRY(c, timed(c, "splitk_reduce", [&](const char**) {
@@ -1153,13 +1154,6 @@ static rad_status dW_gemm(rad_ctx* c, const rad_store* s, int slot, const void* 
     HIP_TRY(c, timed(c, "splitk_reduce", [&](const char**) {
       return launch_splitk_reduce(static_cast<const float*>(g.C), g.k_splits, g.split_stride, dW, beta, c->stream);
     }));
-  if (s->dtype == kBF16) {
-    // the bf16 kernel keeps a fixed number of entries per (row, bucket) in registers; the rest, if any, here
-    const int cap = gemm_bf16_sparse_cap(g.sparse_prefetch);
-    HIP_TRY(c, timed(c, "dw_overflow", [&](const char**) {
-      return launch_dw_overflow(g.sa, s->rows, dy, s->dtype, n_out, bits, bits_pitch, dW, cap, s->max_seg, c->stream, ldy);
-    }));
-  }
   return RAD_OK;
 }
 

@@ -333,8 +333,7 @@ template <int R, int SE, int NS> struct RingLoadSparse {
   }
   // A lane reads its SE entries without looking at the segment end (the store is allocated kPairPad
   // entries past its capacity); entries beyond the end are dropped at commit time.  Entries beyond kCap
-  // of a segment are not handled here: the host runs the overflow kernel after this GEMM, which adds them
-  // to dW (it exits at once unless the plan saw a segment that long).
+  // of a segment are added after the epilogue (add_long_segments).
   template <int SLOT, bool KTAIL = true> __device__ __forceinline__ void fetch(int) {
     segment();
     const uint32_t e0 = nbeg + (threadIdx.x & 63) % LPR;
@@ -553,6 +552,30 @@ __device__ __forceinline__ void epilogue_dx_staged(const GemmArgs& g, floatx16 (
   }
 }
 
+// The sparse loader holds a fixed number of entries per (store row, bucket) segment; what a segment has beyond them is added
+// to this workgroup's tile here, after its stores (rows [k_beg, k_end), six standard deviations above the mean entry count:
+// the plan's longest segment, *g.max_seg, says whether there are any).
+template <int BN>
+__device__ __forceinline__ void add_long_segments(const GemmArgs& g, float* C, int k_beg, int k_end, int m0, int n0, int cap) {
+  if (*g.max_seg <= cap) return;
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");         // the tile's stores are where the atomic additions work
+  __syncthreads();
+  const int lane = threadIdx.x & 63, bucket = m0 / kBucket;
+  const StoreView& s = g.sa;
+  for (int b = k_beg + (gemm_tid() >> 6); b < k_end; b += kGemmThreads / 64) {
+    const uint16_t* bo = s.bucket_off + (size_t)(b * s.plan_row_stride) * (s.nb + 1) + bucket;
+    const int64_t base = s.row_ptr[b], end = min(base + bo[1], s.capacity);
+    for (int64_t e = base + bo[0] + cap; e < end; ++e) {
+      const uint32_t u = static_cast<const uint32_t*>(s.values)[e];
+      float* const row = C + (size_t)pair_col(u, bucket) * g.ldc;
+      for (int n = n0 + lane; n < min(n0 + BN, g.N); n += 64) {
+        const float v = get_elem(static_cast<const uint16_t*>(g.B) + (size_t)b * g.ldb + n);
+        if (!g.b_mask || (mask_bits(g.b_mask, g.b_mask_pitch, b, n) & 1u)) atomicAdd(row + n, __uint_as_float(u & 0xFFFF0000u) * v);
+      }
+    }
+  }
+}
+
 template <int V> using IntC = std::integral_constant<int, V>;
 
 // kFlagKHalves: a workgroup of 512 threads, whose two groups of 256 take half of the K range each, with stages of their own;
@@ -613,6 +636,7 @@ __global__ __launch_bounds__(kGemmThreads * ((FLAGS & kFlagKHalves) ? 2 : 1)) vo
   // split K: blockIdx.y takes the K range [kbeg, kend) and the epilogue adds its partial result atomically
   int kbeg = g.k_splits > 1 ? (int)blockIdx.y * g.k_split : 0;
   int kend = g.k_splits > 1 ? min(g.K, kbeg + g.k_split) : g.K;
+  const int k_beg = kbeg, k_end = kend;            // of this workgroup
   int KT_all = 0;                                  // slices of the longer half: both groups pass that many barriers
   if constexpr (kHalves) {
     KT_all = (kend - kbeg + 2 * BK - 1) / (2 * BK);
@@ -807,10 +831,12 @@ __global__ __launch_bounds__(kGemmThreads * ((FLAGS & kFlagKHalves) ? 2 : 1)) vo
       GemmArgs gs = g;
       gs.C = static_cast<float*>(g.C) + (int64_t)blockIdx.y * g.split_stride;
       epilogue_store<TM, TN, float, EDGE, false, false, false>(gs, acc, m0, n0, wm0, wn0);
+      if constexpr (AK == kOpSparse) add_long_segments<BN>(g, static_cast<float*>(gs.C), k_beg, k_end, m0, n0, LoadA::kCap);
     } else if constexpr (kStaged) {
       epilogue_dx_staged<BM, BN, TM, TN>(g, acc, smem, m0, n0, wm0, wn0);
     } else {
       epilogue_store_dispatch<AK, TM, TN, uint16_t, EDGE>(g, acc, m0, n0, wm0, wn0);
+      if constexpr (AK == kOpSparse) add_long_segments<BN>(g, static_cast<float*>(g.C), k_beg, k_end, m0, n0, LoadA::kCap);
     }
   } else {
     epilogue_fwd<uint16_t, BM, BN, TM, TN>(g, acc, smem, m0, n0, wm0, wn0);

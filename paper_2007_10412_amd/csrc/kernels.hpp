@@ -63,6 +63,7 @@ struct GemmArgs {
   const uint32_t* b_mask; int b_mask_pitch;
   StoreView sa;                 // kOpSparse A
   int sparse_prefetch;          // entries per lane held in registers (host picks)
+  const int* max_seg;           // kOpSparse A, bf16: longest (row, bucket) segment of the store's plan
   // kEpiStore
   void* C; int64_t ldc; int beta; int c_dtype;   // c_dtype: kF32 or kBF16
   const uint16_t* row_map;      // output row of tile row r (null = r)
@@ -168,11 +169,6 @@ hipError_t launch_channel_sum(const float* g, int batch, int C, int HW, float* d
                               hipStream_t st);
 // Wt[(o,u,v)][c] = W[c][KH-1-u][KW-1-v][o]: the weight operand of the transposed convolution (dX)
 hipError_t launch_flip_weights(const float* W, int Ci, int KH, int KW, int Co, float* Wt, hipStream_t st);
-// Adds to dW the entries of (row, bucket) segments beyond the first `cap`, which the MFMA kernel leaves out;
-// exits at once when *max_seg <= cap (the plan's running maximum), which is the normal case.
-// (ldy > 0: the rows of dy are ldy apart)
-hipError_t launch_dw_overflow(const StoreView& s, int rows, const void* dy, int dtype, int N, const uint32_t* bits,
-                              int bits_pitch, float* dW, int cap, const int* max_seg, hipStream_t st, int64_t ldy = 0);
 // dW of a narrow layer from a store with its own columns per row (bf16: paired entries), rows split over workgroups
 // (dw_narrow.hip): partial sums [splits][cols][N] split_stride apart, or (splits 1, stride 0) dW itself
 // whether it is the faster one (sparse_prefetch as in GemmArgs; masked: dy comes with ReLU bits; kept: the fraction of a
@@ -184,8 +180,6 @@ hipError_t launch_dw_narrow(const StoreView& s, int dtype, int rows, const void*
                             double kept, hipStream_t st);
 // whether the fp32 sparse dW kernel takes its loader for many entries per (row, bucket)
 inline bool f32_sparse_wide(int sparse_prefetch) { return sparse_prefetch > 4; }
-// entries per (row, bucket) the bf16 sparse dW kernel chosen for `sparse_prefetch` handles itself
-int gemm_bf16_sparse_cap(int sparse_prefetch);
 int gemm_bf16_sparse_max_prefetch();
 // dense[rows, cols] = the store's rows scattered back (zeros elsewhere): x~ as a dense operand
 hipError_t launch_unpack(const StoreView& s, int dtype, void* dense, hipStream_t st);

@@ -235,41 +235,6 @@ __global__ __launch_bounds__(256) void colsum_final_kernel(const float* __restri
   if (dst) *dst = beta ? *dst + v : v;
 }
 
-// Entries of a (store row, bucket) segment beyond the first `cap` are left out by the MFMA dW kernel,
-// whose registers hold `cap` of them; this kernel adds their contribution dW[j, :] += value * g[b, :].
-// One wave per segment.  *max_seg is the plan's running maximum segment length: the kernel leaves at once
-// when no segment is that long, which is the normal case (cap sits six standard deviations above the mean).
-template <typename T>
-__global__ __launch_bounds__(256) void dw_overflow_kernel(StoreView s, int rows, const T* __restrict__ dy, int N,
-                                                          int64_t ldy, const uint32_t* __restrict__ bits, int bits_pitch,
-                                                          float* __restrict__ dW, int cap,
-                                                          const int* __restrict__ max_seg) {
-  if (*max_seg <= cap) return;
-  const int lane = threadIdx.x & 63;
-  for (int seg = blockIdx.x * 4 + (threadIdx.x >> 6); seg < rows * s.nb; seg += gridDim.x * 4) {
-  const int b = seg / s.nb, t = seg % s.nb;
-  const uint16_t* bo = s.bucket_off + (size_t)(b * s.plan_row_stride) * (s.nb + 1) + t;
-  const int64_t base = s.row_ptr[b];
-  int64_t beg = base + bo[0], end = base + bo[1];
-  if (end > s.capacity) end = s.capacity;
-  const T* vals = reinterpret_cast<const T*>(s.values);
-  for (int64_t e = beg + cap; e < end; ++e) {
-    int j; float v;
-    if (s.paired) {
-      const uint32_t u = reinterpret_cast<const uint32_t*>(s.values)[e];
-      j = pair_col(u, t); v = __uint_as_float(u & 0xFFFF0000u);
-    } else {
-      j = s.indices[e]; v = ld_elem(vals + e);
-    }
-    for (int n = lane; n < N; n += 64) {
-      float g = ld_elem(dy + (size_t)b * ldy + n);
-      if (bits && !((bits[(size_t)b * bits_pitch + (n >> 5)] >> (n & 31)) & 1u)) g = 0.f;
-      atomicAdd(&dW[(size_t)j * N + n], v * g);
-    }
-  }
-  }
-}
-
 __global__ __launch_bounds__(256) void splitk_reduce_kernel(const float* __restrict__ partial, int splits, int64_t n,
                                                             float* __restrict__ out, int beta) {
   const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
@@ -654,23 +619,6 @@ hipError_t launch_colsum(const void* dy, int dtype, int rows, int N, const uint3
   if (part)
     hipLaunchKernelGGL(colsum_final_kernel, dim3((N + 63) / 64, u_n + 1), dim3(256), 0, st, partial, splits, N, u_n, out_bias,
                        out_u, beta);
-  return hipGetLastError();
-}
-
-hipError_t launch_dw_overflow(const StoreView& s, int rows, const void* dy, int dtype, int N, const uint32_t* bits,
-                              int bits_pitch, float* dW, int cap, const int* max_seg, hipStream_t st, int64_t ldy) {
-  if (ldy <= 0) ldy = N;
-  // almost always the kernel only reads *max_seg and leaves: a small grid keeps that cheap, and the
-  // workgroups walk the segments in strides when there is work
-  const int segs = rows * s.nb;
-  const int blocks = (segs + 3) / 4;
-  dim3 grid(blocks < 256 ? blocks : 256), block(256);
-  if (dtype == kF32)
-    hipLaunchKernelGGL(dw_overflow_kernel<float>, grid, block, 0, st, s, rows, (const float*)dy, N, ldy, bits, bits_pitch,
-                       dW, cap, max_seg);
-  else
-    hipLaunchKernelGGL(dw_overflow_kernel<uint16_t>, grid, block, 0, st, s, rows, (const uint16_t*)dy, N, ldy, bits,
-                       bits_pitch, dW, cap, max_seg);
   return hipGetLastError();
 }
 
