@@ -185,6 +185,17 @@ rad_status rad_debug_key_shift(rad_ctx* ctx, int32_t shift);
  * that step; 0 cancels the hook. */
 rad_status rad_debug_poll_limit(rad_ctx* ctx, int32_t polls);
 
+/* Test hook: in the first `launches` kernel launches of the next such step
+ * (one per 32 time steps and direction) the workgroups of the groups in the
+ * bit mask `groups` (bit i: XCD i and its eighth of the batch) do nothing, as
+ * if none had been started there; the stand-in kernel has to notice.  0
+ * launches cancel the hook. */
+rad_status rad_debug_absent_groups(rad_ctx* ctx, uint32_t groups, int32_t launches);
+
+/* Test hook: how many kernel launches of this kind the last such step took and
+ * how many of them were computed again by the stand-in kernel.  Blocks. */
+rad_status rad_debug_redone_launches(rad_ctx* ctx, int32_t* redone, int32_t* launches);
+
 /* Allocates the store for `layer` under `scheme`/`p`: value and index arrays
  * sized for batch*k entries (fixed-k), batch*d_in (EXACT), or the Bernoulli
  * mean plus eight standard deviations; row pointers, per-256-column offsets,

@@ -66,6 +66,8 @@ SIGNATURES = {
     "rad_ctx_timing_reset": (C.c_int, [P]),
     "rad_debug_key_shift": (C.c_int, [P, C.c_int32]),
     "rad_debug_poll_limit": (C.c_int, [P, C.c_int32]),
+    "rad_debug_absent_groups": (C.c_int, [P, C.c_uint32, C.c_int32]),
+    "rad_debug_redone_launches": (C.c_int, [P, C.POINTER(C.c_int32), C.POINTER(C.c_int32)]),
     "rad_probe_ceiling": (C.c_int, [P, C.c_int32, P, P, C.c_uint64, C.c_int32, C.POINTER(C.c_double)]),
     "rad_store_create": (C.c_int, [P, C.POINTER(rad_layer), C.c_int32, C.c_double, C.c_int32, C.POINTER(P)]),
     "rad_store_destroy": (C.c_int, [P]),
@@ -210,6 +212,17 @@ def rad_debug_key_shift(ctx, shift):
 
 def rad_debug_poll_limit(ctx, polls):
     _check(ctx, lib().rad_debug_poll_limit(ctx, polls))
+
+
+def rad_debug_absent_groups(ctx, groups, launches):
+    _check(ctx, lib().rad_debug_absent_groups(ctx, groups, launches))
+
+
+def rad_debug_redone_launches(ctx):
+    """(launches computed again, launches) of the last recurrent step of that kind."""
+    redone, launches = C.c_int32(), C.c_int32()
+    _check(ctx, lib().rad_debug_redone_launches(ctx, C.byref(redone), C.byref(launches)))
+    return redone.value, launches.value
 
 
 def rad_store_create(ctx, layer, scheme, p, steps=1):

@@ -24,6 +24,10 @@ struct rad_ctx {
   int key_shift = 0;
   int compute_units = 0;
   uint32_t poll_limit = 0;        // test hook: bound of the waits of the next recurrent step's kernels, 0 = the library's own
+  uint32_t absent = 0;            // test hook: groups that stay away from the first launches of the next recurrent step
+  int absent_launches = 0;
+  size_t redone_at = 0;           // where in WS_RNNSYNC the last such step counts, per launch, whether it was computed again
+  int redone_launches = 0;
   // side stream of the recurrent model's backward pass (created on first use): the gradients formed per chunk of
   // time steps run there, beside the chain of dX GEMMs.  While calls are enqueued there, `stream` and `side` are
   // swapped and on_side is 1 (swap_streams).
@@ -233,6 +237,26 @@ extern "C" rad_status rad_debug_poll_limit(rad_ctx* c, int32_t polls) {
   if (!c) return RAD_ERR_NULL;
   if (polls < 0) return fail(c, RAD_ERR_PARAM, "polls must not be negative");
   c->poll_limit = (uint32_t)polls;
+  return RAD_OK;
+}
+
+// test hooks of the same kernels
+extern "C" rad_status rad_debug_absent_groups(rad_ctx* c, uint32_t groups, int32_t launches) {
+  if (!c) return RAD_ERR_NULL;
+  if (launches < 0) return fail(c, RAD_ERR_PARAM, "launches must not be negative");
+  c->absent = groups; c->absent_launches = launches;
+  return RAD_OK;
+}
+extern "C" rad_status rad_debug_redone_launches(rad_ctx* c, int32_t* redone, int32_t* launches) {
+  if (!c) return RAD_ERR_NULL;
+  if (!redone || !launches) return fail(c, RAD_ERR_NULL, "redone or launches is null");
+  HIP_TRY(c, hipStreamSynchronize(c->stream));
+  std::vector<uint32_t> words((size_t)c->redone_launches, 0u);
+  if (c->ws[0][WS_RNNSYNC] && !words.empty())
+    HIP_TRY(c, hipMemcpy(words.data(), static_cast<char*>(c->ws[0][WS_RNNSYNC]) + c->redone_at, words.size() * 4, hipMemcpyDeviceToHost));
+  *launches = c->redone_launches;
+  *redone = 0;
+  for (uint32_t w : words) *redone += w != 0u;
   return RAD_OK;
 }
 
@@ -1833,6 +1857,8 @@ static rad_status rnn_wide_begin(rad_ctx* c, const rad_model* m, const float* xs
   void* ws = nullptr;
   RAD_TRY(ws_get(c, WS_RNNSYNC, bytes, &ws));
   rnn_wide_sync_layout(a, ws, launches);
+  c->redone_at = (size_t)(reinterpret_cast<char*>(a->redone) - static_cast<char*>(ws));
+  c->redone_launches = 0;
   HIP_TRY(c, timed(c, "fill", [&](const char**) {
     return launch_fill_u32(static_cast<uint32_t*>(ws), 0u, (int64_t)(bytes / 4), c->stream);
   }));
@@ -1841,8 +1867,9 @@ static rad_status rnn_wide_begin(rad_ctx* c, const rad_model* m, const float* xs
 
 static rad_status rnn_wide_launch(rad_ctx* c, bool forward, RnnWideArgs* a) {
   a->seq0 = 1u + (uint32_t)a->launch * kRnnWideChunk;
+  a->absent = a->launch < c->absent_launches ? c->absent : 0u;
   HIP_TRY(c, timed(c, forward ? "rnn_wide_fwd" : "rnn_wide_bwd", [&](const char**) { return launch_rnn_wide(forward, *a, c->stream); }));
-  ++a->launch;
+  c->redone_launches = ++a->launch;
   return RAD_OK;
 }
 
@@ -1977,6 +2004,7 @@ static rad_status rnn_step(rad_ctx* c, rad_model* m, const rad_sampling* sm, con
   }
   if (m->rnn_wide) {
     RAD_TRY(rnn_wide_backward(c, m, &wa, dz, W_ho, dW_hh, db, dW_ih));
+    c->absent_launches = 0;
     return step_finish(c, m, loss_host);
   }
   // dyb holds g_t = dL/dh_t masked by the ReLU bits of step t (applied in the epilogue of the GEMM that

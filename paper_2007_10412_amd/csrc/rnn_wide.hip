@@ -19,10 +19,12 @@
 // does not fit 32 columns a CU, keeps a launch per step.
 //
 // The workgroups find their XCD in the hardware register and take a place in it from a counter; the loads of flags and
-// exchanged values pass by the L1 (agent scope, sc1), which is all the coherence that sharers of one L2 need.  Every wait is bounded: if
-// the workgroups of a group do not all get to run (another process's kernel on some CUs, another partition mode), one of
-// them gives up, sets the launch's abort word, and rnn_wide_redo_kernel, which follows every launch and otherwise returns
-// at once, computes the chunk again without any exchange.
+// exchanged values pass by the L1 (agent scope, sc1), which is all the coherence that sharers of one L2 need.
+// What has to hold and is not the library's to decide is that the workgroups of a group run side by side on one XCD (another
+// kernel on some CUs, another partition mode).  Every wait is bounded: a workgroup that waited too long gives up and sets the
+// launch's abort word.  A group that too few workgroups reached shows in its counter, also where nobody waits for it.
+// rnn_wide_redo_kernel follows every launch, looks at both and, unless all is there, computes the chunk again without any
+// exchange.
 #include <algorithm>
 
 #include "gemm.hpp"
@@ -33,6 +35,10 @@ namespace {
 
 constexpr int kWaves = 8, kGroups = kRnnWideGroups, kFlagsPerGroup = 256;     // flags: 64 blocks x 4 accumulator elements
 constexpr int kXccIdReg = 20;                                                 // HW_REG_XCC_ID
+
+__host__ __device__ constexpr int rows_per_group(int B) { return (B + kGroups - 1) / kGroups; }
+constexpr int columns_per_member(int H) { return (H + 127) / 128 <= 4 ? 16 : 32; }
+constexpr int members_of(int H) { return (H + columns_per_member(H) - 1) / columns_per_member(H); }
 
 __device__ __forceinline__ float load_or_zero(const float* p, bool ok) { return ok ? *p : 0.f; }
 
@@ -47,13 +53,13 @@ __global__ __launch_bounds__(64 * kWaves, R == 1 ? 4 : 2) void rnn_wide_kernel(R
   uint32_t* const abort_word = a.abort_words + a.launch;
   if (threadIdx.x == 0) {
     s_dead = 0;
-    s_member = xcc < kGroups ? (int)atomicAdd(a.tickets + a.launch * kGroups + xcc, 1u) : 0x7fffffff;
-    if (xcc >= kGroups) __hip_atomic_store(abort_word, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const bool counts = xcc < kGroups && !((a.absent >> xcc) & 1u);
+    s_member = counts ? (int)atomicAdd(a.tickets + a.launch * kGroups + xcc, 1u) : 0x7fffffff;
   }
   __syncthreads();
   const int member = __builtin_amdgcn_readfirstlane(s_member), nblk = (H + 15) / 16;
-  const int rg = (B + kGroups - 1) / kGroups, row0 = xcc * rg, row_end = min(B, row0 + rg);
-  if (member >= (nblk + NC - 1) / NC || row0 >= row_end) return;
+  const int rg = rows_per_group(B), row0 = xcc * rg, row_end = min(B, row0 + rg);
+  if (member >= a.members || row0 >= row_end) return;
   const int n0 = member * 16 * NC;
 
   float wr[J][4][NC];                        // W_hh[k][n] (forward) or W_hh[n][k], k = 16 (J w + j) + 4 kq + e
@@ -211,10 +217,21 @@ __global__ __launch_bounds__(64 * kWaves, R == 1 ? 4 : 2) void rnn_wide_kernel(R
   }
 }
 
-// The chunk again, an example at a time per workgroup (few: normally it returns at once), if the launch before gave up.
+// Whether the launch before left anything out: a wait that ran out, or a group of examples that fewer workgroups reached
+// than its columns take.  (The second does not follow from the first: a chunk of one step has no waits, and a group that
+// nobody reached has nobody to wait.)
+__device__ __forceinline__ bool left_out(const RnnWideArgs& a) {
+  const int g = threadIdx.x & 63;
+  const bool short_group = g < kGroups && g * rows_per_group(a.B) < a.B && a.tickets[a.launch * kGroups + min(g, kGroups - 1)] < (uint32_t)a.members;
+  return __any(short_group) || a.abort_words[a.launch] != 0u;
+}
+
+// The chunk again, an example at a time per workgroup (few: normally it returns at once), if the launch before left
+// something out.
 template <bool FWD>
 __global__ __launch_bounds__(1024) void rnn_wide_redo_kernel(RnnWideArgs a) {
-  if (a.abort_words[a.launch] == 0u) return;
+  if (!left_out(a)) return;
+  if (blockIdx.x == 0 && threadIdx.x == 0) a.redone[a.launch] = 1u;
   __shared__ float s[1024];
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, H = a.H, B = a.B, n = threadIdx.x;
   for (int row = blockIdx.x; row < B; row += gridDim.x) {
@@ -259,11 +276,11 @@ __global__ __launch_bounds__(1024) void rnn_wide_redo_kernel(RnnWideArgs a) {
 }
 
 template <int J, int NC> hipError_t start(bool forward, const RnnWideArgs& a, hipStream_t st) {
-  const int members = ((a.H + 15) / 16 + NC - 1) / NC;
+  static_assert(columns_per_member(128 * J) == 16 * NC, "members_of counts this kernel's workgroups");
   const bool two = a.B > 16 * kGroups;
   auto kern = two ? (forward ? rnn_wide_kernel<J, NC, 2, true> : rnn_wide_kernel<J, NC, 2, false>)
                   : (forward ? rnn_wide_kernel<J, NC, 1, true> : rnn_wide_kernel<J, NC, 1, false>);
-  hipLaunchKernelGGL(kern, dim3(members * kGroups), dim3(64 * kWaves), 0, st, a);
+  hipLaunchKernelGGL(kern, dim3(a.members * kGroups), dim3(64 * kWaves), 0, st, a);
   return hipGetLastError();
 }
 
@@ -275,7 +292,7 @@ bool rnn_wide_ok(int64_t B, int64_t H, int64_t I, int compute_units) {
 
 size_t rnn_wide_sync_bytes(int B, int H, int launches) {
   const size_t J = (size_t)(H + 127) / 128, R = B > 16 * kGroups ? 2 : 1;
-  return ((size_t)2 * kGroups * kWaves * R * J * 256 + (size_t)kGroups * kFlagsPerGroup + (size_t)launches * (kGroups + 1)) * 4;
+  return ((size_t)2 * kGroups * kWaves * R * J * 256 + (size_t)kGroups * kFlagsPerGroup + (size_t)launches * (kGroups + 2)) * 4;
 }
 
 void rnn_wide_sync_layout(RnnWideArgs* a, void* ws, int launches) {
@@ -284,10 +301,13 @@ void rnn_wide_sync_layout(RnnWideArgs* a, void* ws, int launches) {
   a->flags = reinterpret_cast<uint32_t*>(a->xch + (size_t)2 * kGroups * kWaves * R * J * 256);
   a->tickets = a->flags + (size_t)kGroups * kFlagsPerGroup;
   a->abort_words = a->tickets + (size_t)launches * kGroups;
+  a->redone = a->abort_words + launches;
 }
 
-hipError_t launch_rnn_wide(bool forward, const RnnWideArgs& a, hipStream_t st) {
+hipError_t launch_rnn_wide(bool forward, const RnnWideArgs& args, hipStream_t st) {
+  RnnWideArgs a = args;
   if (!rnn_wide_ok(a.B, a.H, a.I, 32 * kGroups) || a.n < 1) return hipErrorInvalidValue;
+  a.members = members_of(a.H);
   hipError_t e = hipErrorInvalidValue;
   switch ((a.H + 127) / 128) {
     case 2: e = start<2, 1>(forward, a, st); break;

@@ -60,6 +60,21 @@ def test_chunks_whose_launch_gave_up(ctx, hidden, batch, scheme):  # noqa: F811
     run_rnn(ctx, data(hidden, batch, 40, hidden, d_input=2), scheme, 0.2 if scheme else 1.0, seed=6)
 
 
+@pytest.mark.parametrize("T", [1, 2, 3, 33])
+@pytest.mark.parametrize("groups", [0x01, 0x84, 0xff])
+def test_groups_that_no_workgroup_reached(ctx, T, groups):  # noqa: F811
+    """Nobody waits in a chunk of one time step, and nobody waits for a group without workgroups: what they left out shows
+    in the groups' counters only.  Three groups of examples, the third of them with one example."""
+    from paper_2007_10412_amd import binding as B
+    launches = -(-T // 32) * (1 + (T > 1))
+    for n in (1, launches):
+        B.rad_debug_absent_groups(ctx, groups, n)
+        run_rnn(ctx, data(T, 19, T, 250, d_input=2), 1, 0.3, seed=T, check_store=T > 1)
+        assert B.rad_debug_redone_launches(ctx) == (n, launches)
+    run_rnn(ctx, data(T, 19, T, 250, d_input=2), 1, 0.3, seed=T, check_store=T > 1)
+    assert B.rad_debug_redone_launches(ctx) == (0, launches)
+
+
 def test_repeated_steps_are_identical(ctx):  # noqa: F811
     from paper_2007_10412_amd import binding as B
     from tests.gpu_util import dev, host, empty
