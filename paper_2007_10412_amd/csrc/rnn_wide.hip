@@ -226,52 +226,113 @@ __device__ __forceinline__ bool left_out(const RnnWideArgs& a) {
   return __any(short_group) || a.abort_words[a.launch] != 0u;
 }
 
-// The chunk again, an example at a time per workgroup (few: normally it returns at once), if the launch before left
-// something out.
-template <bool FWD>
-__global__ __launch_bounds__(1024) void rnn_wide_redo_kernel(RnnWideArgs a) {
+// four consecutive numbers at element alignment, those past `n` zero
+__device__ __forceinline__ floatx4 load4_or_zero(const float* p, int n) {
+  floatx4 v = {0.f, 0.f, 0.f, 0.f};
+  if (n >= 4) __builtin_memcpy(&v, p, 16);
+  else {
+#pragma unroll
+    for (int e = 0; e < 3; ++e) if (e < n) v[e] = p[e];
+  }
+  return v;
+}
+
+// The chunk again if the launch before left something out (normally it returns at once).  A workgroup takes sixteen examples
+// and all columns, so nothing is exchanged: h or g is in LDS in the order of the A fragments, and two groups of eight waves
+// take the 16-column blocks in turn, with the products, the split of k over the waves and the order of every sum of
+// rnn_wide_kernel, so that a step's numbers do not depend on which of the two computed it.  W_hh is read from L2 again every
+// step by the few CUs that run, and sixteen rows are 55 us of matrix instructions for one of them at hidden 1024.  A step, us,
+// forward / backward: 128 x 1024 86 / 125 (with an example at a time on the vector ALU 650 for either), 192 x 1000 93 / 98,
+// 16 x 700 44 / 46, 40 x 300 13 / 14.  (The next block's columns loaded a block ahead: 116 / 150 in the first case.)
+template <int J, bool FWD>
+__global__ __launch_bounds__(128 * kWaves) void rnn_wide_redo_kernel(RnnWideArgs a) {
   if (!left_out(a)) return;
   if (blockIdx.x == 0 && threadIdx.x == 0) a.redone[a.launch] = 1u;
-  __shared__ float s[1024];
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, H = a.H, B = a.B, n = threadIdx.x;
-  for (int row = blockIdx.x; row < B; row += gridDim.x) {
-  __syncthreads();
-  s[n] = a.src && n < H ? a.src[(size_t)row * H + n] : 0.f;
-  for (int i = 0; i < a.n; ++i) {
-    const int t = FWD ? a.t0 + i : a.t0 - i;
-    const size_t out = ((size_t)(t - a.t_lo) * B + row) * H;
-    uint32_t* const words = a.bits + ((size_t)(t - 1) * B + row) * a.bp;
-    __syncthreads();
-    if (FWD) {
-      float v = 0.f;
-      if (n < H) {
-        for (int k = 0; k < H; ++k) v = fmaf(s[k], a.W_hh[(size_t)k * H + n], v);
-        v += a.b[n];
-        for (int q = 0; q < a.I; ++q) v = fmaf(a.xs[((size_t)row * a.T + (t - 1)) * a.I + q], a.W_ih[(size_t)q * H + n], v);
-        v = v > 0.f ? v : 0.f;
-        if (t <= a.t_out) a.out[out + n] = v;
-        if (i + 1 == a.n && a.carry) a.carry[(size_t)row * H + n] = v;
-      }
-      const uint64_t on = __ballot(v > 0.f);
-      if ((lane & 31) == 0 && n / 32 < a.bp) words[n / 32] = (uint32_t)(on >> lane);
-      __syncthreads();
-      s[n] = v;
-    } else {
-      __shared__ float nxt[1024];
-      for (int k = w; k < H; k += 16) {
-        float v = 0.f;
-        for (int m = lane; m < H; m += 64) v = fmaf(s[m], a.W_hh[(size_t)k * H + m], v);
-        for (int d = 32; d > 0; d >>= 1) v += __shfl_xor(v, d);
-        if (lane == 0) nxt[k] = ((words[k / 32] >> (k % 32)) & 1u) ? v : 0.f;
-      }
-      __syncthreads();
-      s[n] = n < H ? nxt[n] : 0.f;
-      if (n < H) {
-        if (t <= a.t_out) a.out[out + n] = s[n];
-        if (i + 1 == a.n && a.carry) a.carry[(size_t)row * H + n] = s[n];
+  __shared__ __align__(16) float state[kWaves * J * 256];
+  __shared__ float part[2][2][kWaves][4][64];
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const int grp = wave / kWaves, w = wave % kWaves, r = lane & 15, kq = lane >> 4;
+  const int H = a.H, B = a.B, nblk = (H + 15) / 16, row0 = 16 * (int)blockIdx.x;
+  uint16_t* const bits16 = reinterpret_cast<uint16_t*>(a.bits);
+  for (int q = threadIdx.x; q < kWaves * J * 64; q += 128 * kWaves) {       // fragment lane q % 64 of block q / 64
+    const int row = row0 + (q & 15), k = q / 64 * 16 + (q % 64) / 16 * 4;
+    const bool any = a.src && row < B && k < H;
+    reinterpret_cast<floatx4*>(state)[q] = load4_or_zero(a.src + (any ? (size_t)row * H + k : 0), any ? H - k : 0);
+  }
+  auto W = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(a.W_hh), 0, H * H * 4, 0x00020000);
+  // W_hh of this lane's column of a block, in the wave's range of k (what lies past the matrix reads as zero: rows k >= H are behind its
+  // end, and so is a column that does not exist)
+  floatx4 wr[J];
+  auto load_columns = [&](int col) {
+    const int k = 16 * J * w + 4 * kq;
+    const uint32_t at = col >= H ? 0x40000000u : 4u * (uint32_t)(FWD ? k * H + col : col * H + k);
+#pragma unroll
+    for (int j = 0; j < J; ++j) {
+      if (FWD) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          wr[j][e] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(W, at + 4u * (uint32_t)((16 * j + e) * H), 0, 0));
+      } else {
+        wr[j] = __builtin_bit_cast(floatx4, __builtin_amdgcn_raw_buffer_load_b128(W, at + 64u * (uint32_t)j, 0, 0));
+#pragma unroll
+        for (int e = 0; e < 4; ++e) wr[j][e] = k + 16 * j + e < H ? wr[j][e] : 0.f;
       }
     }
-  }
+  };
+  const int fe = w & 3, row = row0 + 4 * kq + fe;       // what a finishing wave (w < 4) adds up: element fe of each block
+  const bool row_ok = row < B;
+  for (int i = 0; i < a.n; ++i) {
+    const int t = FWD ? a.t0 + i : a.t0 - i;
+    __syncthreads();
+    floatx4 av[J];
+#pragma unroll
+    for (int j = 0; j < J; ++j) av[j] = reinterpret_cast<const floatx4*>(state)[(J * w + j) * 64 + lane];
+    for (int b0 = 0, par = 0; b0 < nblk; b0 += 2, par ^= 1) {
+      const int blk = b0 + grp, col = 16 * blk + r;
+      const bool col_ok = col < H, finishes = w < 4 && blk < nblk;
+      float addend = 0.f;
+      uint32_t keep = 0u;
+      if (finishes && row_ok) {
+        if (FWD) {
+          addend = load_or_zero(a.b + col, col_ok);
+          for (int q = 0; q < a.I; ++q)
+            addend = fmaf(a.xs[((size_t)row * a.T + (t - 1)) * a.I + q], load_or_zero(a.W_ih + (size_t)q * H + col, col_ok), addend);
+        } else {
+          keep = bits16[((size_t)(t - 1) * B + row) * (2 * a.bp) + blk];
+        }
+      }
+      floatx4 acc = {0.f, 0.f, 0.f, 0.f};
+      load_columns(col);
+#pragma unroll
+      for (int j = 0; j < J; ++j)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(av[j][e], wr[j][e], acc, 0, 0, 0);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) part[par][grp][w][e][lane] = acc[e];
+      __syncthreads();                       // (all waves hold av since the first of these: state may change)
+      if (!finishes) continue;
+      const float* const p = &part[par][grp][0][fe][lane];
+      float s0 = p[0], s1 = p[4 * 64];
+#pragma unroll
+      for (int q = 2; q < kWaves; q += 2) { s0 += p[q * 4 * 64]; s1 += p[(q + 1) * 4 * 64]; }
+      float v = s0 + s1;
+      if (FWD) { v += addend; v = v > 0.f ? v : 0.f; }
+      else if (!((keep >> r) & 1u)) v = 0.f;
+      if (!col_ok) v = 0.f;
+      state[blk * 256 + ((r >> 2) * 16 + 4 * kq + fe) * 4 + (r & 3)] = v;
+      if (row_ok && col_ok) {
+        if (t <= a.t_out) a.out[((size_t)(t - a.t_lo) * B + row) * H + col] = v;
+        if (i + 1 == a.n && a.carry) a.carry[(size_t)row * H + col] = v;
+      }
+      if (FWD) {
+        const uint64_t on = __ballot(v > 0.f);
+        if (r == 0 && row_ok) {
+          uint16_t* const word = bits16 + ((size_t)(t - 1) * B + row) * (2 * a.bp) + blk;
+          word[0] = (uint16_t)(on >> (16 * kq));
+          if (blk == nblk - 1 && (nblk & 1)) word[1] = 0;
+        }
+      }
+    }
   }
 }
 
@@ -281,6 +342,10 @@ template <int J, int NC> hipError_t start(bool forward, const RnnWideArgs& a, hi
   auto kern = two ? (forward ? rnn_wide_kernel<J, NC, 2, true> : rnn_wide_kernel<J, NC, 2, false>)
                   : (forward ? rnn_wide_kernel<J, NC, 1, true> : rnn_wide_kernel<J, NC, 1, false>);
   hipLaunchKernelGGL(kern, dim3(a.members * kGroups), dim3(64 * kWaves), 0, st, a);
+  const hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  auto redo = forward ? rnn_wide_redo_kernel<J, true> : rnn_wide_redo_kernel<J, false>;
+  hipLaunchKernelGGL(redo, dim3((a.B + 15) / 16), dim3(128 * kWaves), 0, st, a);
   return hipGetLastError();
 }
 
@@ -308,20 +373,16 @@ hipError_t launch_rnn_wide(bool forward, const RnnWideArgs& args, hipStream_t st
   RnnWideArgs a = args;
   if (!rnn_wide_ok(a.B, a.H, a.I, 32 * kGroups) || a.n < 1) return hipErrorInvalidValue;
   a.members = members_of(a.H);
-  hipError_t e = hipErrorInvalidValue;
   switch ((a.H + 127) / 128) {
-    case 2: e = start<2, 1>(forward, a, st); break;
-    case 3: e = start<3, 1>(forward, a, st); break;
-    case 4: e = start<4, 1>(forward, a, st); break;
-    case 5: e = start<5, 2>(forward, a, st); break;
-    case 6: e = start<6, 2>(forward, a, st); break;
-    case 7: e = start<7, 2>(forward, a, st); break;
-    case 8: e = start<8, 2>(forward, a, st); break;
+    case 2: return start<2, 1>(forward, a, st);
+    case 3: return start<3, 1>(forward, a, st);
+    case 4: return start<4, 1>(forward, a, st);
+    case 5: return start<5, 2>(forward, a, st);
+    case 6: return start<6, 2>(forward, a, st);
+    case 7: return start<7, 2>(forward, a, st);
+    case 8: return start<8, 2>(forward, a, st);
   }
-  if (e != hipSuccess) return e;
-  auto redo = forward ? rnn_wide_redo_kernel<true> : rnn_wide_redo_kernel<false>;
-  hipLaunchKernelGGL(redo, dim3(std::min(a.B, 32)), dim3(1024), 0, st, a);
-  return hipGetLastError();
+  return hipErrorInvalidValue;
 }
 
 }  // namespace rad

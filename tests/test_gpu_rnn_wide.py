@@ -58,6 +58,37 @@ def test_chunks_whose_launch_gave_up(ctx, hidden, batch, scheme):  # noqa: F811
     from paper_2007_10412_amd import binding as B
     B.rad_debug_poll_limit(ctx, 1)
     run_rnn(ctx, data(hidden, batch, 40, hidden, d_input=2), scheme, 0.2 if scheme else 1.0, seed=6)
+    redone, launches = B.rad_debug_redone_launches(ctx)
+    assert launches == 4 and 1 <= redone <= 4
+
+
+@pytest.mark.parametrize("hidden", [193, 250, 300, 511, 640, 690, 801, 1000, 1024])
+@pytest.mark.parametrize("batch", [5, 150])
+def test_the_stand_in_gives_the_same_bits(ctx, hidden, batch):  # noqa: F811
+    """Loss, gradients and store of a step do not depend on which launches were computed again: none, the first, those of
+    some examples only (whose groups are absent), all."""
+    from paper_2007_10412_amd import binding as B, synth
+    from tests.gpu_util import dev, host, empty
+    T, names = 35, ["W_ih", "W_hh", "b", "W_ho", "b_o"]
+    d = synth.rnn(seed=hidden, batch=batch, T=T, d_input=2, hidden=hidden, classes=10, identity=False)
+    print("rnn wide bits", hidden, batch, flush=True)
+    m = B.rad_model_create_rnn(ctx, batch, T, 2, hidden, 10, 1, 0.2)
+    try:
+        params, grads = [dev(d[n]) for n in names], [empty(d[n].shape) for n in names]
+        x, labels, runs = dev(d["x"]), dev(d["labels"]), []
+        for groups, launches, redone in ((0, 0, 0), (0xff, 1, 1), (0x0a, 4, 4), (0xff, 4, 4)):
+            for g in grads:
+                g.fill_(float("nan"))
+            B.rad_debug_absent_groups(ctx, groups, launches)
+            loss = B.rad_train_step(ctx, m, B.make_sampling(1, 0.2, 5, 20, 0), x, labels, params, grads)
+            assert B.rad_debug_redone_launches(ctx) == (redone, 4)
+            runs.append([np.float32(loss)] + [host(g).copy() for g in grads] +
+                        list(B.rad_store_export_csr(ctx, B.rad_model_store(m, 0), (T - 1) * batch)))
+        for run in runs[1:]:
+            assert all(np.array_equal(a, b) for a, b in zip(run, runs[0]))
+        assert all(np.isfinite(a).all() for a in runs[0])
+    finally:
+        B.rad_model_destroy(m)
 
 
 @pytest.mark.parametrize("T", [1, 2, 3, 33])
