@@ -216,7 +216,7 @@ hipError_t launch_rnn_backward(const RnnArgs& a, float* dW_hh, float* db, float*
 // (rnn_wide.hip).  Forward: h_t of steps t0 .. t0 + n - 1; backward: g_t of steps t0, t0 - 1, .. t0 - n + 1 (step t under the
 // ReLU bits of step t).  src: dense h or g of the step before the first (null: zeros); out: [steps t_lo .. t_out][B][H];
 // carry: the last step's output too, or null (not src: a launch that gave up is computed again from src).
-// xch, flags, tickets, abort_words and redone lie in a workspace of rnn_wide_sync_bytes that is zero before the first of
+// xch, flags, tickets, abort_words, redone and backoff lie in a workspace of rnn_wide_sync_bytes that is zero before the first of
 // `launches` launches (numbered by `launch`); seq0 grows by at least n from launch to launch and starts at 1 or more.
 // redone[launch] becomes 1 where the chunk was computed again.  absent, a test hook: the workgroups of these groups (bits)
 // return at once, as if none had run on their XCDs.
@@ -228,7 +228,7 @@ struct RnnWideArgs {
   const float* xs; const float* W_ih; const float* W_hh; const float* b;
   uint32_t* bits;                        // (h_t > 0) bits, [T][B][bp]: written forward, read backward
   const float* src; float* out; float* carry;
-  float* xch; uint32_t* flags; uint32_t* tickets; uint32_t* abort_words; uint32_t* redone;
+  float* xch; uint32_t* flags; uint32_t* tickets; uint32_t* abort_words; uint32_t* redone; uint32_t* backoff;
 };
 bool rnn_wide_ok(int64_t B, int64_t H, int64_t I, int compute_units);
 size_t rnn_wide_sync_bytes(int B, int H, int launches);

@@ -24,7 +24,12 @@
 // kernel on some CUs, another partition mode).  Every wait is bounded: a workgroup that waited too long gives up and sets the
 // launch's abort word.  A group that too few workgroups reached shows in its counter, also where nobody waits for it.
 // rnn_wide_redo_kernel follows every launch, looks at both and, unless all is there, computes the chunk again without any
-// exchange.
+// exchange.  It also counts the launches that failed in a row and has the next ones come to it at once.
+// Models of several contexts on streams of their own share the chip: a launch waits for the CUs that another one holds, and
+// where the workgroups of two arrive together and each holds a part of an XCD, the one with the lower bound gives up and the
+// other goes on (the bounds differ from context to context).  Steps of T = 200, ms for one of each context, a launch per step /
+// this: three contexts 128 x 1024 9.4 / 7.9 (one launch in 35 computed again), two 192 x 1000 30.2 / 8.0, two 160 x 600 6.0 / 4.0
+// (none).
 #include <algorithm>
 
 #include "gemm.hpp"
@@ -54,7 +59,12 @@ __global__ __launch_bounds__(64 * kWaves, R == 1 ? 4 : 2) void rnn_wide_kernel(R
   if (threadIdx.x == 0) {
     s_dead = 0;
     const bool counts = xcc < kGroups && !((a.absent >> xcc) & 1u);
+    const uint32_t resume = a.backoff[1];
     s_member = counts ? (int)atomicAdd(a.tickets + a.launch * kGroups + xcc, 1u) : 0x7fffffff;
+    if ((uint32_t)a.launch < resume) {                 // launches gave up just now: not yet again
+      s_member = 0x7fffffff;
+      __hip_atomic_store(abort_word, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
   }
   __syncthreads();
   const int member = __builtin_amdgcn_readfirstlane(s_member), nblk = (H + 15) / 16;
@@ -140,7 +150,7 @@ __global__ __launch_bounds__(64 * kWaves, R == 1 ? 4 : 2) void rnn_wide_kernel(R
         if (__all((int)(v - need) >= 0)) break;
         ++polls;
         if (polls >= a.poll_limit ||
-            (polls % 256u == 0 && __hip_atomic_load(abort_word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))) {
+            (polls % 64u == 0 && __hip_atomic_load(abort_word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))) {
           s_dead = 1;                        // seen by the whole workgroup at the barrier below
           if (lane == 0) __hip_atomic_store(abort_word, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
           break;
@@ -246,8 +256,18 @@ __device__ __forceinline__ floatx4 load4_or_zero(const float* p, int n) {
 // 16 x 700 44 / 46, 40 x 300 13 / 14.  (The next block's columns loaded a block ahead: 116 / 150 in the first case.)
 template <int J, bool FWD>
 __global__ __launch_bounds__(128 * kWaves) void rnn_wide_redo_kernel(RnnWideArgs a) {
-  if (!left_out(a)) return;
-  if (blockIdx.x == 0 && threadIdx.x == 0) a.redone[a.launch] = 1u;
+  const bool again = left_out(a);
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    // [0] launches in a row that gave up, [1] the next one that tries: a wait that runs out costs a quarter of a chunk here, so
+    // the first failure costs no launch, the next one, then three, seven and up to fifteen
+    const uint32_t fails = a.backoff[0];
+    if ((uint32_t)a.launch >= a.backoff[1]) {
+      if (again) { a.backoff[0] = fails + 1u; a.backoff[1] = (uint32_t)a.launch + (1u << min(fails, 4u)); }
+      else if (fails) a.backoff[0] = 0u;
+    }
+    if (again) a.redone[a.launch] = 1u;
+  }
+  if (!again) return;
   __shared__ __align__(16) float state[kWaves * J * 256];
   __shared__ float part[2][2][kWaves][4][64];
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
@@ -357,7 +377,7 @@ bool rnn_wide_ok(int64_t B, int64_t H, int64_t I, int compute_units) {
 
 size_t rnn_wide_sync_bytes(int B, int H, int launches) {
   const size_t J = (size_t)(H + 127) / 128, R = B > 16 * kGroups ? 2 : 1;
-  return ((size_t)2 * kGroups * kWaves * R * J * 256 + (size_t)kGroups * kFlagsPerGroup + (size_t)launches * (kGroups + 2)) * 4;
+  return ((size_t)2 * kGroups * kWaves * R * J * 256 + (size_t)kGroups * kFlagsPerGroup + (size_t)launches * (kGroups + 2) + 2) * 4;
 }
 
 void rnn_wide_sync_layout(RnnWideArgs* a, void* ws, int launches) {
@@ -367,6 +387,7 @@ void rnn_wide_sync_layout(RnnWideArgs* a, void* ws, int launches) {
   a->tickets = a->flags + (size_t)kGroups * kFlagsPerGroup;
   a->abort_words = a->tickets + (size_t)launches * kGroups;
   a->redone = a->abort_words + launches;
+  a->backoff = a->redone + launches;
 }
 
 hipError_t launch_rnn_wide(bool forward, const RnnWideArgs& args, hipStream_t st) {

@@ -106,6 +106,55 @@ def test_groups_that_no_workgroup_reached(ctx, T, groups):  # noqa: F811
     assert B.rad_debug_redone_launches(ctx) == (0, launches)
 
 
+@pytest.mark.parametrize("failing,redone", [(1, 1), (2, 3), (4, 7), (14, 14)])
+def test_failing_launches_are_not_repeated_at_once(ctx, failing, redone):  # noqa: F811
+    """14 launches, the first ones of which find no workgroups: after the second failure in a row one launch goes to the
+    stand-in without trying, then three, then seven."""
+    from paper_2007_10412_amd import binding as B
+    B.rad_debug_absent_groups(ctx, 0xff, failing)
+    run_rnn(ctx, data(3, 6, 200, 200), 1, 0.2, seed=7)
+    assert B.rad_debug_redone_launches(ctx) == (redone, 14)
+
+
+@pytest.mark.parametrize("contexts,batch,hidden", [(2, 160, 600), (3, 128, 1000), (3, 20, 300)])
+def test_models_of_several_contexts_at_once(contexts, batch, hidden):
+    """Each on a stream of its own, steps enqueued in turn: the launches of one wait for, or give way to, those of another, and
+    every step has the bits of a step taken alone."""
+    import torch
+    from paper_2007_10412_amd import binding as B, synth
+    from tests.gpu_util import dev, host, empty
+    T, names = 70, ["W_ih", "W_hh", "b", "W_ho", "b_o"]
+    d = synth.rnn(seed=1, batch=batch, T=T, d_input=1, hidden=hidden, classes=10, identity=False)
+    print("rnn wide contexts", contexts, batch, hidden, flush=True)
+    sides = []
+    try:
+        for _ in range(contexts):
+            stream = torch.cuda.Stream()
+            c = B.rad_ctx_create(stream)
+            sides.append((c, B.rad_model_create_rnn(c, batch, T, 1, hidden, 10, 1, 0.1), dev(d["x"]), dev(d["labels"]),
+                          [dev(d[n]) for n in names], [empty(d[n].shape) for n in names], stream))
+        torch.cuda.synchronize()
+
+        def step(side, seed):
+            B.rad_train_step(side[0], side[1], B.make_sampling(1, 0.1, seed, 20, 0), side[2], side[3], side[4], side[5],
+                             want_loss=False)
+        step(sides[0], 5)
+        torch.cuda.synchronize()
+        alone = [host(g).copy() for g in sides[0][5]]
+        for _ in range(3):
+            for seed in (1, 2, 5):
+                for side in sides:
+                    step(side, seed)
+            torch.cuda.synchronize()
+            print([B.rad_debug_redone_launches(side[0]) for side in sides], flush=True)
+            for side in sides:
+                assert all(np.array_equal(host(g), a) for g, a in zip(side[5], alone))
+    finally:
+        for side in sides:
+            B.rad_model_destroy(side[1])
+            B.rad_ctx_destroy(side[0])
+
+
 def test_repeated_steps_are_identical(ctx):  # noqa: F811
     from paper_2007_10412_amd import binding as B
     from tests.gpu_util import dev, host, empty
