@@ -22,7 +22,7 @@ struct rad_ctx {
   int device = 0;
   std::string err;
   int key_shift = 0;
-  int compute_units = 0;
+  int compute_units = 0;          // of the device, 0 where the stream is kept to a part of them (hipExtStreamCreateWithCUMask)
   uint32_t poll_limit = 0;        // test hook: bound of the waits of the next recurrent step's kernels, 0 = the library's own
   uint32_t absent = 0;            // test hook: groups that stay away from the first launches of the next recurrent step
   int absent_launches = 0;
@@ -154,6 +154,14 @@ extern "C" rad_status rad_ctx_create(rad_ctx** out, void* hip_stream) {
   if (hipGetDeviceProperties(&prop, c->device) != hipSuccess) { delete c; return RAD_ERR_DEVICE; }
   if (std::strncmp(prop.gcnArchName, "gfx950", 6) != 0) { delete c; return RAD_ERR_UNSUPPORTED; }
   c->compute_units = prop.multiProcessorCount;
+  uint32_t cu_mask[64] = {};
+  const uint32_t words = (uint32_t)std::min((c->compute_units + 31) / 32, 64);
+  if (hipExtStreamGetCUMask(c->stream, words, cu_mask) == hipSuccess) {
+    for (int u = 0; u < prop.multiProcessorCount && u < 64 * 32; ++u)
+      if (!((cu_mask[u / 32] >> (u % 32)) & 1u)) c->compute_units = 0;
+  } else {
+    (void)hipGetLastError();      // (not known: taken for the whole device)
+  }
   if (hipMalloc(reinterpret_cast<void**>(&c->loss_dev), sizeof(float)) != hipSuccess) { delete c; return RAD_ERR_DEVICE; }
   if (scratch_resolve(c->device) != hipSuccess) { (void)hipFree(c->loss_dev); delete c; return RAD_ERR_DEVICE; }
   *out = c;

@@ -155,6 +155,24 @@ def test_models_of_several_contexts_at_once(contexts, batch, hidden):
             B.rad_ctx_destroy(side[0])
 
 
+def test_stream_kept_to_a_part_of_the_chip():
+    """The workgroups of a chunk's launch could not all run on such a stream: its models take a launch per time step."""
+    import ctypes
+    import torch
+    from paper_2007_10412_amd import binding as B
+    torch.zeros(1, device="cuda")
+    hip = ctypes.CDLL("libamdhip64.so")
+    stream, mask = ctypes.c_void_p(), (ctypes.c_uint32 * 8)(*([0x0fffffff] * 8))
+    assert hip.hipExtStreamCreateWithCUMask(ctypes.byref(stream), 8, mask) == 0
+    c = B.rad_ctx_create(torch.cuda.ExternalStream(stream.value))
+    try:
+        run_rnn(c, data(2, 9, 40, 300), 1, 0.2, seed=6)
+        assert B.rad_debug_redone_launches(c) == (0, 0)
+    finally:
+        B.rad_ctx_destroy(c)
+        assert hip.hipStreamDestroy(stream) == 0
+
+
 def test_repeated_steps_are_identical(ctx):  # noqa: F811
     from paper_2007_10412_amd import binding as B
     from tests.gpu_util import dev, host, empty
