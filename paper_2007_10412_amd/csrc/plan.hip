@@ -887,6 +887,7 @@ hipError_t launch_plan(const PlanArgs* args, int n, hipStream_t st) {
   }
   if (wave_rows <= 4096)
     for (int i = 0; i < n; ++i) if (kind[i] >= kPlanWave1 && kind[i] <= kPlanWave4) kind[i] = widest;
+  constexpr int64_t kMaxBlocks = (((int64_t)1 << 32) - 1) / kPlanThreads;      // a grid has fewer than 2^32 threads
   bool done[kPlanBatch] = {};
   for (int i = 0; i < n; ++i) {
     if (done[i]) continue;
@@ -897,9 +898,11 @@ hipError_t launch_plan(const PlanArgs* args, int n, hipStream_t st) {
     int widest_cols = 0;
     for (int j = i; j < n; ++j) {
       if (done[j] || kind[j] != k) continue;
+      const int blocks = wave ? (args[j].plan_rows + 3) / 4 : args[j].plan_rows;
+      if (p.n > 0 && (int64_t)p.first[p.n] + blocks > kMaxBlocks) continue;       // (another launch draws for it)
       done[j] = true;
       p.a[p.n] = args[j];
-      p.first[p.n + 1] = p.first[p.n] + (wave ? (args[j].plan_rows + 3) / 4 : args[j].plan_rows);
+      p.first[p.n + 1] = p.first[p.n] + blocks;
       ++p.n;
       widest_cols = args[j].cols > widest_cols ? args[j].cols : widest_cols;
     }

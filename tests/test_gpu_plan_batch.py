@@ -36,3 +36,31 @@ def test_columns_of_every_layer(ctx, batch, dims, scheme, p):
             assert np.array_equal(rp, ref["stores"][l][0]) and np.array_equal(col, ref["stores"][l][1]), l
     finally:
         B.rad_model_destroy(m)
+
+
+@pytest.mark.parametrize("scheme", [1, 5])
+def test_rows_of_all_layers_beyond_one_grid(ctx, scheme):
+    """Four layers of 4.3 million rows, a workgroup of 256 threads each: together more threads than a grid may have.  The keep
+    sets are those of stores that draw on their own."""
+    import torch
+    from paper_2007_10412_amd import binding as B
+    from tests.gpu_util import empty
+    batch, dims, p = 4300000, (3, 4, 2, 3, 2), 0.5
+    print("plan batch beyond a grid", scheme, flush=True)
+    rng = torch.Generator(device="cuda").manual_seed(1)
+    r = lambda *shape: torch.randn(*shape, device="cuda", generator=rng)  # noqa: E731
+    params = [r(a, b) for a, b in zip(dims, dims[1:])]
+    grads, x = [empty(tuple(w.shape)) for w in params], r(batch, dims[0])
+    labels = torch.randint(0, dims[-1], (batch,), device="cuda", dtype=torch.int32, generator=rng)
+    m = B.rad_model_create_mlp(ctx, B.RAD_F32, batch, list(dims), False, scheme, p)
+    try:
+        B.rad_train_step(ctx, m, B.make_sampling(scheme, p, 11, 40, 0), x, labels, params, grads)
+        for l in range(len(dims) - 1):
+            rp, col, _ = B.rad_store_export_csr(ctx, B.rad_model_store(m, l), batch)
+            st = B.rad_store_create(ctx, B.make_layer(batch, dims[l], dims[l + 1]), scheme, p)
+            B.rad_sample_pack(ctx, B.make_sampling(scheme, p, 11, 40 + l, 0), torch.zeros(batch, dims[l], device="cuda"), st)
+            want = B.rad_store_export_csr(ctx, st, batch)
+            B.rad_store_destroy(st)
+            assert np.array_equal(rp, want[0]) and np.array_equal(col, want[1]), l
+    finally:
+        B.rad_model_destroy(m)
