@@ -1258,18 +1258,21 @@ static rad_status colsum_call(rad_ctx* c, const void* dy, int dtype, int rows, i
 // 256 x 4096 x 4096 181 / 126.  The pass costs 3 us a call, so narrow outputs, whose few slices mask fast, keep the
 // masking loaders (1000 x 1000 x 128 67.7 / 67.7, 200 x 500 x 64 43 / 46), and so do many rows of a narrow input, whose
 // gradient few tiles read (8192 x 300 x 300 88 / 90).
+// The products number the elements of an operand with 32 bits: where the padding of the rows would pass that, dy itself is read.
+static int64_t masked_pitch(const rad_layer* L) { return (L->d_out + 63) / 64 * 64; }
 static bool premask_pays(const rad_layer* L, const uint32_t* bits) {
-  return L->dtype == kBF16 && bits && L->d_out >= 256 && (L->d_in >= 512 || L->batch <= 1024);
+  return L->dtype == kBF16 && bits && L->d_out >= 256 && (L->d_in >= 512 || L->batch <= 1024) &&
+         L->batch * masked_pitch(L) < ((int64_t)1 << 32);
 }
 // dX of few columns over whole 256-row tiles: the direct-to-LDS kernel on masked rows is ahead at any width of dy
 static bool premask_pays_dx(const rad_layer* L, const uint32_t* bits) {
   return premask_pays(L, bits) || (L->dtype == kBF16 && bits && L->batch % 256 == 0 && L->d_in % 256 == 0 && L->d_out % 8 == 0 &&
-                                   (L->batch / 256) * (L->d_in / 256) >= 128);
+                                   (L->batch / 256) * (L->d_in / 256) >= 128 && L->batch * masked_pitch(L) < ((int64_t)1 << 32));
 }
 // g for them.  On the dW side the column sums of a wide layer's bias gradient read dy anyway and write g on the way.
 static rad_status masked_dy(rad_ctx* c, const rad_layer* L, const rad_store* s, const void* dy, float* dbias, int beta,
                             void** g, int64_t* g_ld) {
-  *g_ld = (L->d_out + 63) / 64 * 64;
+  *g_ld = masked_pitch(L);
   RAD_TRY(ws_get(c, WS_CONVG, (size_t)L->batch * *g_ld * 2, g));
   const int rows = (int)L->batch, N = (int)L->d_out;
   if (dbias && N >= 512 && *g_ld == N)

@@ -47,3 +47,43 @@ def test_masked_backward(ctx, batch, d_in, d_out, bias):
     assert_grad_close(f(dX), g @ f(W).T, 2e-2, d_out, "dX", acc_u=U_F32, out_u=2.0 ** -8)
     if bias:
         assert_grad_close(host(db), g.sum(0), 1e-4, batch, "db", acc_u=U_F32)
+
+
+def test_padded_rows_beyond_32_bit_element_numbers(ctx):
+    """8.2 million rows of 513 columns are 4.2 billion elements; padded to 576 columns they would be more than the products'
+    32-bit element numbers reach.  dW and dX of rows near both ends and around the number that wraps."""
+    import torch
+    from paper_2007_10412_amd import binding as B
+    batch, d_in, d_out, p = 8200000, 512, 513, 0.02
+    print("mask rows beyond 2^32", flush=True)
+    rng = torch.Generator(device="cuda").manual_seed(3)
+    bf = torch.bfloat16
+    # few rows hold anything, so that dW can be formed from them: the ends, and both sides of 2^32 elements of padded rows
+    rows = sorted({0, 1, 4095, 4096, 700000, 2 ** 32 // 576 - 1, 2 ** 32 // 576, 2 ** 32 // 576 + 1, 2 ** 32 // 576 + 4096, batch - 2, batch - 1})
+    at = torch.tensor(rows, device="cuda")
+    r = lambda *shape: torch.randn(*shape, device="cuda", generator=rng).to(bf)  # noqa: E731
+    x, dy = torch.zeros(batch, d_in, device="cuda", dtype=bf), torch.zeros(batch, d_out, device="cuda", dtype=bf)
+    x[at], dy[at] = r(len(rows), d_in), r(len(rows), d_out)
+    W = r(d_in, d_out)
+    y, dX = torch.empty_like(dy), torch.empty_like(x)
+    dW = torch.empty(d_in, d_out, device="cuda")
+    layer = B.make_layer(batch, d_in, d_out, dtype=B.RAD_BF16, relu=True)
+    store = B.rad_store_create(ctx, layer, B.RAD_FIXEDK_PER_EXAMPLE, p)
+    try:
+        B.rad_forward_sample(ctx, layer, B.make_sampling(B.RAD_FIXEDK_PER_EXAMPLE, p, 1, 0, 0), x, W, None, y, store)
+        B.rad_backward_dW(ctx, layer, store, dy, dW, None)
+        B.rad_backward_dX(ctx, layer, store, dy, W, dX)
+        rp, col, val = B.rad_store_export_csr(ctx, store, batch)
+    finally:
+        B.rad_store_destroy(store)
+    f = lambda t: t.double().cpu().numpy()  # noqa: E731
+    g = f(dy[at]) * (f(y[at]) > 0)
+    xs = np.zeros((len(rows), d_in))
+    for i, b in enumerate(rows):
+        xs[i, col[rp[b]:rp[b + 1]]] = val[rp[b]:rp[b + 1]]
+    want_X, want_W = g @ f(W).T, xs.T @ g
+    # fp32 sums of at most 11 and 513 products; dX in bf16
+    assert np.abs(f(dW) - want_W).max() <= 1e-5 * np.abs(want_W).max()
+    assert np.abs(f(dX[at]) - want_X).max() <= 2.0 ** -8 * np.abs(want_X).max()
+    dX[at] = 0
+    assert not dX.any().item()
