@@ -1006,7 +1006,8 @@ extern "C" rad_status rad_store_set_index_free(rad_ctx* c, rad_store* s, int32_t
 static int sparse_prefetch_for(const rad_store* s, int lanes_per_row) {
   const double pi = s->scheme == RAD_BERNOULLI ? s->p : (double)s->k / (double)s->cols;
   const double mean = pi * (s->cols < kBucket ? s->cols : kBucket);
-  return (int)std::ceil((mean + 6.0 * std::sqrt(mean)) / lanes_per_row);   // overflow beyond this is rare and handled apart
+  // (what a segment has beyond this is rare: bf16 add_long_segments, after the epilogue; fp32 a loop where entries are committed)
+  return (int)std::ceil((mean + 6.0 * std::sqrt(mean)) / lanes_per_row);
 }
 
 // fraction of a row's columns that a sampled store holds (expected, for Bernoulli draws)
@@ -1333,8 +1334,7 @@ extern "C" rad_status rad_backward_dW(rad_ctx* c, const rad_layer* L, const rad_
     return conv_dW_call(c, s, (int)L->batch, L->c_in, L->c_out, L->h, L->w, L->kh, g, dW, dbias);
   }
   const int N = (int)L->d_out;
-  const bool narrow = s->per_entry() && dw_narrow_pays(s->dtype, s->rows, s->cols, N, sparse_prefetch_for(s, 8), s->bits != nullptr, kept_fraction(s));
-  if (!narrow && premask_pays(L, s->bits)) {          // (the kernel for narrow layers masks a row once)
+  if (premask_pays(L, s->bits)) {          // (never where dw_narrow_pays: for bf16 that asks for 12 outputs or fewer)
     void* g = nullptr;
     int64_t g_ld = 0;
     RAD_TRY(masked_dy(c, L, s, dy, dbias, beta != 0.f, &g, &g_ld));
