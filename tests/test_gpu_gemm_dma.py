@@ -122,7 +122,7 @@ def test_narrow_layer_with_long_contractions(ctx, scheme, p, relu):
 @pytest.mark.parametrize("N", [256, 1000])
 def test_dW_with_segments_longer_than_the_register_budget(ctx, N):
     """The bf16 dW kernel keeps a fixed number of entries per (store row, 256-column bucket) in registers and
-    leaves longer segments to a second kernel.  One-bit keys (test hook) make every row keep the lowest columns
+    adds what longer segments have beyond them after its epilogue.  One-bit keys (test hook) make every row keep the lowest columns
     whose key is 0, about half of the first bucket, far more than the kernel holds.  dW is compared with the
     product formed from the store the GPU itself exports, so the check does not depend on the draw."""
     from paper_2007_10412_amd import binding as B

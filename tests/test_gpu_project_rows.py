@@ -99,6 +99,19 @@ def test_layer_bf16(ctx, Bt, D, N, p):
     _layer(ctx, Bt, D, N, p, 1, seed=12)
 
 
+@pytest.mark.parametrize("Bt,D,N,p", [(130, 520, 263, 0.25), (70, 700, 1001, 0.1)])
+def test_layer_bf16_masked_rows_padded(ctx, Bt, D, N, p):
+    """Output widths whose masked gradient has rows longer than the layer's: its pitch reaches the projection's products."""
+    from paper_2007_10412_amd import binding as B
+    B.rad_ctx_timing(ctx, "mask_rows")
+    B.rad_ctx_timing_reset(ctx)
+    try:
+        _layer(ctx, Bt, D, N, p, 1, seed=12)
+        assert B.rad_ctx_timing_read(ctx, "mask_rows")[0] == 2
+    finally:
+        B.rad_ctx_timing(ctx, "")
+
+
 @pytest.mark.parametrize("dtype,dims,Bt", [(0, (784, 300, 300, 10), 150), (1, (1024, 768, 512, 1000), 256)])
 def test_mlp_train_step(ctx, dtype, dims, Bt):
     from paper_2007_10412_amd import binding as B, synth

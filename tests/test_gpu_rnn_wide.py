@@ -47,6 +47,20 @@ def test_lengths(ctx, T, scheme, p):  # noqa: F811
     run_rnn(ctx, data(T, 6, T, 210, d_input=3, classes=5), scheme, p, seed=T, check_store=T > 1)
 
 
+@pytest.mark.parametrize("scheme,p", [(0, 1.0), (1, 0.1)])
+@pytest.mark.parametrize("batch,hidden,T", [(100, 900, 34), (100, 1001, 34), (150, 770, 35)])
+def test_split_rows_of_a_chunk(ctx, batch, hidden, T, scheme, p):  # noqa: F811
+    """dW_hh of a chunk with its rows split (2048 rows and more at 1024 units), at widths that end inside a tile."""
+    from paper_2007_10412_amd import binding as B
+    B.rad_ctx_timing(ctx, "gemm_f32_dw_splitk_128")
+    B.rad_ctx_timing_reset(ctx)
+    try:
+        run_rnn(ctx, data(batch, batch, T, hidden), scheme, p, seed=8)
+        assert B.rad_ctx_timing_read(ctx, "gemm_f32_dw_splitk_128")[0] >= 1
+    finally:
+        B.rad_ctx_timing(ctx, "")
+
+
 def test_wider_than_the_chip_holds(ctx):  # noqa: F811
     run_rnn(ctx, data(9, 6, 4, 1100), 1, 0.2, seed=5)
 
