@@ -132,7 +132,13 @@ typedef struct {
 int64_t rad_fixed_k(double p, int64_t d);
 
 /* Creates a context bound to hip_stream (a hipStream_t, borrowed; null = the
- * default stream) on the current device.  Allocates workspaces lazily. */
+ * default stream) on the current device.  Allocates workspaces lazily.  A
+ * workspace grows when a call needs a larger one, which frees the old one: a
+ * HIP graph recorded from calls of a context refers to the workspaces of that
+ * time, so make the context's largest calls before recording.  Calls that only
+ * gain by a workspace (the masked gradient of bf16 layers with ReLU, the split
+ * rows of dW from the store) do without one that cannot be had: while the
+ * stream is being captured, or where the device's memory is used up. */
 rad_status rad_ctx_create(rad_ctx** out, void* hip_stream);
 rad_status rad_ctx_destroy(rad_ctx* ctx);
 /* Text of the last failure on this context (static string if ctx is null). */

@@ -108,6 +108,21 @@ static rad_status ws_get(rad_ctx* c, int which, size_t bytes, void** out) {
   return RAD_OK;
 }
 
+// Whether a workspace holds `bytes`, grown where that is possible: not while the stream is being captured, not beyond the
+// device's memory.  For paths that can do without it.
+static bool ws_ready(rad_ctx* c, int which, size_t bytes) {
+  if (bytes <= c->ws_bytes[c->on_side][which]) return true;
+  hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+  const std::string err = c->err;
+  void* ws = nullptr;
+  if (hipStreamIsCapturing(c->stream, &capture) == hipSuccess && capture == hipStreamCaptureStatusNone &&
+      ws_get(c, which, bytes, &ws) == RAD_OK)
+    return true;
+  (void)hipGetLastError();
+  c->err = err;
+  return false;
+}
+
 static void swap_streams(rad_ctx* c) {
   std::swap(c->stream, c->side);
   c->on_side ^= 1;
@@ -1122,8 +1137,9 @@ static rad_status dW_gemm(rad_ctx* c, const rad_store* s, int slot, const void* 
     g.A = dense; g.lda = s->cols;
     return dw_dense_f32(c, g, alg);
   }
-  if (n_slots == 1 && n_out == N && dw_narrow_pays(s->dtype, s->rows, s->cols, N, g.sparse_prefetch, bits != nullptr, kept_fraction(s))) {
-    const int splits = dw_narrow_splits(s->rows, s->cols, N);
+  const int splits = dw_narrow_splits(s->rows, s->cols, N);
+  if (n_slots == 1 && n_out == N && dw_narrow_pays(s->dtype, s->rows, s->cols, N, g.sparse_prefetch, bits != nullptr, kept_fraction(s)) &&
+      (splits <= 1 || ws_ready(c, WS_SPLITK, (size_t)splits * s->cols * N * 4))) {
     float* out = dW;
     if (splits > 1) {
       void* part = nullptr;
@@ -1258,9 +1274,11 @@ static rad_status colsum_call(rad_ctx* c, const void* dy, int dtype, int rows, i
 // 1000 x 768 x 3072 138 / 106, 512 x 1024 x 1024 72 / 62, 2000 x 1000 x 1000 119 / 104, 4096 x 512 x 1024 175 / 123,
 // 256 x 4096 x 4096 181 / 126.  The pass costs 3 us a call, so narrow outputs, whose few slices mask fast, keep the
 // masking loaders (1000 x 1000 x 128 67.7 / 67.7, 200 x 500 x 64 43 / 46), and so do many rows of a narrow input, whose
-// gradient few tiles read (8192 x 300 x 300 88 / 90).
+// gradient few tiles read (8192 x 300 x 300 88 / 90).  So do calls that cannot have the workspace (ws_ready): it is not what
+// the products need.
 // The products number the elements of an operand with 32 bits: where the padding of the rows would pass that, dy itself is read.
 static int64_t masked_pitch(const rad_layer* L) { return (L->d_out + 63) / 64 * 64; }
+static size_t masked_bytes(const rad_layer* L) { return (size_t)(L->batch * masked_pitch(L)) * 2; }
 static bool premask_pays(const rad_layer* L, const uint32_t* bits) {
   return L->dtype == kBF16 && bits && L->d_out >= 256 && (L->d_in >= 512 || L->batch <= 1024) &&
          L->batch * masked_pitch(L) < ((int64_t)1 << 32);
@@ -1274,7 +1292,7 @@ static bool premask_pays_dx(const rad_layer* L, const uint32_t* bits) {
 static rad_status masked_dy(rad_ctx* c, const rad_layer* L, const rad_store* s, const void* dy, float* dbias, int beta,
                             void** g, int64_t* g_ld) {
   *g_ld = masked_pitch(L);
-  RAD_TRY(ws_get(c, WS_CONVG, (size_t)L->batch * *g_ld * 2, g));
+  RAD_TRY(ws_get(c, WS_CONVG, masked_bytes(L), g));
   const int rows = (int)L->batch, N = (int)L->d_out;
   if (dbias && N >= 512 && *g_ld == N)
     return colsum_call(c, dy, L->dtype, rows, N, s->bits, s->bits_pitch, nullptr, 0, 0, dbias, nullptr, beta, 0, 0, 0, *g);
@@ -1334,7 +1352,8 @@ extern "C" rad_status rad_backward_dW(rad_ctx* c, const rad_layer* L, const rad_
     return conv_dW_call(c, s, (int)L->batch, L->c_in, L->c_out, L->h, L->w, L->kh, g, dW, dbias);
   }
   const int N = (int)L->d_out;
-  if (premask_pays(L, s->bits)) {          // (never where dw_narrow_pays: for bf16 that asks for 12 outputs or fewer)
+  // (never where dw_narrow_pays: for bf16 that asks for 12 outputs or fewer)
+  if (premask_pays(L, s->bits) && ws_ready(c, WS_CONVG, masked_bytes(L))) {
     void* g = nullptr;
     int64_t g_ld = 0;
     RAD_TRY(masked_dy(c, L, s, dy, dbias, beta != 0.f, &g, &g_ld));
@@ -1360,7 +1379,7 @@ extern "C" rad_status rad_backward_dX(rad_ctx* c, const rad_layer* L, const rad_
     return conv_dX_call(c, (int)L->batch, L->c_in, L->c_out, L->h, L->w, L->kh, g, static_cast<const float*>(W),
                         static_cast<float*>(dX));
   }
-  if (premask_pays_dx(L, s->bits)) {
+  if (premask_pays_dx(L, s->bits) && ws_ready(c, WS_CONVG, masked_bytes(L))) {
     void* g = nullptr;
     int64_t g_ld = 0;
     RAD_TRY(masked_dy(c, L, s, dy, nullptr, 0, &g, &g_ld));
