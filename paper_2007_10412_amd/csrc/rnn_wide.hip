@@ -15,8 +15,8 @@
 // A step takes 3.6 us forward and 4.1 backward at batch 128, hidden 1024 (1.7 us of matrix instructions, then the
 // latencies of the flags, of the fragments from L2 and of the sum through LDS).  A training step with fraction 0.1, a launch per
 // step / this, us: batch 128, hidden 1024, T = 784 14757 / 9329; T = 200: batch 192, hidden 1000 14777 / 4024, 192 x 640
-// 3932 / 2545, 16 x 700 4153 / 1507; batch 40, hidden 300, T = 300 4806 / 1574.  A batch above 192, or a hidden state that
-// does not fit 32 columns a CU, keeps a launch per step.
+// 3932 / 2545, 16 x 700 4153 / 1507; batch 40, hidden 300, T = 300 4806 / 1574.  A hidden state that does not fit 32 columns
+// a CU keeps a launch per step, and so does a batch above 192 (rnn_wide_ok; the kernels for two row tiles hold up to 256).
 //
 // The workgroups find their XCD in the hardware register and take a place in it from a counter; the loads of flags and
 // exchanged values pass by the L1 (agent scope, sc1), which is all the coherence that sharers of one L2 need.
@@ -371,6 +371,9 @@ template <int J, int NC> hipError_t start(bool forward, const RnnWideArgs& a, hi
 
 }  // namespace
 
+// The batch: two row tiles a group are 256 examples, but those above 192 are still on the launch per step, though it is the slower
+// one: T = 100, fraction 0.1, us, a launch per step / these kernels, 193 x 1000 7428 / 2032, 256 x 1000 7654 / 2221, 256 x 1024
+// 3472 / 2146, 193 x 600 2334 / 1327, 256 x 600 4364 / 1435, 256 x 300 2174 / 893, 224 x 200 2015 / 1346.
 bool rnn_wide_ok(int64_t B, int64_t H, int64_t I, int compute_units) {
   return H > rnn_fused_max_hidden() && H <= 1024 && B <= 24 * kGroups && I <= kRnnWideMaxIn && compute_units == 32 * kGroups;
 }
