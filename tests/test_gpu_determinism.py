@@ -63,8 +63,8 @@ def test_mlp_f32_two_runs_identical(ctx, scheme, p):
 @pytest.mark.parametrize("scheme,p", [(1, 0.1), (2, 0.25), (3, 0.25)])
 @pytest.mark.parametrize("hidden", [128, 200])
 def test_rnn_two_runs_identical(ctx, scheme, p, hidden):
-    """Hidden 200: the recurrent gradients are accumulated chunk by chunk on a second stream, in stream order.  Hidden
-    128: a partial array per workgroup, added in a fixed order."""
+    """Hidden 200: the recurrent gradients are accumulated chunk by chunk (test_gpu_rnn_steps.py has the route with a second
+    stream).  Hidden 128: a partial array per workgroup, added in a fixed order."""
     from paper_2007_10412_amd import binding as B, synth
     from tests.gpu_util import dev, host, empty
     d = synth.rnn(seed=2, batch=32, T=21, d_input=1, hidden=hidden, classes=10, identity=True)

@@ -159,7 +159,7 @@ def test_paper_convnet_keeps_the_bytes_the_paper_counts(ctx):
 @pytest.mark.parametrize("scheme", [1, 3, 5])
 @pytest.mark.parametrize("T", [2, 3, 21])
 def test_wide_rnn_equals_indexed_model(ctx, scheme, T):
-    """Hidden above 192: x~ of a chunk of time steps is rebuilt on the side stream, from the keep bitmap of the step's own
+    """Hidden above 192: x~ of a chunk of time steps is rebuilt after the chunk's launch, from the keep bitmap of the step's own
     plan, or (T = 2, a store of one step) by drawing again.  Stores and loss are the same bits; the gradients sum the same
     products in the order of another kernel."""
     from paper_2007_10412_amd import synth

@@ -95,17 +95,16 @@ def test_paper_rnn_widths(ctx, scheme):
 @pytest.mark.parametrize("hidden", [64, 200])
 def test_rnn_lengths_around_the_chunks_of_the_recurrent_dW(ctx, T, scheme, p, hidden):
     """With a hidden state above 192 the recurrent dW, the bias gradient and the input-weight gradient are formed over
-    chunks of eight time steps (T - 1 = 0: none; 1: a single short chunk; 9: one whole chunk and one step; 16: two whole
-    chunks); the shared scheme keeps the step-by-step form.  Narrower states take one launch per direction.  Every
-    gradient against the oracle."""
+    chunks of time steps, 32 of them here (eight with a launch per time step, see test_gpu_rnn_steps.py); the shared scheme
+    forms dW step by step.  Narrower states take one launch per direction.  Every gradient against the oracle."""
     from paper_2007_10412_amd import synth
     d = synth.rnn(seed=20 + T, batch=8, T=T, d_input=2, hidden=hidden, classes=5, identity=False)
     run_rnn(ctx, d, scheme, p, seed=T, check_store=T > 1)
 
 
 def test_rnn_hidden_width_whose_split_ranges_need_rounding(ctx):
-    """Hidden width 576 with whole 64 x 64 tiles: the per-step forward and dX GEMMs take the unguarded split-K
-    kernels, whose K ranges must be whole 32-deep slices (576 / 4 = 144 is not)."""
+    """Hidden width 576 with whole 64 x 64 tiles.  With a launch per time step (test_gpu_rnn_steps.py) the forward and dX
+    GEMMs split K into ranges that must be whole 32-deep slices (576 / 4 = 144 is not)."""
     from paper_2007_10412_amd import synth
     d = synth.rnn(seed=6, batch=64, T=6, d_input=1, hidden=576, classes=10, identity=False)
     run_rnn(ctx, d, 1, 0.2, seed=3)

@@ -1,4 +1,4 @@
-"""The recurrent model with a hidden state wider than one launch per direction takes (above 192): per-chunk gradients on
+"""The recurrent model with a launch per time step (hidden states above 192 with batches above 192): per-chunk gradients on
 the side stream while the main stream goes on with the chain of dX products."""
 import numpy as np
 import pytest
