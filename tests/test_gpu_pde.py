@@ -1,6 +1,6 @@
 """GPU parity of the reaction-diffusion study (Section 5, Appendix B) against the oracle: loss, the sampled
 gradient estimate for the same keys, and the number of kept entries, over grids, step counts on both sides of the
-kernels' 1024-step tables, fractions, and several problems per launch.  Both sides compute in fp64; they differ
+kernels' 64-step tables, fractions, and several problems per launch.  Both sides compute in fp64; they differ
 in the order of sums (stencil neighbours, the reduction over nodes), so values agree to about 1e-12 relative and
 the tests ask for 1e-9."""
 import numpy as np
@@ -46,6 +46,19 @@ def test_matches_the_oracle(ctx, n, steps, p):
         assert stored[q] == s_ref, (q, stored[q], s_ref)
         assert abs(loss[q] - l_ref) <= 1e-9 * abs(l_ref), (q, loss[q], l_ref)
         assert np.abs(grad[q] - g_ref).max() <= 1e-9 * np.abs(g_ref).max(), (q, grad[q], g_ref)
+
+
+@pytest.mark.parametrize("n", [2, 3, 4, 17, 18, 24, 32])     # 1, 4, 9, 256 (one stencil wave), 289, 529, 961 cells
+@pytest.mark.parametrize("steps", [1, 2, 3, 63, 64, 65, 130])                          # around the table's halves
+def test_cells_and_steps_at_the_edges(ctx, n, steps):
+    thetas = np.random.default_rng(n * 1000 + steps).uniform(-1, 1, (2, 7))
+    for p in (0.4, 1.0):
+        loss, grad, stored = run(ctx, n, steps, p, thetas, seed=3, stream=9)
+        for q in range(2):
+            l_ref, g_ref, s_ref = R.pde_rad_gradient(thetas[q], n, steps, p, 3, stream_id=9 + q)
+            assert stored[q] == s_ref
+            assert abs(loss[q] - l_ref) <= 1e-9 * abs(l_ref) + 1e-28       # n = 2: the target is phi_0 to rounding
+            assert np.abs(grad[q] - g_ref).max() <= 1e-9 * np.abs(g_ref).max() + 1e-28
 
 
 def test_paper_grid_full_length(ctx):
