@@ -1541,8 +1541,15 @@ extern "C" rad_status rad_path_sample_gradient(rad_ctx* c, const rad_graph* g, i
 // ------------------------------------------------------------------ models
 enum ModelKind { kMlp = 0, kRnn = 1, kCnn = 2 };
 constexpr int kRnnChunk = 8;            // time steps whose recurrent dW is one contraction over steps x batch
-constexpr int kRnnWideChunk = 32;       // the same where a launch takes a chunk of time steps (rnn_wide.hip): a launch costs about
-                                        // five steps' time, and the dense h or g of a chunk is kept (batch x hidden numbers a step)
+// The same where a launch takes a chunk of time steps (rnn_wide.hip).  A launch costs about five steps' time (W_hh into the
+// registers) and every chunk the small kernels behind it, so chunks are long; but the dense h or g of a chunk is kept (batch x
+// hidden numbers a step, and once more as x~ for dW_hh), which should stay a small part of what all steps' would take: an
+// eighth of the steps, at least 32 and at most 128.  Training step, us, chunks of 32 / 64 / 128 steps, and by this rule: 128 x
+// 1024, T = 784 9234 / 8456 / 8032, 8068; 16 x 700, T = 700 5109 / 4409 / 4200, 4276; 40 x 300, T = 300 1577 / 1408 / 1341, 1506.
+constexpr int kRnnWideChunkMin = 32, kRnnWideChunkMax = 128;
+static int rnn_wide_chunk(int64_t T) {
+  return (int)std::min<int64_t>(T, std::max<int64_t>(kRnnWideChunkMin, std::min<int64_t>(kRnnWideChunkMax, (T + 7) / 8)));
+}
 
 struct rad_model {
   int kind = kMlp;
@@ -1560,7 +1567,8 @@ struct rad_model {
   int64_t T = 0, d_input = 0, hidden = 0, classes = 0;
   uint32_t* rnn_bits = nullptr;         // [T][batch][hidden/32]
   bool rnn_wide = false;                // a chunk of time steps per launch
-  float* rnn_g = nullptr;               // wide: [kRnnWideChunk][batch][hidden], dense h or g of the chunk at hand; else
+  int rnn_chunk = 0;                    // wide: time steps of a chunk (the last one may be shorter)
+  float* rnn_g = nullptr;               // wide: [rnn_chunk][batch][hidden], dense h or g of the chunk at hand; else
                                         // [2][kRnnChunk][batch][hidden]: g of the time steps whose dW is formed together,
                                         // two chunks: one being read by the side stream, one being filled (none
                                         // where all time steps are one launch per direction)
@@ -1815,8 +1823,9 @@ extern "C" rad_status rad_model_create_rnn(rad_ctx* c, int64_t batch, int64_t T,
   ok = ok && hipMalloc(&m->logits, (size_t)batch * classes * 4) == hipSuccess;
   ok = ok && hipMalloc((void**)&m->rnn_bits, (size_t)T * batch * ((hidden + 31) / 32) * 4) == hipSuccess;
   m->rnn_wide = rnn_wide_ok(batch, hidden, d_input, c->compute_units) && !m->stores[0]->project() && !m->stores[1]->project();
+  m->rnn_chunk = rnn_wide_chunk(T);
   if (!rnn_one_launch(m))
-    ok = ok && hipMalloc((void**)&m->rnn_g, (m->rnn_wide ? (size_t)std::min<int64_t>(T, kRnnWideChunk) : (size_t)2 * kRnnChunk) * hb) == hipSuccess;
+    ok = ok && hipMalloc((void**)&m->rnn_g, (m->rnn_wide ? (size_t)m->rnn_chunk : (size_t)2 * kRnnChunk) * hb) == hipSuccess;
   const size_t bmw = m->stores[0]->bitmap_words() + m->stores[1]->bitmap_words();
   if (bmw) ok = ok && hipMalloc((void**)&m->bitmap_ws, bmw * 4) == hipSuccess;
   if (!ok) { rad_model_destroy(m); return fail(c, RAD_ERR_DEVICE, "model allocation failed"); }
@@ -1880,12 +1889,13 @@ static rad_status rnn_wide_begin(rad_ctx* c, const rad_model* m, const float* xs
   std::memset(a, 0, sizeof(*a));
   a->B = (int)m->batch; a->T = (int)m->T; a->H = (int)m->hidden; a->I = (int)m->d_input; a->bp = (a->H + 31) / 32;
   a->xs = xs; a->W_ih = W_ih; a->W_hh = W_hh; a->b = b; a->bits = m->rnn_bits;
-  // A look takes 0.3 us or more: 0.6 ms, several times what the other kernels of a training step hold a CU, and a quarter of what
-  // the stand-in takes for a chunk.  The part that depends on the context decides which of two launches gives way.
+  // A look takes 0.3 us or more: 0.6 ms for chunks of 32 steps, several times what the other kernels of a training step hold a
+  // CU and what another context's chunk takes, and a quarter of what the stand-in takes for a chunk; longer chunks wait longer.
+  // The part that depends on the context decides which of two launches gives way.
   const uint32_t own = (uint32_t)(reinterpret_cast<uintptr_t>(c) >> 4) * 0x9E3779B1u >> 29;
-  a->poll_limit = c->poll_limit ? c->poll_limit : 2048u + 256u * own;
+  a->poll_limit = c->poll_limit ? c->poll_limit : (2048u + 256u * own) * (uint32_t)std::max(32, m->rnn_chunk) / 32u;
   c->poll_limit = 0;
-  const int launches = 2 * ((a->T + kRnnWideChunk - 1) / kRnnWideChunk);
+  const int launches = 2 * ((a->T + m->rnn_chunk - 1) / m->rnn_chunk);
   const size_t bytes = rnn_wide_sync_bytes(a->B, a->H, launches);
   void* ws = nullptr;
   RAD_TRY(ws_get(c, WS_RNNSYNC, bytes, &ws));
@@ -1898,31 +1908,31 @@ static rad_status rnn_wide_begin(rad_ctx* c, const rad_model* m, const float* xs
   return RAD_OK;
 }
 
-static rad_status rnn_wide_launch(rad_ctx* c, bool forward, RnnWideArgs* a) {
-  a->seq0 = 1u + (uint32_t)a->launch * kRnnWideChunk;
+static rad_status rnn_wide_launch(rad_ctx* c, const rad_model* m, bool forward, RnnWideArgs* a) {
+  a->seq0 = 1u + (uint32_t)a->launch * (uint32_t)m->rnn_chunk;
   a->absent = a->launch < c->absent_launches ? c->absent : 0u;
   HIP_TRY(c, timed(c, forward ? "rnn_wide_fwd" : "rnn_wide_bwd", [&](const char**) { return launch_rnn_wide(forward, *a, c->stream); }));
   c->redone_launches = ++a->launch;
   return RAD_OK;
 }
 
-// forward, kRnnWideChunk time steps per launch; their dense outputs are in the chunk buffer (exact store: in the store)
+// forward, a chunk of time steps per launch; their dense outputs are in the chunk buffer (exact store: in the store)
 // until the chunk is packed.  The last h of a chunk is carried to the next launch in act[], ending in h_T's place.
 static rad_status rnn_wide_forward(rad_ctx* c, rad_model* m, RnnWideArgs* a) {
-  const int B = a->B, H = a->H, T = a->T, chunks = (T + kRnnWideChunk - 1) / kRnnWideChunk;
+  const int B = a->B, H = a->H, T = a->T, chunk = m->rnn_chunk, chunks = (T + chunk - 1) / chunk;
   rad_store *s_hh = m->stores[0], *s_ho = m->stores[1];
   const float* src = nullptr;
   a->t_out = T - 1;                                       // (h_T has no slot in the recurrent store)
   for (int q = 0; q < chunks; ++q) {
-    a->t0 = a->t_lo = 1 + q * kRnnWideChunk;
-    a->n = std::min(T, a->t0 + kRnnWideChunk - 1) - a->t0 + 1;
+    a->t0 = a->t_lo = 1 + q * chunk;
+    a->n = std::min(T, a->t0 + chunk - 1) - a->t0 + 1;
     a->src = src;
     a->out = s_hh->scheme == RAD_EXACT ? static_cast<float*>(s_hh->values) + (size_t)(a->t0 - 1) * B * H : m->rnn_g;
     a->carry = static_cast<float*>(q == chunks - 1 && s_ho->scheme == RAD_EXACT ? s_ho->values : m->act[(T + chunks - 1 - q) & 1]);
-    RAD_TRY(rnn_wide_launch(c, true, a));
+    RAD_TRY(rnn_wide_launch(c, m, true, a));
     src = a->carry;
     if (s_hh->scheme == RAD_EXACT) continue;
-    const int per = rnn_rows_planned(s_hh) ? kRnnWideChunk : 1;      // step slots per pack launch
+    const int per = rnn_rows_planned(s_hh) ? chunk : 1;      // step slots per pack launch
     for (int t = a->t0; t < std::min(T, a->t0 + a->n); t += per) {
       StoreView v = store_view(s_hh, t - 1);
       v.rows = B * std::min(per, std::min(T, a->t0 + a->n) - t);
@@ -1938,14 +1948,14 @@ static rad_status rnn_wide_forward(rad_ctx* c, rad_model* m, RnnWideArgs* a) {
 // streams had hardware queues of their own and lost 1 % where they had not: both want the matrix units.)
 static rad_status rnn_wide_backward(rad_ctx* c, rad_model* m, RnnWideArgs* a, const float* dz, const float* W_ho, float* dW_hh,
                                     float* db, float* dW_ih) {
-  const int B = a->B, H = a->H, T = a->T, I = a->I, C = (int)m->classes;
+  const int B = a->B, H = a->H, T = a->T, I = a->I, C = (int)m->classes, chunk = m->rnn_chunk;
   rad_store* s_hh = m->stores[0];
   const size_t block = (size_t)B * H;
   const bool together = s_hh->scheme == RAD_EXACT || rnn_rows_planned(s_hh);
   a->out = m->rnn_g; a->t_out = T;
   bool first = true;
-  for (int t_hi = T, q = 0; t_hi >= 1; t_hi -= kRnnWideChunk, ++q) {
-    const int t_lo = std::max(1, t_hi - kRnnWideChunk + 1);
+  for (int t_hi = T, q = 0; t_hi >= 1; t_hi -= chunk, ++q) {
+    const int t_lo = std::max(1, t_hi - chunk + 1);
     float* const g_hi = m->rnn_g + (size_t)(t_hi - t_lo) * block;
     if (q == 0)
       RAD_TRY(dX_gemm(c, kF32, B, H, C, dz, nullptr, 0, W_ho, g_hi, a->bits + (size_t)(T - 1) * B * a->bp, a->bp));
@@ -1953,9 +1963,9 @@ static rad_status rnn_wide_backward(rad_ctx* c, rad_model* m, RnnWideArgs* a, co
     a->t_lo = t_lo; a->n = a->t0 - t_lo + 1;
     a->src = q == 0 ? g_hi : static_cast<const float*>(m->act[(q - 1) & 1]);
     a->carry = static_cast<float*>(m->act[q & 1]);
-    if (a->n > 0) RAD_TRY(rnn_wide_launch(c, false, a));
+    if (a->n > 0) RAD_TRY(rnn_wide_launch(c, m, false, a));
     // step t's sampled h_{t-1} is in slot t - 2; step 1 has none
-    const int t2 = std::max(2, t_lo), per = together ? kRnnWideChunk : 1;
+    const int t2 = std::max(2, t_lo), per = together ? chunk : 1;
     for (int t = t2; t <= t_hi; t += per) {
       RAD_TRY(dW_gemm(c, s_hh, t - 2, m->rnn_g + (size_t)(t - t_lo) * block, H, nullptr, 0, dW_hh, first ? 0 : 1,
                       std::min(per, t_hi - t + 1)));

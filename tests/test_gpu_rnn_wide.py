@@ -47,6 +47,15 @@ def test_lengths(ctx, T, scheme, p):  # noqa: F811
     run_rnn(ctx, data(T, 6, T, 210, d_input=3, classes=5), scheme, p, seed=T, check_store=T > 1)
 
 
+@pytest.mark.parametrize("T,chunks", [(256, 8), (257, 8), (264, 8), (1024, 8), (1025, 9)])
+@pytest.mark.parametrize("scheme,p", [(0, 1.0), (1, 0.3)])
+def test_longer_chunks_of_longer_sequences(ctx, T, chunks, scheme, p):  # noqa: F811
+    """An eighth of the sequence from 257 steps on (the last chunk shorter), at most 128 steps."""
+    from paper_2007_10412_amd import binding as B
+    run_rnn(ctx, data(T, 2, T, 200), scheme, p, seed=T)
+    assert B.rad_debug_redone_launches(ctx) == (0, 2 * chunks)
+
+
 @pytest.mark.parametrize("scheme,p", [(0, 1.0), (1, 0.1)])
 @pytest.mark.parametrize("batch,hidden,T", [(100, 900, 34), (100, 1001, 34), (150, 770, 35)])
 def test_split_rows_of_a_chunk(ctx, batch, hidden, T, scheme, p):  # noqa: F811
