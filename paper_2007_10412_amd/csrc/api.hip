@@ -1157,6 +1157,12 @@ static rad_status dW_gemm(rad_ctx* c, const rad_store* s, int slot, const void* 
       }));
     return RAD_OK;
   }
+  if (n_slots == 1 && n_out == N && dw_small_pays(s->dtype, s->rows, s->cols, N, g.sparse_prefetch, bits != nullptr, kept_fraction(s))) {
+    HIP_TRY(c, timed(c, "dw_small", [&](const char**) {
+      return launch_dw_small(g.sa, s->rows, dy, ldy, N, bits, bits_pitch, dW, beta, kept_fraction(s), c->stream);
+    }));
+    return RAD_OK;
+  }
   // Wide bf16 layers whose shape the direct-to-LDS dense kernel takes (whole 256-row tiles of x~, an output width
   // of whole 16-byte vectors, no loader mask): the
   // store is unpacked into a transient dense x~ (one pass over 2 B D bytes) and contracted by that kernel, which

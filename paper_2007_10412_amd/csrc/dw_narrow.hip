@@ -224,7 +224,128 @@ template <typename T> hipError_t launch_t(const NarrowArgs& a, int nt, int entri
   }
 }
 
+// ---------------------------------------------------------------------------------------------------- few rows, fp32
+// dW of a layer with up to 256 rows: bound by latencies, of which the tile kernel has one chain per 16 rows (bounds, entries,
+// scatter, barrier).  Here the rows of a 32 x 32 output tile are shared out to eight waves, at most 32 to each: a wave loads
+// all of its bounds, entries and g at once, scatters the entries into an LDS stage of its own, multiplies 32x32x2 and the
+// eight sums meet in LDS: one barrier.
+// rad_backward_dW with 10 % of the columns, us, tile kernel / this: 150 x 784 x 300 13.4 / 6.5, 150 x 300 x 300 11.9 / 6.2,
+// 64 x 784 x 300 7.2 / 6.4, 256 x 784 x 300 19.9 / 6.6, 256 x 1024 x 1024 21.2 / 17.8.  Every workgroup reads the whole
+// bucket's entries for its 32 columns, so it loses with many tiles: 150 x 2048 x 1024 17.4 / 31.7.
+constexpr int kSmallWaves = 8, kSmallTile = 32, kSmallRows = 32;       // rows of a wave at most
+constexpr int kSmallPasses = kSmallRows / kRows;
+
+template <int HELD, bool MASKED>
+__global__ __launch_bounds__(64 * kSmallWaves) void dw_small_kernel(NarrowArgs a) {
+  __shared__ __align__(16) float stage[kSmallWaves][kSmallRows * kSmallTile];
+  const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const int m0 = (int)blockIdx.x * kSmallTile, n0 = (int)blockIdx.y * kSmallTile, bucket = m0 / kBucket;
+  const int r0 = w * a.rows_per_split, rend = min(a.rows, r0 + a.rows_per_split);      // an even number of rows a wave
+  float* const st = stage[w];
+  const uint32_t cap = (uint32_t)a.s.capacity;             // (an overflowed draw never reads past the arrays)
+
+  // g of the wave's rows in the order of the B operand; loads are unconditional at clamped addresses
+  const int n = min(n0 + (lane & 31), a.N - 1), hi = lane >> 5;
+  float gv[kSmallRows / 2];
+  uint32_t gm[MASKED ? kSmallRows / 2 : 1];
+#pragma unroll
+  for (int j = 0; j < kSmallRows / 2; ++j) {
+    const int row = min(r0 + 2 * j + hi, a.rows - 1);
+    gv[j] = static_cast<const float*>(a.dy)[(size_t)row * a.ldy + n];
+    if (MASKED) gm[MASKED ? j : 0] = a.bits[(size_t)row * a.bits_pitch + (n >> 5)];
+  }
+  uint32_t beg[kSmallPasses], end[kSmallPasses];           // segment of row r0 + 8 q + lane / 8 in this bucket
+  {
+    uint32_t base[kSmallPasses], b0[kSmallPasses], b1[kSmallPasses];
+#pragma unroll
+    for (int q = 0; q < kSmallPasses; ++q) {
+      const int row = min(r0 + q * kRows + lane / kLanes, a.rows - 1);
+      const uint16_t* const bo = a.s.bucket_off + (size_t)(row * a.s.plan_row_stride) * (a.s.nb + 1) + bucket;
+      base[q] = a.s.row_ptr[row]; b0[q] = bo[0]; b1[q] = bo[1];
+    }
+#pragma unroll
+    for (int q = 0; q < kSmallPasses; ++q) {
+      end[q] = min(base[q] + b1[q], cap);
+      beg[q] = (r0 + q * kRows + lane / kLanes < rend ? min(base[q] + b0[q], end[q]) : end[q]) + lane % kLanes;
+    }
+  }
+  const float* const vals = reinterpret_cast<const float*>(a.s.values);
+  float val[kSmallPasses][HELD];
+  uint32_t col[kSmallPasses][HELD];
+#pragma unroll
+  for (int q = 0; q < kSmallPasses; ++q)
+#pragma unroll
+    for (int i = 0; i < HELD; ++i) {
+      const uint32_t e = min(beg[q] + i * kLanes, cap - 1u);
+      col[q][i] = a.s.indices[e]; val[q][i] = vals[e];
+    }
+  const floatx4 z4 = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int q = 0; q < kSmallRows * kSmallTile / 256; ++q) reinterpret_cast<floatx4*>(st)[q * 64 + lane] = z4;
+  __builtin_amdgcn_wave_barrier();                         // the stage belongs to this wave: its accesses complete in order
+#pragma unroll
+  for (int q = 0; q < kSmallPasses; ++q) {
+    float* const at = st + (q * kRows + lane / kLanes) * kSmallTile;
+#pragma unroll
+    for (int i = 0; i < HELD; ++i) {
+      const uint32_t c = col[q][i] - (uint32_t)m0;
+      if (beg[q] + i * kLanes < end[q] && c < (uint32_t)kSmallTile) at[c] = val[q][i];
+    }
+    for (uint32_t e = beg[q] + HELD * kLanes; e < end[q]; e += kLanes) {
+      const uint32_t c = a.s.indices[e] - (uint32_t)m0;
+      if (c < (uint32_t)kSmallTile) at[c] = vals[e];
+    }
+  }
+  __builtin_amdgcn_wave_barrier();
+  floatx16 acc;
+#pragma unroll
+  for (int e = 0; e < 16; ++e) acc[e] = 0.f;
+  const bool n_ok = n0 + (lane & 31) < a.N;
+#pragma unroll
+  for (int j = 0; j < kSmallRows / 2; ++j) {
+    const bool ok = n_ok && r0 + 2 * j + hi < rend && (!MASKED || ((gm[MASKED ? j : 0] >> (n & 31)) & 1u));
+    acc = __builtin_amdgcn_mfma_f32_32x32x2f32(st[(2 * j + hi) * kSmallTile + (lane & 31)], ok ? gv[j] : 0.f, acc, 0, 0, 0);
+  }
+  __builtin_amdgcn_wave_barrier();
+#pragma unroll
+  for (int e = 0; e < 16; ++e) st[e * 64 + lane] = acc[e];
+  __syncthreads();
+  // wave w adds accumulator elements 2 w and 2 w + 1 of all waves
+#pragma unroll
+  for (int u = 0; u < 2; ++u) {
+    const int e = 2 * w + u, m = m0 + acc_row(e, lane);
+    float v = stage[0][e * 64 + lane];
+#pragma unroll
+    for (int q = 1; q < kSmallWaves; ++q) v += stage[q][e * 64 + lane];
+    if (m < a.M && n_ok) {
+      float* const dst = a.out + (size_t)m * a.N + n;
+      *dst = a.beta ? *dst + v : v;
+    }
+  }
+}
+
+template <int HELD> hipError_t launch_small_held(const NarrowArgs& a, hipStream_t st) {
+  auto kern = a.bits ? dw_small_kernel<HELD, true> : dw_small_kernel<HELD, false>;
+  hipLaunchKernelGGL(kern, dim3((unsigned)((a.M + kSmallTile - 1) / kSmallTile), (unsigned)((a.N + kSmallTile - 1) / kSmallTile)),
+                     dim3(64 * kSmallWaves), 0, st, a);
+  return hipGetLastError();
+}
+
 }  // namespace
+
+hipError_t launch_dw_small(const StoreView& s, int rows, const void* dy, int64_t ldy, int N, const uint32_t* bits, int bits_pitch,
+                           float* out, int beta, double kept, hipStream_t st) {
+  if (rows < 1 || rows > kSmallWaves * kSmallRows) return hipErrorInvalidValue;
+  NarrowArgs a;
+  a.s = s; a.rows = rows; a.N = N; a.M = s.cols; a.dy = dy; a.ldy = ldy; a.bits = bits; a.bits_pitch = bits_pitch;
+  a.out = out; a.split_stride = 0; a.beta = beta;
+  a.rows_per_split = ((rows + kSmallWaves - 1) / kSmallWaves + 1) / 2 * 2;
+  const double mean = kept * std::min(s.cols, kBucket);
+  const int entries = (int)(mean + 2.5 * std::sqrt(mean));             // (a row beyond that: one in a hundred)
+  if (entries <= 3 * kLanes) return launch_small_held<3>(a, st);
+  if (entries <= 5 * kLanes) return launch_small_held<5>(a, st);
+  return launch_small_held<10>(a, st);
+}
 
 // columns per workgroup: the output width in equal parts of at most 16, rounded up to whole vectors
 static int narrow_nt(int N) {
@@ -249,6 +370,16 @@ int dw_narrow_splits(int rows, int cols, int N) {
   return (groups + per - 1) / per;
 }
 
+// us of the fp32 tile kernel, which walks all rows as one chain (see dw_narrow_pays)
+static double dw_tile_estimate(int rows, int cols, int N, int sparse_prefetch, bool masked) {
+  const bool wide = f32_sparse_wide(sparse_prefetch);
+  const double tiles128 = ((cols + 127) / 128) * (double)((N + 127) / 128), tiles64 = ((cols + 63) / 64) * (double)((N + 63) / 64);
+  const double load = tiles128 >= 192 ? tiles128 / 256 : tiles64 / 512;
+  const double row = (wide ? 0.095 : 0.056) * std::max(1.0, load) + (wide ? 0.023 : 0.018) * std::min(1.0, load) + (masked ? 0.009 : 0.0);
+  const double edge = tiles128 >= 192 && (cols % 128 || N % 128) ? 1.33 : 1.0;         // guarded loads on a full chip
+  return 3.7 + rows * row * edge;
+}
+
 // Whether this kernel is faster than the tile kernels, both sides measured (us of rad_backward_dW, tile kernel / here).
 // bf16, whose tile kernel runs at 16 times the matrix rate with a split K, up to 12 columns: 65536 x 4096 x 10 792 / 130,
 // 4096 x 1000 x 10 28 / 17, 150 x 784 x 10 12.8 / 9.2; with the sampling 16 columns 582 / 535 and 45 / 47, 32 582 / 647.
@@ -269,16 +400,23 @@ bool dw_narrow_pays(int dtype, int rows, int cols, int N, int sparse_prefetch, b
   if (rows <= 64) return false;
   if (dtype == kBF16 || N <= 12) return N <= 12;
   if (N > 128 && (N > 16384 || (int64_t)cols * N > 2200000)) return false;
-  const bool wide = f32_sparse_wide(sparse_prefetch);
   const double out = (double)cols * N / 1e6, blocks = (double)narrow_blocks(cols, N);
   const int splits = dw_narrow_splits(rows, cols, N), per = (narrow_groups(rows) + splits - 1) / splits;
   const double group = 0.5 + (1.6 + 0.030 * kept * std::min(cols, kBucket)) * std::min(1.0, blocks * splits / 1024);
   const double here = 3.4 * narrow_nt(N) / 16 + per * std::max(1.0, blocks / 1024) * group + (splits > 1 ? 4.7 + 6.3 * splits * out : 24.7);
-  const double tiles128 = ((cols + 127) / 128) * (double)((N + 127) / 128), tiles64 = ((cols + 63) / 64) * (double)((N + 63) / 64);
-  const double load = tiles128 >= 192 ? tiles128 / 256 : tiles64 / 512;
-  const double row = (wide ? 0.095 : 0.056) * std::max(1.0, load) + (wide ? 0.023 : 0.018) * std::min(1.0, load) + (masked ? 0.009 : 0.0);
-  const double edge = tiles128 >= 192 && (cols % 128 || N % 128) ? 1.33 : 1.0;         // guarded loads on a full chip
-  return here < 1.04 * (3.7 + rows * row * edge);                   // (the factor that loses least over the pairs)
+  return here < 1.04 * dw_tile_estimate(rows, cols, N, sparse_prefetch, masked);        // (the factor that loses least over the pairs)
+}
+
+// Whether it is faster than the tile kernel (which the rows a bucket's segment takes count for, see dw_narrow_pays): five
+// microseconds and 0.052 an entry of a row's bucket while every workgroup has a CU, from there on with the tiles.  At fraction
+// 0.1, us, tile kernel / here: 16 x 784 x 300 4.6 / 6.6, 64 x 2048 x 300 7.5 / 13.2, 256 x 2048 x 300 20.3 / 13.4, 256 x 4096 x
+// 128 20.2 / 9.7, 150 x 1024 x 1024 14.2 / 17.7; at 0.5 150 x 300 x 300 13.0 / 11.2, 150 x 2048 x 300 19.8 / 33.2.  Up to
+// twelve outputs dw_narrow_kernel and the tiles stay.
+bool dw_small_pays(int dtype, int rows, int cols, int N, int sparse_prefetch, bool masked, double kept) {
+  if (dtype != kF32 || rows > kSmallWaves * kSmallRows || N <= 12) return false;
+  const double tiles = ((cols + kSmallTile - 1) / kSmallTile) * (double)((N + kSmallTile - 1) / kSmallTile);
+  const double here = (4.9 + 0.052 * kept * std::min(cols, kBucket)) * std::max(1.0, 0.9 * tiles / 256);
+  return here < 0.95 * dw_tile_estimate(rows, cols, N, sparse_prefetch, masked);
 }
 
 hipError_t launch_dw_narrow(const StoreView& s, int dtype, int rows, const void* dy, int64_t ldy, int N,

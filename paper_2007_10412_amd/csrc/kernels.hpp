@@ -175,6 +175,9 @@ hipError_t launch_flip_weights(const float* W, int Ci, int KH, int KW, int Co, f
 // row's columns that the store holds)
 bool dw_narrow_pays(int dtype, int rows, int cols, int N, int sparse_prefetch, bool masked, double kept);
 int dw_narrow_splits(int rows, int cols, int N);
+bool dw_small_pays(int dtype, int rows, int cols, int N, int sparse_prefetch, bool masked, double kept);
+hipError_t launch_dw_small(const StoreView& s, int rows, const void* dy, int64_t ldy, int N, const uint32_t* bits, int bits_pitch,
+                           float* out, int beta, double kept, hipStream_t st);
 hipError_t launch_dw_narrow(const StoreView& s, int dtype, int rows, const void* dy, int64_t ldy, int N,
                             const uint32_t* bits, int bits_pitch, float* out, int beta, int splits, int64_t split_stride,
                             double kept, hipStream_t st);

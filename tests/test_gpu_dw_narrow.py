@@ -117,3 +117,35 @@ def test_faster_route(ctx, n, d, o, p, here):
     finally:
         B.rad_ctx_timing(ctx, "")
         B.rad_ctx_timing_reset(ctx)
+
+
+@pytest.mark.parametrize("n", [97, 127, 128, 129, 241, 255, 256])               # rows of eight waves, even a wave, the most
+@pytest.mark.parametrize("d,o", [(31, 13), (32, 32), (33, 33), (257, 65), (784, 300), (300, 31)])
+@pytest.mark.parametrize("scheme,p", [("bernoulli", 0.1), ("per_example", 0.02), ("replace_shared", 0.2)])
+def test_few_rows(ctx, n, d, o, scheme, p):
+    """Up to 256 fp32 rows on 32 x 32 tiles: both calls of check_dW reach that kernel, unless the row split is the faster one."""
+    from paper_2007_10412_amd import binding as B
+    count = 0
+    for name in ("dw_small", "dw_narrow"):
+        B.rad_ctx_timing(ctx, name)
+        B.rad_ctx_timing_reset(ctx)
+        try:
+            check_dW(ctx, n, d, o, "f32", scheme, p)
+            count += B.rad_ctx_timing_read(ctx, None)[0]
+        finally:
+            B.rad_ctx_timing(ctx, "")
+            B.rad_ctx_timing_reset(ctx)
+    assert count == 2
+
+
+def test_few_rows_long_segments(ctx):
+    """Rows with more entries in a bucket than the kernel holds in registers."""
+    from paper_2007_10412_amd import binding as B
+    B.rad_ctx_timing(ctx, "dw_small")
+    B.rad_ctx_timing_reset(ctx)
+    try:
+        check_dW(ctx, 100, 784, 300, "f32", "bernoulli", 0.4)
+        assert B.rad_ctx_timing_read(ctx, None)[0] == 2
+    finally:
+        B.rad_ctx_timing(ctx, "")
+        B.rad_ctx_timing_reset(ctx)
