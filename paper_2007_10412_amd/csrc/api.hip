@@ -1137,6 +1137,12 @@ static rad_status dW_gemm(rad_ctx* c, const rad_store* s, int slot, const void* 
     g.A = dense; g.lda = s->cols;
     return dw_dense_f32(c, g, alg);
   }
+  if (n_slots == 1 && n_out == N && dw_small_pays(s->dtype, s->rows, s->cols, N, g.sparse_prefetch, bits != nullptr, kept_fraction(s))) {
+    HIP_TRY(c, timed(c, "dw_small", [&](const char**) {
+      return launch_dw_small(g.sa, s->rows, dy, ldy, N, bits, bits_pitch, dW, beta, kept_fraction(s), c->stream);
+    }));
+    return RAD_OK;
+  }
   const int splits = dw_narrow_splits(s->rows, s->cols, N);
   if (n_slots == 1 && n_out == N && dw_narrow_pays(s->dtype, s->rows, s->cols, N, g.sparse_prefetch, bits != nullptr, kept_fraction(s)) &&
       (splits <= 1 || ws_ready(c, WS_SPLITK, (size_t)splits * s->cols * N * 4))) {
@@ -1155,12 +1161,6 @@ static rad_status dW_gemm(rad_ctx* c, const rad_store* s, int slot, const void* 
       HIP_TRY(c, timed(c, "splitk_reduce", [&](const char**) {
         return launch_splitk_reduce(out, splits, (int64_t)s->cols * N, dW, beta, c->stream);
       }));
-    return RAD_OK;
-  }
-  if (n_slots == 1 && n_out == N && dw_small_pays(s->dtype, s->rows, s->cols, N, g.sparse_prefetch, bits != nullptr, kept_fraction(s))) {
-    HIP_TRY(c, timed(c, "dw_small", [&](const char**) {
-      return launch_dw_small(g.sa, s->rows, dy, ldy, N, bits, bits_pitch, dW, beta, kept_fraction(s), c->stream);
-    }));
     return RAD_OK;
   }
   // Wide bf16 layers whose shape the direct-to-LDS dense kernel takes (whole 256-row tiles of x~, an output width

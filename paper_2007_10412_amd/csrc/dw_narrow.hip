@@ -233,7 +233,7 @@ template <typename T> hipError_t launch_t(const NarrowArgs& a, int nt, int entri
 // 64 x 784 x 300 7.2 / 6.4, 256 x 784 x 300 19.9 / 6.6, 256 x 1024 x 1024 21.2 / 17.8.  Every workgroup reads the whole
 // bucket's entries for its 32 columns, so it loses with many tiles: 150 x 2048 x 1024 17.4 / 31.7.
 constexpr int kSmallWaves = 8, kSmallTile = 32, kSmallRows = 32;       // rows of a wave at most
-constexpr int kSmallPasses = kSmallRows / kRows;
+constexpr int kSmallPasses = kSmallRows / kRows, kSmallHeld = 10;      // entries a lane of a row holds at most
 
 template <int HELD, bool MASKED>
 __global__ __launch_bounds__(64 * kSmallWaves) void dw_small_kernel(NarrowArgs a) {
@@ -333,6 +333,12 @@ template <int HELD> hipError_t launch_small_held(const NarrowArgs& a, hipStream_
 
 }  // namespace
 
+// entries of a row's bucket that a kernel is chosen for (a row with more: one in a hundred)
+static int bucket_entries(int cols, double kept) {
+  const double mean = kept * std::min(cols, kBucket);
+  return (int)(mean + 2.5 * std::sqrt(mean));
+}
+
 hipError_t launch_dw_small(const StoreView& s, int rows, const void* dy, int64_t ldy, int N, const uint32_t* bits, int bits_pitch,
                            float* out, int beta, double kept, hipStream_t st) {
   if (rows < 1 || rows > kSmallWaves * kSmallRows) return hipErrorInvalidValue;
@@ -340,11 +346,10 @@ hipError_t launch_dw_small(const StoreView& s, int rows, const void* dy, int64_t
   a.s = s; a.rows = rows; a.N = N; a.M = s.cols; a.dy = dy; a.ldy = ldy; a.bits = bits; a.bits_pitch = bits_pitch;
   a.out = out; a.split_stride = 0; a.beta = beta;
   a.rows_per_split = ((rows + kSmallWaves - 1) / kSmallWaves + 1) / 2 * 2;
-  const double mean = kept * std::min(s.cols, kBucket);
-  const int entries = (int)(mean + 2.5 * std::sqrt(mean));             // (a row beyond that: one in a hundred)
+  const int entries = bucket_entries(s.cols, kept);
   if (entries <= 3 * kLanes) return launch_small_held<3>(a, st);
   if (entries <= 5 * kLanes) return launch_small_held<5>(a, st);
-  return launch_small_held<10>(a, st);
+  return launch_small_held<kSmallHeld>(a, st);
 }
 
 // columns per workgroup: the output width in equal parts of at most 16, rounded up to whole vectors
@@ -380,6 +385,14 @@ static double dw_tile_estimate(int rows, int cols, int N, int sparse_prefetch, b
   return 3.7 + rows * row * edge;
 }
 
+// us of dw_narrow_kernel and the reduction behind it (see dw_narrow_pays)
+static double dw_narrow_estimate(int rows, int cols, int N, double kept) {
+  const double out = (double)cols * N / 1e6, blocks = (double)narrow_blocks(cols, N);
+  const int splits = dw_narrow_splits(rows, cols, N), per = (narrow_groups(rows) + splits - 1) / splits;
+  const double group = 0.5 + (1.6 + 0.030 * kept * std::min(cols, kBucket)) * std::min(1.0, blocks * splits / 1024);
+  return 3.4 * narrow_nt(N) / 16 + per * std::max(1.0, blocks / 1024) * group + (splits > 1 ? 4.7 + 6.3 * splits * out : 24.7);
+}
+
 // Whether this kernel is faster than the tile kernels, both sides measured (us of rad_backward_dW, tile kernel / here).
 // bf16, whose tile kernel runs at 16 times the matrix rate with a split K, up to 12 columns: 65536 x 4096 x 10 792 / 130,
 // 4096 x 1000 x 10 28 / 17, 150 x 784 x 10 12.8 / 9.2; with the sampling 16 columns 582 / 535 and 45 / 47, 32 582 / 647.
@@ -400,23 +413,26 @@ bool dw_narrow_pays(int dtype, int rows, int cols, int N, int sparse_prefetch, b
   if (rows <= 64) return false;
   if (dtype == kBF16 || N <= 12) return N <= 12;
   if (N > 128 && (N > 16384 || (int64_t)cols * N > 2200000)) return false;
-  const double out = (double)cols * N / 1e6, blocks = (double)narrow_blocks(cols, N);
-  const int splits = dw_narrow_splits(rows, cols, N), per = (narrow_groups(rows) + splits - 1) / splits;
-  const double group = 0.5 + (1.6 + 0.030 * kept * std::min(cols, kBucket)) * std::min(1.0, blocks * splits / 1024);
-  const double here = 3.4 * narrow_nt(N) / 16 + per * std::max(1.0, blocks / 1024) * group + (splits > 1 ? 4.7 + 6.3 * splits * out : 24.7);
-  return here < 1.04 * dw_tile_estimate(rows, cols, N, sparse_prefetch, masked);        // (the factor that loses least over the pairs)
+  // (the factor that loses least over the pairs)
+  return dw_narrow_estimate(rows, cols, N, kept) < 1.04 * dw_tile_estimate(rows, cols, N, sparse_prefetch, masked);
 }
 
-// Whether it is faster than the tile kernel (which the rows a bucket's segment takes count for, see dw_narrow_pays): five
+// Whether it is faster than the tile kernel and, where that one is, than dw_narrow_kernel (see dw_narrow_pays): five
 // microseconds and 0.052 an entry of a row's bucket while every workgroup has a CU, from there on with the tiles.  At fraction
 // 0.1, us, tile kernel / here: 16 x 784 x 300 4.6 / 6.6, 64 x 2048 x 300 7.5 / 13.2, 256 x 2048 x 300 20.3 / 13.4, 256 x 4096 x
-// 128 20.2 / 9.7, 150 x 1024 x 1024 14.2 / 17.7; at 0.5 150 x 300 x 300 13.0 / 11.2, 150 x 2048 x 300 19.8 / 33.2.  Up to
+// 128 20.2 / 9.7, 150 x 1024 x 1024 14.2 / 17.7; at 0.5 150 x 784 x 300
+// 19.3 / 12.1, 150 x 2048 x 300 19.8 / 33.2; row split / here at 0.1 150 x 300 x 300 11.9 / 6.2, 256 x 300 x 300 14.9 / 6.2.  Up to
 // twelve outputs dw_narrow_kernel and the tiles stay.
 bool dw_small_pays(int dtype, int rows, int cols, int N, int sparse_prefetch, bool masked, double kept) {
   if (dtype != kF32 || rows > kSmallWaves * kSmallRows || N <= 12) return false;
   const double tiles = ((cols + kSmallTile - 1) / kSmallTile) * (double)((N + kSmallTile - 1) / kSmallTile);
   const double here = (4.9 + 0.052 * kept * std::min(cols, kBucket)) * std::max(1.0, 0.9 * tiles / 256);
-  return here < 0.95 * dw_tile_estimate(rows, cols, N, sparse_prefetch, masked);
+  double other = dw_tile_estimate(rows, cols, N, sparse_prefetch, masked);
+  if (dw_narrow_pays(dtype, rows, cols, N, sparse_prefetch, masked, kept)) {
+    if (bucket_entries(cols, kept) > kSmallHeld * kLanes) return false;       // (segments beyond the registers: not measured)
+    other = dw_narrow_estimate(rows, cols, N, kept);
+  }
+  return here < 0.95 * other;
 }
 
 hipError_t launch_dw_narrow(const StoreView& s, int dtype, int rows, const void* dy, int64_t ldy, int N,
@@ -427,8 +443,7 @@ hipError_t launch_dw_narrow(const StoreView& s, int dtype, int rows, const void*
   a.s = s; a.rows = rows; a.N = N; a.M = s.cols; a.dy = dy; a.ldy = ldy; a.bits = bits; a.bits_pitch = bits_pitch;
   a.out = out; a.split_stride = split_stride; a.beta = beta;
   a.rows_per_split = (narrow_groups(rows) + splits - 1) / splits * (kRows * kWaves);
-  const double mean = kept * std::min(s.cols, kBucket);
-  const int entries = (int)(mean + 2.5 * std::sqrt(mean));             // (a row beyond that: one in a hundred)
+  const int entries = bucket_entries(s.cols, kept);
   return dtype == kBF16 ? launch_t<uint16_t>(a, narrow_nt(N), entries, splits, st)
                         : launch_t<float>(a, narrow_nt(N), entries, splits, st);
 }
