@@ -26,6 +26,7 @@
 #include <cmath>
 
 #include "kernels.hpp"
+#include "pde_layout.hpp"
 #include "philox.hpp"
 
 namespace rad {
@@ -252,7 +253,7 @@ __global__ __launch_bounds__(3 * kPdeLanes) void pde_forward_kernel(PdeArgs a) {
       pde_barrier();
     };
     uint32_t t = 0;
-    for (; t + 2 <= steps; t += 2) { step(t, 0); step(t + 1, 1); }
+    for (; pde_pair_left(t, steps); t += 2) { step(t, 0); step(t + 1, 1); }
     if (t < steps) step(t, 0);
     add_loss(sh.point(steps).s);
     loss = (sum[0] + sum[1]) + (sum[2] + sum[3]);
