@@ -425,6 +425,7 @@ bool dw_narrow_pays(int dtype, int rows, int cols, int N, int sparse_prefetch, b
 // twelve outputs dw_narrow_kernel and the tiles stay.
 bool dw_small_pays(int dtype, int rows, int cols, int N, int sparse_prefetch, bool masked, double kept) {
   if (dtype != kF32 || rows > kSmallWaves * kSmallRows || N <= 12) return false;
+  if (N > 65535 * kSmallTile) return false;                    // the grid's second axis
   const double tiles = ((cols + kSmallTile - 1) / kSmallTile) * (double)((N + kSmallTile - 1) / kSmallTile);
   const double here = (4.9 + 0.052 * kept * std::min(cols, kBucket)) * std::max(1.0, 0.9 * tiles / 256);
   double other = dw_tile_estimate(rows, cols, N, sparse_prefetch, masked);
