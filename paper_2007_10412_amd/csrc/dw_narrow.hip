@@ -229,9 +229,9 @@ template <typename T> hipError_t launch_t(const NarrowArgs& a, int nt, int entri
 // scatter, barrier).  Here the rows of a 32 x 32 output tile are shared out to eight waves, at most 32 to each: a wave loads
 // all of its bounds, entries and g at once, scatters the entries into an LDS stage of its own, multiplies 32x32x2 and the
 // eight sums meet in LDS: one barrier.
-// rad_backward_dW with 10 % of the columns, us, tile kernel / this: 150 x 784 x 300 13.4 / 6.5, 150 x 300 x 300 11.9 / 6.2,
-// 64 x 784 x 300 7.2 / 6.4, 256 x 784 x 300 19.9 / 6.6, 256 x 1024 x 1024 21.2 / 17.8.  Every workgroup reads the whole
-// bucket's entries for its 32 columns, so it loses with many tiles: 150 x 2048 x 1024 17.4 / 31.7.
+// rad_backward_dW with 10 % of the columns and no mask, us, tile kernel / this: 150 x 784 x 300 11.8 / 5.5, 64 x 784 x 300 6.5 /
+// 5.4, 256 x 784 x 300 17.3 / 5.7, 256 x 1024 x 1024 17.9 / 14.5; row split / this: 150 x 300 x 300 11.7 / 5.2.  Every workgroup
+// reads the whole bucket's entries for its 32 columns, so it loses with many tiles: 150 x 2048 x 1024 15.7 / 25.4.
 constexpr int kSmallWaves = 8, kSmallTile = 32, kSmallRows = 32;       // rows of a wave at most
 constexpr int kSmallPasses = kSmallRows / kRows, kSmallHeld = 10;      // entries a lane of a row holds at most
 
@@ -339,13 +339,16 @@ static int bucket_entries(int cols, double kept) {
   return (int)(mean + 2.5 * std::sqrt(mean));
 }
 
+// rows of a wave of dw_small_kernel
+static int small_rows_per_wave(int rows) { return ((rows + kSmallWaves - 1) / kSmallWaves + 1) / 2 * 2; }
+
 hipError_t launch_dw_small(const StoreView& s, int rows, const void* dy, int64_t ldy, int N, const uint32_t* bits, int bits_pitch,
                            float* out, int beta, double kept, hipStream_t st) {
   if (rows < 1 || rows > kSmallWaves * kSmallRows) return hipErrorInvalidValue;
   NarrowArgs a;
   a.s = s; a.rows = rows; a.N = N; a.M = s.cols; a.dy = dy; a.ldy = ldy; a.bits = bits; a.bits_pitch = bits_pitch;
   a.out = out; a.split_stride = 0; a.beta = beta;
-  a.rows_per_split = ((rows + kSmallWaves - 1) / kSmallWaves + 1) / 2 * 2;
+  a.rows_per_split = small_rows_per_wave(rows);
   const int entries = bucket_entries(s.cols, kept);
   if (entries <= 3 * kLanes) return launch_small_held<3>(a, st);
   if (entries <= 5 * kLanes) return launch_small_held<5>(a, st);
@@ -417,23 +420,33 @@ bool dw_narrow_pays(int dtype, int rows, int cols, int N, int sparse_prefetch, b
   return dw_narrow_estimate(rows, cols, N, kept) < 1.04 * dw_tile_estimate(rows, cols, N, sparse_prefetch, masked);
 }
 
-// Whether it is faster than the tile kernel and, where that one is, than dw_narrow_kernel (see dw_narrow_pays): five
-// microseconds and 0.052 an entry of a row's bucket while every workgroup has a CU, from there on with the tiles.  At fraction
-// 0.1, us, tile kernel / here: 16 x 784 x 300 4.6 / 6.6, 64 x 2048 x 300 7.5 / 13.2, 256 x 2048 x 300 20.3 / 13.4, 256 x 4096 x
-// 128 20.2 / 9.7, 150 x 1024 x 1024 14.2 / 17.7; at 0.5 150 x 784 x 300
-// 19.3 / 12.1, 150 x 2048 x 300 19.8 / 33.2; row split / here at 0.1 150 x 300 x 300 11.9 / 6.2, 256 x 300 x 300 14.9 / 6.2.  Up to
-// twelve outputs dw_narrow_kernel and the tiles stay.
+// us of dw_small_kernel: its start and 2.6 (5.6 where its lanes hold ten entries of a row, which leaves two waves a SIMD) for
+// every workgroup a CU takes one after the other, more under a mask; entries beyond those held cost 0.2 a round of eight lanes.
+static double dw_small_estimate(int rows, int cols, int N, bool masked, double kept) {
+  const int entries = bucket_entries(cols, kept);
+  const double round = entries <= 5 * kLanes ? 2.6 : 5.6, start = entries <= 3 * kLanes ? 2.2 : entries <= 5 * kLanes ? 2.6 : 0.9;
+  const double tiles = ((cols + kSmallTile - 1) / kSmallTile) * (double)((N + kSmallTile - 1) / kSmallTile) / 256;
+  const int passes = (small_rows_per_wave(rows) + kRows - 1) / kRows;
+  const double beyond = passes * std::max(0.0, kept * std::min(cols, kBucket) - kSmallHeld * kLanes) / kLanes;
+  return start + round * (tiles > 1 ? tiles + 0.6 : 1.0) * (masked ? 1.15 : 1.0) + (masked ? 0.5 : 0.0) + 0.2 * beyond * std::max(1.0, tiles);
+}
+
+// Whether it is faster than the tile kernel and, where that one is, than dw_narrow_kernel (see dw_narrow_pays): estimates of
+// both sides.  Fitted to 1088 pairs of calls (1 to 256 rows, 32 to 5800 columns, 14 to 4000 outputs, fractions 0.01 to 0.8, with
+// and without a mask): nine tenths of the estimates are within 12 %, and with the factor the choice is behind the other side by
+// more than 3 % in one pair (12 %), in none of 1400 further ones.  us, the other side / here: at fraction 0.1 256 x 512 x 2048
+// 17.9 / 13.6; at 0.25 105 x 141 x 3927 under a mask 16.4 / 19.9; at 0.6 235 x 230 x 2396 25.8 / 34.0; at 0.8 145 x 3087 x 90
+// 21.8 / 29.4.  Rows with more entries in a bucket than the registers hold keep the row split where that is ahead of the tiles,
+// though it is often the slower one (175 x 701 x 347 at 0.35 19.0 / 9.5).  Up to twelve outputs dw_narrow_kernel and the tiles stay.
 bool dw_small_pays(int dtype, int rows, int cols, int N, int sparse_prefetch, bool masked, double kept) {
   if (dtype != kF32 || rows > kSmallWaves * kSmallRows || N <= 12) return false;
   if (N > 65535 * kSmallTile) return false;                    // the grid's second axis
-  const double tiles = ((cols + kSmallTile - 1) / kSmallTile) * (double)((N + kSmallTile - 1) / kSmallTile);
-  const double here = (4.9 + 0.052 * kept * std::min(cols, kBucket)) * std::max(1.0, 0.9 * tiles / 256);
   double other = dw_tile_estimate(rows, cols, N, sparse_prefetch, masked);
   if (dw_narrow_pays(dtype, rows, cols, N, sparse_prefetch, masked, kept)) {
-    if (bucket_entries(cols, kept) > kSmallHeld * kLanes) return false;       // (segments beyond the registers: not measured)
+    if (bucket_entries(cols, kept) > kSmallHeld * kLanes) return false;
     other = dw_narrow_estimate(rows, cols, N, kept);
   }
-  return here < 0.95 * other;
+  return dw_small_estimate(rows, cols, N, masked, kept) < 0.85 * other;
 }
 
 hipError_t launch_dw_narrow(const StoreView& s, int dtype, int rows, const void* dy, int64_t ldy, int N,
