@@ -1549,12 +1549,22 @@ enum ModelKind { kMlp = 0, kRnn = 1, kCnn = 2 };
 constexpr int kRnnChunk = 8;            // time steps whose recurrent dW is one contraction over steps x batch
 // The same where a launch takes a chunk of time steps (rnn_wide.hip).  A launch costs about five steps' time (W_hh into the
 // registers) and every chunk the small kernels behind it, so chunks are long; but the dense h or g of a chunk is kept (batch x
-// hidden numbers a step, and once more as x~ for dW_hh), which should stay a small part of what all steps' would take: an
-// eighth of the steps, at least 32 and at most 128.  Training step, us, chunks of 32 / 64 / 128 steps, and by this rule: 128 x
-// 1024, T = 784 9234 / 8456 / 8032, 8068; 16 x 700, T = 700 5109 / 4409 / 4200, 4276; 40 x 300, T = 300 1577 / 1408 / 1341, 1506.
+// hidden numbers a step): an eighth of what all steps' would take, of at least 32 steps and at most 128 (and x~ of a part of
+// them for dW_hh, rnn_wide_dw_steps).  Training step, us, x~ of a whole chunk at once,
+// chunks of 32 / 64 / 128 steps, and by this rule: 128 x 1024, T = 784 9234 / 8456 / 8032, 8068; 16 x 700, T = 700 5109 / 4409
+// / 4200, 4276; 40 x 300, T = 300 1577 / 1408 / 1341, 1506.
 constexpr int kRnnWideChunkMin = 32, kRnnWideChunkMax = 128;
 static int rnn_wide_chunk(int64_t T) {
   return (int)std::min<int64_t>(T, std::max<int64_t>(kRnnWideChunkMin, std::min<int64_t>(kRnnWideChunkMax, (T + 7) / 8)));
+}
+
+// Time steps of a chunk of `n` whose dense x~ is there at once for dW_hh: equal parts of at most 32 MB (or 32 steps), so that
+// long chunks of large models do not take a second buffer of their own size along.  A part costs 19 us (the product's start and
+// its partial sums): 128 x 1024, T = 784, chunks of 98 steps: 8110 us at once (51 MB), 8270 in two parts, 8380 in three.
+constexpr size_t kRnnWideDwBytes = (size_t)32 << 20;
+static int rnn_wide_dw_steps(int n, size_t step_bytes) {
+  const int most = std::max(kRnnWideChunkMin, (int)(kRnnWideDwBytes / step_bytes)), parts = (n + most - 1) / most;
+  return (n + parts - 1) / parts;
 }
 
 struct rad_model {
@@ -1971,7 +1981,8 @@ static rad_status rnn_wide_backward(rad_ctx* c, rad_model* m, RnnWideArgs* a, co
     a->carry = static_cast<float*>(m->act[q & 1]);
     if (a->n > 0) RAD_TRY(rnn_wide_launch(c, m, false, a));
     // step t's sampled h_{t-1} is in slot t - 2; step 1 has none
-    const int t2 = std::max(2, t_lo), per = together ? chunk : 1;
+    const int t2 = std::max(2, t_lo);
+    const int per = !together || t2 > t_hi ? 1 : s_hh->scheme == RAD_EXACT ? chunk : rnn_wide_dw_steps(t_hi - t2 + 1, block * 4);
     for (int t = t2; t <= t_hi; t += per) {
       RAD_TRY(dW_gemm(c, s_hh, t - 2, m->rnn_g + (size_t)(t - t_lo) * block, H, nullptr, 0, dW_hh, first ? 0 : 1,
                       std::min(per, t_hi - t + 1)));

@@ -76,6 +76,52 @@ def test_longest_chunks(ctx):  # noqa: F811
         B.rad_model_destroy(m)
 
 
+def test_transient_memory_of_long_chunks():
+    """Chunks of 128 steps of 160 x 1000 (82 MB of dense h or g, the model's): what the step takes beside them is 32 MB of x~
+    at most, four split sums of dW_hh (16 MB) and a few of flags and small sums, not another 82 MB of x~."""
+    import torch
+    from paper_2007_10412_amd import binding as B, synth
+    from tests.gpu_util import dev, empty
+    names, batch, T, hidden, took = ["W_ih", "W_hh", "b", "W_ho", "b_o"], 160, 1024, 1000, []
+    d = synth.rnn(seed=1, batch=batch, T=T, d_input=1, hidden=hidden, classes=10, identity=True)
+    params, grads = [dev(d[n]) for n in names], [empty(d[n].shape) for n in names]
+    x, labels = dev(d["x"]), dev(d["labels"])
+    for _ in range(2):                       # the first one loads the kernels
+        c = B.rad_ctx_create()
+        m = B.rad_model_create_rnn(c, batch, T, 1, hidden, 10, 1, 0.05)
+        try:
+            torch.cuda.synchronize()
+            before = torch.cuda.mem_get_info()[0]
+            B.rad_train_step(c, m, B.make_sampling(1, 0.05, 5, 20, 0), x, labels, params, grads)
+            torch.cuda.synchronize()
+            took.append((before - torch.cuda.mem_get_info()[0]) / 1e6)
+        finally:
+            B.rad_model_destroy(m)
+            B.rad_ctx_destroy(c)
+    print("rnn wide transient MB", took, flush=True)
+    assert took[1] < 72, took
+
+
+@pytest.mark.parametrize("batch,hidden,T", [(128, 1024, 264), (160, 1000, 530)])
+def test_parts_of_a_chunk_under_dW(ctx, batch, hidden, T):  # noqa: F811
+    """Chunks of 33 steps (17 MB of x~, at once) and of 67 (43 MB, parts of 34 and 33): with every number kept, the gradients of
+    the exact store, which takes a chunk at once, up to the order of the fp32 sums over steps x batch."""
+    from paper_2007_10412_amd import binding as B, synth
+    from tests.gpu_util import dev, host, empty, assert_grad_close, U_F32
+    names, runs = ["W_ih", "W_hh", "b", "W_ho", "b_o"], []
+    d = synth.rnn(seed=1, batch=batch, T=T, d_input=1, hidden=hidden, classes=10, identity=True)
+    for scheme in (0, 1):
+        m = B.rad_model_create_rnn(ctx, batch, T, 1, hidden, 10, scheme, 1.0)
+        try:
+            params, grads = [dev(d[n]) for n in names], [empty(d[n].shape) for n in names]
+            B.rad_train_step(ctx, m, B.make_sampling(scheme, 1.0, 5, 20, 0), dev(d["x"]), dev(d["labels"]), params, grads)
+            runs.append([host(g).copy() for g in grads])
+        finally:
+            B.rad_model_destroy(m)
+    for name, a, b in zip(names, *runs):
+        assert_grad_close(b, a.astype(np.float64), 1e-4, T * batch, name, acc_u=U_F32, c=32.0)
+
+
 @pytest.mark.parametrize("scheme,p", [(0, 1.0), (1, 0.1)])
 @pytest.mark.parametrize("batch,hidden,T", [(100, 900, 34), (100, 1001, 34), (150, 770, 35)])
 def test_split_rows_of_a_chunk(ctx, batch, hidden, T, scheme, p):  # noqa: F811
