@@ -13,6 +13,7 @@
 
 #include "../../include/rad.h"
 #include "kernels.hpp"
+#include "rnn_chunk.hpp"
 
 using namespace rad;
 
@@ -1905,11 +1906,8 @@ static rad_status rnn_wide_begin(rad_ctx* c, const rad_model* m, const float* xs
   std::memset(a, 0, sizeof(*a));
   a->B = (int)m->batch; a->T = (int)m->T; a->H = (int)m->hidden; a->I = (int)m->d_input; a->bp = (a->H + 31) / 32;
   a->xs = xs; a->W_ih = W_ih; a->W_hh = W_hh; a->b = b; a->bits = m->rnn_bits;
-  // A look takes 0.3 us or more: 0.6 ms for chunks of 32 steps, several times what the other kernels of a training step hold a
-  // CU and what another context's chunk takes, and a quarter of what the stand-in takes for a chunk; longer chunks wait longer.
-  // The part that depends on the context decides which of two launches gives way.
   const uint32_t own = (uint32_t)(reinterpret_cast<uintptr_t>(c) >> 4) * 0x9E3779B1u >> 29;
-  a->poll_limit = c->poll_limit ? c->poll_limit : (2048u + 256u * own) * (uint32_t)std::max(32, m->rnn_chunk) / 32u;
+  a->poll_limit = c->poll_limit ? c->poll_limit : rnn_wide_polls(m->rnn_chunk, own);
   c->poll_limit = 0;
   const int launches = 2 * ((a->T + m->rnn_chunk - 1) / m->rnn_chunk);
   const size_t bytes = rnn_wide_sync_bytes(a->B, a->H, launches);

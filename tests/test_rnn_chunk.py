@@ -1,0 +1,26 @@
+"""Waits of the recurrent kernels that take a chunk of time steps per launch, on the CPU: the header that they share."""
+import os
+import subprocess
+
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+CSRC = os.path.join(os.path.dirname(HERE), "paper_2007_10412_amd", "csrc")
+
+
+@pytest.fixture(scope="module")
+def probe(tmp_path_factory):
+    exe = str(tmp_path_factory.mktemp("rnn") / "rnn_chunk_probe")
+    subprocess.check_call(["g++", "-O1", "-std=c++17", "-I" + CSRC, os.path.join(HERE, "rnn_chunk_probe.cpp"), "-o", exe])
+    return [[int(v) for v in line.split()] for line in subprocess.check_output([exe], text=True).splitlines()]
+
+
+def test_bounds_of_two_contexts_differ(probe):
+    """Of two launches that each hold a part of an XCD one has to give way first, whatever the lengths of their models."""
+    by_own = {}
+    for chunk, own, bound in probe:
+        by_own.setdefault(own, set()).add(bound)
+        assert max(2048, 64 * (chunk - 16)) <= bound - 256 * own <= max(2048, 64 * (chunk + 16))
+    for a in by_own:
+        for b in by_own:
+            assert a == b or min(abs(u - v) for u in by_own[a] for v in by_own[b]) >= 256
