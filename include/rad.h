@@ -192,7 +192,8 @@ rad_status rad_debug_key_shift(rad_ctx* ctx, int32_t shift);
 rad_status rad_debug_poll_limit(rad_ctx* ctx, int32_t polls);
 
 /* Test hook: in the first `launches` kernel launches of the next such step
- * (one per 32 time steps and direction) the workgroups of the groups in the
+ * (one per chunk of time steps, an eighth of the sequence, 32 to 128 steps,
+ * and direction) the workgroups of the groups in the
  * bit mask `groups` (bit i: XCD i and its eighth of the batch) do nothing, as
  * if none had been started there; the stand-in kernel has to notice.  0
  * launches cancel the hook. */

@@ -1905,6 +1905,7 @@ static rad_status rnn_wide_begin(rad_ctx* c, const rad_model* m, const float* xs
                                  const float* b, RnnWideArgs* a) {
   std::memset(a, 0, sizeof(*a));
   a->B = (int)m->batch; a->T = (int)m->T; a->H = (int)m->hidden; a->I = (int)m->d_input; a->bp = (a->H + 31) / 32;
+  a->chunk = m->rnn_chunk;
   a->xs = xs; a->W_ih = W_ih; a->W_hh = W_hh; a->b = b; a->bits = m->rnn_bits;
   const uint32_t own = (uint32_t)(reinterpret_cast<uintptr_t>(c) >> 4) * 0x9E3779B1u >> 29;
   a->poll_limit = c->poll_limit ? c->poll_limit : rnn_wide_polls(m->rnn_chunk, own);

@@ -220,12 +220,12 @@ hipError_t launch_rnn_backward(const RnnArgs& a, float* dW_hh, float* db, float*
 // ReLU bits of step t).  src: dense h or g of the step before the first (null: zeros); out: [steps t_lo .. t_out][B][H];
 // carry: the last step's output too, or null (not src: a launch that gave up is computed again from src).
 // xch, flags, tickets, abort_words, redone and backoff lie in a workspace of rnn_wide_sync_bytes that is zero before the first of
-// `launches` launches (numbered by `launch`); seq0 grows by at least n from launch to launch and starts at 1 or more.
+// `launches` launches (numbered by `launch`) of at most `chunk` steps; seq0 grows by at least n from launch to launch and starts at 1 or more.
 // redone[launch] becomes 1 where the chunk was computed again.  absent, a test hook: the workgroups of these groups (bits)
 // return at once, as if none had run on their XCDs.
 constexpr int kRnnWideGroups = 8, kRnnWideMaxIn = 8;
 struct RnnWideArgs {
-  int B, T, H, I, t0, n, t_lo, t_out, bp, launch;
+  int B, T, H, I, t0, n, t_lo, t_out, bp, launch, chunk;
   uint32_t seq0, poll_limit, absent;
   int members;                           // workgroups a group needs, set by the launch
   const float* xs; const float* W_ih; const float* W_hh; const float* b;

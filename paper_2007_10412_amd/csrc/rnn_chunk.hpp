@@ -13,4 +13,11 @@ constexpr uint32_t rnn_wide_polls(int chunk, uint32_t own) {
   return 2048u * (uint32_t)(chunk < 48 ? 1 : (chunk + 16) / 32) + 256u * own;
 }
 
+// Launches that go to the stand-in without trying after the (fails + 1)-th one in a row gave up: none after the first, then about
+// 32, 96, 224 and up to 480 time steps' worth.
+constexpr uint32_t rnn_wide_skip(uint32_t fails, int chunk) {
+  const uint32_t steps = 32u * ((1u << (fails < 4u ? fails : 4u)) - 1u), per = chunk < 32 ? 32u : (uint32_t)chunk;
+  return (steps + per / 2u) / per;
+}
+
 }  // namespace rad

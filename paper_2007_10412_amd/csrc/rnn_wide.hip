@@ -31,9 +31,15 @@
 // other goes on (the bounds differ from context to context).  Steps of T = 200, ms for one of each context, a launch per step /
 // this: three contexts 128 x 1024 9.4 / 7.9 (one launch in 35 computed again), two 192 x 1000 30.2 / 8.0, two 160 x 600 6.0 / 4.0
 // (none).
+// A launch of a long chunk that gives up costs its whole chunk on the stand-in (98 steps of 128 x 1024 8.4 ms forward, 12.3
+// backward), but its waits are longer and fewer give up.  T = 784, ms for one step of each, chunks of 32 / of 98: three contexts
+// 128 x 1024 28.0 / 26.1, two 192 x 1000 57.7 (one in 15 computed again) / 26.5 to 46.5 (none), three 160 x 600 23.1 / 21.7, 128
+// x 1024 beside twenty bf16 products of 8192 49.8 (one in 100) / 47.3 to 51.8 (none); slower only 128 x 1024 beside 192 x 1000 of T = 300:
+// 15.0 (none) / 15.4 to 16.4 (one in 35).
 #include <algorithm>
 
 #include "gemm.hpp"
+#include "rnn_chunk.hpp"
 
 namespace rad {
 
@@ -260,10 +266,10 @@ __global__ __launch_bounds__(128 * kWaves) void rnn_wide_redo_kernel(RnnWideArgs
   const bool again = left_out(a);
   if (blockIdx.x == 0 && threadIdx.x == 0) {
     // [0] launches in a row that gave up, [1] the next one that tries: a wait that runs out costs a quarter of a chunk here, so
-    // the first failure costs no launch, the next one, then three, seven and up to fifteen
+    // the first failure costs no launch and further ones more and more time steps (rnn_wide_skip)
     const uint32_t fails = a.backoff[0];
     if ((uint32_t)a.launch >= a.backoff[1]) {
-      if (again) { a.backoff[0] = fails + 1u; a.backoff[1] = (uint32_t)a.launch + (1u << min(fails, 4u)); }
+      if (again) { a.backoff[0] = fails + 1u; a.backoff[1] = (uint32_t)a.launch + 1u + rnn_wide_skip(fails, a.chunk); }
       else if (fails) a.backoff[0] = 0u;
     }
     if (again) a.redone[a.launch] = 1u;

@@ -1,10 +1,11 @@
-// Prints "chunk own bound" for the chunks of 1 to 128 steps and the parts of a context.
+// Prints, for the chunks of 1 to 128 steps, "chunk own bound" for the parts of a context, or, with an argument, "chunk fails skip".
 #include <cstdio>
 
 #include "rnn_chunk.hpp"
 
-int main() {
+int main(int argc, char**) {
   for (int chunk = 1; chunk <= 128; ++chunk)
-    for (uint32_t own = 0; own < 8; ++own) std::printf("%d %u %u\n", chunk, own, rad::rnn_wide_polls(chunk, own));
+    for (uint32_t k = 0; k < 8; ++k)
+      std::printf("%d %u %u\n", chunk, k, argc > 1 ? rad::rnn_wide_skip(k, chunk) : rad::rnn_wide_polls(chunk, k));
   return 0;
 }

@@ -205,6 +205,30 @@ def test_failing_launches_are_not_repeated_at_once(ctx, failing, redone):  # noq
     assert B.rad_debug_redone_launches(ctx) == (redone, 14)
 
 
+@pytest.mark.parametrize("failing,redone", [(1, 1), (2, 2), (3, 4), (5, 7), (16, 16)])
+def test_failing_launches_of_long_chunks(failing, redone):
+    """16 launches of 98 steps, the first ones of which find no workgroups: what goes to the stand-in without trying counts in
+    time steps (none after two failures in a row, one launch after three, two after four), and the numbers are those of an
+    undisturbed step."""
+    from paper_2007_10412_amd import binding as B, synth
+    from tests.gpu_util import dev, host, empty
+    names, runs, T = ["W_ih", "W_hh", "b", "W_ho", "b_o"], [], 784
+    d = synth.rnn(seed=2, batch=6, T=T, d_input=1, hidden=200, classes=10, identity=True)
+    c = B.rad_ctx_create()
+    m = B.rad_model_create_rnn(c, 6, T, 1, 200, 10, 1, 0.2)
+    try:
+        params, grads = [dev(d[n]) for n in names], [empty(d[n].shape) for n in names]
+        for n, expected in ((0, 0), (failing, redone)):
+            B.rad_debug_absent_groups(c, 0xff, n)
+            B.rad_train_step(c, m, B.make_sampling(1, 0.2, 5, 20, 0), dev(d["x"]), dev(d["labels"]), params, grads)
+            assert B.rad_debug_redone_launches(c) == (expected, 16)
+            runs.append([host(g).copy() for g in grads])
+        assert all(np.array_equal(a, b) and np.isfinite(a).all() for a, b in zip(*runs))
+    finally:
+        B.rad_model_destroy(m)
+        B.rad_ctx_destroy(c)
+
+
 @pytest.mark.parametrize("contexts,batch,hidden", [(2, 160, 600), (3, 128, 1000), (3, 20, 300)])
 def test_models_of_several_contexts_at_once(contexts, batch, hidden):
     """Each on a stream of its own, steps enqueued in turn: the launches of one wait for, or give way to, those of another, and
@@ -238,6 +262,42 @@ def test_models_of_several_contexts_at_once(contexts, batch, hidden):
             print([B.rad_debug_redone_launches(side[0]) for side in sides], flush=True)
             for side in sides:
                 assert all(np.array_equal(host(g), a) for g, a in zip(side[5], alone))
+    finally:
+        for side in sides:
+            B.rad_model_destroy(side[1])
+            B.rad_ctx_destroy(side[0])
+
+
+@pytest.mark.parametrize("models", [[(128, 1000, 264), (128, 1000, 600), (128, 1000, 264)], [(192, 1000, 300), (160, 900, 420)]])
+def test_long_chunks_of_several_contexts_at_once(models):
+    """Chunks of 33 to 75 steps of models of different lengths, each on a stream of its own: every step has the bits of one
+    taken alone."""
+    import torch
+    from paper_2007_10412_amd import binding as B, synth
+    from tests.gpu_util import dev, host, empty
+    names, sides, alone = ["W_ih", "W_hh", "b", "W_ho", "b_o"], [], []
+    try:
+        for k, (batch, hidden, T) in enumerate(models):
+            d = synth.rnn(seed=k, batch=batch, T=T, d_input=1, hidden=hidden, classes=10, identity=True)
+            print("rnn wide contexts", batch, hidden, T, flush=True)
+            c = B.rad_ctx_create(torch.cuda.Stream())
+            sides.append((c, B.rad_model_create_rnn(c, batch, T, 1, hidden, 10, 1, 0.1), dev(d["x"]), dev(d["labels"]),
+                          [dev(d[n]) for n in names], [empty(d[n].shape) for n in names]))
+        torch.cuda.synchronize()
+
+        def step(side):
+            B.rad_train_step(side[0], side[1], B.make_sampling(1, 0.1, 5, 20, 0), side[2], side[3], side[4], side[5], want_loss=False)
+        for side in sides:
+            step(side)
+            torch.cuda.synchronize()
+            alone.append([host(g).copy() for g in side[5]])
+        for _ in range(4):
+            for side in sides:
+                step(side)
+        torch.cuda.synchronize()
+        print([B.rad_debug_redone_launches(side[0]) for side in sides], flush=True)
+        for side, want in zip(sides, alone):
+            assert all(np.array_equal(host(g), a) and np.isfinite(a).all() for g, a in zip(side[5], want))
     finally:
         for side in sides:
             B.rad_model_destroy(side[1])
