@@ -22,7 +22,6 @@
 // problems 9500 / 6260; one problem 4690 / 3100; one of 8 x 8 3570 / 2100.  40960 steps: 22.0 + 25.3 / 12.5 + 18.5 ms.
 // Slower: sampling waves that draw every step (18.0 + 31.2); three sets (13.2 + 33.1, registers spill); skipping the
 // places of a quad that no lane of the wave kept (12.6 + 22.6); the stencil waves sampling for themselves (43 in all).
-#include <algorithm>
 #include <cmath>
 
 #include "kernels.hpp"
@@ -33,8 +32,7 @@ namespace rad {
 
 namespace {
 
-constexpr int kPdeWaves = 4, kPdeLanes = 64 * kPdeWaves;       // stencil waves at most, their lanes (four cells each)
-constexpr int kPdeCells = 256;                                 // cells of a stencil wave at most
+constexpr int kPdeLanes = 64 * kPdeWaves;                      // lanes of the stencil waves (four cells each)
 constexpr int kPdePad = 32;                                    // zeros before the first cell: a grid row and more
 constexpr int kPdePlane = 320;                                 // pitch of the planes; a multiple of 64: paired LDS writes
 constexpr int kPdeBuf = 4 * kPdePlane;
@@ -79,8 +77,8 @@ struct PdeArgs {
   uint32_t seed_lo, seed_hi, stream_id;
   const double* theta;                        // [problems][7]
   double* vals; int64_t per_problem;          // [problems][per_problem] kept entries, a run for each sampling wave
-  int64_t run_at[2][kPdeWaves], run_cap[2][kPdeWaves];   // of even and of odd steps
-  uint32_t* wave_end;                         // [problems][16] entries each wave kept in all
+  PdeRunLayout runs;                          // of even and of odd steps
+  uint32_t* wave_end;                         // [problems][kPdeRuns] entries each wave kept in all
   int* overflow;                              // [problems]
   double* loss; double* grad; int64_t* stored;
 };
@@ -261,8 +259,8 @@ __global__ __launch_bounds__(3 * kPdeLanes) void pde_forward_kernel(PdeArgs a) {
     const int sw = wave - waves, odd = sw >= waves ? 1 : 0;     // even or odd steps
     PdeSampler<kAll> me; me.init(a, (int)threadIdx.x - 64 * waves * (1 + odd), pb);
     const bool filler = sw == 0;                                // fills the table
-    double* at = a.vals + (size_t)pb * a.per_problem + a.run_at[odd][sw - odd * waves];
-    const int64_t cap = a.run_cap[odd][sw - odd * waves];
+    double* at = a.vals + (size_t)pb * a.per_problem + a.runs.at[odd][sw - odd * waves];
+    const int64_t cap = a.runs.cap[odd][sw - odd * waves];
     int64_t offset = 0;                                         // entries this wave has kept so far
     uint64_t m[4];
     double x[4];
@@ -298,7 +296,7 @@ __global__ __launch_bounds__(3 * kPdeLanes) void pde_forward_kernel(PdeArgs a) {
       pde_barrier();
     }
     if ((threadIdx.x & 63) == 0) {
-      a.wave_end[(size_t)pb * 16 + sw] = (uint32_t)(offset < cap ? offset : cap);
+      a.wave_end[(size_t)pb * kPdeRuns + sw] = (uint32_t)(offset < cap ? offset : cap);
       kept = (double)offset;
     }
   }
@@ -362,9 +360,9 @@ __global__ __launch_bounds__(3 * kPdeLanes) void pde_backward_kernel(PdeArgs a) 
       const PdeCell cell(a.n, 4 * (int)me.q + e);
       phi0[e] = cell.phi0; tgt[e] = cell.tgt; w1[e] = ws[e] = wc[e] = 0.0;
     }
-    const double* const run = a.vals + (size_t)pb * a.per_problem + a.run_at[odd][sw - odd * waves];
+    const double* const run = a.vals + (size_t)pb * a.per_problem + a.runs.at[odd][sw - odd * waves];
     double* const ring = rings[sw];
-    const uint32_t end = (uint32_t)__builtin_amdgcn_readfirstlane((int)a.wave_end[(size_t)pb * 16 + sw]);
+    const uint32_t end = (uint32_t)__builtin_amdgcn_readfirstlane((int)a.wave_end[(size_t)pb * kPdeRuns + sw]);
     int64_t offset = (int64_t)end;                              // walks back one step's count at a time
     uint32_t unit = (uint32_t)((offset + kPdeUnit - 1) / kPdeUnit);   // entries from unit * kPdeUnit on are in the ring
     double pending[4] = {0, 0, 0, 0};                           // the unit below, on its way
@@ -473,22 +471,10 @@ hipError_t launch_pde(int problems, int n, int64_t steps, double D, double dt, d
   a.seed_lo = seed_lo; a.seed_hi = seed_hi; a.stream_id = stream_id;
   a.theta = theta; a.vals = vals; a.wave_end = wave_end; a.overflow = overflow;
   a.loss = loss; a.grad = grad; a.stored = stored;
-  // The workspace has room for 16 runs of `cap` entries, sized for at most 62 cells each; a stencil wave's run is
-  // sized in the same way for its own cells (256, the last one less), which takes less in all: fewer cells
-  // together, and eight standard deviations of fewer, longer runs.
   const int cells = (n - 1) * (n - 1), waves = (cells + kPdeCells - 1) / kPdeCells;
-  a.per_problem = 16 * cap;
-  int64_t at = 0;
-  for (int odd = 0; odd < 2; ++odd)
-    for (int w = 0; w < kPdeWaves; ++w) {
-      const int own = std::min(kPdeCells, std::max(0, cells - w * kPdeCells));
-      const double total = own * (double)((steps + 2 - odd) / 2);
-      const double want = std::ceil(total * p + 8.0 * std::sqrt(total * p * (1.0 - p))) + 64.0;
-      a.run_at[odd][w] = at;
-      a.run_cap[odd][w] = (int64_t)std::min(want, total);
-      at += a.run_cap[odd][w];
-    }
-  if (waves > kPdeWaves || at > a.per_problem) return hipErrorInvalidValue;
+  a.runs = pde_run_layout(cells, steps, p);
+  a.per_problem = kPdeRuns * cap;
+  if (waves > kPdeWaves || a.runs.total > a.per_problem) return hipErrorInvalidValue;
   const dim3 grid((unsigned)problems), block((unsigned)(192 * waves));
   hipLaunchKernelGGL(all ? pde_forward_kernel<true> : pde_forward_kernel<false>, grid, block, 0, st, a);
   hipError_t e = hipGetLastError();

@@ -1,4 +1,4 @@
-"""Step counts of the reaction-diffusion kernels, on the CPU: the header that the kernels and the launch share."""
+"""Step counts and runs of the reaction-diffusion kernels, on the CPU: the header that entry points, launch and kernels share."""
 import os
 import subprocess
 
@@ -24,3 +24,12 @@ def test_pairs_of_steps_end(probe):
     counts = [1, 2, 3, 4, 5, 40960, 40961, 2 ** 31 - 1, 2 ** 31, 2 ** 32 - 5, 2 ** 32 - 4, 2 ** 32 - 3, 2 ** 32 - 2]
     for steps, turns, t in probe(*counts):
         assert turns <= 2 and 0 <= steps - t < 2, (steps, turns, t)
+
+
+def test_runs_fit_the_workspace(probe):
+    """The sampling waves' runs do not overlap, hold every entry at fraction 1 and fit what rad_pde_workspace_bytes asks for."""
+    for cells, steps, ppm, entries, wrong, room in probe("runs"):
+        assert not wrong and entries <= room, (cells, steps, ppm)
+        assert entries <= cells * (steps + 1) and entries >= cells * (steps + 1) * ppm // 1000000
+        if ppm == 1000000:
+            assert entries == cells * (steps + 1)
