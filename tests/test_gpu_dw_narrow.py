@@ -119,33 +119,41 @@ def test_faster_route(ctx, n, d, o, p, here):
         B.rad_ctx_timing_reset(ctx)
 
 
-@pytest.mark.parametrize("n", [97, 127, 128, 129, 241, 255, 256])               # rows of eight waves, even a wave, the most
-@pytest.mark.parametrize("d,o", [(31, 13), (32, 32), (33, 33), (257, 65), (784, 300), (300, 31)])
-@pytest.mark.parametrize("scheme,p", [("bernoulli", 0.1), ("per_example", 0.02), ("replace_shared", 0.2)])
-def test_few_rows(ctx, n, d, o, scheme, p):
-    """Up to 256 fp32 rows on 32 x 32 tiles: both calls of check_dW reach that kernel, unless the row split is the faster one."""
-    from paper_2007_10412_amd import binding as B
-    count = 0
-    for name in ("dw_small", "dw_narrow"):
-        B.rad_ctx_timing(ctx, name)
-        B.rad_ctx_timing_reset(ctx)
-        try:
-            check_dW(ctx, n, d, o, "f32", scheme, p)
-            count += B.rad_ctx_timing_read(ctx, None)[0]
-        finally:
-            B.rad_ctx_timing(ctx, "")
-            B.rad_ctx_timing_reset(ctx)
-    assert count == 2
-
-
-def test_few_rows_long_segments(ctx):
-    """Rows with more entries in a bucket than the kernel holds in registers."""
+def check_small(ctx, *case):
+    """check_dW, with both of its calls on the one-pass kernel for few rows."""
     from paper_2007_10412_amd import binding as B
     B.rad_ctx_timing(ctx, "dw_small")
     B.rad_ctx_timing_reset(ctx)
     try:
-        check_dW(ctx, 100, 784, 300, "f32", "bernoulli", 0.4)
+        check_dW(ctx, *case)
         assert B.rad_ctx_timing_read(ctx, None)[0] == 2
     finally:
         B.rad_ctx_timing(ctx, "")
         B.rad_ctx_timing_reset(ctx)
+
+
+@pytest.mark.parametrize("n", [97, 127, 128, 129, 241, 255, 256])               # rows of eight waves, even a wave, the most
+@pytest.mark.parametrize("d,o", [(31, 13), (32, 32), (33, 33), (257, 65), (784, 300), (300, 31)])
+@pytest.mark.parametrize("scheme,p", [("bernoulli", 0.1), ("per_example", 0.02), ("replace_shared", 0.2)])
+def test_few_rows(ctx, n, d, o, scheme, p):
+    """Up to 256 fp32 rows on 32 x 32 tiles; three near-ties of 51 and 60 entries a row are the row split's."""
+    split = (n, d, o) in [(128, 257, 65), (128, 300, 31), (256, 300, 31)] and p == 0.2
+    (check_here if split else check_small)(ctx, n, d, o, "f32", scheme, p)
+
+
+@pytest.mark.parametrize("n,d,o,p", [(49, 300, 64, 0.02), (56, 784, 300, 0.02), (64, 784, 300, 0.1), (65, 784, 301, 0.1), (80, 300, 65, 0.1),
+                                     (96, 2000, 31, 0.05)])
+def test_fewer_rows(ctx, n, d, o, p):
+    """Waves with a few rows, the last ones with none."""
+    check_small(ctx, n, d, o, "f32", "bernoulli", p)
+
+
+def test_few_rows_long_segments(ctx):
+    """Rows with more entries in a bucket than the kernel holds in registers."""
+    check_small(ctx, 100, 784, 300, "f32", "bernoulli", 0.4)
+
+
+@pytest.mark.parametrize("n,d,o,p", [(100, 784, 301, 0.4), (101, 784, 300, 0.4)])
+def test_few_masked_rows_long_segments(ctx, n, d, o, p):
+    """The same under ReLU bits, written and accumulated."""
+    check_small(ctx, n, d, o, "f32", "bernoulli", p)
