@@ -518,7 +518,7 @@ def pde_study(B, ctx, torch, steps, warmup, p, problems=256):
     """The reaction-diffusion study at the paper's size (32 x 32 intervals, 40960 time steps, fraction p of every
     state kept): one call = loss and sampled gradient of `problems` control vectors, one workgroup (CU) each.
     The time steps of a problem depend on each other, so the kernels are bound by the latency of one step
-    (instruction issue of the workgroup's 16 waves plus a barrier), not by a memory or arithmetic roofline:
+    (instruction issue of the workgroup's twelve waves plus a barrier), not by a memory or arithmetic roofline:
     what is reported is the time per step of the chain."""
     grid = B.make_pde_grid(32, 40960)
     ws = torch.empty(B.rad_pde_workspace_bytes(ctx, grid, p, problems), dtype=torch.uint8, device="cuda")

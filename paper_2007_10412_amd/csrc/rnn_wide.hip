@@ -15,7 +15,7 @@
 // A step takes 3.2 us forward and 3.6 backward at batch 128, hidden 1024, T = 784, its share of the launch included (3.6 and
 // 4.1 with launches of 32 steps; 1.7 us of matrix instructions, then the
 // latencies of the flags, of the fragments from L2 and of the sum through LDS).  A training step with fraction 0.1, a launch per
-// step / this, us: batch 128, hidden 1024, T = 784 14757 / 8270 (9310 with chunks of 32 steps); T = 200: batch 192, hidden 1000 14777 / 4024, 192 x 640
+// step / this, us: batch 128, hidden 1024, T = 784 14757 / 8264 (9310 with chunks of 32 steps); T = 200: batch 192, hidden 1000 14777 / 4024, 192 x 640
 // 3932 / 2545, 16 x 700 4153 / 1507; batch 40, hidden 300, T = 300 4806 / 1505.  A hidden state that does not fit 32 columns
 // a CU keeps a launch per step, and so does a batch above 192 (rnn_wide_ok; the kernels for two row tiles hold up to 256).
 //
